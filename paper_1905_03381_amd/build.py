@@ -22,7 +22,8 @@ OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libautoassist.so")
 TRACE_LIB = os.path.join(HERE, "libautoassist_trace.so")
 PROBE = os.path.join(HERE, "bare_read_probe")
-SOURCES = ["aa_api.hip", "aa_batching.hip", "aa_dense.hip", "aa_general.hip", "aa_select.hip"]
+SOURCES = ["aa_api.hip", "aa_batching.hip", "aa_dense.hip", "aa_general.hip", "aa_select.hip",
+           "aa_wide.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-munsafe-fp-atomics",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wall", "-Wno-unused-function", "-Rpass-analysis=kernel-resource-usage"]

@@ -6,6 +6,7 @@
 #include "aa_common.hpp"
 #include "aa_dense.hpp"
 #include "aa_general.hpp"
+#include "aa_wide.hpp"
 #include "aa_batching.hpp"
 #include "aa_select.hpp"
 
@@ -180,23 +181,31 @@ bool use_fast(const PassSpec &s) {
   return true;
 }
 
+// Rows of more than 1024 columns that those kernels do not take (wider than 2048, or a width,
+// leading dimension or address off 16 bytes).
+bool use_wide(const PassSpec &s) { return !use_fast(s) && wide_rows_ok(s.F); }
+
 size_t grad_bytes_for(const PassSpec &s) {
   const int nvec = ((s.mode & kSvm) ? 1 : 0) + ((s.mode & kAssist) ? 1 : 0);
   if (nvec == 0) return 0;
   if (use_fast(s))
     return (size_t)dense_pass_blocks(s.F->d, s.count_max, s.mode) * nvec *
            dense_d_pad(s.F->d) * sizeof(float);
+  // (what k_wide_pass needs, 256 partials of nvec rounded-up rows, is less than this)
   return general_acc_bytes(s.F->d, s.count_max);
 }
 
 // Launch the pass (and, for the general family, the accumulator clear before it).
 hipError_t run_pass(const PassSpec &s, const Ws &ws, int32_t *nblk_out, hipStream_t st) {
   const float omg = 1.0f - s.gamma;
-  if (use_fast(s)) {
+  const bool wide = use_wide(s);
+  if (wide || use_fast(s)) {
     PassArgs a{};
     a.x = s.F->x;
     a.ld = s.F->ld;
     a.d4 = s.F->d / 4;
+    a.d = s.F->d;
+    a.d_pad = wide ? wide_d_pad(s.F->d) : dense_d_pad(s.F->d);
     a.y = s.y;
     a.rows = s.rows;
     a.count_max = s.count_max;
@@ -226,6 +235,11 @@ hipError_t run_pass(const PassSpec &s, const Ws &ws, int32_t *nblk_out, hipStrea
 #ifdef AA_PHASE_TRACE
     a.trace = g_phase_trace;
 #endif
+    if (wide) {
+      *nblk_out = wide_pass_blocks(s.count_max);
+      const Hook hook;
+      return launch_wide_pass(a, s.mode, *nblk_out, st, hook.started, hook.stopped);
+    }
     const int32_t nblk = dense_pass_blocks(s.F->d, s.count_max, s.mode);
     if (a.prev.flags && (a.prev.P > dense_carry_capacity(nblk) ||
                          (reinterpret_cast<uintptr_t>(a.prev.flags) & 15) != 0))
@@ -314,13 +328,14 @@ struct UpdateSpec {
 hipError_t run_update(const PassSpec &s, const UpdateSpec &u, const Ws &ws, int32_t nblk,
                       hipStream_t st) {
   const bool pool = (s.mode & kPool) != 0;
-  if (use_fast(s)) {
+  const bool wide = use_wide(s);
+  if (wide || use_fast(s)) {
     FinalizeArgs f{};
     f.partial = reinterpret_cast<const float *>(ws.grad);
     f.nblk = nblk;
     f.nvec = ((s.mode & kSvm) ? 1 : 0) + ((s.mode & kAssist) ? 1 : 0);
     f.d = s.F->d;
-    f.d_pad = dense_d_pad(s.F->d);
+    f.d_pad = wide ? wide_d_pad(s.F->d) : dense_d_pad(s.F->d);
     f.blk_cnt = ws.blk_cnt;
     f.blk_gb = ws.blk_gb;
     f.m_dev = pool ? nullptr : s.m_dev;
@@ -494,7 +509,7 @@ int32_t fused_step_impl(const aa_features *F, const float *y, const int32_t *idx
   u.l2_a = cfg->l2_a;
   u.t_upd = t_upd;
   u.kept_hist = kept_hist;
-  u.keep_ready = ep && !fast && general_keeps_ready(F->d, hard ? 1 : 2, F->layout == AA_CSR);
+  u.keep_ready = ep && !fast && !use_wide(s) && general_keeps_ready(F->d, hard ? 1 : 2, F->layout == AA_CSR);
   if (kept_pos || kept_ids || loss || kept_count) {
     CompactArgs c{};
     c.flags = s.flags;

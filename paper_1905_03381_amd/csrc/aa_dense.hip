@@ -64,32 +64,6 @@ __device__ __forceinline__ int wave_sum_int(int v) {
   return v;
 }
 
-// v + (v moved by a DPP control): one VALU instruction, no LDS.
-template <int CTRL>
-__device__ __forceinline__ float dpp_add(float v) {
-  const int moved = __builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true);
-  return v + __int_as_float(moved);
-}
-
-__device__ __forceinline__ float lane_read(float v, int lane) {
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
-}
-
-// Sum over aligned groups of LPR lanes (16, 32 or 64); every lane of a group
-// gets the same bits.  Inside a 16-lane row: quad swaps, half mirror, mirror.
-template <int LPR>
-__device__ __forceinline__ float row_group_sum(float v, int lane) {
-  v = dpp_add<0xB1>(v);   // quad_perm [1,0,3,2]
-  v = dpp_add<0x4E>(v);   // quad_perm [2,3,0,1]
-  v = dpp_add<0x141>(v);  // row_half_mirror
-  v = dpp_add<0x140>(v);  // row_mirror
-  if (LPR == 16) return v;
-  const float s0 = lane_read(v, 0), s1 = lane_read(v, 16), s2 = lane_read(v, 32),
-              s3 = lane_read(v, 48);
-  if (LPR == 32) return lane < 32 ? s0 + s1 : s2 + s3;
-  return (s0 + s1) + (s2 + s3);
-}
-
 // Phase time stamps of measurement builds (compiled out otherwise).
 #ifdef AA_PHASE_TRACE
 #define AA_STAMP(k) (t_stamp[k] = (unsigned long long)wall_clock64())

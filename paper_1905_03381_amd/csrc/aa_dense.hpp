@@ -17,6 +17,7 @@ struct PassArgs {
   const float *x;
   int64_t ld;
   int32_t d4;             // d / 4
+  int32_t d;
   const float *y;         // labels indexed by data-set row (kSvm)
   const int32_t *rows;    // pool ids idx[P] or kept ids rows[m]; NULL = 0..count-1
   int32_t count_max;      // P (pool) or m_max (kept)
@@ -34,6 +35,7 @@ struct PassArgs {
   float *loss_out;        // kSvm: loss per position (pool) or per row (kept); may be NULL
   const float *loss_in;   // kAssist without kSvm: Boss losses per row
   float *partial;         // [nblk][nvec][d_pad]
+  int32_t d_pad;
   int32_t *blk_cnt;       // [nblk] kept count per block (pool mode)
   float *blk_gb;          // [nblk] bias-gradient partial (kAssist)
   const int32_t *t_upd;   // optional update counter; block 0 snapshots it into *t_snap

@@ -1,0 +1,332 @@
+// Wide dense rows: more columns than a wave can hold sums for in registers (d > 2048), and
+// rows of over 1024 columns with a width, leading dimension or base address that is not a
+// multiple of 16 bytes.  A block of 8 waves owns a row, each thread the same columns of every
+// row: it keeps those columns of the model and of the gradient sums in registers for the whole
+// launch, so a row crosses memory once and no sum needs an atomic or a trip through LDS.
+//
+// What bounds it: HBM.  Only the dot products cross threads: one value per wave, row and
+// vector goes through LDS, one barrier per R rows, while the next R rows are in flight in a
+// second set of registers.
+#include "aa_wide.hpp"
+
+namespace aa {
+
+namespace {
+
+typedef float f4 __attribute__((ext_vector_type(4)));
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));  // (any float address)
+
+constexpr int kWideWaves = 8, kWideThreads = kWideWaves * kWave;
+
+// Thread t owns the 128-bit pieces t, t + 512, ... of a row.  The last piece of a row whose
+// width is not a multiple of four is read from d - 4 on and a piece past the end likewise:
+// every load is a whole one, in bounds and without a condition.  Columns such a piece shares
+// with the one before are masked to zero.
+//
+// The gradient sums are doubles, rounded once per block (fp64 FMAs run at the fp32 rate here
+// and the pass waits for memory).  VPT pieces of R rows, twice, are in registers: 4 rows of
+// 17 KB at d = 4137, so that about 130 KB of a compute unit's rows are on their way at a time.
+// Measured: epochs of 4 pools of 4096 rows (the general kernels' times in brackets, whose sums go
+// through LDS and sorted records): d = 2052 66 us (141), 4093 89 (232), 6145 116 (898), 8000 137
+// (1488) = 3.8 TB/s of rows; the pass alone at d = 4137 19.3 us (53).  Scalars per row -- sigmoid,
+// draw, loss -- are worked out for all R rows at once, a row per eight lanes: done row by row in
+// every lane they took longer than the dot products (22.0 us).
+template <int VPT, int R, int MODE>
+__global__ __launch_bounds__(kWideThreads)
+    __attribute__((amdgpu_waves_per_eu(2, 2))) void k_wide_pass(const PassArgs a) {
+  constexpr bool POOL = (MODE & kPool) != 0;
+  constexpr bool SVM = (MODE & kSvm) != 0;
+  constexpr bool ASSIST = (MODE & kAssist) != 0;
+  constexpr bool HARD = (MODE & kHard) != 0;  // keep by the row's own loss, no Assistant
+  constexpr bool GRAD = SVM || ASSIST;
+  constexpr bool NEED_PHI = (POOL && !HARD) || ASSIST;
+  constexpr int NVEC = (SVM ? 1 : 0) + (ASSIST ? 1 : 0);
+  constexpr int NDOT = (SVM ? 1 : 0) + (NEED_PHI ? 1 : 0);
+  constexpr int Q = NDOT * R;  // dot products per batch
+  constexpr int kDotW = NEED_PHI ? R : 0;  // the Boss's dots come after the Assistant's
+  constexpr int kDotStride = 4 * kWideWaves + 4;
+  static_assert(Q <= 16 && 8 * R <= kWave, "a lane of 16 per dot, eight lanes per row");
+
+  __shared__ __attribute__((aligned(16))) float s_dot[2][Q * kDotStride];  // [dot][wave][quarter]
+
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+
+  int total = a.count_max;
+  if (!POOL && a.m_dev) total = min(max(*a.m_dev, 0), a.count_max);
+  const int per = total / (int)gridDim.x, rem = total % (int)gridDim.x;
+  const int lo = blockIdx.x * per + min((int)blockIdx.x, rem);
+  const int hi = lo + per + ((int)blockIdx.x < rem ? 1 : 0);
+
+  // the thread's columns: piece v holds columns first[v] .. first[v] + 3
+  int first[VPT];
+#pragma unroll
+  for (int v = 0; v < VPT; ++v) first[v] = min(4 * (v * kWideThreads + (int)threadIdx.x), a.d - 4);
+  // only the last piece can be short or absent: which of its columns are the thread's own
+  const int c_last = 4 * ((VPT - 1) * kWideThreads + (int)threadIdx.x);
+  bool own[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) own[i] = first[VPT - 1] + i >= c_last;
+
+  f4 mw[SVM ? VPT : 1], mp[NEED_PHI ? VPT : 1];
+#pragma unroll
+  for (int v = 0; v < VPT; ++v) {
+    if (SVM) mw[v] = *reinterpret_cast<const f4u *>(a.w + first[v]);
+    if (NEED_PHI) mp[v] = *reinterpret_cast<const f4u *>(a.phi + first[v]);
+  }
+  const float b = (NEED_PHI && a.bias) ? *a.bias : 0.f;
+  const float T = (ASSIST || HARD) ? *a.T : 0.f;
+  if (GRAD && a.t_upd && blockIdx.x == 0 && threadIdx.x == 0) *a.t_snap = *a.t_upd;
+
+  double gw[SVM ? VPT : 1][4], gp[ASSIST ? VPT : 1][4];
+#pragma unroll
+  for (int v = 0; v < VPT; ++v) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (SVM) gw[v][i] = 0.0;
+      if (ASSIST) gp[v][i] = 0.0;
+    }
+  }
+  float gb = 0.f;
+  int kept = 0;
+  int parity = 0;
+
+  for (int base = lo; base < hi; base += kWave) {
+    const int cnt = min(kWave, hi - base);
+    // one row per lane (the same 64 rows in every wave): id, label, draw, incoming loss
+    const int mine = base + min(lane, cnt - 1);
+    const int row_l = a.rows ? a.rows[mine] : mine;
+    float y_l = 0.f, u_l = 2.f, lin_l = 0.f;
+    if (SVM) y_l = a.y[row_l];
+    if (ASSIST && !SVM) lin_l = a.loss_in[mine];
+    if (POOL && a.do_keep) u_l = keep_uniform(a.key, (uint32_t)mine);
+    float o_logit = 0.f, o_prob = 0.f, o_loss = 0.f;  // outputs of the group, one row per lane
+    int o_keep = 0;
+
+    f4u x[2][R][VPT];
+    auto issue = [&](int it, f4u (&xb)[R][VPT]) __attribute__((always_inline)) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        // (a slot past the end of the group re-reads its last row and is not used)
+        const int row = __builtin_amdgcn_readlane(row_l, min(it + r, cnt - 1));
+        const float *xr = a.x + (int64_t)row * a.ld;
+#pragma unroll
+        for (int v = 0; v < VPT; ++v)
+          xb[r][v] = __builtin_nontemporal_load(reinterpret_cast<const f4u *>(xr + first[v]));
+      }
+    };
+    auto consume = [&](int it, f4u (&xb)[R][VPT]) __attribute__((always_inline)) {
+      // dot products: a quarter wave's sums stay in its lanes (dot q in lane q of 16), the
+      // quarters and the waves are added behind the barrier
+      float dots = 0.f;
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        float dp = 0.f, dw = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) xb[r][VPT - 1][i] = own[i] ? xb[r][VPT - 1][i] : 0.f;
+#pragma unroll
+        for (int v = 0; v < VPT; ++v) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            if (NEED_PHI) dp = __fmaf_rn(xb[r][v][i], mp[v][i], dp);
+            if (SVM) dw = __fmaf_rn(xb[r][v][i], mw[v][i], dw);
+          }
+        }
+        if (NEED_PHI) {
+          dp = row_group_sum<16>(dp, lane);
+          dots = (lane & 15) == r ? dp : dots;
+        }
+        if (SVM) {
+          dw = row_group_sum<16>(dw, lane);
+          dots = (lane & 15) == kDotW + r ? dw : dots;
+        }
+      }
+      if ((lane & 15) < Q) s_dot[parity][(lane & 15) * kDotStride + wave * 4 + (lane >> 4)] = dots;
+      __syncthreads();
+      // (the other parity is written next: no second barrier)
+      // lanes 8 r .. 8 r + 7 add up row r, one wave's four quarters each, and go on with it
+      auto dot_of = [&](int q) __attribute__((always_inline)) {
+        const f4 t = *reinterpret_cast<const f4 *>(&s_dot[parity][q * kDotStride + (lane & 7) * 4]);
+        float v = (t.x + t.y) + (t.z + t.w);
+        v = dpp_add<0xB1>(v);   // quad_perm [1,0,3,2]
+        v = dpp_add<0x4E>(v);   // quad_perm [2,3,0,1]
+        return dpp_add<0x141>(v);  // row_half_mirror
+      };
+      const int my = min(lane >> 3, R - 1), li = it + my;
+      const bool live = li < cnt && lane < 8 * R;
+      const int src = min(li, cnt - 1);
+      float g = 0.f, s = 0.f, loss = (ASSIST && !SVM) ? __shfl(lin_l, src, kWave) : 0.f;
+      bool keep = live;
+      if (NEED_PHI) {
+        s = dot_of(my) + b;
+        g = sigmoidf_(s);
+        if (POOL && a.do_keep)
+          keep = live && keep_decision(__shfl(u_l, src, kWave), g, a.gamma, a.one_minus_gamma);
+      }
+      float cw = 0.f, resid = 0.f;
+      if (SVM) {
+        const float yy = __shfl(y_l, src, kWave);
+        const float marg = yy * dot_of(kDotW + my);
+        loss = fmaxf(0.f, 1.f - marg);
+        if (HARD) keep = live && loss > T;      // shrinking by the objective value itself
+        cw = (keep && marg < 1.f) ? yy : 0.f;   // -d hinge / d margin, times y
+      }
+      if (ASSIST && keep) resid = g - (loss > T ? 1.f : 0.f);  // label: Boss loss above the threshold
+      if ((lane & 7) == 0) {
+        gb += resid;
+        kept += keep ? 1 : 0;
+      }
+      parity ^= 1;
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const float c = lane_read(cw, 8 * r), q = lane_read(resid, 8 * r);
+        if (SVM && c != 0.f) {
+#pragma unroll
+          for (int v = 0; v < VPT; ++v) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) gw[v][i] = __fma_rn((double)c, (double)xb[r][v][i], gw[v][i]);
+          }
+        }
+        if (ASSIST && q != 0.f) {
+#pragma unroll
+          for (int v = 0; v < VPT; ++v) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) gp[v][i] = __fma_rn((double)q, (double)xb[r][v][i], gp[v][i]);
+          }
+        }
+      }
+      if (wave == 0 && (POOL || SVM)) {  // row it + r's outputs: from lane 8 r to lane it + r
+        const int from = min(max(lane - it, 0), R - 1) * 8;
+        const bool here = lane >= it && lane < it + R;
+        const float ts = __shfl(s, from, kWave), tg = __shfl(g, from, kWave);
+        const float tl = __shfl(loss, from, kWave);
+        const int tk = __shfl(keep ? 1 : 0, from, kWave);
+        o_logit = here ? ts : o_logit;
+        o_prob = here ? tg : o_prob;
+        o_loss = here ? tl : o_loss;
+        o_keep = here ? tk : o_keep;
+      }
+    };
+
+    // The next batch is requested before this one is used, unconditionally (the last batch has a
+    // place of its own): a request under a condition would turn every wait into one for all.
+    issue(0, x[0]);
+    int it = 0;
+    for (; it + 2 * R < cnt; it += 2 * R) {
+      issue(it + R, x[1]);
+      consume(it, x[0]);
+      issue(it + 2 * R, x[0]);
+      consume(it + R, x[1]);
+    }
+    if (it + R < cnt) {
+      issue(it + R, x[1]);
+      consume(it, x[0]);
+      consume(it + R, x[1]);
+    } else {
+      consume(it, x[0]);
+    }
+    if (wave == 0 && lane < cnt) {
+      if (NEED_PHI && POOL && a.logit) a.logit[mine] = o_logit;
+      if (NEED_PHI && POOL && a.prob) a.prob[mine] = o_prob;
+      if (POOL && a.flags) a.flags[mine] = (uint8_t)o_keep;
+      if (SVM && a.loss_out && (HARD || o_keep)) a.loss_out[mine] = o_loss;
+    }
+  }
+
+  if (GRAD) {
+    const int d_pad = a.d_pad;
+    float *const part = a.partial + (size_t)blockIdx.x * NVEC * d_pad;
+#pragma unroll
+    for (int v = 0; v < VPT; ++v) {
+      const int c = 4 * (v * kWideThreads + (int)threadIdx.x);
+      f4 tw = {0.f, 0.f, 0.f, 0.f}, tp = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (SVM) tw[i] = (float)gw[v][i];
+        if (ASSIST) tp[i] = (float)gp[v][i];
+      }
+      if (c + 4 <= a.d) {
+        if (SVM) *reinterpret_cast<f4 *>(part + c) = tw;
+        if (ASSIST) *reinterpret_cast<f4 *>(part + (SVM ? d_pad : 0) + c) = tp;
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int k = first[v] + i;
+          if (k < c) continue;
+          if (SVM) part[k] = tw[i];
+          if (ASSIST) part[(SVM ? d_pad : 0) + k] = tp[i];
+        }
+      }
+    }
+    if (wave == 0) {  // (every wave counted the same)
+#pragma unroll
+      for (int off = kWave / 2; off > 0; off >>= 1) kept += __shfl_xor(kept, off, kWave);
+      gb = group_sum<kWave>(gb);
+      if (lane == 0) {
+        a.blk_cnt[blockIdx.x] = kept;
+        a.blk_gb[blockIdx.x] = gb;
+      }
+    }
+  }
+}
+
+template <int VPT, int R>
+hipError_t launch_vpt(const PassArgs &a, int mode, int nblk, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
+  const dim3 grid(nblk), block(kWideThreads);
+  switch (mode) {
+    case kPool:
+      launch_stamped((k_wide_pass<VPT, R, kPool>), grid, block, st, e0, e1, a);
+      break;
+    case kSvm:
+      launch_stamped((k_wide_pass<VPT, R, kSvm>), grid, block, st, e0, e1, a);
+      break;
+    case kAssist:
+      launch_stamped((k_wide_pass<VPT, R, kAssist>), grid, block, st, e0, e1, a);
+      break;
+    case kSvm | kAssist:
+      launch_stamped((k_wide_pass<VPT, R, kSvm | kAssist>), grid, block, st, e0, e1, a);
+      break;
+    case kPool | kSvm | kAssist:
+      launch_stamped((k_wide_pass<VPT, R, kPool | kSvm | kAssist>), grid, block, st, e0, e1, a);
+      break;
+    case kPool | kSvm | kHard:
+      launch_stamped((k_wide_pass<VPT, R, kPool | kSvm | kHard>), grid, block, st, e0, e1, a);
+      break;
+    default:
+      return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+}  // namespace
+
+bool wide_rows_ok(const aa_features *F) {
+  return F->layout == AA_DENSE && F->d >= kWideMinD && F->d <= kWideMaxD;
+}
+
+int32_t wide_d_pad(int32_t d) { return (d + 31) / 32 * 32; }
+
+// A block's partial sums are as long as a row per updated vector, written and read again, so few
+// rows per block are as much traffic for the sums as for the rows; few blocks leave compute units
+// idle.  Four rows a block up to half the compute units, eight beyond that.  Epochs of 4 pools at
+// d = 4137, one / four / eight rows a block: pools of 256 rows 53.7 / 43.8 / 48.8 us, of 500 55.9 /
+// 48.6 / 52.0, of 1000 59.2 / 59.2 / 56.7, of 1600 69.3 / 69.3 / 64.6 us.
+int32_t wide_pass_blocks(int32_t count) {
+  const int32_t half = kWideBlocks / 2, four = (int32_t)(((int64_t)count + 3) / 4);
+  const int32_t eight = (int32_t)(((int64_t)count + 7) / 8);
+  int32_t want = four < half ? four : eight > half ? eight : half;
+  if (want > kWideBlocks) want = kWideBlocks;
+  return want < 1 ? 1 : want;
+}
+
+hipError_t launch_wide_pass(const PassArgs &a, int mode, int32_t nblk, hipStream_t st, hipEvent_t e0,
+                            hipEvent_t e1) {
+  if (a.d < 4 || a.d > kWideMaxD) return hipErrorInvalidValue;
+  switch ((a.d + 4 * kWideThreads - 1) / (4 * kWideThreads)) {
+    case 1: return launch_vpt<1, 8>(a, mode, nblk, st, e0, e1);
+    case 2: return launch_vpt<2, 4>(a, mode, nblk, st, e0, e1);
+    case 3: return launch_vpt<3, 4>(a, mode, nblk, st, e0, e1);
+    default: return launch_vpt<4, 1>(a, mode, nblk, st, e0, e1);
+  }
+}
+
+}  // namespace aa

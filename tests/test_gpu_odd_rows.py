@@ -1,0 +1,58 @@
+"""GPU parity of dense rows the aligned register layouts do not take -- wider than 2048, or a width,
+leading dimension or address off 16 bytes -- at the edges of their own kernels' pieces."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1905_03381_amd import api
+
+import test_gpu_dense as dense
+import test_gpu_sk as sk
+from gpu_util import dense_features
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ws():
+    return api.Workspace(4000, 9000)
+
+
+# a block of 512 threads owns 2048 columns per piece: one column either side of each number of
+# pieces, widths of every remainder by four, padded and odd leading dimensions, and pools that give
+# some blocks no row, one row, and more than a register set of them
+SHAPES = [(40, 1025, None, 33), (300, 1027, 1029, 300), (300, 2047, None, 257), (64, 2049, None, 64),
+          (300, 2050, 2052, 255), (600, 4095, None, 520), (40, 4096, 4096, 40), (600, 4097, 4099, 513),
+          (300, 6144, None, 256), (1500, 6145, None, 1400), (300, 8191, None, 300), (20, 8192, None, 1),
+          (20, 8193, None, 20), (3300, 1367, None, 3300)]
+
+
+@pytest.mark.parametrize("n,d,ld,P", SHAPES)
+def test_odd_rows_match_the_oracle(ref, ws, n, d, ld, P):
+    dense.test_assistant_score(ref, n, d, ld, P, True)
+    dense.test_fused_step_matches_oracle_step(ref, ws, n, d, ld, P, 0.1)
+    dense.test_svm_sgd_step(ref, ws, n, d, ld, min(P, 300), False)
+    dense.test_assistant_update(ref, ws, n, d, ld, P)
+    r = dense.rng(7)
+    X = r.standard_normal((n, ld or d)).astype(np.float32)
+    X /= np.linalg.norm(X[:, :d], axis=1, keepdims=True)
+    y = np.where(r.random(n) < 0.5, 1.0, -1.0).astype(np.float32)
+    idx = r.permutation(n)[:P].astype(np.int32)
+    sk._run_and_check(ref, ws, ref.Features.dense(X, d=d), dense_features(X, d=d), y, idx, P, d, 0.4)
+
+
+@pytest.mark.parametrize("d", [1027, 4097])
+def test_odd_rows_with_infinities_in_the_last_columns(ws, d):
+    """The last columns of a row that is no whole number of pieces are read twice and count once:
+    an infinite value there gives an infinite score, not a NaN, and reaches no other row."""
+    P = 9
+    X = torch.randn(P, d, generator=torch.Generator().manual_seed(d)).cuda()
+    X[3, d - 2] = float("inf")
+    phi = torch.full((d,), 0.01, device="cuda")
+    logit, prob = torch.zeros(P, device="cuda"), torch.zeros(P, device="cuda")
+    api.assistant_score(api.Features.dense(X), None, P, phi, None, logit, prob)
+    assert logit[3].item() == float("inf") and prob[3].item() == 1.0
+    rest = torch.arange(P, device="cuda") != 3
+    want = (X[rest].double().cpu() @ phi.double().cpu()).float().cuda()
+    # (a sum of d terms of size 0.01: rounding below 1e-5)
+    assert torch.all((logit[rest] - want).abs() <= 1e-5)
