@@ -117,8 +117,6 @@ __global__ __launch_bounds__(NW * 64)
   __shared__ f4 s_w[SVM ? ROW4 : 1];
   __shared__ f4 s_phi[NEED_PHI ? ROW4 : 1];
   __shared__ f4 s_red[GRAD ? NW * NVEC * ROW4 : 1];  // one slot per wave and vector
-  constexpr bool MEDIAN = ASSIST && !SVM && !POOL;   // may take its threshold from the batch itself
-  __shared__ __attribute__((aligned(16))) float s_med[MEDIAN ? kRankSelectMax + 2 : 1];
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int grp = lane / LPR, sub = lane % LPR;
@@ -149,8 +147,7 @@ __global__ __launch_bounds__(NW * 64)
     st_p[q] = (NEED_PHI && c < a.d4) ? reinterpret_cast<const f4 *>(a.phi)[c] : zero4;
   }
   const float b = (NEED_PHI && a.bias) ? *a.bias : 0.f;
-  float T = (ASSIST || HARD) ? *a.T : 0.f;
-  const int med_init_old = (MEDIAN && a.med_init) ? *a.med_init : 0;
+  const float T = (ASSIST || HARD) ? *a.T : 0.f;
 
   f4 x[RIF][VPL];
   // Every load of the next RIF rows, before any is used.  When the row fills the lane layout
@@ -231,14 +228,6 @@ __global__ __launch_bounds__(NW * 64)
     if (lane == 0) s_carry[wave] = carry_cnt;
   }
   __syncthreads();
-  if (MEDIAN && a.med_init && total > 0) {  // (the same in every thread of the grid)
-    float lo_mid, hi_mid;
-    if (block_middle_values(a.loss_in, total, s_med, &lo_mid, &hi_mid))
-      T = running_threshold(lo_mid, hi_mid, total, med_init_old, T, a.med_momentum);
-    else
-      T = __builtin_nanf("");  // a NaN loss has no rank: the threshold becomes NaN, visibly
-    if (blockIdx.x == 0 && threadIdx.x == 0) *a.T_next = T;
-  }
   if (POOL && GRAD && carry && wave == NW - 1) {
     int before = 0;
 #pragma unroll
@@ -376,6 +365,192 @@ __global__ __launch_bounds__(NW * 64)
     }
   }
   if (GRAD && a.t_upd && blockIdx.x == 0 && threadIdx.x == 0) *a.t_snap = *a.t_upd;
+}
+
+// A small batch of rows already chosen (at most kRankSelectMax): one row per lane group, no loop.
+// Nothing but round trips bounds it: the row count, then the ids and losses, then the rows.  Each
+// is requested for all it depends on at once and without a condition; the model goes straight to
+// the registers of the lanes that use it (no barrier in front of the rows).
+//
+// kAssist alone can take its labels against the running threshold AFTER this batch (med_init):
+// every block finds the batch's two middle losses for itself while its rows are on their way.
+// sorted[k] is the largest loss with at most k losses below it, so a loss only has to count the
+// smaller ones: two instructions per pair, half of the pairs per thread for up to 256 losses.
+// Measured on 256 rows of 512 floats: k_rows_pass 12.6 us, this 6.1 us.
+template <int LPR, int VPL, int MODE, int NW>
+__global__ __launch_bounds__(NW * 64) void k_rows_once(const PassArgs a) {
+  constexpr bool SVM = (MODE & kSvm) != 0;
+  constexpr bool ASSIST = (MODE & kAssist) != 0;
+  constexpr int G = kWave / LPR;  // rows per wave
+  constexpr int ROW4 = LPR * VPL;
+  constexpr int NVEC = (SVM ? 1 : 0) + (ASSIST ? 1 : 0);
+  constexpr int NT = NW * 64;
+  constexpr bool MEDIAN = ASSIST && !SVM;
+  static_assert(NT >= kRankSelectMax, "a loss per thread");
+
+  __shared__ int s_int[NW];
+  __shared__ float s_flt[NW];
+  __shared__ f4 s_red[NW * NVEC * ROW4];  // one slot per wave and vector
+  __shared__ __attribute__((aligned(16))) float s_med[MEDIAN ? kRankSelectMax : 1];
+  __shared__ int s_below[MEDIAN ? kRankSelectMax : 1];
+  __shared__ int s_key[MEDIAN ? 2 * NW : 1];
+  __shared__ int s_nan[MEDIAN ? NW : 1];
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int grp = lane / LPR, sub = lane % LPR;
+  const f4 zero4 = {0.f, 0.f, 0.f, 0.f};
+
+  const int m_given = *a.m_dev;
+  const float *const model = SVM ? a.w : a.phi;
+  f4 mw[SVM ? VPL : 1], mp[ASSIST ? VPL : 1];
+#pragma unroll
+  for (int v = 0; v < VPL; ++v) {  // (columns past the row meet zeros of the row)
+    const int c = min(v * LPR + sub, a.d4 - 1);
+    if (SVM) mw[v] = reinterpret_cast<const f4 *>(a.w)[c];
+    if (ASSIST) mp[v] = reinterpret_cast<const f4 *>(a.phi)[c];
+  }
+  float b = ASSIST ? *(a.bias ? a.bias : a.phi) : 0.f;
+  if (!a.bias) b = 0.f;
+  float T = ASSIST ? *a.T : 0.f;
+  const bool median = MEDIAN && a.med_init != nullptr;
+  const int med_init_old = *(median ? a.med_init : a.m_dev);
+  if (a.t_upd && blockIdx.x == 0 && tid == 0) *a.t_snap = *a.t_upd;
+
+  const int total = min(max(m_given, 0), a.count_max);
+  if (total == 0) return;  // (an empty batch updates nothing: no sum of this pass is used)
+  const int last = total - 1;
+  const int pos = (blockIdx.x * NW + wave) * G + grp;
+  const bool keep = pos <= last;
+  const int at = min(pos, last);  // (a group past the end re-reads the last row and drops it)
+  int row = a.rows ? a.rows[at] : at;
+  float lin = MEDIAN ? a.loss_in[at] : 0.f;
+  const int mine = min(tid, last);
+  float x_loss = MEDIAN ? (median ? a.loss_in : model)[median ? mine : 0] : 0.f;
+  arrived(row);
+  const float yy = SVM ? a.y[row] : 0.f;
+  const f4 *xr = reinterpret_cast<const f4 *>(a.x + (int64_t)row * a.ld);
+  f4 x[VPL];
+#pragma unroll
+  for (int v = 0; v < VPL; ++v) x[v] = AA_ROW_LOAD(xr + min(v * LPR + sub, a.d4 - 1));
+
+  if (median) {
+    // (ids and losses were requested before the rows: no wait here is a wait for the rows)
+    const int per = total <= kRankSelectMax / 2 ? kRankSelectMax / 2 : kRankSelectMax;
+    const int i = tid & (per - 1), part = tid / per, parts = min(NT / per, 2);
+    if (tid < kRankSelectMax) s_med[tid] = tid < total ? x_loss : __builtin_inff();
+    const unsigned long long nan = __ballot(x_loss != x_loss);
+    if (lane == 0) s_nan[wave] = nan != 0ull;
+    __syncthreads();
+    int has_nan = 0;
+#pragma unroll
+    for (int q = 0; q < NW; ++q) has_nan |= s_nan[q];
+    const float v_mine = s_med[i];
+    const int n4 = (total + 3) / 4, share = (n4 + parts - 1) / parts;
+    int below = 0;
+    if (part < parts && i < total) {
+      const int end = min(n4, (part + 1) * share);
+#pragma unroll 4
+      for (int q = part * share; q < end; ++q) {  // 128-bit LDS broadcasts
+        const f4 v = *reinterpret_cast<const f4 *>(s_med + 4 * q);
+        below += v.x < v_mine ? 1 : 0;
+        below += v.y < v_mine ? 1 : 0;
+        below += v.z < v_mine ? 1 : 0;
+        below += v.w < v_mine ? 1 : 0;
+      }
+    }
+    if (parts == 2) {
+      if (part == 1 && i < total) s_below[i] = below;
+      __syncthreads();
+      if (part == 0 && i < total) below += s_below[i];
+    }
+    // the largest losses with at most (total - 1) / 2 and total / 2 losses below them, as
+    // integers in the order of the floats
+    const int bits = __float_as_int(v_mine), key = bits ^ ((bits >> 31) & 0x7fffffff);
+    const bool cand = part == 0 && i < total;
+    int k_lo = cand && below <= (total - 1) / 2 ? key : (int)0x80000000;
+    int k_hi = cand && below <= total / 2 ? key : (int)0x80000000;
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) {
+      k_lo = max(k_lo, __shfl_xor(k_lo, off, kWave));
+      k_hi = max(k_hi, __shfl_xor(k_hi, off, kWave));
+    }
+    if (lane == 0) {
+      s_key[wave] = k_lo;
+      s_key[NW + wave] = k_hi;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < NW; ++q) {
+      k_lo = max(k_lo, s_key[q]);
+      k_hi = max(k_hi, s_key[NW + q]);
+    }
+    const float lo_mid = __int_as_float(k_lo ^ ((k_lo >> 31) & 0x7fffffff));
+    const float hi_mid = __int_as_float(k_hi ^ ((k_hi >> 31) & 0x7fffffff));
+    if (has_nan)
+      T = __builtin_nanf("");  // a NaN loss has no rank: the threshold becomes NaN, visibly
+    else
+      T = running_threshold(lo_mid, hi_mid, total, med_init_old, T, a.med_momentum);
+    if (blockIdx.x == 0 && tid == 0) *a.T_next = T;
+  }
+
+  if (a.d4 != ROW4) {
+#pragma unroll
+    for (int v = 0; v < VPL; ++v)
+      if (v * LPR + sub >= a.d4) x[v] = zero4;
+  }
+  float g = 0.f, loss = lin, cw = 0.f, resid = 0.f;
+  if (ASSIST) {
+    float dp = 0.f;
+#pragma unroll
+    for (int v = 0; v < VPL; ++v) dp = dot4(x[v], mp[v], dp);
+    g = sigmoidf_(row_group_sum<LPR>(dp, lane) + b);
+  }
+  if (SVM) {
+    float dw = 0.f;
+#pragma unroll
+    for (int v = 0; v < VPL; ++v) dw = dot4(x[v], mw[v], dw);
+    const float marg = yy * row_group_sum<LPR>(dw, lane);
+    loss = fmaxf(0.f, 1.f - marg);
+    cw = marg < 1.f ? yy : 0.f;  // -d hinge / d margin, times y
+    if (sub == 0 && keep && a.loss_out) a.loss_out[pos] = loss;
+  }
+  if (ASSIST) resid = keep ? g - (loss > T ? 1.f : 0.f) : 0.f;  // label: Boss loss above the threshold
+  f4 *slot = s_red + wave * NVEC * ROW4;
+  f4 acc[VPL];
+  if (SVM) {
+#pragma unroll
+    for (int v = 0; v < VPL; ++v) acc[v] = keep ? axpy4(cw, x[v], zero4) : zero4;
+    wave_slot_store<LPR, VPL>(acc, slot, lane);
+  }
+  if (ASSIST) {
+#pragma unroll
+    for (int v = 0; v < VPL; ++v) acc[v] = keep ? axpy4(resid, x[v], zero4) : zero4;
+    wave_slot_store<LPR, VPL>(acc, slot + (SVM ? ROW4 : 0), lane);
+  }
+  const int kw = wave_sum_int(sub == 0 && keep ? 1 : 0);
+  const float gbw = group_sum<kWave>(sub == 0 ? resid : 0.f);
+  if (lane == 0) {
+    s_int[wave] = kw;
+    s_flt[wave] = gbw;
+  }
+  __syncthreads();
+  f4 *part = reinterpret_cast<f4 *>(a.partial) + (size_t)blockIdx.x * NVEC * ROW4;
+  for (int c = tid; c < NVEC * ROW4; c += NT) {
+    f4 t = s_red[c];
+#pragma unroll
+    for (int q = 1; q < NW; ++q) t += s_red[q * NVEC * ROW4 + c];
+    part[c] = t;
+  }
+  if (tid == 0) {
+    int ks = 0;
+    float gs = 0.f;
+    for (int i = 0; i < NW; ++i) {
+      ks += s_int[i];
+      gs += s_flt[i];
+    }
+    a.blk_cnt[blockIdx.x] = ks;
+    a.blk_gb[blockIdx.x] = gs;
+  }
 }
 
 // The whole-step pool pass (score, keep, both gradient sums; or the hard-threshold variant)
@@ -875,6 +1050,18 @@ hipError_t launch_grad(const PassArgs &a, int mode, int nblk, hipStream_t st, hi
   return hipGetLastError();
 }
 
+template <int LPR, int VPL, int NW>
+hipError_t launch_once(const PassArgs &a, int mode, int nblk, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
+  const dim3 grid(nblk), block(NW * 64);
+  if (mode == kSvm)
+    launch_stamped((k_rows_once<LPR, VPL, kSvm, NW>), grid, block, st, e0, e1, a);
+  else if (mode == kAssist)
+    launch_stamped((k_rows_once<LPR, VPL, kAssist, NW>), grid, block, st, e0, e1, a);
+  else
+    launch_stamped((k_rows_once<LPR, VPL, kSvm | kAssist, NW>), grid, block, st, e0, e1, a);
+  return hipGetLastError();
+}
+
 template <int VPL, int NW, int RIF>
 hipError_t launch_step(const PassArgs &a, bool hard, int nblk, hipStream_t st, hipEvent_t e0,
                        hipEvent_t e1) {
@@ -910,6 +1097,8 @@ int32_t dense_pass_blocks(int32_t d, int32_t count, int mode) {
   const int rows_per_block = nw * (kWave / s.lpr);
   const bool grad = (mode & (kSvm | kAssist)) != 0;
   int64_t want = ((int64_t)count + rows_per_block - 1) / rows_per_block;
+  // a small batch of chosen rows: a lane group for each row, however few compute units there are
+  if (grad && !(mode & kPool) && count <= kRankSelectMax) return want < 1 ? 1 : (int32_t)want;
   // 16 waves per CU: one block of 16 waves, two of 8 or four of 4; the wide whole-step passes
   // hold several rows per wave in registers and fit one block per CU
   const bool one_per_cu = s.vpl == 8 || (step_pass_ok(s, d, mode) && s.vpl >= 4);
@@ -945,6 +1134,19 @@ hipError_t launch_dense_pass(const PassArgs &a, int mode, int32_t d, int32_t nbl
       default: return launch_step<8, 8, 2>(a, hard, nblk, st, e0, e1);
     }
   }
+  // rows already chosen, a lane group for each: the pass without a loop
+  if (!(mode & kPool) && a.count_max <= kRankSelectMax) {
+    if ((int64_t)nblk * waves_per_block(s, d, mode) * (kWave / s.lpr) < a.count_max) return hipErrorInvalidValue;
+    if (s.lpr == 16) return launch_once<16, 1, 8>(a, mode, nblk, st, e0, e1);
+    if (s.lpr == 32) return launch_once<32, 1, 8>(a, mode, nblk, st, e0, e1);
+    switch (s.vpl) {
+      case 1: return launch_once<64, 1, 8>(a, mode, nblk, st, e0, e1);
+      case 2: return launch_once<64, 2, 8>(a, mode, nblk, st, e0, e1);
+      case 4: return launch_once<64, 4, AA_NW_D1024>(a, mode, nblk, st, e0, e1);
+      default: return launch_once<64, 8, 8>(a, mode, nblk, st, e0, e1);
+    }
+  }
+  if (a.med_init) return hipErrorInvalidValue;  // (only the pass above finds a batch's median)
   if (s.lpr == 16) return launch_grad<16, 1, 8, 8>(a, mode, nblk, st, e0, e1);
   if (s.lpr == 32) return launch_grad<32, 1, 8, 8>(a, mode, nblk, st, e0, e1);
   switch (s.vpl) {
