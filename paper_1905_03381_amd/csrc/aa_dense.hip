@@ -20,15 +20,6 @@
 #ifndef AA_RIF_D1024
 #define AA_RIF_D1024 1   // rows in flight per wave there
 #endif
-#ifndef AA_STEP_NW_D1024
-#define AA_STEP_NW_D1024 8   // whole-step pass at d = 1024: waves per block (one block per CU)
-#endif
-#ifndef AA_STEP_RIF_D1024
-#define AA_STEP_RIF_D1024 2  // and rows requested at once per wave
-#endif
-#ifndef AA_STEP_ROLL
-#define AA_STEP_ROLL 0       // 1: a consumed row's slot is refilled at once instead of batch-wise
-#endif
 
 // Feature rows are read once per step: non-temporal loads keep them from displacing the
 // model vectors and block partials in L2.
@@ -554,7 +545,9 @@ __global__ __launch_bounds__(NW * 64) void k_rows_once(const PassArgs a) {
 }
 
 // The whole-step pool pass (score, keep, both gradient sums; or the hard-threshold variant)
-// for rows that fill the 64-lane layout exactly (d == 256 VPL).  Same arithmetic and the same
+// for rows of more than 128 floats.  FULL: the row fills the 64-lane layout exactly (d == 256 VPL);
+// otherwise a piece past the end of the row re-reads its last piece and is masked, so the loads
+// stay unconditional.  Same arithmetic and the same
 // summation order as k_rows_pass; the schedule differs.  A wave requests RIF rows at once and
 // nothing sits between those requests and their use that the memory pipeline would have to
 // finish first: every small load that does not depend on the row ids (model vectors,
@@ -563,7 +556,7 @@ __global__ __launch_bounds__(NW * 64) void k_rows_once(const PassArgs a) {
 // keep flag, loss) are collected one per lane and stored once per group of 64 rows, so no
 // store is pending while rows arrive.  Loads return in request order, so row r of a batch
 // is consumed as soon as it is there while rows r+1.. are still on their way.
-template <int VPL, bool HARD, int NW, int RIF>
+template <int VPL, bool HARD, bool FULL, int NW, int RIF>
 __global__ __launch_bounds__(NW * 64)
     __attribute__((amdgpu_waves_per_eu(NW / 4, NW / 4))) void k_step_pass(const PassArgs a) {
   constexpr bool ASSIST = !HARD;
@@ -599,7 +592,7 @@ __global__ __launch_bounds__(NW * 64)
   // ---- Requests that depend on nothing, all unconditional: a load under a condition would
   // make every later wait for an older load a wait for everything (the pending counts of the
   // two paths are merged pessimistically), so absent inputs read a stand-in address (the
-  // start of w, which always holds at least 1 KiB) and indices are clamped; what was read for
+  // start of w, which always holds 132 floats) and indices are clamped; what was read for
   // nothing is dropped by a select.
   const int32_t *stand_in = reinterpret_cast<const int32_t *>(a.w);
   const int32_t *rows_p = a.rows ? a.rows : stand_in;
@@ -615,12 +608,12 @@ __global__ __launch_bounds__(NW * 64)
   uint4 carry_v = p16[min((int)threadIdx.x, max(n16, 1) - 1)];
   const int cpos = carry ? min(cj0 + lane, a.prev.P - 1) : 0;
   uint8_t carry_flag = (carry ? a.prev.flags : reinterpret_cast<const uint8_t *>(a.w))[cpos];
-  int carry_id = ((carry && a.prev.idx) ? a.prev.idx : stand_in)[cpos];
-  float carry_loss = ((carry && a.prev.loss) ? a.prev.loss_pool : a.w)[cpos];
+  int carry_id = ((carry && a.prev.idx) ? a.prev.idx : stand_in)[a.prev.idx ? cpos : 0];
+  float carry_loss = ((carry && a.prev.loss) ? a.prev.loss_pool : a.w)[a.prev.loss ? cpos : 0];
   f4 st_w[STG], st_p[STG];
 #pragma unroll
   for (int q = 0; q < STG; ++q) {
-    const int c = min(q * NT + (int)threadIdx.x, ROW4 - 1);
+    const int c = min(q * NT + (int)threadIdx.x, FULL ? ROW4 - 1 : a.d4 - 1);
     st_w[q] = reinterpret_cast<const f4 *>(a.w)[c];
     st_p[q] = reinterpret_cast<const f4 *>(ASSIST ? a.phi : a.w)[c];
   }
@@ -651,9 +644,9 @@ __global__ __launch_bounds__(NW * 64)
 #pragma unroll
   for (int q = 0; q < STG; ++q) {
     const int c = q * NT + threadIdx.x;
-    if (c < ROW4) {
-      s_w[c] = st_w[q];
-      if (ASSIST) s_phi[c] = st_p[q];
+    if (c < ROW4) {  // (columns past the row: any finite value would do, the row is zero there)
+      s_w[c] = FULL || c < a.d4 ? st_w[q] : zero4;
+      if (ASSIST) s_phi[c] = FULL || c < a.d4 ? st_p[q] : zero4;
     }
   }
   if (carry) {
@@ -670,9 +663,10 @@ __global__ __launch_bounds__(NW * 64)
       // a slot past the end of the group re-reads the group's last row and is never consumed
       const int li = min(it0 + r, cnt - 1);
       const int row = __builtin_amdgcn_readlane(row_l, li);
-      const f4 *xr = reinterpret_cast<const f4 *>(a.x + (int64_t)row * a.ld) + lane;
+      const f4 *xr = reinterpret_cast<const f4 *>(a.x + (int64_t)row * a.ld);
 #pragma unroll
-      for (int v = 0; v < VPL; ++v) x[r][v] = AA_ROW_LOAD(xr + v * kWave);
+      for (int v = 0; v < VPL; ++v)
+        x[r][v] = AA_ROW_LOAD(xr + (FULL ? v * kWave + lane : min(v * kWave + lane, a.d4 - 1)));
     }
   };
   // The barrier that publishes the model vectors comes before the row requests: the memory
@@ -724,6 +718,11 @@ __global__ __launch_bounds__(NW * 64)
         const int src = li & 63;
         float g = 0.f, s = 0.f, loss = 0.f;
         bool keep = live;
+        if (!FULL) {  // (the layouts double in width: only the second half can lie past the row)
+#pragma unroll
+          for (int v = VPL / 2; v < VPL; ++v)
+            if (v * kWave + lane >= a.d4) x[r][v] = zero4;
+        }
         if (ASSIST) {
           float dp = 0.f;
 #pragma unroll
@@ -764,14 +763,8 @@ __global__ __launch_bounds__(NW * 64)
 #ifdef AA_PHASE_TRACE
         if (t_stamp[4] == 0) AA_STAMP(4);  // first row arrived and used
 #endif
-        if (AA_STEP_ROLL && li + RIF < cnt) {  // the freed slot takes the row RIF further on
-          const int row = __builtin_amdgcn_readlane(row_l, (li + RIF) & 63);
-          const f4 *xr = reinterpret_cast<const f4 *>(a.x + (int64_t)row * a.ld) + lane;
-#pragma unroll
-          for (int v = 0; v < VPL; ++v) x[r][v] = AA_ROW_LOAD(xr + v * kWave);
-        }
       }
-      if (!AA_STEP_ROLL && it0 + RIF < cnt) issue_rows(it0 + RIF);
+      if (it0 + RIF < cnt) issue_rows(it0 + RIF);
     }
     if (lane < cnt) {
       const int j = base + lane;
@@ -1009,18 +1002,36 @@ Shape pick_shape(int32_t d) {
   return {64, 8};
 }
 
-// The whole-step pool passes take k_step_pass when the row fills the 64-lane layout exactly.
-bool step_pass_ok(const Shape &s, int32_t d, int mode) {
+// The whole-step pool passes take k_step_pass on every 64-lane layout.
+bool step_pass_ok(const Shape &s, int mode) {
   const bool whole = mode == (kPool | kSvm | kAssist) || mode == (kPool | kSvm | kHard);
-  return whole && s.lpr == kWave && d == 4 * kWave * s.vpl;
+  return whole && s.lpr == kWave;
+}
+
+// Waves per block and rows requested at once per wave of k_step_pass; one block per compute unit.
+// A batch costs the same whether its slots hold rows or not, and two blocks per compute unit
+// twice the partial sums: with 8 rows at once in two blocks of 8 waves, pools of 8192 rows of
+// 512 floats took 18.5 us per step (16.3 with hard thresholds), with 4 in one block 10.8 (10.3).
+// Per step at d = 512, P = 4096: 2 rows at once 9.3 us, 4 9.8; P = 16,384: 13.8, 13.7; at
+// d = 256, P = 40,000 17.5, 15.7.  Rows of 1 KB or less leave a wave idle soonest: from 16,384
+// of them on 16 waves (P = 60,000 21.2 us against 23.1, 200,000 48.5 against 55.5; below it
+// 8 waves are level or ahead, 9.6 against 10.6 at 8192).
+struct StepShape {
+  int nw, rif;
+};
+
+StepShape step_shape(int vpl, int32_t count) {
+  if (vpl == 1 && count > 16384) return {16, 4};
+  if (vpl <= 2) return {8, count <= 4096 ? 2 : 4};
+  return {8, 2};
 }
 
 // Waves per block: passes with gradient sums use one fat block per CU (few block
 // partials); the general 1024-wide pass runs 16 waves of 128 registers, everything else 8.
-int waves_per_block(const Shape &s, int32_t d, int mode) {
+int waves_per_block(const Shape &s, int32_t count, int mode) {
   const bool grad = (mode & (kSvm | kAssist)) != 0;
   if (!grad) return 4;
-  if (step_pass_ok(s, d, mode)) return s.vpl == 4 ? AA_STEP_NW_D1024 : 8;
+  if (step_pass_ok(s, mode)) return step_shape(s.vpl, count).nw;
   return s.vpl == 4 ? AA_NW_D1024 : 8;
 }
 
@@ -1038,13 +1049,17 @@ hipError_t launch_grad(const PassArgs &a, int mode, int nblk, hipStream_t st, hi
     case kSvm | kAssist:
       launch_stamped((k_rows_pass<LPR, VPL, kSvm | kAssist, NW, RIF>), grid, block, st, e0, e1, a);
       break;
-    case kPool | kSvm | kAssist:
-      launch_stamped((k_rows_pass<LPR, VPL, kPool | kSvm | kAssist, NW, RIF>), grid, block, st, e0, e1, a);
-      break;
-    case kPool | kSvm | kHard:
-      launch_stamped((k_rows_pass<LPR, VPL, kPool | kSvm | kHard, NW, RIF>), grid, block, st, e0, e1, a);
-      break;
     default:
+      if constexpr (LPR < kWave) {  // (the others take k_step_pass)
+        if (mode == (kPool | kSvm | kAssist)) {
+          launch_stamped((k_rows_pass<LPR, VPL, kPool | kSvm | kAssist, NW, RIF>), grid, block, st, e0, e1, a);
+          break;
+        }
+        if (mode == (kPool | kSvm | kHard)) {
+          launch_stamped((k_rows_pass<LPR, VPL, kPool | kSvm | kHard, NW, RIF>), grid, block, st, e0, e1, a);
+          break;
+        }
+      }
       return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -1066,10 +1081,15 @@ template <int VPL, int NW, int RIF>
 hipError_t launch_step(const PassArgs &a, bool hard, int nblk, hipStream_t st, hipEvent_t e0,
                        hipEvent_t e1) {
   const dim3 grid(nblk), block(NW * 64);
-  if (hard)
-    launch_stamped((k_step_pass<VPL, true, NW, RIF>), grid, block, st, e0, e1, a);
+  const bool full = a.d4 == kWave * VPL;
+  if (hard && full)
+    launch_stamped((k_step_pass<VPL, true, true, NW, RIF>), grid, block, st, e0, e1, a);
+  else if (hard)
+    launch_stamped((k_step_pass<VPL, true, false, NW, RIF>), grid, block, st, e0, e1, a);
+  else if (full)
+    launch_stamped((k_step_pass<VPL, false, true, NW, RIF>), grid, block, st, e0, e1, a);
   else
-    launch_stamped((k_step_pass<VPL, false, NW, RIF>), grid, block, st, e0, e1, a);
+    launch_stamped((k_step_pass<VPL, false, false, NW, RIF>), grid, block, st, e0, e1, a);
   return hipGetLastError();
 }
 
@@ -1093,7 +1113,7 @@ int32_t dense_d_pad(int32_t d) {
 
 int32_t dense_pass_blocks(int32_t d, int32_t count, int mode) {
   const Shape s = pick_shape(d);
-  const int nw = waves_per_block(s, d, mode);
+  const int nw = waves_per_block(s, count, mode);
   const int rows_per_block = nw * (kWave / s.lpr);
   const bool grad = (mode & (kSvm | kAssist)) != 0;
   int64_t want = ((int64_t)count + rows_per_block - 1) / rows_per_block;
@@ -1101,7 +1121,7 @@ int32_t dense_pass_blocks(int32_t d, int32_t count, int mode) {
   if (grad && !(mode & kPool) && count <= kRankSelectMax) return want < 1 ? 1 : (int32_t)want;
   // 16 waves per CU: one block of 16 waves, two of 8 or four of 4; the wide whole-step passes
   // hold several rows per wave in registers and fit one block per CU
-  const bool one_per_cu = s.vpl == 8 || (step_pass_ok(s, d, mode) && s.vpl >= 4);
+  const bool one_per_cu = s.vpl == 8 || step_pass_ok(s, mode);
   const int64_t cap = grad ? (int64_t)num_cu() * (one_per_cu ? 1 : 16 / nw) : (int64_t)num_cu() * 8;
   if (want > cap) want = cap;
   if (want > kMaxBlocks) want = kMaxBlocks;
@@ -1122,12 +1142,18 @@ hipError_t launch_dense_pass(const PassArgs &a, int mode, int32_t d, int32_t nbl
       default: return launch_pool<64, 8, 2>(a, nblk, st, e0, e1);
     }
   }
-  if (step_pass_ok(s, d, mode)) {
+  if (step_pass_ok(s, mode)) {
     const bool hard = (mode & kHard) != 0;
+    const StepShape p = step_shape(s.vpl, a.count_max);
     switch (s.vpl) {
-      case 1: return launch_step<1, 8, 8>(a, hard, nblk, st, e0, e1);
-      case 2: return launch_step<2, 8, 8>(a, hard, nblk, st, e0, e1);
-      case 4: return launch_step<4, AA_STEP_NW_D1024, AA_STEP_RIF_D1024>(a, hard, nblk, st, e0, e1);
+      case 1:
+        if (p.nw == 16) return launch_step<1, 16, 4>(a, hard, nblk, st, e0, e1);
+        if (p.rif == 2) return launch_step<1, 8, 2>(a, hard, nblk, st, e0, e1);
+        return launch_step<1, 8, 4>(a, hard, nblk, st, e0, e1);
+      case 2:
+        if (p.rif == 2) return launch_step<2, 8, 2>(a, hard, nblk, st, e0, e1);
+        return launch_step<2, 8, 4>(a, hard, nblk, st, e0, e1);
+      case 4: return launch_step<4, 8, 2>(a, hard, nblk, st, e0, e1);
       // (two rows of 8 KB in flight per wave: with four the hard-threshold variant does not fit
       // its registers -- the compiler then parks every arriving row in scratch, one load at a
       // time, 67 us per step instead of 30 -- and the other is 4 % slower at the register limit)
@@ -1136,7 +1162,7 @@ hipError_t launch_dense_pass(const PassArgs &a, int mode, int32_t d, int32_t nbl
   }
   // rows already chosen, a lane group for each: the pass without a loop
   if (!(mode & kPool) && a.count_max <= kRankSelectMax) {
-    if ((int64_t)nblk * waves_per_block(s, d, mode) * (kWave / s.lpr) < a.count_max) return hipErrorInvalidValue;
+    if ((int64_t)nblk * waves_per_block(s, a.count_max, mode) * (kWave / s.lpr) < a.count_max) return hipErrorInvalidValue;
     if (s.lpr == 16) return launch_once<16, 1, 8>(a, mode, nblk, st, e0, e1);
     if (s.lpr == 32) return launch_once<32, 1, 8>(a, mode, nblk, st, e0, e1);
     switch (s.vpl) {

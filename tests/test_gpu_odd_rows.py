@@ -1,5 +1,6 @@
-"""GPU parity of dense rows the aligned register layouts do not take -- wider than 2048, or a width,
-leading dimension or address off 16 bytes -- at the edges of their own kernels' pieces."""
+"""GPU parity of dense rows that do not fill a register layout: rows that end inside one, and rows none
+takes -- wider than 2048, or a width, leading dimension or address off 16 bytes -- at the edges of
+their kernels' pieces."""
 import numpy as np
 import pytest
 import torch
@@ -39,6 +40,45 @@ def test_odd_rows_match_the_oracle(ref, ws, n, d, ld, P):
     y = np.where(r.random(n) < 0.5, 1.0, -1.0).astype(np.float32)
     idx = r.permutation(n)[:P].astype(np.int32)
     sk._run_and_check(ref, ws, ref.Features.dense(X, d=d), dense_features(X, d=d), y, idx, P, d, 0.4)
+
+
+# rows that end inside a 64-lane layout, and pools on both sides of the switches between the numbers
+# of rows a wave requests at once
+@pytest.mark.parametrize("d,P", [(132, 1), (132, 4097), (252, 16_385), (256, 4096), (256, 16_400), (260, 700), (508, 4097),
+                                 (516, 513), (1020, 300), (1028, 400), (2044, 65)])
+def test_whole_step_on_rows_inside_a_layout(ref, d, P):
+    n, big = P + 3, api.Workspace(P + 3, d)
+    dense.test_fused_step_matches_oracle_step(ref, big, n, d, None, P, 0.1)
+    r = dense.rng(7)
+    X = r.standard_normal((n, d)).astype(np.float32)
+    X /= np.linalg.norm(X, axis=1, keepdims=True)
+    y = np.where(r.random(n) < 0.5, 1.0, -1.0).astype(np.float32)
+    idx = r.permutation(n)[:P].astype(np.int32)
+    sk._run_and_check(ref, big, ref.Features.dense(X), dense_features(X), y, idx, P, d, 0.4)
+
+
+@pytest.mark.parametrize("d,P", [(260, 300), (1020, 5000)])
+def test_epoch_on_rows_inside_a_layout_is_its_steps(d, P):
+    """One call per epoch (compaction carried by the next pass) against one call per step: same bits."""
+    n = 3 * P + P // 3
+    g = torch.Generator().manual_seed(d)
+    X = torch.randn(n, d, generator=g)
+    F = api.Features.dense((X / X.norm(dim=1, keepdim=True)).cuda())
+    y = (2.0 * torch.randint(0, 2, (n,), generator=g) - 1.0).cuda()
+    perm = torch.randperm(n, generator=g).to(torch.int32).cuda()
+    T, work = torch.full((1,), 0.3, device="cuda"), api.Workspace(P, d)
+    got = []
+    for calls in ([(0, n)], [(lo, min(P, n - lo)) for lo in range(0, n, P)]):
+        w, phi, b = torch.ones(d, device="cuda"), torch.ones(d, device="cuda"), torch.zeros(1, device="cuda")
+        t = torch.zeros(1, dtype=torch.int32, device="cuda")
+        hist = torch.zeros(4, dtype=torch.int32, device="cuda")
+        ids, loss = torch.zeros(4 * P, dtype=torch.int32, device="cuda"), torch.zeros(4 * P, device="cuda")
+        for lo, count in calls:
+            cfg = api.step_config(0.1, 1e-3, 2.0, 0.3, 0.0, 5, lo // P, T)
+            api.train_epoch(F, y, perm[lo:], count, P, w, phi, b, cfg, t, hist[lo // P:], work, ids[lo:], loss[lo:])
+        got.append((w, phi, b, t, hist, ids, loss))
+    assert all(torch.equal(u, v) for u, v in zip(*got))
+    assert 0 < got[0][4].min() and got[0][4][0] < P
 
 
 @pytest.mark.parametrize("d", [1027, 4097])
