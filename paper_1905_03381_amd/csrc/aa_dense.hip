@@ -1026,6 +1026,12 @@ StepShape step_shape(int vpl, int32_t count) {
   return {8, 2};
 }
 
+// The passes over rows of up to 128 floats (several rows per wave) that keep gradient sums: up to
+// 8192 rows, two at once per lane group in one block per compute unit; beyond that eight in
+// two.  Whole step at d = 128: P = 600 9.2 -> 8.9 us, 8192 11.7 -> 10.1 (hard thresholds 10.3 ->
+// 8.8); with two at once and P = 60,000 24.5 us instead of 19.8.
+constexpr int32_t kNarrowFewRows = 8192;
+
 // Waves per block: passes with gradient sums use one fat block per CU (few block
 // partials); the general 1024-wide pass runs 16 waves of 128 registers, everything else 8.
 int waves_per_block(const Shape &s, int32_t count, int mode) {
@@ -1121,7 +1127,8 @@ int32_t dense_pass_blocks(int32_t d, int32_t count, int mode) {
   if (grad && !(mode & kPool) && count <= kRankSelectMax) return want < 1 ? 1 : (int32_t)want;
   // 16 waves per CU: one block of 16 waves, two of 8 or four of 4; the wide whole-step passes
   // hold several rows per wave in registers and fit one block per CU
-  const bool one_per_cu = s.vpl == 8 || step_pass_ok(s, mode);
+  const bool one_per_cu = s.vpl == 8 || step_pass_ok(s, mode) ||
+                          (s.lpr < kWave && count <= kNarrowFewRows);
   const int64_t cap = grad ? (int64_t)num_cu() * (one_per_cu ? 1 : 16 / nw) : (int64_t)num_cu() * 8;
   if (want > cap) want = cap;
   if (want > kMaxBlocks) want = kMaxBlocks;
@@ -1173,7 +1180,10 @@ hipError_t launch_dense_pass(const PassArgs &a, int mode, int32_t d, int32_t nbl
     }
   }
   if (a.med_init) return hipErrorInvalidValue;  // (only the pass above finds a batch's median)
+  const bool few = a.count_max <= kNarrowFewRows;
+  if (s.lpr == 16 && few) return launch_grad<16, 1, 8, 2>(a, mode, nblk, st, e0, e1);
   if (s.lpr == 16) return launch_grad<16, 1, 8, 8>(a, mode, nblk, st, e0, e1);
+  if (s.lpr == 32 && few) return launch_grad<32, 1, 8, 2>(a, mode, nblk, st, e0, e1);
   if (s.lpr == 32) return launch_grad<32, 1, 8, 8>(a, mode, nblk, st, e0, e1);
   switch (s.vpl) {
     case 1: return launch_grad<64, 1, 8, 8>(a, mode, nblk, st, e0, e1);
