@@ -58,56 +58,58 @@ __device__ inline int count_flags_before(const uint8_t *flags, int j0, int *smem
   return total;
 }
 
-// Compact tile `tile` with a 256-thread block.  `smem` holds at least 8 ints.
+// Compact tile `tile` with a block of NW waves.  `smem` holds at least 8 ints, and NW.
+template <int NW = 4>
 __device__ inline void tile_compact(const CompactArgs &c, int tile, int *smem) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int j0 = tile * kCompactTile;
-  const int seg = j0 + wave * (kCompactTile / 4);
+  constexpr int R = kCompactTile / NW / kWave;  // rounds of 64 flags per wave
+  const int seg = j0 + wave * (kCompactTile / NW);
   // The tile's own loads go out first, then the count of the flags before the tile.  No load
   // sits under a per-element condition (the compiler would wait for each before requesting
   // the next): a position past the pool reads the pool's last element instead, and whether
-  // an array takes part at all is decided once, around its eight loads.
-  uint8_t fl[8];
-  int ids[8];
-  float ls[8];
+  // an array takes part at all is decided once, around its loads.
+  uint8_t fl[R];
+  int ids[R];
+  float ls[R];
   const int last = c.P - 1;  // (a tile exists: P > 0)
 #pragma unroll
-  for (int r = 0; r < 8; ++r) fl[r] = c.flags[min(seg + r * kWave + lane, last)];
+  for (int r = 0; r < R; ++r) fl[r] = c.flags[min(seg + r * kWave + lane, last)];
   if (c.kept_ids && c.idx) {
 #pragma unroll
-    for (int r = 0; r < 8; ++r) ids[r] = c.idx[min(seg + r * kWave + lane, last)];
+    for (int r = 0; r < R; ++r) ids[r] = c.idx[min(seg + r * kWave + lane, last)];
   } else {
 #pragma unroll
-    for (int r = 0; r < 8; ++r) ids[r] = seg + r * kWave + lane;
+    for (int r = 0; r < R; ++r) ids[r] = seg + r * kWave + lane;
   }
   if (c.loss) {
 #pragma unroll
-    for (int r = 0; r < 8; ++r) ls[r] = c.loss_pool[min(seg + r * kWave + lane, last)];
+    for (int r = 0; r < R; ++r) ls[r] = c.loss_pool[min(seg + r * kWave + lane, last)];
   } else {
 #pragma unroll
-    for (int r = 0; r < 8; ++r) ls[r] = 0.f;
+    for (int r = 0; r < R; ++r) ls[r] = 0.f;
   }
   const int prefix = c.tile_off ? c.tile_off[tile] : count_flags_before(c.flags, j0, smem);
 #pragma unroll
-  for (int r = 0; r < 8; ++r)
+  for (int r = 0; r < R; ++r)
     if (seg + r * kWave + lane > last) fl[r] = 0;
-  unsigned long long masks[8];
+  unsigned long long masks[R];
   int wave_total = 0;
 #pragma unroll
-  for (int r = 0; r < 8; ++r) {
+  for (int r = 0; r < R; ++r) {
     masks[r] = __ballot(fl[r] != 0);
     wave_total += __popcll(masks[r]);
   }
   if (lane == 0) smem[wave] = wave_total;
   __syncthreads();
   int running = prefix, total = 0;
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < NW; ++i) {
     const int t = smem[i];
     if (i < wave) running += t;
     total += t;
   }
 #pragma unroll
-  for (int r = 0; r < 8; ++r) {
+  for (int r = 0; r < R; ++r) {
     const unsigned long long m = masks[r];
     if ((m >> lane) & 1ull) {
       const int pos = running + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),

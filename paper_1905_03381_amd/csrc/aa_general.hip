@@ -824,14 +824,18 @@ __global__ __launch_bounds__(256) void k_prepare_general(float *p, size_t count,
   for (size_t c = head + tid; c < (size_t)d; c += stride) wp[c] = make_float2(w[c], phi[c]);
 }
 
-// Folds the gradient sums into the model.  Blocks [0, nh): 16 of the first `head` columns each,
+// Folds the gradient sums into the model.  Blocks [0, nh): 32 of the first `head` columns each,
 // 16 threads per column adding the per-block sums of the pass in a fixed order; blocks after
 // them: the other columns -- one block per bin, which adds the bin's records up in LDS (plus
 // whatever overflowed into the dense accumulators), or with no bins a strided share of the
 // accumulators; then one block per compaction tile.  Every block adds up the per-block kept
 // counts of the pass for itself.
-constexpr int kHeadCols = 16;
-constexpr int kApplyThreads = 256;
+// Eight waves: a bin's owner waits for records, then for its LDS sums, then for its columns, and has a
+// compute unit to itself -- more waves keep more of that in flight, until their barriers and
+// the shares of the blocks with little to do cost more.  Sparse epoch (d = 2^20, pools of 65,536),
+// per step, 4 / 8 / 16 waves: 73.4 / 68.2 / 69.6 us; pools of 8000 35.0 / 31.3 / 34.0.
+constexpr int kApplyWaves = 8, kApplyThreads = kApplyWaves * kWave;
+constexpr int kHeadCols = kApplyThreads / 16;
 static_assert(kGeneralGradBlocks <= kApplyThreads, "one per-block count of the pass per thread");
 
 typedef float f4v __attribute__((ext_vector_type(4), aligned(4)));  // (any float address)
@@ -907,7 +911,7 @@ __device__ __forceinline__ int pass_totals(const ApplyArgs &a, int cnt, float gb
   }
   __syncthreads();
   *gb_out = (s_g[0] + s_g[1]) + (s_g[2] + s_g[3]);
-  const int m_pass = s_m[0] + s_m[1] + s_m[2] + s_m[3];
+  const int m_pass = s_m[0] + s_m[1] + s_m[2] + s_m[3];  // (the counts are in the first four waves)
   return a.m_dev ? min(max(*a.m_dev, 0), a.m_max) : m_pass;
 }
 
@@ -925,10 +929,12 @@ __device__ __forceinline__ int bin_column(int k, int bin, const ApplyArgs &a) {
 // per thread, in registers) is requested before anything is used: one round trip, not five.
 __device__ __forceinline__ void apply_bin(const ApplyArgs &a, int bin, double *s_bin, int *s_m,
                                           float *s_g) {
-  // per thread: kRec records per batch; kCol runs of four columns (a bin's columns come in
-  // groups of at least four neighbours) -- 4 * kCol * kApplyThreads covers any bin of a pass
-  // that updates two vectors, and half of the largest bin of one that updates one
-  constexpr int kRec = 16, kCol = 4;
+  // per thread: kRec records per batch (the first batch is requested before the bin's fill count
+  // is known: 1024 records a bin; with 4096, small pools read megabytes of stale ones); kCol runs
+  // of four columns (a bin's columns come in groups of at least four neighbours) --
+  // 4 * kCol * kApplyThreads covers any bin of a pass that updates two vectors, and half of the
+  // largest bin of one that updates one
+  constexpr int kRec = 2, kCol = 2;
   const int tid = threadIdx.x, cols = a.plan.cols, cap = a.plan.cap;
   const int cnt = tid < a.nblk_pass ? a.blk_cnt[tid] : 0;
   const int fill = (int)min(a.bin_fill[bin], (unsigned long long)cap);
@@ -1083,8 +1089,8 @@ __device__ __forceinline__ void apply_bin(const ApplyArgs &a, int bin, double *s
 __global__ __launch_bounds__(kApplyThreads) void k_apply_general(const ApplyArgs a, int nh, int nrest) {
   __shared__ int s_int[40];
   __shared__ float s_part[2][16][kHeadCols];
-  __shared__ int s_m[4];
-  __shared__ float s_g[4];
+  __shared__ int s_m[kApplyWaves];
+  __shared__ float s_g[kApplyWaves];
   __shared__ double s_bin[kBinColsMax + 1];  // (+1: the odd stride of a single copy)
   // roles by block number: the other columns first (the bin owners have the longest way to
   // go), then the first columns, then the compaction tiles
@@ -1100,7 +1106,7 @@ __global__ __launch_bounds__(kApplyThreads) void k_apply_general(const ApplyArgs
     c.loss = a.loss;
     c.kept_count = a.kept_count;
     c.tile_off = nullptr;
-    tile_compact(c, bid - nh - nrest, s_int);
+    tile_compact<kApplyWaves>(c, bid - nh - nrest, s_int);
     return;
   }
   if (bid < nrest && a.plan.nb > 0) {  // nrest == nb
@@ -1111,7 +1117,7 @@ __global__ __launch_bounds__(kApplyThreads) void k_apply_general(const ApplyArgs
   const int cnt = t < a.nblk_pass ? a.blk_cnt[t] : 0;
   const float gbs = (t < a.nblk_pass && a.phi && a.bias) ? a.blk_gb[t] : 0.f;
   if (hb >= 0) {
-    const int cl = t & (kHeadCols - 1), q = t >> 4;
+    const int cl = t % kHeadCols, q = t / kHeadCols;
     const int k = hb * kHeadCols + cl;
     float sw = 0.f, sp = 0.f;
     // (loads without conditions, so that they are all in flight together; with one updated
