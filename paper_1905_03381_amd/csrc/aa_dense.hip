@@ -14,13 +14,6 @@
 #include "aa_compact.hpp"
 #include "aa_dense.hpp"
 
-#ifndef AA_NW_D1024
-#define AA_NW_D1024 16   // waves per block of the gradient passes at 512 < d <= 1024
-#endif
-#ifndef AA_RIF_D1024
-#define AA_RIF_D1024 1   // rows in flight per wave there
-#endif
-
 // Feature rows are read once per step: non-temporal loads keep them from displacing the
 // model vectors and block partials in L2.
 #ifndef AA_ROW_LOAD
@@ -88,8 +81,7 @@ __device__ __forceinline__ void wave_slot_store(f4 (&acc)[VPL], f4 *slot, int la
 
 template <int LPR, int VPL, int MODE, int NW, int RIF>
 __global__ __launch_bounds__(NW * 64)
-    __attribute__((amdgpu_waves_per_eu((MODE & 3) ? (VPL == 8 ? 2 : 4) : 1,
-                                       (MODE & 3) ? (VPL == 8 ? 2 : 4) : 8))) void k_rows_pass(const PassArgs a) {
+    __attribute__((amdgpu_waves_per_eu((MODE & 3) ? 4 : 1, (MODE & 3) ? 4 : 8))) void k_rows_pass(const PassArgs a) {
   constexpr bool POOL = (MODE & kPool) != 0;
   constexpr bool SVM = (MODE & kSvm) != 0;
   constexpr bool ASSIST = (MODE & kAssist) != 0;
@@ -544,11 +536,11 @@ __global__ __launch_bounds__(NW * 64) void k_rows_once(const PassArgs a) {
   }
 }
 
-// The whole-step pool pass (score, keep, both gradient sums; or the hard-threshold variant)
-// for rows of more than 128 floats.  FULL: the row fills the 64-lane layout exactly (d == 256 VPL);
-// otherwise a piece past the end of the row re-reads its last piece and is masked, so the loads
-// stay unconditional.  Same arithmetic and the same
-// summation order as k_rows_pass; the schedule differs.  A wave requests RIF rows at once and
+// The gradient passes over rows of more than 128 floats: the whole-step pool pass (score, keep, both
+// gradient sums; or the hard-threshold variant) and the Boss / Assistant passes over rows already
+// chosen.  FULL: the row fills the 64-lane layout exactly (d == 256 VPL); otherwise a piece past
+// the end of the row re-reads its last piece and is masked, so the loads stay unconditional.  A
+// wave requests RIF rows at once and
 // nothing sits between those requests and their use that the memory pipeline would have to
 // finish first: every small load that does not depend on the row ids (model vectors,
 // scalars, the flags of the carried compaction) is requested before the ids are waited for,
@@ -556,21 +548,33 @@ __global__ __launch_bounds__(NW * 64) void k_rows_once(const PassArgs a) {
 // keep flag, loss) are collected one per lane and stored once per group of 64 rows, so no
 // store is pending while rows arrive.  Loads return in request order, so row r of a batch
 // is consumed as soon as it is there while rows r+1.. are still on their way.
-template <int VPL, bool HARD, bool FULL, int NW, int RIF>
-__global__ __launch_bounds__(NW * 64)
-    __attribute__((amdgpu_waves_per_eu(NW / 4, NW / 4))) void k_step_pass(const PassArgs a) {
-  constexpr bool ASSIST = !HARD;
+// Without gradient sums (MODE == kPool) it is the generator's half of k_boss_and_draw.
+template <int VPL, int MODE, int NW>
+struct StepLds {
+  static constexpr bool kGrad = (MODE & (kSvm | kAssist)) != 0;
+  static constexpr bool kPhi = ((MODE & kPool) && !(MODE & kHard)) || (MODE & kAssist);
+  static constexpr int kVec = ((MODE & kSvm) ? 1 : 0) + ((MODE & kAssist) ? 1 : 0);
+  int n[NW];
+  float g[NW];
+  int carry[NW];
+  __attribute__((aligned(16))) f4 w[(MODE & kSvm) ? kWave * VPL : 1];
+  f4 phi[kPhi ? kWave * VPL : 1];
+  f4 red[kGrad ? NW * kVec * kWave * VPL : 1];  // one slot per wave and vector
+};
+
+template <int VPL, int MODE, bool FULL, int NW, int RIF>
+__device__ __forceinline__ void step_rows(const PassArgs &a, int bid, int nblk, StepLds<VPL, MODE, NW> &lds) {
+  constexpr bool POOL = (MODE & kPool) != 0;
+  constexpr bool SVM = (MODE & kSvm) != 0;
+  constexpr bool ASSIST = (MODE & kAssist) != 0;
+  constexpr bool HARD = (MODE & kHard) != 0;  // keep by the row's own loss, no Assistant
+  constexpr bool GRAD = SVM || ASSIST;
+  constexpr bool NEED_PHI = (POOL && !HARD) || ASSIST;
   constexpr int ROW4 = kWave * VPL;
-  constexpr int NVEC = ASSIST ? 2 : 1;
+  constexpr int NVEC = (SVM ? 1 : 0) + (ASSIST ? 1 : 0);
   constexpr int NT = NW * 64;
   constexpr int STG = (ROW4 + NT - 1) / NT;
-
-  __shared__ int s_int[NW];
-  __shared__ float s_flt[NW];
-  __shared__ int s_carry[NW];
-  __shared__ f4 s_w[ROW4];
-  __shared__ f4 s_phi[ASSIST ? ROW4 : 1];
-  __shared__ f4 s_red[NW * NVEC * ROW4];  // one slot per wave and vector
+  const float *const model = SVM ? a.w : a.phi;  // (always there)
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const f4 zero4 = {0.f, 0.f, 0.f, 0.f};
@@ -579,9 +583,10 @@ __global__ __launch_bounds__(NW * 64)
 #endif
   AA_STAMP(0);  // entry
 
-  // balanced contiguous chunk of pool positions for this wave
-  const int total = a.count_max;
-  const int nwaves = gridDim.x * NW, gwave = blockIdx.x * NW + wave;
+  // balanced contiguous chunk of pool positions (or of the rows given) for this wave
+  int total = a.count_max;
+  if (!POOL) total = min(max(*a.m_dev, 0), a.count_max);
+  const int nwaves = nblk * NW, gwave = bid * NW + wave;
   const int per = total / nwaves, rem = total % nwaves;
   const int lo = gwave * per + min(gwave, rem);
   const int hi = lo + per + (gwave < rem ? 1 : 0);
@@ -592,34 +597,36 @@ __global__ __launch_bounds__(NW * 64)
   // ---- Requests that depend on nothing, all unconditional: a load under a condition would
   // make every later wait for an older load a wait for everything (the pending counts of the
   // two paths are merged pessimistically), so absent inputs read a stand-in address (the
-  // start of w, which always holds 132 floats) and indices are clamped; what was read for
-  // nothing is dropped by a select.
-  const int32_t *stand_in = reinterpret_cast<const int32_t *>(a.w);
-  const int32_t *rows_p = a.rows ? a.rows : stand_in;
+  // start of a model vector, which always holds 132 floats) and indices are clamped; what was
+  // read for nothing is dropped by a select.
+  const int32_t *stand_in = reinterpret_cast<const int32_t *>(model);
   const int in_group = min(lane, max(cnt, 1) - 1);
-  int row_l = rows_p[a.rows && cnt > 0 ? base + in_group : 0];
+  const bool listed = a.rows != nullptr && cnt > 0;
+  int row_l = (listed ? a.rows : stand_in)[listed ? base + in_group : 0];
   if (!a.rows) row_l = base + in_group;
+  float lin_l = 0.f;  // Boss losses that come with the rows
+  if (ASSIST && !SVM) lin_l = (cnt > 0 ? a.loss_in : model)[cnt > 0 ? base + in_group : 0];
 
-  const bool carry = a.prev.flags != nullptr && (int)blockIdx.x * kWave < a.prev.P;
-  const int cj0 = blockIdx.x * kWave;     // this block places positions [cj0, cj0 + 64)
+  const bool carry = POOL && GRAD && a.prev.flags != nullptr && bid * kWave < a.prev.P;
+  const int cj0 = bid * kWave;     // this block places positions [cj0, cj0 + 64)
   const int n16 = carry ? (cj0 >> 4) : 0;  // 16-byte pieces of flags before them
   const uint4 *p16 = n16 > 0 ? reinterpret_cast<const uint4 *>(a.prev.flags)
-                             : reinterpret_cast<const uint4 *>(a.w);
+                             : reinterpret_cast<const uint4 *>(model);
   uint4 carry_v = p16[min((int)threadIdx.x, max(n16, 1) - 1)];
   const int cpos = carry ? min(cj0 + lane, a.prev.P - 1) : 0;
-  uint8_t carry_flag = (carry ? a.prev.flags : reinterpret_cast<const uint8_t *>(a.w))[cpos];
+  uint8_t carry_flag = (carry ? a.prev.flags : reinterpret_cast<const uint8_t *>(model))[cpos];
   int carry_id = ((carry && a.prev.idx) ? a.prev.idx : stand_in)[a.prev.idx ? cpos : 0];
-  float carry_loss = ((carry && a.prev.loss) ? a.prev.loss_pool : a.w)[a.prev.loss ? cpos : 0];
+  float carry_loss = ((carry && a.prev.loss) ? a.prev.loss_pool : model)[a.prev.loss ? cpos : 0];
   f4 st_w[STG], st_p[STG];
 #pragma unroll
   for (int q = 0; q < STG; ++q) {
     const int c = min(q * NT + (int)threadIdx.x, FULL ? ROW4 - 1 : a.d4 - 1);
-    st_w[q] = reinterpret_cast<const f4 *>(a.w)[c];
-    st_p[q] = reinterpret_cast<const f4 *>(ASSIST ? a.phi : a.w)[c];
+    if (SVM) st_w[q] = reinterpret_cast<const f4 *>(a.w)[c];
+    if (NEED_PHI) st_p[q] = reinterpret_cast<const f4 *>(a.phi)[c];
   }
-  float b = (ASSIST && a.bias ? a.bias : a.w)[0];
-  if (!(ASSIST && a.bias)) b = 0.f;
-  float T = *a.T;
+  float b = (NEED_PHI && a.bias ? a.bias : model)[0];
+  if (!(NEED_PHI && a.bias)) b = 0.f;
+  float T = (ASSIST || HARD) ? *a.T : 0.f;
 
   // Everything above is there after one memory round trip.  It is all consumed here, before
   // the rows are requested: the model vectors go to LDS, the carried flags are counted, and
@@ -630,6 +637,7 @@ __global__ __launch_bounds__(NW * 64)
   arrived(carry_loss);
   arrived(b);
   arrived(T);
+  if (ASSIST && !SVM) arrived(lin_l);
   AA_STAMP(1);  // ids, model, scalars, carried flags are there
   int carry_cnt = 0;
   if ((int)threadIdx.x < n16)
@@ -645,13 +653,13 @@ __global__ __launch_bounds__(NW * 64)
   for (int q = 0; q < STG; ++q) {
     const int c = q * NT + threadIdx.x;
     if (c < ROW4) {  // (columns past the row: any finite value would do, the row is zero there)
-      s_w[c] = FULL || c < a.d4 ? st_w[q] : zero4;
-      if (ASSIST) s_phi[c] = FULL || c < a.d4 ? st_p[q] : zero4;
+      if (SVM) lds.w[c] = FULL || c < a.d4 ? st_w[q] : zero4;
+      if (NEED_PHI) lds.phi[c] = FULL || c < a.d4 ? st_p[q] : zero4;
     }
   }
   if (carry) {
     carry_cnt = wave_sum_int(carry_cnt);
-    if (lane == 0) s_carry[wave] = carry_cnt;
+    if (lane == 0) lds.carry[wave] = carry_cnt;
   }
 
   // ---- requests that need the ids: the labels, then the rows; nothing is requested after
@@ -676,15 +684,15 @@ __global__ __launch_bounds__(NW * 64)
   AA_STAMP(2);  // past the start-up barrier
   float y_l = 0.f, u_l = 2.f;
   if (cnt > 0) {
-    y_l = a.y[row_l];
+    if (SVM) y_l = a.y[row_l];
     issue_rows(0);
-    if (!HARD) u_l = keep_uniform(a.key, (uint32_t)(base + in_group));
+    if (POOL && !HARD) u_l = keep_uniform(a.key, (uint32_t)(base + in_group));
   }
   AA_STAMP(3);  // rows requested, draws made
   if (carry && wave == NW - 1) {
     int before = 0;
 #pragma unroll
-    for (int i = 0; i < NW; ++i) before += s_carry[i];
+    for (int i = 0; i < NW; ++i) before += lds.carry[i];
     const unsigned long long mask = carry_mask;
     if (carry_flag != 0) {
       const int pos = before + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
@@ -723,28 +731,31 @@ __global__ __launch_bounds__(NW * 64)
           for (int v = VPL / 2; v < VPL; ++v)
             if (v * kWave + lane >= a.d4) x[r][v] = zero4;
         }
-        if (ASSIST) {
+        if (NEED_PHI) {
           float dp = 0.f;
 #pragma unroll
-          for (int v = 0; v < VPL; ++v) dp = dot4(x[r][v], s_phi[v * kWave + lane], dp);
+          for (int v = 0; v < VPL; ++v) dp = dot4(x[r][v], lds.phi[v * kWave + lane], dp);
           dp = row_group_sum<kWave>(dp, lane);
           s = dp + b;
           g = sigmoidf_(s);
-          const float u = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(u_l), src));
-          keep = live && keep_decision(u, g, a.gamma, a.one_minus_gamma);
+          if (POOL) keep = live && keep_decision(lane_read(u_l, src), g, a.gamma, a.one_minus_gamma);
         }
-        const float yy = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(y_l), src));
-        if (HARD || keep) {
-          float dw = 0.f;
+        const float yy = SVM ? lane_read(y_l, src) : 0.f;
+        if (GRAD && (HARD || keep)) {
+          if (SVM) {
+            float dw = 0.f;
 #pragma unroll
-          for (int v = 0; v < VPL; ++v) dw = dot4(x[r][v], s_w[v * kWave + lane], dw);
-          dw = row_group_sum<kWave>(dw, lane);
-          const float marg = yy * dw;
-          loss = fmaxf(0.f, 1.f - marg);
-          if (HARD) keep = live && loss > T;  // shrinking by the objective value itself
-          const float cw = (keep && marg < 1.f) ? yy : 0.f;  // -d hinge / d margin, times y
+            for (int v = 0; v < VPL; ++v) dw = dot4(x[r][v], lds.w[v * kWave + lane], dw);
+            dw = row_group_sum<kWave>(dw, lane);
+            const float marg = yy * dw;
+            loss = fmaxf(0.f, 1.f - marg);
+            if (HARD) keep = live && loss > T;  // shrinking by the objective value itself
+            const float cw = (keep && marg < 1.f) ? yy : 0.f;  // -d hinge / d margin, times y
 #pragma unroll
-          for (int v = 0; v < VPL; ++v) gw[v] = axpy4(cw, x[r][v], gw[v]);
+            for (int v = 0; v < VPL; ++v) gw[v] = axpy4(cw, x[r][v], gw[v]);
+          } else {
+            loss = lane_read(lin_l, src);
+          }
           if (ASSIST) {
             const float z = loss > T ? 1.f : 0.f;    // label: Boss loss above the threshold
             const float resid = g - z;               // d cross-entropy / d logit (kept rows only)
@@ -768,19 +779,20 @@ __global__ __launch_bounds__(NW * 64)
     }
     if (lane < cnt) {
       const int j = base + lane;
-      if (ASSIST && a.logit) a.logit[j] = o_logit;
-      if (ASSIST && a.prob) a.prob[j] = o_prob;
-      if (a.flags) a.flags[j] = (uint8_t)o_keep;
-      if ((HARD || o_keep) && a.loss_out) a.loss_out[j] = o_loss;
+      if (POOL && !HARD && a.logit) a.logit[j] = o_logit;
+      if (POOL && !HARD && a.prob) a.prob[j] = o_prob;
+      if (POOL && a.flags) a.flags[j] = (uint8_t)o_keep;
+      if (SVM && (HARD || o_keep) && a.loss_out) a.loss_out[j] = o_loss;
     }
     base += kWave;
     cnt = min(kWave, hi - base);
     if (cnt > 0) {
       const int in_next = min(lane, cnt - 1);
       row_l = a.rows ? a.rows[base + in_next] : base + in_next;
-      y_l = a.y[row_l];
+      if (SVM) y_l = a.y[row_l];
+      if (ASSIST && !SVM) lin_l = a.loss_in[base + in_next];
       issue_rows(0);
-      if (!HARD) u_l = keep_uniform(a.key, (uint32_t)(base + in_next));
+      if (POOL && !HARD) u_l = keep_uniform(a.key, (uint32_t)(base + in_next));
     }
   }
 
@@ -788,44 +800,52 @@ __global__ __launch_bounds__(NW * 64)
   // Block reduction behind a single barrier: every wave drops its sums into its own LDS
   // slot, then one thread per 128-bit column adds the slots in wave order and stores the
   // block's partial vectors.
-  f4 *slot = s_red + wave * NVEC * ROW4;
+  if (GRAD) {
+    f4 *slot = lds.red + wave * NVEC * ROW4;
 #pragma unroll
-  for (int v = 0; v < VPL; ++v) slot[v * kWave + lane] = gw[v];
-  if (ASSIST) {
-#pragma unroll
-    for (int v = 0; v < VPL; ++v) slot[ROW4 + v * kWave + lane] = gp[v];
-  }
-  if (lane == 0) {
-    s_int[wave] = kept;
-    s_flt[wave] = gb;
-  }
-  __syncthreads();
-  AA_STAMP(6);  // past the reduction barrier
-  f4 *part = reinterpret_cast<f4 *>(a.partial) + (size_t)blockIdx.x * NVEC * ROW4;
-  for (int c = threadIdx.x; c < NVEC * ROW4; c += NT) {
-    f4 t = s_red[c];
-#pragma unroll
-    for (int q = 1; q < NW; ++q) t += s_red[q * NVEC * ROW4 + c];
-    part[c] = t;
-  }
-  if (threadIdx.x == 0) {
-    int ks = 0;
-    float gs = 0.f;
-    for (int i = 0; i < NW; ++i) {
-      ks += s_int[i];
-      gs += s_flt[i];
+    for (int v = 0; v < VPL; ++v) {
+      if (SVM) slot[v * kWave + lane] = gw[v];
+      if (ASSIST) slot[(SVM ? ROW4 : 0) + v * kWave + lane] = gp[v];
     }
-    a.blk_cnt[blockIdx.x] = ks;
-    a.blk_gb[blockIdx.x] = gs;
+    if (lane == 0) {
+      lds.n[wave] = kept;
+      lds.g[wave] = gb;
+    }
+    __syncthreads();
+    AA_STAMP(6);  // past the reduction barrier
+    f4 *part = reinterpret_cast<f4 *>(a.partial) + (size_t)bid * NVEC * ROW4;
+    for (int c = threadIdx.x; c < NVEC * ROW4; c += NT) {
+      f4 t = lds.red[c];
+#pragma unroll
+      for (int q = 1; q < NW; ++q) t += lds.red[q * NVEC * ROW4 + c];
+      part[c] = t;
+    }
+    if (threadIdx.x == 0) {
+      int ks = 0;
+      float gs = 0.f;
+      for (int i = 0; i < NW; ++i) {
+        ks += lds.n[i];
+        gs += lds.g[i];
+      }
+      a.blk_cnt[bid] = ks;
+      a.blk_gb[bid] = gs;
+    }
   }
-  if (a.t_upd && blockIdx.x == 0 && threadIdx.x == 0) *a.t_snap = *a.t_upd;
+  if (GRAD && a.t_upd && bid == 0 && threadIdx.x == 0) *a.t_snap = *a.t_upd;
 #ifdef AA_PHASE_TRACE
   AA_STAMP(7);  // partials stored
-  if (a.trace && lane == 0) {
-    unsigned long long *tr = a.trace + ((size_t)blockIdx.x * NW + wave) * kTraceStamps;
+  if (POOL && GRAD && a.trace && lane == 0) {
+    unsigned long long *tr = a.trace + ((size_t)bid * NW + wave) * kTraceStamps;
     for (int k = 0; k < kTraceStamps; ++k) tr[k] = t_stamp[k];
   }
 #endif
+}
+
+template <int VPL, int MODE, bool FULL, int NW, int RIF>
+__global__ __launch_bounds__(NW * 64)
+    __attribute__((amdgpu_waves_per_eu(NW / 4, NW / 4))) void k_step_pass(const PassArgs a) {
+  __shared__ StepLds<VPL, MODE, NW> lds;
+  step_rows<VPL, MODE, FULL, NW, RIF>(a, blockIdx.x, gridDim.x, lds);
 }
 
 #ifndef AA_FIN_COLS4
@@ -1002,11 +1022,8 @@ Shape pick_shape(int32_t d) {
   return {64, 8};
 }
 
-// The whole-step pool passes take k_step_pass on every 64-lane layout.
-bool step_pass_ok(const Shape &s, int mode) {
-  const bool whole = mode == (kPool | kSvm | kAssist) || mode == (kPool | kSvm | kHard);
-  return whole && s.lpr == kWave;
-}
+// The gradient passes take k_step_pass on every 64-lane layout.
+bool step_pass_ok(const Shape &s, int mode) { return (mode & (kSvm | kAssist)) != 0 && s.lpr == kWave; }
 
 // Waves per block and rows requested at once per wave of k_step_pass; one block per compute unit.
 // A batch costs the same whether its slots hold rows or not, and two blocks per compute unit
@@ -1032,13 +1049,11 @@ StepShape step_shape(int vpl, int32_t count) {
 // 8.8); with two at once and P = 60,000 24.5 us instead of 19.8.
 constexpr int32_t kNarrowFewRows = 8192;
 
-// Waves per block: passes with gradient sums use one fat block per CU (few block
-// partials); the general 1024-wide pass runs 16 waves of 128 registers, everything else 8.
+// Waves per block.
 int waves_per_block(const Shape &s, int32_t count, int mode) {
   const bool grad = (mode & (kSvm | kAssist)) != 0;
   if (!grad) return 4;
-  if (step_pass_ok(s, mode)) return step_shape(s.vpl, count).nw;
-  return s.vpl == 4 ? AA_NW_D1024 : 8;
+  return step_pass_ok(s, mode) ? step_shape(s.vpl, count).nw : 8;
 }
 
 template <int LPR, int VPL, int NW, int RIF>
@@ -1055,17 +1070,13 @@ hipError_t launch_grad(const PassArgs &a, int mode, int nblk, hipStream_t st, hi
     case kSvm | kAssist:
       launch_stamped((k_rows_pass<LPR, VPL, kSvm | kAssist, NW, RIF>), grid, block, st, e0, e1, a);
       break;
+    case kPool | kSvm | kAssist:
+      launch_stamped((k_rows_pass<LPR, VPL, kPool | kSvm | kAssist, NW, RIF>), grid, block, st, e0, e1, a);
+      break;
+    case kPool | kSvm | kHard:
+      launch_stamped((k_rows_pass<LPR, VPL, kPool | kSvm | kHard, NW, RIF>), grid, block, st, e0, e1, a);
+      break;
     default:
-      if constexpr (LPR < kWave) {  // (the others take k_step_pass)
-        if (mode == (kPool | kSvm | kAssist)) {
-          launch_stamped((k_rows_pass<LPR, VPL, kPool | kSvm | kAssist, NW, RIF>), grid, block, st, e0, e1, a);
-          break;
-        }
-        if (mode == (kPool | kSvm | kHard)) {
-          launch_stamped((k_rows_pass<LPR, VPL, kPool | kSvm | kHard, NW, RIF>), grid, block, st, e0, e1, a);
-          break;
-        }
-      }
       return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -1083,20 +1094,36 @@ hipError_t launch_once(const PassArgs &a, int mode, int nblk, hipStream_t st, hi
   return hipGetLastError();
 }
 
-template <int VPL, int NW, int RIF>
-hipError_t launch_step(const PassArgs &a, bool hard, int nblk, hipStream_t st, hipEvent_t e0,
-                       hipEvent_t e1) {
+template <int VPL, bool FULL, int NW, int RIF>
+hipError_t launch_step_mode(const PassArgs &a, int mode, int nblk, hipStream_t st, hipEvent_t e0,
+                            hipEvent_t e1) {
   const dim3 grid(nblk), block(NW * 64);
-  const bool full = a.d4 == kWave * VPL;
-  if (hard && full)
-    launch_stamped((k_step_pass<VPL, true, true, NW, RIF>), grid, block, st, e0, e1, a);
-  else if (hard)
-    launch_stamped((k_step_pass<VPL, true, false, NW, RIF>), grid, block, st, e0, e1, a);
-  else if (full)
-    launch_stamped((k_step_pass<VPL, false, true, NW, RIF>), grid, block, st, e0, e1, a);
-  else
-    launch_stamped((k_step_pass<VPL, false, false, NW, RIF>), grid, block, st, e0, e1, a);
+  switch (mode) {
+    case kSvm:
+      launch_stamped((k_step_pass<VPL, kSvm, FULL, NW, RIF>), grid, block, st, e0, e1, a);
+      break;
+    case kAssist:
+      launch_stamped((k_step_pass<VPL, kAssist, FULL, NW, RIF>), grid, block, st, e0, e1, a);
+      break;
+    case kSvm | kAssist:
+      launch_stamped((k_step_pass<VPL, kSvm | kAssist, FULL, NW, RIF>), grid, block, st, e0, e1, a);
+      break;
+    case kPool | kSvm | kAssist:
+      launch_stamped((k_step_pass<VPL, kPool | kSvm | kAssist, FULL, NW, RIF>), grid, block, st, e0, e1, a);
+      break;
+    case kPool | kSvm | kHard:
+      launch_stamped((k_step_pass<VPL, kPool | kSvm | kHard, FULL, NW, RIF>), grid, block, st, e0, e1, a);
+      break;
+    default:
+      return hipErrorInvalidValue;
+  }
   return hipGetLastError();
+}
+
+template <int VPL, int NW, int RIF>
+hipError_t launch_step(const PassArgs &a, int mode, int nblk, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
+  return a.d4 == kWave * VPL ? launch_step_mode<VPL, true, NW, RIF>(a, mode, nblk, st, e0, e1)
+                             : launch_step_mode<VPL, false, NW, RIF>(a, mode, nblk, st, e0, e1);
 }
 
 template <int LPR, int VPL, int RIF>
@@ -1125,11 +1152,9 @@ int32_t dense_pass_blocks(int32_t d, int32_t count, int mode) {
   int64_t want = ((int64_t)count + rows_per_block - 1) / rows_per_block;
   // a small batch of chosen rows: a lane group for each row, however few compute units there are
   if (grad && !(mode & kPool) && count <= kRankSelectMax) return want < 1 ? 1 : (int32_t)want;
-  // 16 waves per CU: one block of 16 waves, two of 8 or four of 4; the wide whole-step passes
-  // hold several rows per wave in registers and fit one block per CU
-  const bool one_per_cu = s.vpl == 8 || step_pass_ok(s, mode) ||
-                          (s.lpr < kWave && count <= kNarrowFewRows);
-  const int64_t cap = grad ? (int64_t)num_cu() * (one_per_cu ? 1 : 16 / nw) : (int64_t)num_cu() * 8;
+  // one block per compute unit, two for many narrow rows; the scoring pass has no sums to leave
+  const bool one_per_cu = step_pass_ok(s, mode) || count <= kNarrowFewRows;
+  const int64_t cap = (int64_t)num_cu() * (!grad ? 8 : one_per_cu ? 1 : 2);
   if (want > cap) want = cap;
   if (want > kMaxBlocks) want = kMaxBlocks;
   if (want < 1) want = 1;
@@ -1149,24 +1174,6 @@ hipError_t launch_dense_pass(const PassArgs &a, int mode, int32_t d, int32_t nbl
       default: return launch_pool<64, 8, 2>(a, nblk, st, e0, e1);
     }
   }
-  if (step_pass_ok(s, mode)) {
-    const bool hard = (mode & kHard) != 0;
-    const StepShape p = step_shape(s.vpl, a.count_max);
-    switch (s.vpl) {
-      case 1:
-        if (p.nw == 16) return launch_step<1, 16, 4>(a, hard, nblk, st, e0, e1);
-        if (p.rif == 2) return launch_step<1, 8, 2>(a, hard, nblk, st, e0, e1);
-        return launch_step<1, 8, 4>(a, hard, nblk, st, e0, e1);
-      case 2:
-        if (p.rif == 2) return launch_step<2, 8, 2>(a, hard, nblk, st, e0, e1);
-        return launch_step<2, 8, 4>(a, hard, nblk, st, e0, e1);
-      case 4: return launch_step<4, 8, 2>(a, hard, nblk, st, e0, e1);
-      // (two rows of 8 KB in flight per wave: with four the hard-threshold variant does not fit
-      // its registers -- the compiler then parks every arriving row in scratch, one load at a
-      // time, 67 us per step instead of 30 -- and the other is 4 % slower at the register limit)
-      default: return launch_step<8, 8, 2>(a, hard, nblk, st, e0, e1);
-    }
-  }
   // rows already chosen, a lane group for each: the pass without a loop
   if (!(mode & kPool) && a.count_max <= kRankSelectMax) {
     if ((int64_t)nblk * waves_per_block(s, a.count_max, mode) * (kWave / s.lpr) < a.count_max) return hipErrorInvalidValue;
@@ -1175,22 +1182,33 @@ hipError_t launch_dense_pass(const PassArgs &a, int mode, int32_t d, int32_t nbl
     switch (s.vpl) {
       case 1: return launch_once<64, 1, 8>(a, mode, nblk, st, e0, e1);
       case 2: return launch_once<64, 2, 8>(a, mode, nblk, st, e0, e1);
-      case 4: return launch_once<64, 4, AA_NW_D1024>(a, mode, nblk, st, e0, e1);
+      case 4: return launch_once<64, 4, 8>(a, mode, nblk, st, e0, e1);
       default: return launch_once<64, 8, 8>(a, mode, nblk, st, e0, e1);
     }
   }
   if (a.med_init) return hipErrorInvalidValue;  // (only the pass above finds a batch's median)
+  if (step_pass_ok(s, mode)) {
+    const StepShape p = step_shape(s.vpl, a.count_max);
+    switch (s.vpl) {
+      case 1:
+        if (p.nw == 16) return launch_step<1, 16, 4>(a, mode, nblk, st, e0, e1);
+        if (p.rif == 2) return launch_step<1, 8, 2>(a, mode, nblk, st, e0, e1);
+        return launch_step<1, 8, 4>(a, mode, nblk, st, e0, e1);
+      case 2:
+        if (p.rif == 2) return launch_step<2, 8, 2>(a, mode, nblk, st, e0, e1);
+        return launch_step<2, 8, 4>(a, mode, nblk, st, e0, e1);
+      case 4: return launch_step<4, 8, 2>(a, mode, nblk, st, e0, e1);
+      // (two rows of 8 KB in flight per wave: with four the hard-threshold variant does not fit
+      // its registers -- the compiler then parks every arriving row in scratch, one load at a
+      // time, 67 us per step instead of 30 -- and the other is 4 % slower at the register limit)
+      default: return launch_step<8, 8, 2>(a, mode, nblk, st, e0, e1);
+    }
+  }
   const bool few = a.count_max <= kNarrowFewRows;
   if (s.lpr == 16 && few) return launch_grad<16, 1, 8, 2>(a, mode, nblk, st, e0, e1);
   if (s.lpr == 16) return launch_grad<16, 1, 8, 8>(a, mode, nblk, st, e0, e1);
-  if (s.lpr == 32 && few) return launch_grad<32, 1, 8, 2>(a, mode, nblk, st, e0, e1);
-  if (s.lpr == 32) return launch_grad<32, 1, 8, 8>(a, mode, nblk, st, e0, e1);
-  switch (s.vpl) {
-    case 1: return launch_grad<64, 1, 8, 8>(a, mode, nblk, st, e0, e1);
-    case 2: return launch_grad<64, 2, 8, 8>(a, mode, nblk, st, e0, e1);
-    case 4: return launch_grad<64, 4, AA_NW_D1024, AA_RIF_D1024>(a, mode, nblk, st, e0, e1);
-    default: return launch_grad<64, 8, 8, 2>(a, mode, nblk, st, e0, e1);
-  }
+  if (few) return launch_grad<32, 1, 8, 2>(a, mode, nblk, st, e0, e1);
+  return launch_grad<32, 1, 8, 8>(a, mode, nblk, st, e0, e1);
 }
 
 hipError_t launch_dense_finalize(const FinalizeArgs &a, hipStream_t st) {
