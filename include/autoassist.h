@@ -58,8 +58,9 @@ extern "C" {
 
 /* The feature side of the training set D = {x_i, y_i} (Algorithm 1, input).
  * Dense: x is row-major [n, ld] with ld >= d (elements).  The fast kernels need
- * x 16-byte aligned, ld % 4 == 0, d % 4 == 0 and d <= 2048; anything else runs
- * on slower general kernels, not an error.
+ * x 16-byte aligned, ld % 4 == 0, d % 4 == 0 and d <= 2048; other rows of 1025 to
+ * 8192 columns have a pass of their own, anything else runs on slower general
+ * kernels, not an error.
  * CSR: rowptr[n+1], col[nnz], val[nnz]; val == NULL means every stored entry
  * is 1 (token lists).  Duplicate column ids within a row are allowed and add.
  * Exactly one of the two layouts is read, chosen by `layout`. */
@@ -326,20 +327,19 @@ int32_t aa_sk_epoch(const aa_features *F, const float *y, const int32_t *perm, i
                     size_t ws_bytes, void *stream);
 
 /* ---- The asynchronous Boss / Assistant schedule of Section 5.3 in a deterministic
- * form, on two streams.  Pool s is perm[s*P : min((s+1)*P, n_perm)].  The
- * generator (stream_gen) makes batch s -- score, keep draw with Philox step
+ * form.  Pool s is perm[s*P : min((s+1)*P, n_perm)].  The
+ * generator makes batch s -- score, keep draw with Philox step
  * cfg->step + s, stable compaction to kept ids -- with the Assistant as it stood
  * after max(0, s - staleness) updates, so `staleness` batches wait in the Boss
- * queue while the Assistant keeps learning.  The Boss (stream_boss), tick s: SVM
+ * queue while the Assistant keeps learning.  The Boss, tick s: SVM
  * step on batch s (losses at the pre-update w, lr_t = cfg->lr / sqrt(t_upd) as in
  * aa_train_epoch), then the Assistant update from those losses at its current
- * parameters.  Generation of batch s + staleness overlaps Boss tick s; events
- * order the two streams, the result does not depend on timing.  staleness = 0 is
- * the synchronous schedule (the generator then waits for every Boss tick).
- * On return all work is enqueued; the last Boss tick waits for every generator
- * launch, so synchronising stream_boss is enough.  The caller makes its inputs
- * visible to stream_boss; stream_gen must be a different stream with no
- * unrelated work pending.  0 <= staleness <= 15.
+ * parameters.  The scoring of batch s + staleness shares a launch with Boss tick s
+ * where the rows take a 64-lane register layout; the result does not depend on
+ * timing.  staleness = 0 is the synchronous schedule.
+ * All work is enqueued on stream_boss, so synchronising it is enough, and the
+ * caller makes its inputs visible to stream_boss.  stream_gen must be a
+ * different stream; nothing is put on it.  0 <= staleness <= 15.
  * kept_hist[steps] (may be NULL): kept count of each tick.  kept_ids_hist
  * [steps][P] (may be NULL): the kept ids of each batch, row s holding
  * kept_hist[s] entries.  ws must hold aa_pipeline_workspace_bytes(P, d,

@@ -195,46 +195,51 @@ size_t grad_bytes_for(const PassSpec &s) {
   return general_acc_bytes(s.F->d, s.count_max);
 }
 
+// What the kernels for dense rows in registers are told (wide: k_wide_pass).
+PassArgs dense_args(const PassSpec &s, const Ws &ws, bool wide) {
+  PassArgs a{};
+  a.x = s.F->x;
+  a.ld = s.F->ld;
+  a.d4 = s.F->d / 4;
+  a.d = s.F->d;
+  a.d_pad = wide ? wide_d_pad(s.F->d) : dense_d_pad(s.F->d);
+  a.y = s.y;
+  a.rows = s.rows;
+  a.count_max = s.count_max;
+  a.m_dev = s.m_dev;
+  a.w = s.w;
+  a.phi = s.phi;
+  a.bias = s.bias;
+  a.T = s.T;
+  a.gamma = s.gamma;
+  a.one_minus_gamma = 1.0f - s.gamma;
+  a.key = make_draw_key(s.seed, s.step);
+  a.do_keep = s.do_keep;
+  a.logit = s.logit;
+  a.prob = s.prob;
+  a.flags = s.flags;
+  a.loss_out = s.loss_out;
+  a.loss_in = s.loss_in;
+  a.partial = reinterpret_cast<float *>(ws.grad);
+  a.blk_cnt = ws.blk_cnt;
+  a.blk_gb = ws.blk_gb;
+  a.t_upd = s.t_upd;
+  a.t_snap = ws.ctl + kCtlUpdateSnapshot;
+  a.prev = s.prev;
+  a.med_init = s.med_init;
+  a.med_momentum = s.med_momentum;
+  a.T_next = reinterpret_cast<float *>(ws.ctl + kCtlThresholdNext);
+#ifdef AA_PHASE_TRACE
+  a.trace = g_phase_trace;
+#endif
+  return a;
+}
+
 // Launch the pass (and, for the general family, the accumulator clear before it).
 hipError_t run_pass(const PassSpec &s, const Ws &ws, int32_t *nblk_out, hipStream_t st) {
-  const float omg = 1.0f - s.gamma;
   const bool wide = use_wide(s);
   if (wide || use_fast(s)) {
-    PassArgs a{};
-    a.x = s.F->x;
-    a.ld = s.F->ld;
-    a.d4 = s.F->d / 4;
-    a.d = s.F->d;
-    a.d_pad = wide ? wide_d_pad(s.F->d) : dense_d_pad(s.F->d);
-    a.y = s.y;
-    a.rows = s.rows;
-    a.count_max = s.count_max;
-    a.m_dev = s.m_dev;
-    a.w = s.w;
-    a.phi = s.phi;
-    a.bias = s.bias;
-    a.T = s.T;
-    a.gamma = s.gamma;
-    a.one_minus_gamma = omg;
-    a.key = make_draw_key(s.seed, s.step);
-    a.do_keep = s.do_keep;
-    a.logit = s.logit;
-    a.prob = s.prob;
-    a.flags = s.flags;
-    a.loss_out = s.loss_out;
-    a.loss_in = s.loss_in;
-    a.partial = reinterpret_cast<float *>(ws.grad);
-    a.blk_cnt = ws.blk_cnt;
-    a.blk_gb = ws.blk_gb;
-    a.t_upd = s.t_upd;
-    a.t_snap = ws.ctl + kCtlUpdateSnapshot;
-    a.prev = s.prev;
-    a.med_init = s.med_init;
-    a.med_momentum = s.med_momentum;
-    a.T_next = reinterpret_cast<float *>(ws.ctl + kCtlThresholdNext);
-#ifdef AA_PHASE_TRACE
-    a.trace = g_phase_trace;
-#endif
+    const PassArgs a = dense_args(s, ws, wide);
     if (wide) {
       *nblk_out = wide_pass_blocks(s.count_max);
       const Hook hook;
@@ -276,7 +281,7 @@ hipError_t run_pass(const PassSpec &s, const Ws &ws, int32_t *nblk_out, hipStrea
   a.bias = s.bias;
   a.T = s.T;
   a.gamma = s.gamma;
-  a.one_minus_gamma = omg;
+  a.one_minus_gamma = 1.0f - s.gamma;
   a.key = make_draw_key(s.seed, s.step);
   a.do_keep = s.do_keep;
   a.logit = s.logit;
@@ -310,8 +315,6 @@ struct UpdateSpec {
   float lambda, lr, lr_a, l2_a;
   int32_t *t_upd;
   int32_t *kept_hist;
-  float *phi_copy;   // optional second destination of the updated Assistant
-  float *bias_copy;
   // compaction of a pool pass (flags == NULL: none)
   const uint8_t *flags;
   int32_t P;
@@ -349,8 +352,6 @@ hipError_t run_update(const PassSpec &s, const UpdateSpec &u, const Ws &ws, int3
     f.l2_a = u.l2_a;
     f.t_upd = u.t_upd;
     f.kept_hist = u.kept_hist;
-    f.phi_copy = u.phi_copy;
-    f.bias_copy = u.bias_copy;
     f.t_snap = ws.ctl + kCtlUpdateSnapshot;
     if (s.med_init) {
       f.T_next = reinterpret_cast<const float *>(ws.ctl + kCtlThresholdNext);
@@ -398,8 +399,6 @@ hipError_t run_update(const PassSpec &s, const UpdateSpec &u, const Ws &ws, int3
   p.lr_a = u.lr_a;
   p.l2_a = u.l2_a;
   p.kept_hist = u.kept_hist;
-  p.phi_copy = u.phi_copy;
-  p.bias_copy = u.bias_copy;
   p.flags = u.flags;
   p.P = u.P;
   p.idx = u.idx;
@@ -539,15 +538,15 @@ int32_t fused_step_impl(const aa_features *F, const float *y, const int32_t *idx
   return rc;
 }
 
-// Extra workspace of the two-stream pipeline behind the common layout: `ring` batch slots
-// (kept ids + kept count) and `ring` Assistant snapshots (phi, then the bias).
+// Extra workspace of the stale pipeline behind the common layout: `ring` batch slots (kept ids +
+// kept count), and room for as many copies of the Assistant, which callers have always provided
+// and the schedule no longer uses.
 struct PipeWs {
   size_t ids_stride, slot_stride, snap_stride;
-  char *slots, *snaps;
+  char *slots;
   size_t total;
   int32_t *ids(int r) const { return reinterpret_cast<int32_t *>(slots + r * slot_stride); }
   int32_t *count(int r) const { return reinterpret_cast<int32_t *>(slots + r * slot_stride + ids_stride); }
-  float *phi(int r) const { return reinterpret_cast<float *>(snaps + r * snap_stride); }
 };
 
 PipeWs carve_pipeline(char *base, size_t off, int32_t P, int32_t d, int32_t ring) {
@@ -556,19 +555,91 @@ PipeWs carve_pipeline(char *base, size_t off, int32_t P, int32_t d, int32_t ring
   p.slot_stride = p.ids_stride + 256;
   p.snap_stride = align_up(sizeof(float) * ((size_t)d + 4), 256);
   p.slots = base + off;
-  p.snaps = p.slots + (size_t)ring * p.slot_stride;
   p.total = off + (size_t)ring * (p.slot_stride + p.snap_stride);
   return p;
 }
 
-__global__ void k_copy_model(const float *phi, const float *bias, int32_t d, float *phi_out,
-                             float *bias_out) {
-  for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < d; k += gridDim.x * blockDim.x)
-    phi_out[k] = phi[k];
-  if (blockIdx.x == 0 && threadIdx.x == 0 && bias) *bias_out = *bias;
-}
-
 constexpr int kMaxStaleness = 15;
+
+// The stale schedule, all on the Boss stream.  Tick s runs the Boss on batch s and draws batch
+// s + staleness with the Assistant as it stands, which is the one after s updates: the order of
+// the launches is the schedule, and no snapshot of the Assistant is needed.  Where both passes
+// take the same register layout they are one launch, and the compaction of what was drawn rides
+// on the update kernel: two launches a tick.  A second stream for the generator never paid:
+// its launches, event records and waits held the host for 36 us a tick.  Per tick, two streams
+// / this: 1024 floats, pools of 16,384, two batches in the queue 37 / 27 us, none 58 / 32; pools
+// of 500 38 / 11; CSR rows (d = 2^20, pools of 65,536) one batch 95 / 87, pools of 8000 48 / 38.
+int32_t stale_epoch(const aa_features *F, const int32_t *perm, int64_t n_perm, int32_t P, int32_t staleness,
+                    const aa_step_config *cfg, int32_t *kept_hist, int32_t *kept_ids_hist, const Ws &ws,
+                    const PipeWs &pw, PassSpec boss, hipStream_t st) {
+  const int ring = staleness + 1;
+  const int64_t steps = (n_perm + P - 1) / P;
+  auto pool_size = [&](int64_t s) { return (int32_t)((n_perm - s * P) < P ? (n_perm - s * P) : P); };
+  auto ids_of = [&](int64_t s) { return kept_ids_hist ? kept_ids_hist + s * (int64_t)P : pw.ids((int)(s % ring)); };
+  auto generator = [&](int64_t s) {
+    PassSpec g{};
+    g.F = F;
+    g.mode = kPool;
+    g.rows = perm + s * P;
+    g.count_max = pool_size(s);
+    g.phi = boss.phi;
+    g.bias = boss.bias;
+    g.gamma = cfg->gamma;
+    g.seed = cfg->seed;
+    g.step = cfg->step + (uint64_t)s;
+    g.do_keep = 1;
+    g.flags = ws.flags;
+    return g;
+  };
+  auto draw = [&](int64_t s) {  // batch s by itself
+    int32_t nblk = 0;
+    const hipError_t e = run_pass(generator(s), ws, &nblk, st);
+    if (e != hipSuccess) return e;
+    CompactArgs c{};
+    c.flags = ws.flags;
+    c.P = pool_size(s);
+    c.idx = perm + s * P;
+    c.kept_ids = ids_of(s);
+    c.kept_count = pw.count((int)(s % ring));
+    return launch_compact(c, ws.tile_off, st);
+  };
+  const bool merge = staleness > 0 && use_fast(boss) && use_fast(generator(0)) && boss_and_draw_ok(F->d);
+  for (int64_t s = 0; s < staleness && s < steps; ++s)  // the queue fills before the Boss starts
+    if (draw(s) != hipSuccess) return AA_ERR_HIP;
+  for (int64_t s = 0; s < steps; ++s) {
+    const int64_t ahead = s + staleness;  // the batch that joins the queue (staleness 0: this one)
+    const bool joint = merge && ahead < steps;
+    if (!joint && ahead < steps && draw(ahead) != hipSuccess) return AA_ERR_HIP;
+    boss.rows = ids_of(s);
+    boss.count_max = pool_size(s);
+    boss.m_dev = pw.count((int)(s % ring));
+    UpdateSpec u{};
+    u.lambda = cfg->lambda;
+    u.lr = cfg->lr;
+    u.lr_a = cfg->lr_a;
+    u.l2_a = cfg->l2_a;
+    u.t_upd = const_cast<int32_t *>(boss.t_upd);
+    u.kept_hist = kept_hist ? kept_hist + s : nullptr;
+    int32_t nblk = 0;
+    if (joint) {
+      const PassSpec g = generator(ahead);
+      nblk = dense_pass_blocks(F->d, boss.count_max, boss.mode);
+      const Hook hook;
+      if (launch_boss_and_draw(dense_args(boss, ws, false), dense_args(g, ws, false), F->d, nblk, st,
+                               hook.started, hook.stopped) != hipSuccess)
+        return AA_ERR_HIP;
+      u.flags = g.flags;
+      u.P = g.count_max;
+      u.idx = g.rows;
+      u.kept_ids = ids_of(ahead);
+      u.kept_count = pw.count((int)(ahead % ring));
+    } else if (run_pass(boss, ws, &nblk, st) != hipSuccess) {
+      return AA_ERR_HIP;
+    }
+    if (run_update(boss, u, ws, nblk, st) != hipSuccess) return AA_ERR_HIP;
+  }
+  return AA_OK;
+}
 
 // Device address of this GPU's copy of `scratch`, resolved on the first call per device.
 constexpr int kMaxDevices = 64;
@@ -1142,10 +1213,8 @@ int32_t aa_train_epoch_stale(const aa_features *F, const float *y, const int32_t
   if (n_perm == 0) return AA_OK;
   if (int32_t rc = check_features(F)) return rc;
   if (!y || !w || !phi || !cfg || !cfg->T || !perm) return AA_ERR_NULL;
-  hipStream_t sb = as_stream(stream_boss), sg = as_stream(stream_gen);
-  if (sb == sg) return AA_ERR_SHAPE;  // the generator needs a stream of its own
+  if (stream_boss == stream_gen) return AA_ERR_SHAPE;
   const int ring = staleness + 1;
-  const int64_t steps = (n_perm + P - 1) / P;
 
   // Boss pass over kept rows: the description every tick shares
   PassSpec boss{};
@@ -1165,93 +1234,8 @@ int32_t aa_train_epoch_stale(const aa_features *F, const float *y, const int32_t
   if (int32_t rc = check_ws(ws_ptr, ws_bytes, pw.total)) return rc;
   boss.loss_out = ws.loss;
 
-  hipEvent_t ev_boss[kMaxStaleness + 1], ev_gen[kMaxStaleness + 1], ev_start;
-  if (hipEventCreateWithFlags(&ev_start, hipEventDisableTiming) != hipSuccess) return AA_ERR_HIP;
-  int made = 0;  // complete (Boss, generator) event pairs
-  int32_t rc = AA_OK;
-  while (made < ring) {
-    if (hipEventCreateWithFlags(&ev_boss[made], hipEventDisableTiming) != hipSuccess) break;
-    if (hipEventCreateWithFlags(&ev_gen[made], hipEventDisableTiming) != hipSuccess) {
-      (void)hipEventDestroy(ev_boss[made]);
-      break;
-    }
-    ++made;
-  }
-  if (made < ring) rc = AA_ERR_HIP;
-  auto hip_ok = [&rc](hipError_t e) {
-    if (e != hipSuccess && rc == AA_OK) rc = AA_ERR_HIP;
-    return rc == AA_OK;
-  };
-
-  if (rc == AA_OK) {
-    // version 0 of the Assistant: what every batch made before the first feedback is drawn with
-    hipLaunchKernelGGL(k_copy_model, dim3((F->d + 1023) / 1024 > 64 ? 64 : (F->d + 1023) / 1024),
-                       dim3(1024), 0, sb, phi, bias, F->d, pw.phi(0), pw.phi(0) + F->d);
-    hip_ok(hipGetLastError());
-    hip_ok(hipEventRecord(ev_start, sb));
-    hip_ok(hipStreamWaitEvent(sg, ev_start, 0));
-  }
-  for (int64_t s = 0; s < steps && rc == AA_OK; ++s) {
-    const int64_t lo = s * P;
-    const int32_t Ps = (int32_t)((n_perm - lo) < P ? (n_perm - lo) : P);
-    const int slot = (int)(s % ring);
-    int32_t *ids = kept_ids_hist ? kept_ids_hist + s * (int64_t)P : pw.ids(slot);
-    int32_t *count = pw.count(slot);
-
-    // ---- generator: batch s from the Assistant as it stood after s - staleness updates
-    const int64_t version = s > staleness ? s - staleness : 0;
-    // that version is written by the Boss tick before it, which also is the last reader of
-    // the batch slot and the writer of the snapshot slot reused here
-    if (version > 0) hip_ok(hipStreamWaitEvent(sg, ev_boss[(version - 1) % ring], 0));
-    PassSpec g{};
-    g.F = F;
-    g.mode = kPool;
-    g.rows = perm + lo;
-    g.count_max = Ps;
-    g.phi = pw.phi((int)(version % ring));
-    g.bias = bias ? g.phi + F->d : nullptr;
-    g.gamma = cfg->gamma;
-    g.seed = cfg->seed;
-    g.step = cfg->step + (uint64_t)s;
-    g.do_keep = 1;
-    g.flags = ws.flags;
-    int32_t nblk = 0;
-    if (rc == AA_OK) hip_ok(run_pass(g, ws, &nblk, sg));
-    CompactArgs c{};
-    c.flags = ws.flags;
-    c.P = Ps;
-    c.idx = perm + lo;
-    c.kept_ids = ids;
-    c.kept_count = count;
-    if (rc == AA_OK) hip_ok(launch_compact(c, ws.tile_off, sg));
-    if (rc == AA_OK) hip_ok(hipEventRecord(ev_gen[slot], sg));
-
-    // ---- Boss tick s, then the Assistant update from its losses; the updated Assistant is
-    // also stored as version s + 1
-    if (rc == AA_OK) hip_ok(hipStreamWaitEvent(sb, ev_gen[slot], 0));
-    boss.rows = ids;
-    boss.count_max = Ps;
-    boss.m_dev = count;
-    if (rc == AA_OK) hip_ok(run_pass(boss, ws, &nblk, sb));
-    UpdateSpec u{};
-    u.lambda = cfg->lambda;
-    u.lr = cfg->lr;
-    u.lr_a = cfg->lr_a;
-    u.l2_a = cfg->l2_a;
-    u.t_upd = t_upd;
-    u.kept_hist = kept_hist ? kept_hist + s : nullptr;
-    u.phi_copy = pw.phi((int)((s + 1) % ring));
-    u.bias_copy = u.phi_copy + F->d;
-    if (rc == AA_OK) hip_ok(run_update(boss, u, ws, nblk, sb));
-    if (rc == AA_OK) hip_ok(hipEventRecord(ev_boss[slot], sb));
-  }
-  // every generator launch is waited for by a Boss tick, so the Boss stream ends the epoch
-  (void)hipEventDestroy(ev_start);
-  for (int i = 0; i < made; ++i) {
-    (void)hipEventDestroy(ev_boss[i]);
-    (void)hipEventDestroy(ev_gen[i]);
-  }
-  return rc;
+  return stale_epoch(F, perm, n_perm, P, staleness, cfg, kept_hist, kept_ids_hist, ws, pw, boss,
+                     as_stream(stream_boss));
 }
 
 }  // extern "C"

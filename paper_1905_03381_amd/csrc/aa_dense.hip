@@ -848,6 +848,29 @@ __global__ __launch_bounds__(NW * 64)
   step_rows<VPL, MODE, FULL, NW, RIF>(a, blockIdx.x, gridDim.x, lds);
 }
 
+// One launch for the two halves of a pipeline tick that do not depend on each other: the Boss and
+// Assistant pass over the rows of one batch, and the scoring and keep draws of a later pool with
+// the Assistant as it stands.  Blocks take turns between the two, so a compute unit works on one of each
+// and the memory system sees a launch of both sizes; as two launches on two streams they cost
+// the host two more launches, two event records and two waits per tick.  Per tick at d = 1024,
+// pools of 16,384, two batches in the queue: 37 us as two, 27 us so (this kernel 20.8 us for
+// 106 MB).
+template <int VPL, bool FULL, int RIF>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_boss_and_draw(
+    const PassArgs boss, const PassArgs gen, int nb_boss, int nb_gen) {
+  __shared__ union {
+    StepLds<VPL, kSvm | kAssist, 8> boss;
+    StepLds<VPL, kPool, 8> gen;
+  } lds;
+  const int both = 2 * min(nb_boss, nb_gen), i = blockIdx.x;
+  const bool draws = i < both ? (i & 1) != 0 : nb_gen > nb_boss;
+  const int bid = i < both ? i >> 1 : i - (both >> 1);
+  if (draws)
+    step_rows<VPL, kPool, FULL, 8, RIF>(gen, bid, nb_gen, lds.gen);
+  else
+    step_rows<VPL, kSvm | kAssist, FULL, 8, RIF>(boss, bid, nb_boss, lds.boss);
+}
+
 #ifndef AA_FIN_COLS4
 #define AA_FIN_COLS4 8
 #endif
@@ -981,12 +1004,6 @@ __global__ __launch_bounds__(256) void k_finalize(const FinalizeArgs a) {
       *a.bias = b_new;
     }
   }
-  if (a.phi_copy && !boss && pg == 0) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      if (k0 + i < a.d) a.phi_copy[k0 + i] = now[i];
-  }
-  if (a.bias_copy && bias_thread) *a.bias_copy = b_new;
   if (blockIdx.x == 0 && tid == 0 && a.kept_hist) *a.kept_hist = m;
   if (blockIdx.x == 0 && tid == 0 && a.T_next && m > 0) {
     *a.T_out = t_next;
@@ -1209,6 +1226,33 @@ hipError_t launch_dense_pass(const PassArgs &a, int mode, int32_t d, int32_t nbl
   if (s.lpr == 16) return launch_grad<16, 1, 8, 8>(a, mode, nblk, st, e0, e1);
   if (few) return launch_grad<32, 1, 8, 2>(a, mode, nblk, st, e0, e1);
   return launch_grad<32, 1, 8, 8>(a, mode, nblk, st, e0, e1);
+}
+
+bool boss_and_draw_ok(int32_t d) {
+  const Shape s = pick_shape(d);
+  return s.lpr == kWave && s.vpl <= 4;  // (wider: one block's sums fill the LDS of a compute unit)
+}
+
+hipError_t launch_boss_and_draw(const PassArgs &boss, const PassArgs &gen, int32_t d, int32_t nb_boss,
+                                hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
+  const Shape s = pick_shape(d);
+  if (!boss_and_draw_ok(d) || nb_boss < 1) return hipErrorInvalidValue;
+  int nb_gen = (gen.count_max + 15) / 16;  // two rows a wave, up to a block per compute unit
+  if (nb_gen > num_cu()) nb_gen = num_cu();
+  const dim3 grid(nb_boss + nb_gen), block(512);
+  const bool full = boss.d4 == kWave * s.vpl;
+  auto go = [&](auto kernel) {
+    if (e0 && e1)
+      hipExtLaunchKernelGGL(kernel, grid, block, 0, st, e0, e1, 0, boss, gen, (int)nb_boss, nb_gen);
+    else
+      hipLaunchKernelGGL(kernel, grid, block, 0, st, boss, gen, (int)nb_boss, nb_gen);
+    return hipGetLastError();
+  };
+  switch (s.vpl) {
+    case 1: return full ? go(k_boss_and_draw<1, true, 4>) : go(k_boss_and_draw<1, false, 4>);
+    case 2: return full ? go(k_boss_and_draw<2, true, 4>) : go(k_boss_and_draw<2, false, 4>);
+    default: return full ? go(k_boss_and_draw<4, true, 2>) : go(k_boss_and_draw<4, false, 2>);
+  }
 }
 
 hipError_t launch_dense_finalize(const FinalizeArgs &a, hipStream_t st) {

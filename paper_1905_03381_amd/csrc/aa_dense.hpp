@@ -73,8 +73,6 @@ struct FinalizeArgs {
   float *w;                // updated if non-NULL (vector 0)
   float *phi;              // updated if non-NULL (next vector)
   float *bias;
-  float *phi_copy;         // optional: the Assistant after this update is also stored here
-  float *bias_copy;        //   (even when m == 0 and nothing changed)
   float lambda, lr, lr_a, l2_a;
   int32_t *t_upd;          // optional device update counter driving lr/sqrt(t)
   const int32_t *t_snap;   // its value before this step (written by the pass kernel)
@@ -108,6 +106,12 @@ int32_t dense_pass_blocks(int32_t d, int32_t count, int mode);
 hipError_t launch_dense_pass(const PassArgs &a, int mode, int32_t d, int32_t nblk,
                              hipStream_t stream, hipEvent_t started = nullptr,
                              hipEvent_t stopped = nullptr);
+// The Boss and Assistant pass over `boss` (nb_boss partials) and the scoring pass with keep draws
+// over `gen` in one launch; for the widths boss_and_draw_ok accepts.
+bool boss_and_draw_ok(int32_t d);
+hipError_t launch_boss_and_draw(const PassArgs &boss, const PassArgs &gen, int32_t d, int32_t nb_boss,
+                                hipStream_t stream, hipEvent_t started = nullptr,
+                                hipEvent_t stopped = nullptr);
 hipError_t launch_dense_finalize(const FinalizeArgs &a, hipStream_t stream);
 
 }  // namespace aa

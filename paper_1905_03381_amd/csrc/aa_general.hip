@@ -840,7 +840,7 @@ static_assert(kGeneralGradBlocks <= kApplyThreads, "one per-block count of the p
 
 typedef float f4v __attribute__((ext_vector_type(4), aligned(4)));  // (any float address)
 
-// The update of one column from its gradient sums (m == 0: the model stays, its copy is still due).
+// The update of one column from its gradient sums (m == 0: the model stays).
 struct Fold {
   const ApplyArgs &a;
   int m;
@@ -854,17 +854,11 @@ struct Fold {
   }
   // w_old, ph: the column's current values, loaded by the caller
   __device__ __forceinline__ void loaded(int k, float gw, float gp, float w_old, float ph) const {
-    if (m <= 0) {
-      if (a.phi && a.phi_copy) a.phi_copy[k] = ph;
-      return;
-    }
+    if (m <= 0) return;
     const float wn = __fmaf_rn(scale, gw, shrink * w_old);
     const float pn = ph - a.lr_a * __fmaf_rn(a.l2_a, ph, gp * inv_m);
     if (a.w) a.w[k] = wn;
-    if (a.phi) {
-      a.phi[k] = pn;
-      if (a.phi_copy) a.phi_copy[k] = pn;
-    }
+    if (a.phi) a.phi[k] = pn;
     if (a.wp_out) a.wp_out[k] = make_float2(wn, pn);  // (both vectors are updated then)
   }
   __device__ __forceinline__ void column(int k, float gw, float gp) const {
@@ -872,10 +866,7 @@ struct Fold {
   }
   // four columns from k on (the same arithmetic per column), as 128-bit stores
   __device__ __forceinline__ void loaded4(int k, f4v gw, f4v gp, f4v w_old, f4v ph) const {
-    if (m <= 0) {
-      if (a.phi && a.phi_copy) *reinterpret_cast<f4v *>(a.phi_copy + k) = ph;
-      return;
-    }
+    if (m <= 0) return;
     f4v wn, pn;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -883,10 +874,7 @@ struct Fold {
       pn[i] = ph[i] - a.lr_a * __fmaf_rn(a.l2_a, ph[i], gp[i] * inv_m);
     }
     if (a.w) *reinterpret_cast<f4v *>(a.w + k) = wn;
-    if (a.phi) {
-      *reinterpret_cast<f4v *>(a.phi + k) = pn;
-      if (a.phi_copy) *reinterpret_cast<f4v *>(a.phi_copy + k) = pn;
-    }
+    if (a.phi) *reinterpret_cast<f4v *>(a.phi + k) = pn;
     if (a.wp_out) {  // (both vectors are updated then)
       const f4v lo = {wn[0], pn[0], wn[1], pn[1]}, hi = {wn[2], pn[2], wn[3], pn[3]};
       f4v *const dst = reinterpret_cast<f4v *>(a.wp_out + k);
@@ -1151,11 +1139,7 @@ __global__ __launch_bounds__(kApplyThreads) void k_apply_general(const ApplyArgs
       }
       fold.loaded(k, gw, gp, wo, po);
     }
-    if (hb == 0 && t == 0 && a.phi && a.bias) {
-      const float bn = m > 0 ? *a.bias - a.lr_a * (gb_pass * fold.inv_m) : *a.bias;
-      if (m > 0) *a.bias = bn;
-      if (a.bias_copy) *a.bias_copy = bn;
-    }
+    if (hb == 0 && t == 0 && a.phi && a.bias && m > 0) *a.bias = *a.bias - a.lr_a * (gb_pass * fold.inv_m);
   } else {
     float gb_pass;
     const int m = pass_totals(a, cnt, gbs, s_m, s_g, &gb_pass);

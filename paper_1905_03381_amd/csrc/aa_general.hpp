@@ -144,8 +144,6 @@ struct ApplyArgs {
   float *w;
   float *phi;
   float *bias;
-  float *phi_copy;   // optional second destination of the updated Assistant (written even if m == 0)
-  float *bias_copy;
   const float *part;  // per-block sums of the first `head` columns (see GenArgs)
   int32_t head, nvec, nblk_pass;
   const TailRecord *bins;  // records of the other columns (see GenArgs)
