@@ -23,7 +23,7 @@ LIB = os.path.join(HERE, "libautoassist.so")
 TRACE_LIB = os.path.join(HERE, "libautoassist_trace.so")
 PROBE = os.path.join(HERE, "bare_read_probe")
 SOURCES = ["aa_api.hip", "aa_batching.hip", "aa_dense.hip", "aa_general.hip", "aa_select.hip",
-           "aa_wide.hip"]
+           "aa_small.hip", "aa_wide.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-munsafe-fp-atomics",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wall", "-Wno-unused-function", "-Rpass-analysis=kernel-resource-usage"]

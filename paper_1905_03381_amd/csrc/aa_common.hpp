@@ -102,6 +102,29 @@ __device__ __forceinline__ float fold_groups(float v) {
   return v;
 }
 
+typedef float f4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ float dot4(const f4 a, const f4 b, float acc) {
+  acc = __fmaf_rn(a.x, b.x, acc);
+  acc = __fmaf_rn(a.y, b.y, acc);
+  acc = __fmaf_rn(a.z, b.z, acc);
+  acc = __fmaf_rn(a.w, b.w, acc);
+  return acc;
+}
+
+__device__ __forceinline__ f4 axpy4(const float s, const f4 x, f4 acc) {
+  acc.x = __fmaf_rn(s, x.x, acc.x);
+  acc.y = __fmaf_rn(s, x.y, acc.y);
+  acc.z = __fmaf_rn(s, x.z, acc.z);
+  acc.w = __fmaf_rn(s, x.w, acc.w);
+  return acc;
+}
+
+// Marks a loaded value as used at this point of the program: the wait for its load is placed
+// here and cannot sink below later memory requests.
+__device__ __forceinline__ void arrived(int &v) { asm volatile("" : "+v"(v)); }
+__device__ __forceinline__ void arrived(float &v) { asm volatile("" : "+v"(v)); }
+
 // v + (v moved by a DPP control): one VALU instruction, no LDS.
 template <int CTRL>
 __device__ __forceinline__ float dpp_add(float v) {

@@ -1,0 +1,38 @@
+// Host-side launch interface of the one-block epoch over small pools.
+#pragma once
+
+#include "aa_common.hpp"
+
+namespace aa {
+
+struct SmallEpochArgs {
+  const float *x;
+  int64_t ld;
+  int32_t d, d4;
+  const float *y;
+  const int32_t *perm;    // pool t is perm[t * P : min((t + 1) * P, n_perm)]
+  int64_t n_perm;
+  int32_t P, steps;       // steps of this launch
+  float *w, *phi, *bias;  // phi and bias NULL for hard thresholds; bias may be NULL
+  const float *T;
+  float gamma, one_minus_gamma;
+  uint32_t k0, k1;        // Philox key
+  uint64_t step;          // Philox step of the first pool
+  float lambda, lr, lr_a, l2_a;
+  int32_t *t_upd;
+  int32_t *kept_hist;     // [steps] or NULL
+  // the batch of each step; pool t's ids and losses start at t * out_stride
+  int32_t *ids, *kept_pos;
+  float *loss, *prob;
+  uint8_t *flags;
+  int64_t ids_stride, loss_stride;
+};
+
+constexpr int kSmallEpochSteps = 1024;  // steps of one launch at most
+
+// True if pools of P rows of d floats (16-byte aligned, d % 4 == 0) fit the registers of a block.
+bool small_epoch_ok(int32_t d, int64_t ld, int32_t P);
+
+hipError_t launch_small_epoch(const SmallEpochArgs &a, bool hard, hipStream_t stream);
+
+}  // namespace aa

@@ -13,7 +13,6 @@ namespace aa {
 
 namespace {
 
-typedef float f4 __attribute__((ext_vector_type(4)));
 typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));  // (any float address)
 
 constexpr int kWideWaves = 8, kWideThreads = kWideWaves * kWave;
