@@ -4,9 +4,9 @@
 // network, padded with +inf) and folds the median into the threshold.
 //
 // Length-bucketed batching: a stable multi-way partition of the kept pairs by
-// length bucket, three launches: per-tile bucket histograms (LDS integer
-// atomics), one block that turns them into per-tile, per-bucket offsets, bucket
-// starts and batch numbers, and a scatter in which a wave ranks each pair among
+// length bucket: per-tile bucket histograms (LDS integer atomics), then a scatter
+// in which every block adds the histograms up into bucket starts, batch numbers and
+// the places of its own tile (for many tiles one block does so in between), and a wave ranks each pair among
 // the earlier pairs of its bucket with one ballot per bucket and mbcnt.
 #include "aa_batching.hpp"
 
@@ -102,25 +102,30 @@ __device__ __forceinline__ int bucket_of(int ls, int lt, int width, int nb) {
   return min(b, nb - 1);
 }
 
-__global__ __launch_bounds__(256) void k_bucket_counts(const BucketArgs a) {
+// Two pairs a thread: a tile is latency, not throughput (460,000 pairs: counts, scan and scatter
+// 4.8 + 9.4 + 13.6 us with eight a thread and a scan in between, 4.8 + 10.0 so).
+constexpr int kBucketThreads = 1024;
+
+__global__ __launch_bounds__(kBucketThreads) void k_bucket_counts(const BucketArgs a) {
   __shared__ int hist[kMaxBuckets];
   const int m = min(max(*a.m_dev, 0), a.m_max);
   if (threadIdx.x < kMaxBuckets) hist[threadIdx.x] = 0;
   __syncthreads();
-  // all sixteen loads of a thread first, none under a condition of its own (a row past the
-  // end reads the last kept row instead and is not counted): one memory round trip, not eight
+  // all loads of a thread first, none under a condition of its own (a row past the
+  // end reads the last kept row instead and is not counted): one memory round trip
+  constexpr int kPer = kBucketTile / kBucketThreads;
   const int r0 = blockIdx.x * kBucketTile, last = m - 1;
-  if (m > 0) {
-    int ls[kBucketTile / 256], lt[kBucketTile / 256];
+  if (r0 < m) {
+    int ls[kPer], lt[kPer];
 #pragma unroll
-    for (int q = 0; q < kBucketTile / 256; ++q) {
-      const int r = min(r0 + q * 256 + (int)threadIdx.x, last);
+    for (int q = 0; q < kPer; ++q) {
+      const int r = min(r0 + q * kBucketThreads + (int)threadIdx.x, last);
       ls[q] = a.len_s[r];
       lt[q] = a.len_t[r];
     }
 #pragma unroll
-    for (int q = 0; q < kBucketTile / 256; ++q)
-      if (r0 + q * 256 + (int)threadIdx.x < m)
+    for (int q = 0; q < kPer; ++q)
+      if (r0 + q * kBucketThreads + (int)threadIdx.x < m)
         atomicAdd(&hist[bucket_of(ls[q], lt[q], a.width, a.n_buckets)], 1);
   }
   __syncthreads();
@@ -182,25 +187,69 @@ __global__ __launch_bounds__(1024) void k_bucket_scan(const BucketArgs a, int nt
   }
 }
 
-__global__ __launch_bounds__(256) void k_bucket_scatter(const BucketArgs a, int ntiles_max) {
-  __shared__ int wave_tot[4][kMaxBuckets];
+// SCANNED: k_bucket_scan has turned the counts into offsets.  Otherwise every block adds the
+// counts up for itself: thread (bucket, share of the tiles), then one lane per bucket.
+template <bool SCANNED>
+__global__ __launch_bounds__(kBucketThreads) void k_bucket_scatter(const BucketArgs a, int ntiles_max) {
+  constexpr int NW = kBucketThreads / kWave, R = kBucketTile / kBucketThreads;
+  constexpr int kShares = kBucketThreads / kMaxBuckets;
+  __shared__ int wave_tot[NW][kMaxBuckets];
+  __shared__ int s_all[SCANNED ? 1 : kShares][kMaxBuckets + 1], s_own[SCANNED ? 1 : kShares][kMaxBuckets + 1];
+  __shared__ int s_run[kMaxBuckets], s_first[kMaxBuckets], s_batch[kMaxBuckets];
   const int m = min(max(*a.m_dev, 0), a.m_max);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int nb = a.n_buckets;
-  const int seg = blockIdx.x * kBucketTile + wave * (kBucketTile / 4);
+  const int seg = blockIdx.x * kBucketTile + wave * (kBucketTile / NW);
+  if (blockIdx.x > 0 && (int)blockIdx.x * kBucketTile >= m) return;  // (the whole block: no pairs here)
+  if (!SCANNED) {
+    const int ntiles = (m + kBucketTile - 1) / kBucketTile;
+    const int b = threadIdx.x % kMaxBuckets, share = threadIdx.x / kMaxBuckets;
+    int all = 0, own = 0;
+    for (int t = share; t < ntiles; t += kShares) {
+      const int c = b < nb ? a.tile_base[t * nb + b] : 0;
+      all += c;
+      own += t < (int)blockIdx.x ? c : 0;
+    }
+    s_all[share][b] = all;
+    s_own[share][b] = own;
+    __syncthreads();
+    if (wave == 0) {  // lane b: bucket b's total, start, first batch, and where this tile's share begins
+      int total = 0, before = 0;
+      if (lane < nb) {
+#pragma unroll
+        for (int q = 0; q < kShares; ++q) {
+          total += s_all[q][lane];
+          before += s_own[q][lane];
+        }
+      }
+      const int cap = max(1, a.token_budget / (2 * a.width * (min(lane, nb - 1) + 1)));
+      const int batches = lane < nb ? (total + cap - 1) / cap : 0;
+      const int start = wave_inclusive_scan(total, lane) - total;
+      const int batch = wave_inclusive_scan(batches, lane) - batches;
+      if (lane < nb) {
+        s_run[lane] = start + before;
+        s_first[lane] = start;
+        s_batch[lane] = batch;
+      }
+      if (blockIdx.x == 0) {
+        if (lane <= nb) a.bucket_start[lane] = start;  // (lane nb: all of them)
+        if (lane == nb) *a.n_batches = batch;
+      }
+    }
+  }
   if (m <= 0) return;  // (the whole block: nothing is kept)
-  int bk[8];
+  int bk[R];
   {  // (loads first and without conditions of their own, as in k_bucket_counts)
-    int ls[8], lt[8];
+    int ls[R], lt[R];
     const int last = m - 1;
 #pragma unroll
-    for (int r = 0; r < 8; ++r) {
+    for (int r = 0; r < R; ++r) {
       const int row = min(seg + r * kWave + lane, last);
       ls[r] = a.len_s[row];
       lt[r] = a.len_t[row];
     }
 #pragma unroll
-    for (int r = 0; r < 8; ++r)
+    for (int r = 0; r < R; ++r)
       bk[r] = seg + r * kWave + lane < m ? bucket_of(ls[r], lt[r], a.width, nb) : -1;
   }
   // Lane b keeps what belongs to bucket b (there are at most 32): the wave's count, then its
@@ -218,20 +267,21 @@ __global__ __launch_bounds__(256) void k_bucket_scatter(const BucketArgs a, int 
   };
   int mine = 0;
 #pragma unroll
-  for (int r = 0; r < 8; ++r)
+  for (int r = 0; r < R; ++r)
     for_each_bucket(bk[r], [&](int b, unsigned long long mask) {
       if (lane == b) mine += __popcll(mask);
     });
   if (lane < nb) wave_tot[wave][lane] = mine;
   const int *tail = a.tile_base + (size_t)ntiles_max * nb;
   const int lb = min(lane, nb - 1);
-  int run = a.tile_base[blockIdx.x * nb + lb];  // where this tile's share of bucket `lane` begins
-  const int first = tail[lb], first_batch = tail[nb + lb];
   const int cap = max(1, a.token_budget / (2 * a.width * (lb + 1)));
   __syncthreads();
+  // where this tile's share of bucket `lane` begins, the bucket's start and its first batch
+  int run = SCANNED ? a.tile_base[blockIdx.x * nb + lb] : s_run[lb];
+  const int first = SCANNED ? tail[lb] : s_first[lb], first_batch = SCANNED ? tail[nb + lb] : s_batch[lb];
   for (int w = 0; w < wave; ++w) run += wave_tot[w][lb];
 #pragma unroll
-  for (int r = 0; r < 8; ++r)
+  for (int r = 0; r < R; ++r)
     for_each_bucket(bk[r], [&](int b, unsigned long long mask) {
       const int base = __shfl(run, b, kWave), b_first = __shfl(first, b, kWave);
       const int b_batch = __shfl(first_batch, b, kWave), b_cap = __shfl(cap, b, kWave);
@@ -254,13 +304,20 @@ hipError_t launch_threshold_update(const ThresholdArgs &a, hipStream_t st) {
 
 hipError_t launch_bucket_batches(const BucketArgs &a, hipStream_t st) {
   const int ntiles = (a.m_max + kBucketTile - 1) / kBucketTile;
+  const dim3 block(kBucketThreads);
   if (ntiles > 0) {
-    hipLaunchKernelGGL(k_bucket_counts, dim3(ntiles), dim3(256), 0, st, a);
+    hipLaunchKernelGGL(k_bucket_counts, dim3(ntiles), block, 0, st, a);
     if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
+  }
+  // Every block reads the whole table of counts (64 KB at 1024 tiles of 16 buckets) instead of
+  // waiting for the 9.4 us of a one-block scan; with more tiles the tables add up.
+  if (ntiles <= kBucketSumTiles) {
+    hipLaunchKernelGGL(k_bucket_scatter<false>, dim3(ntiles > 0 ? ntiles : 1), block, 0, st, a, ntiles);
+    return hipGetLastError();
   }
   hipLaunchKernelGGL(k_bucket_scan, dim3(1), dim3(1024), 0, st, a, ntiles);
   if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
-  if (ntiles > 0) hipLaunchKernelGGL(k_bucket_scatter, dim3(ntiles), dim3(256), 0, st, a, ntiles);
+  hipLaunchKernelGGL(k_bucket_scatter<true>, dim3(ntiles), block, 0, st, a, ntiles);
   return hipGetLastError();
 }
 

@@ -9,6 +9,7 @@ namespace aa {
 constexpr int kMaxBuckets = 32;
 constexpr int kMedianMax = 16384;  // losses sorted in LDS by one block
 constexpr int kBucketTile = 2048;  // kept pairs ranked by one block of the bucket partition
+constexpr int kBucketSumTiles = 1024;  // tiles up to which every block adds the counts up itself
 // Batches up to this size find their two middle losses by rank counting (every thread ranks
 // its losses against all others, read as LDS broadcasts); larger ones are sorted.
 constexpr int kRankSelectMax = 512;

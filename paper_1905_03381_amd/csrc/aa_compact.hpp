@@ -24,6 +24,7 @@ struct CompactArgs {
   float *loss;              // out: loss[r] = loss_pool[kept_pos[r]] (may be NULL)
   int32_t *kept_count;      // out, may be NULL
   const int32_t *tile_off;  // exclusive tile offsets, or NULL: count the flags before the tile
+  bool tile_counts;         // tile_off holds the tiles' own counts, still to be added up
 };
 
 // Number of set flags in [0, j0) (j0 a multiple of 16), whole block cooperates.
@@ -54,6 +55,20 @@ __device__ inline int count_flags_before(const uint8_t *flags, int j0, int *smem
   __syncthreads();
   int total = 0;
   for (int i = 0; i < nw; ++i) total += smem[i];
+  __syncthreads();
+  return total;
+}
+
+// Sum of v[0, n), whole block cooperates.
+__device__ inline int sum_before(const int32_t *v, int n, int *smem) {
+  int sum = 0;
+  for (int i = threadIdx.x; i < n; i += blockDim.x) sum += v[i];
+#pragma unroll
+  for (int off = kWave / 2; off > 0; off >>= 1) sum += __shfl_xor(sum, off, kWave);
+  if ((threadIdx.x & 63) == 0) smem[threadIdx.x >> 6] = sum;
+  __syncthreads();
+  int total = 0;
+  for (int i = 0; i < (int)(blockDim.x >> 6); ++i) total += smem[i];
   __syncthreads();
   return total;
 }
@@ -89,7 +104,9 @@ __device__ inline void tile_compact(const CompactArgs &c, int tile, int *smem) {
 #pragma unroll
     for (int r = 0; r < R; ++r) ls[r] = 0.f;
   }
-  const int prefix = c.tile_off ? c.tile_off[tile] : count_flags_before(c.flags, j0, smem);
+  const int prefix = !c.tile_off     ? count_flags_before(c.flags, j0, smem)
+                     : c.tile_counts ? sum_before(c.tile_off, tile, smem)
+                                     : c.tile_off[tile];
 #pragma unroll
   for (int r = 0; r < R; ++r)
     if (seg + r * kWave + lane > last) fl[r] = 0;
