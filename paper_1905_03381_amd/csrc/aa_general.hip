@@ -26,8 +26,17 @@ namespace aa {
 
 namespace {
 
+// Sum over aligned groups of WIDTH lanes, halves first.  For 16 lanes by rotations inside the row,
+// no trip through LDS: after each addition the values repeat with half the period, so rotating
+// by 8, 4, 2 and 1 adds the same pairs as exchanging with lane ^ 8, ^ 4, ^ 2 and ^ 1.
 template <int WIDTH>
 __device__ __forceinline__ float gsum(float v) {
+  if (WIDTH == 16) {
+    v = dpp_add<0x128>(v);  // row_ror:8
+    v = dpp_add<0x124>(v);
+    v = dpp_add<0x122>(v);
+    return dpp_add<0x121>(v);
+  }
 #pragma unroll
   for (int off = WIDTH / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
   return v;
