@@ -58,8 +58,8 @@ extern "C" {
 
 /* The feature side of the training set D = {x_i, y_i} (Algorithm 1, input).
  * Dense: x is row-major [n, ld] with ld >= d (elements).  The fast kernels need
- * x 16-byte aligned, ld % 4 == 0, d % 4 == 0 and d <= 2048; other rows of 1025 to
- * 8192 columns have a pass of their own, anything else runs on slower general
+ * x 16-byte aligned, ld % 4 == 0, d % 4 == 0 and d <= 2048; other rows of 4 to
+ * 8192 columns have passes of their own, anything else runs on slower general
  * kernels, not an error.
  * CSR: rowptr[n+1], col[nnz], val[nnz]; val == NULL means every stored entry
  * is 1 (token lists).  Duplicate column ids within a row are allowed and add.

@@ -182,7 +182,7 @@ bool use_fast(const PassSpec &s) {
   return true;
 }
 
-// Rows of more than 1024 columns that those kernels do not take (wider than 2048, or a width,
+// Rows of 4 to 8192 columns that those kernels do not take (wider than 2048, or a width,
 // leading dimension or address off 16 bytes).
 bool use_wide(const PassSpec &s) { return !use_fast(s) && wide_rows_ok(s.F); }
 
@@ -201,7 +201,7 @@ PassArgs dense_args(const PassSpec &s, const Ws &ws, bool wide) {
   PassArgs a{};
   a.x = s.F->x;
   a.ld = s.F->ld;
-  a.d4 = s.F->d / 4;
+  a.d4 = (s.F->d + 3) / 4;
   a.d = s.F->d;
   a.d_pad = wide ? wide_d_pad(s.F->d) : dense_d_pad(s.F->d);
   a.y = s.y;
@@ -242,7 +242,7 @@ hipError_t run_pass(const PassSpec &s, const Ws &ws, int32_t *nblk_out, hipStrea
   if (wide || use_fast(s)) {
     const PassArgs a = dense_args(s, ws, wide);
     if (wide) {
-      *nblk_out = wide_pass_blocks(s.count_max);
+      *nblk_out = wide_pass_blocks(s.F->d, s.count_max);
       const Hook hook;
       return launch_wide_pass(a, s.mode, *nblk_out, st, hook.started, hook.stopped);
     }

@@ -120,6 +120,14 @@ __device__ __forceinline__ f4 axpy4(const float s, const f4 x, f4 acc) {
   return acc;
 }
 
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ f64x4 axpy4(const float s, const f4 x, f64x4 acc) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) acc[i] = __fma_rn((double)s, (double)x[i], acc[i]);
+  return acc;
+}
+
 // Marks a loaded value as used at this point of the program: the wait for its load is placed
 // here and cannot sink below later memory requests.
 __device__ __forceinline__ void arrived(int &v) { asm volatile("" : "+v"(v)); }

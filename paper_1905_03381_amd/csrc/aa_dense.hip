@@ -14,6 +14,8 @@
 #include "aa_compact.hpp"
 #include "aa_dense.hpp"
 
+#include <type_traits>
+
 // Feature rows are read once per step: non-temporal loads keep them from displacing the
 // model vectors and block partials in L2.
 #ifndef AA_ROW_LOAD
@@ -526,8 +528,14 @@ __global__ __launch_bounds__(NW * 64) void k_rows_once(const PassArgs a) {
 // store is pending while rows arrive.  Loads return in request order, so row r of a batch
 // is consumed as soon as it is there while rows r+1.. are still on their way.
 // Without gradient sums (MODE == kPool) it is the generator's half of k_boss_and_draw.
-template <int VPL, int MODE, int NW>
+// ANY: rows of any width (at least four floats), stride and address: read in pieces that start at
+// any float, the last one ending with the row, and summed in doubles, as the general kernels do.
+enum StepRows : int { kFullRows, kPartRows, kAnyRows };
+
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));  // (any float address)
+template <int VPL, int MODE, int NW, int ROWS = kFullRows>
 struct StepLds {
+  using Acc = std::conditional_t<ROWS == kAnyRows, f64x4, f4>;
   static constexpr bool kGrad = (MODE & (kSvm | kAssist)) != 0;
   static constexpr bool kPhi = ((MODE & kPool) && !(MODE & kHard)) || (MODE & kAssist);
   static constexpr int kVec = ((MODE & kSvm) ? 1 : 0) + ((MODE & kAssist) ? 1 : 0);
@@ -536,11 +544,13 @@ struct StepLds {
   int carry[NW];
   __attribute__((aligned(16))) f4 w[(MODE & kSvm) ? kWave * VPL : 1];
   f4 phi[kPhi ? kWave * VPL : 1];
-  f4 red[kGrad ? NW * kVec * kWave * VPL : 1];  // one slot per wave and vector
+  Acc red[kGrad ? NW * kVec * kWave * VPL : 1];  // one slot per wave and vector
 };
 
-template <int VPL, int MODE, bool FULL, int NW, int RIF>
-__device__ __forceinline__ void step_rows(const PassArgs &a, int bid, int nblk, StepLds<VPL, MODE, NW> &lds) {
+template <int VPL, int MODE, int ROWS, int NW, int RIF>
+__device__ __forceinline__ void step_rows(const PassArgs &a, int bid, int nblk, StepLds<VPL, MODE, NW, ROWS> &lds) {
+  constexpr bool FULL = ROWS == kFullRows, ANY = ROWS == kAnyRows;
+  using Acc = typename StepLds<VPL, MODE, NW, ROWS>::Acc;
   constexpr bool POOL = (MODE & kPool) != 0;
   constexpr bool SVM = (MODE & kSvm) != 0;
   constexpr bool ASSIST = (MODE & kAssist) != 0;
@@ -594,12 +604,17 @@ __device__ __forceinline__ void step_rows(const PassArgs &a, int bid, int nblk, 
   uint8_t carry_flag = (carry ? a.prev.flags : reinterpret_cast<const uint8_t *>(model))[cpos];
   int carry_id = ((carry && a.prev.idx) ? a.prev.idx : stand_in)[a.prev.idx ? cpos : 0];
   float carry_loss = ((carry && a.prev.loss) ? a.prev.loss_pool : model)[a.prev.loss ? cpos : 0];
+  // 128-bit piece c of a row or model vector (ANY: the last one from d - 4 on)
+  auto piece_of = [&](const float *v, int c) __attribute__((always_inline)) {
+    if (ANY) return (f4)*reinterpret_cast<const f4u *>(v + min(4 * c, a.d - 4));
+    return reinterpret_cast<const f4 *>(v)[c];
+  };
   f4 st_w[STG], st_p[STG];
 #pragma unroll
   for (int q = 0; q < STG; ++q) {
     const int c = min(q * NT + (int)threadIdx.x, FULL ? ROW4 - 1 : a.d4 - 1);
-    if (SVM) st_w[q] = reinterpret_cast<const f4 *>(a.w)[c];
-    if (NEED_PHI) st_p[q] = reinterpret_cast<const f4 *>(a.phi)[c];
+    if (SVM) st_w[q] = piece_of(a.w, c);
+    if (NEED_PHI) st_p[q] = piece_of(a.phi, c);
   }
   float b = (NEED_PHI && a.bias ? a.bias : model)[0];
   if (!(NEED_PHI && a.bias)) b = 0.f;
@@ -648,10 +663,15 @@ __device__ __forceinline__ void step_rows(const PassArgs &a, int bid, int nblk, 
       // a slot past the end of the group re-reads the group's last row and is never consumed
       const int li = min(it0 + r, cnt - 1);
       const int row = __builtin_amdgcn_readlane(row_l, li);
-      const f4 *xr = reinterpret_cast<const f4 *>(a.x + (int64_t)row * a.ld);
+      const float *xr = a.x + (int64_t)row * a.ld;
 #pragma unroll
-      for (int v = 0; v < VPL; ++v)
-        x[r][v] = AA_ROW_LOAD(xr + (FULL ? v * kWave + lane : min(v * kWave + lane, a.d4 - 1)));
+      for (int v = 0; v < VPL; ++v) {
+        const int c = FULL ? v * kWave + lane : min(v * kWave + lane, a.d4 - 1);
+        if (ANY)
+          x[r][v] = AA_ROW_LOAD(reinterpret_cast<const f4u *>(xr + min(4 * c, a.d - 4)));
+        else
+          x[r][v] = AA_ROW_LOAD(reinterpret_cast<const f4 *>(xr) + c);
+      }
     }
   };
   // The barrier that publishes the model vectors comes before the row requests: the memory
@@ -682,11 +702,11 @@ __device__ __forceinline__ void step_rows(const PassArgs &a, int bid, int nblk, 
       *a.prev.kept_count = before + __popcll(mask);
   }
 
-  f4 gw[VPL], gp[VPL];
+  Acc gw[VPL], gp[VPL];
 #pragma unroll
   for (int v = 0; v < VPL; ++v) {
-    gw[v] = zero4;
-    gp[v] = zero4;
+    gw[v] = Acc{0, 0, 0, 0};
+    gp[v] = Acc{0, 0, 0, 0};
   }
   float gb = 0.f;
   int kept = 0;
@@ -705,8 +725,15 @@ __device__ __forceinline__ void step_rows(const PassArgs &a, int bid, int nblk, 
         bool keep = live;
         if (!FULL) {  // (the layouts double in width: only the second half can lie past the row)
 #pragma unroll
-          for (int v = VPL / 2; v < VPL; ++v)
-            if (v * kWave + lane >= a.d4) x[r][v] = zero4;
+          for (int v = VPL / 2; v < VPL; ++v) {
+            const int c = v * kWave + lane;
+            if (c >= a.d4) x[r][v] = zero4;
+            if (ANY) {  // (what the last piece shares with the one before it counts there)
+#pragma unroll
+              for (int i = 0; i < 3; ++i)
+                if (a.d - 4 + i < 4 * c) x[r][v][i] = 0.f;
+            }
+          }
         }
         if (NEED_PHI) {
           float dp = 0.f;
@@ -778,7 +805,7 @@ __device__ __forceinline__ void step_rows(const PassArgs &a, int bid, int nblk, 
   // slot, then one thread per 128-bit column adds the slots in wave order and stores the
   // block's partial vectors.
   if (GRAD) {
-    f4 *slot = lds.red + wave * NVEC * ROW4;
+    Acc *slot = lds.red + wave * NVEC * ROW4;
 #pragma unroll
     for (int v = 0; v < VPL; ++v) {
       if (SVM) slot[v * kWave + lane] = gw[v];
@@ -792,10 +819,19 @@ __device__ __forceinline__ void step_rows(const PassArgs &a, int bid, int nblk, 
     AA_STAMP(6);  // past the reduction barrier
     f4 *part = reinterpret_cast<f4 *>(a.partial) + (size_t)bid * NVEC * ROW4;
     for (int c = threadIdx.x; c < NVEC * ROW4; c += NT) {
-      f4 t = lds.red[c];
+      Acc t = lds.red[c];
 #pragma unroll
       for (int q = 1; q < NW; ++q) t += lds.red[q * NVEC * ROW4 + c];
-      part[c] = t;
+      if constexpr (ANY) {  // (partials as wide as the row, rounded up: see PassArgs::d_pad)
+        float *out = a.partial + ((size_t)bid * NVEC + c / ROW4) * a.d_pad;
+        const int k0 = 4 * (c % ROW4), first = min(k0, a.d - 4);
+        if (k0 >= a.d) continue;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (first + i >= k0) out[first + i] = (float)t[i];
+      } else {
+        part[c] = t;
+      }
     }
     if (threadIdx.x == 0) {
       int ks = 0;
@@ -818,11 +854,11 @@ __device__ __forceinline__ void step_rows(const PassArgs &a, int bid, int nblk, 
 #endif
 }
 
-template <int VPL, int MODE, bool FULL, int NW, int RIF>
+template <int VPL, int MODE, int ROWS, int NW, int RIF>
 __global__ __launch_bounds__(NW * 64)
     __attribute__((amdgpu_waves_per_eu(NW / 4, NW / 4))) void k_step_pass(const PassArgs a) {
-  __shared__ StepLds<VPL, MODE, NW> lds;
-  step_rows<VPL, MODE, FULL, NW, RIF>(a, blockIdx.x, gridDim.x, lds);
+  __shared__ StepLds<VPL, MODE, NW, ROWS> lds;
+  step_rows<VPL, MODE, ROWS, NW, RIF>(a, blockIdx.x, gridDim.x, lds);
 }
 
 // One launch for the two halves of a pipeline tick that do not depend on each other: the Boss and
@@ -832,20 +868,20 @@ __global__ __launch_bounds__(NW * 64)
 // the host two more launches, two event records and two waits per tick.  Per tick at d = 1024,
 // pools of 16,384, two batches in the queue: 37 us as two, 27 us so (this kernel 20.8 us for
 // 106 MB).
-template <int VPL, bool FULL, int RIF>
+template <int VPL, int ROWS, int RIF>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_boss_and_draw(
     const PassArgs boss, const PassArgs gen, int nb_boss, int nb_gen) {
   __shared__ union {
-    StepLds<VPL, kSvm | kAssist, 8> boss;
-    StepLds<VPL, kPool, 8> gen;
+    StepLds<VPL, kSvm | kAssist, 8, ROWS> boss;
+    StepLds<VPL, kPool, 8, ROWS> gen;
   } lds;
   const int both = 2 * min(nb_boss, nb_gen), i = blockIdx.x;
   const bool draws = i < both ? (i & 1) != 0 : nb_gen > nb_boss;
   const int bid = i < both ? i >> 1 : i - (both >> 1);
   if (draws)
-    step_rows<VPL, kPool, FULL, 8, RIF>(gen, bid, nb_gen, lds.gen);
+    step_rows<VPL, kPool, ROWS, 8, RIF>(gen, bid, nb_gen, lds.gen);
   else
-    step_rows<VPL, kSvm | kAssist, FULL, 8, RIF>(boss, bid, nb_boss, lds.boss);
+    step_rows<VPL, kSvm | kAssist, ROWS, 8, RIF>(boss, bid, nb_boss, lds.boss);
 }
 
 #ifndef AA_FIN_COLS4
@@ -1088,25 +1124,31 @@ hipError_t launch_once(const PassArgs &a, int mode, int nblk, hipStream_t st, hi
   return hipGetLastError();
 }
 
-template <int VPL, bool FULL, int NW, int RIF>
+template <int VPL, int ROWS, int NW, int RIF>
 hipError_t launch_step_mode(const PassArgs &a, int mode, int nblk, hipStream_t st, hipEvent_t e0,
                             hipEvent_t e1) {
   const dim3 grid(nblk), block(NW * 64);
   switch (mode) {
+    case kPool:
+      if constexpr (ROWS == kAnyRows) {  // (the others have a scoring pass of their own)
+        launch_stamped((k_step_pass<VPL, kPool, ROWS, NW, RIF>), grid, block, st, e0, e1, a);
+        break;
+      }
+      return hipErrorInvalidValue;
     case kSvm:
-      launch_stamped((k_step_pass<VPL, kSvm, FULL, NW, RIF>), grid, block, st, e0, e1, a);
+      launch_stamped((k_step_pass<VPL, kSvm, ROWS, NW, RIF>), grid, block, st, e0, e1, a);
       break;
     case kAssist:
-      launch_stamped((k_step_pass<VPL, kAssist, FULL, NW, RIF>), grid, block, st, e0, e1, a);
+      launch_stamped((k_step_pass<VPL, kAssist, ROWS, NW, RIF>), grid, block, st, e0, e1, a);
       break;
     case kSvm | kAssist:
-      launch_stamped((k_step_pass<VPL, kSvm | kAssist, FULL, NW, RIF>), grid, block, st, e0, e1, a);
+      launch_stamped((k_step_pass<VPL, kSvm | kAssist, ROWS, NW, RIF>), grid, block, st, e0, e1, a);
       break;
     case kPool | kSvm | kAssist:
-      launch_stamped((k_step_pass<VPL, kPool | kSvm | kAssist, FULL, NW, RIF>), grid, block, st, e0, e1, a);
+      launch_stamped((k_step_pass<VPL, kPool | kSvm | kAssist, ROWS, NW, RIF>), grid, block, st, e0, e1, a);
       break;
     case kPool | kSvm | kHard:
-      launch_stamped((k_step_pass<VPL, kPool | kSvm | kHard, FULL, NW, RIF>), grid, block, st, e0, e1, a);
+      launch_stamped((k_step_pass<VPL, kPool | kSvm | kHard, ROWS, NW, RIF>), grid, block, st, e0, e1, a);
       break;
     default:
       return hipErrorInvalidValue;
@@ -1116,8 +1158,8 @@ hipError_t launch_step_mode(const PassArgs &a, int mode, int nblk, hipStream_t s
 
 template <int VPL, int NW, int RIF>
 hipError_t launch_step(const PassArgs &a, int mode, int nblk, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
-  return a.d4 == kWave * VPL ? launch_step_mode<VPL, true, NW, RIF>(a, mode, nblk, st, e0, e1)
-                             : launch_step_mode<VPL, false, NW, RIF>(a, mode, nblk, st, e0, e1);
+  return a.d4 == kWave * VPL ? launch_step_mode<VPL, kFullRows, NW, RIF>(a, mode, nblk, st, e0, e1)
+                             : launch_step_mode<VPL, kPartRows, NW, RIF>(a, mode, nblk, st, e0, e1);
 }
 
 template <int LPR, int VPL, int RIF>
@@ -1205,6 +1247,16 @@ hipError_t launch_dense_pass(const PassArgs &a, int mode, int32_t d, int32_t nbl
   return launch_grad<32, 1, 8, 8>(a, mode, nblk, st, e0, e1);
 }
 
+// Rows of 4 to 1024 floats that are not laid out in 16-byte pieces.  In the general kernel every
+// element of theirs was an LDS atomic.  Per step at d = 785,
+// pools of 4000: 20.4 us there, 12.0 here; d = 999, 20,000: 60.7, 23.0; d = 131, 200: 12.7, 8.8.
+hipError_t launch_any_rows(const PassArgs &a, int mode, int32_t nblk, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
+  if (a.d < 4 || a.d > 1024) return hipErrorInvalidValue;
+  if (a.d <= 256) return launch_step_mode<1, kAnyRows, 8, 4>(a, mode, nblk, st, e0, e1);
+  if (a.d <= 512) return launch_step_mode<2, kAnyRows, 8, 4>(a, mode, nblk, st, e0, e1);
+  return launch_step_mode<4, kAnyRows, 8, 2>(a, mode, nblk, st, e0, e1);
+}
+
 bool boss_and_draw_ok(int32_t d) {
   const Shape s = pick_shape(d);
   return s.lpr == kWave && s.vpl <= 4;  // (wider: one block's sums fill the LDS of a compute unit)
@@ -1226,9 +1278,9 @@ hipError_t launch_boss_and_draw(const PassArgs &boss, const PassArgs &gen, int32
     return hipGetLastError();
   };
   switch (s.vpl) {
-    case 1: return full ? go(k_boss_and_draw<1, true, 4>) : go(k_boss_and_draw<1, false, 4>);
-    case 2: return full ? go(k_boss_and_draw<2, true, 4>) : go(k_boss_and_draw<2, false, 4>);
-    default: return full ? go(k_boss_and_draw<4, true, 2>) : go(k_boss_and_draw<4, false, 2>);
+    case 1: return full ? go(k_boss_and_draw<1, kFullRows, 4>) : go(k_boss_and_draw<1, kPartRows, 4>);
+    case 2: return full ? go(k_boss_and_draw<2, kFullRows, 4>) : go(k_boss_and_draw<2, kPartRows, 4>);
+    default: return full ? go(k_boss_and_draw<4, kFullRows, 2>) : go(k_boss_and_draw<4, kPartRows, 2>);
   }
 }
 

@@ -16,7 +16,7 @@ enum : int { kSvm = 1, kAssist = 2, kPool = 4, kHard = 8 };
 struct PassArgs {
   const float *x;
   int64_t ld;
-  int32_t d4;             // d / 4
+  int32_t d4;             // pieces of four floats, rounded up
   int32_t d;
   const float *y;         // labels indexed by data-set row (kSvm)
   const int32_t *rows;    // pool ids idx[P] or kept ids rows[m]; NULL = 0..count-1
@@ -106,6 +106,10 @@ int32_t dense_pass_blocks(int32_t d, int32_t count, int mode);
 hipError_t launch_dense_pass(const PassArgs &a, int mode, int32_t d, int32_t nblk,
                              hipStream_t stream, hipEvent_t started = nullptr,
                              hipEvent_t stopped = nullptr);
+// Passes over dense rows of 4 to 1024 floats at any stride and address (partials of a.d_pad floats).
+hipError_t launch_any_rows(const PassArgs &a, int mode, int32_t nblk, hipStream_t stream,
+                           hipEvent_t started = nullptr, hipEvent_t stopped = nullptr);
+
 // The Boss and Assistant pass over `boss` (nb_boss partials) and the scoring pass with keep draws
 // over `gen` in one launch; for the widths boss_and_draw_ok accepts.
 bool boss_and_draw_ok(int32_t d);

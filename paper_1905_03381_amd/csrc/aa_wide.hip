@@ -1,5 +1,5 @@
 // Wide dense rows: more columns than a wave can hold sums for in registers (d > 2048), and
-// rows of over 1024 columns with a width, leading dimension or base address that is not a
+// rows of 1025 to 2048 columns with a width, leading dimension or base address that is not a
 // multiple of 16 bytes.  A block of 8 waves owns a row, each thread the same columns of every
 // row: it keeps those columns of the model and of the gradient sums in registers for the whole
 // launch, so a row crosses memory once and no sum needs an atomic or a trip through LDS.
@@ -299,7 +299,7 @@ hipError_t launch_vpt(const PassArgs &a, int mode, int nblk, hipStream_t st, hip
 }  // namespace
 
 bool wide_rows_ok(const aa_features *F) {
-  return F->layout == AA_DENSE && F->d >= kWideMinD && F->d <= kWideMaxD;
+  return F->layout == AA_DENSE && F->d >= kAnyMinD && F->d <= kWideMaxD;
 }
 
 int32_t wide_d_pad(int32_t d) { return (d + 31) / 32 * 32; }
@@ -309,7 +309,11 @@ int32_t wide_d_pad(int32_t d) { return (d + 31) / 32 * 32; }
 // idle.  Four rows a block up to half the compute units, eight beyond that.  Epochs of 4 pools at
 // d = 4137, one / four / eight rows a block: pools of 256 rows 53.7 / 43.8 / 48.8 us, of 500 55.9 /
 // 48.6 / 52.0, of 1000 59.2 / 59.2 / 56.7, of 1600 69.3 / 69.3 / 64.6 us.
-int32_t wide_pass_blocks(int32_t count) {
+int32_t wide_pass_blocks(int32_t d, int32_t count) {
+  if (d < kWideMinD) {  // a row per wave and block of eight
+    const int32_t want = (int32_t)(((int64_t)count + 7) / 8);
+    return want < 1 ? 1 : want < kWideBlocks ? want : kWideBlocks;
+  }
   const int32_t half = kWideBlocks / 2, four = (int32_t)(((int64_t)count + 3) / 4);
   const int32_t eight = (int32_t)(((int64_t)count + 7) / 8);
   int32_t want = four < half ? four : eight > half ? eight : half;
@@ -319,7 +323,8 @@ int32_t wide_pass_blocks(int32_t count) {
 
 hipError_t launch_wide_pass(const PassArgs &a, int mode, int32_t nblk, hipStream_t st, hipEvent_t e0,
                             hipEvent_t e1) {
-  if (a.d < 4 || a.d > kWideMaxD) return hipErrorInvalidValue;
+  if (a.d < kAnyMinD || a.d > kWideMaxD) return hipErrorInvalidValue;
+  if (a.d < kWideMinD) return launch_any_rows(a, mode, nblk, st, e0, e1);
   switch ((a.d + 4 * kWideThreads - 1) / (4 * kWideThreads)) {
     case 1: return launch_vpt<1, 8>(a, mode, nblk, st, e0, e1);
     case 2: return launch_vpt<2, 4>(a, mode, nblk, st, e0, e1);

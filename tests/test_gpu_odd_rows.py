@@ -22,7 +22,10 @@ def ws():
 # a block of 512 threads owns 2048 columns per piece: one column either side of each number of
 # pieces, widths of every remainder by four, padded and odd leading dimensions, and pools that give
 # some blocks no row, one row, and more than a register set of them
-SHAPES = [(40, 1025, None, 33), (300, 1027, 1029, 300), (300, 2047, None, 257), (64, 2049, None, 64),
+# -- and below that a row per wave, one layout up to 256, 512 and 1024 floats
+SHAPES = [(20, 3, None, 20), (40, 4, 5, 33), (300, 5, None, 300), (300, 63, None, 260), (300, 255, None, 255),
+          (300, 256, 257, 280), (600, 257, None, 590), (300, 511, None, 129), (300, 513, 514, 300), (600, 1023, None, 520),
+          (40, 1025, None, 33), (300, 1027, 1029, 300), (300, 2047, None, 257), (64, 2049, None, 64),
           (300, 2050, 2052, 255), (600, 4095, None, 520), (40, 4096, 4096, 40), (600, 4097, 4099, 513),
           (300, 6144, None, 256), (1500, 6145, None, 1400), (300, 8191, None, 300), (20, 8192, None, 1),
           (20, 8193, None, 20), (3300, 1367, None, 3300)]
@@ -81,7 +84,7 @@ def test_epoch_on_rows_inside_a_layout_is_its_steps(d, P):
     assert 0 < got[0][4].min() and got[0][4][0] < P
 
 
-@pytest.mark.parametrize("d", [1027, 4097])
+@pytest.mark.parametrize("d", [7, 130, 1023, 1027, 4097])
 def test_odd_rows_with_infinities_in_the_last_columns(ws, d):
     """The last columns of a row that is no whole number of pieces are read twice and count once:
     an infinite value there gives an infinite score, not a NaN, and reaches no other row."""
