@@ -4,7 +4,7 @@
     python -m paper_1905_03381_amd.workloads images        # image batch generator
     python -m paper_1905_03381_amd.workloads translation   # translation batch generator
     python -m paper_1905_03381_amd.workloads sk            # hard-threshold shrinking, dense rows
-    python -m paper_1905_03381_amd.workloads stale         # two-stream Boss / Assistant pipeline
+    python -m paper_1905_03381_amd.workloads stale         # stale Boss / Assistant pipeline
     python -m paper_1905_03381_amd.workloads rho           # dense fused step at fixed keep rates
     python -m paper_1905_03381_amd.workloads score         # dense scoring pass at growing pool sizes
 
@@ -262,7 +262,7 @@ def sk(a, torch, api, synth):
 
 
 def stale(a, torch, api, synth):
-    """The two-stream Boss / Assistant pipeline against the fused synchronous epoch."""
+    """The stale Boss / Assistant pipeline against the fused synchronous epoch."""
     n, d, P, F, Xd, yd, perm = _dense_job(a, torch, api, synth)
     steps = (n + P - 1) // P
     T = torch.zeros(1, device="cuda")
@@ -287,7 +287,7 @@ def stale(a, torch, api, synth):
         us = _timed(torch, lambda: api.train_epoch_stale(F, yd, perm, n, P, k, w, phi, b, cfg, tu,
                                                           hist, None, ws, gen), a.repeats, reset) / steps
         rho = float(hist.sum().item()) / n
-        stages.append(_stage(f"two-stream pipeline, staleness {k}, per step", us,
+        stages.append(_stage(f"stale pipeline, staleness {k}, per step", us,
                              P * (4 * d + 9) + rho * P * (4 * d + 12), note=f"keep rate {rho:.3f}"))
     return {"workload": f"dense n={n} d={d}, pool {P}: synchronous step against the stale pipeline",
             "stages": stages}
