@@ -329,7 +329,7 @@ def main():
         # fused pass: row + pool id + label + keep flag per candidate, loss per kept row
         rho = (kept / cands) if kept is not None else 0.5
         alg = sizes * (4 * a.d + 4 + 4 + 1) + rho * sizes * 4
-        kname = "k_step_pass<4, assist, 8, 2> (score+keep+both gradient sums, rows read once)"
+        kname = "k_step_pass<4, 7, 0, 8, 2> (score+keep+both gradient sums, rows read once)"
     else:
         alg = sizes * (4 * a.d + 4 + 4 + 1)
         kname = "k_rows_pass<pool> (score, plus keep+compact in two_pass)"
