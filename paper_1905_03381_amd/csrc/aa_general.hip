@@ -1,5 +1,5 @@
-// General row passes: CSR rows, and dense rows the register-resident kernels
-// cannot take (d > 2048, d % 4 != 0, unaligned).  A group of GL lanes walks the
+// General row passes: CSR rows, and dense rows no other pass takes (fewer than 4
+// or more than 8192 floats).  A group of GL lanes walks the
 // stored entries of a row; phi and w are read through the caches (they are the
 // only reused data; a gradient pass keeps their first entries in LDS); a second
 // kernel folds the gradient sums into the model.
