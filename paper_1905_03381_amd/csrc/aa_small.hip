@@ -176,9 +176,16 @@ __global__ __launch_bounds__(kSmallWaves * 64)
     const float gb = HARD ? 0.f : row_group_sum<kWave>(once ? resid : 0.f, lane);
 
     f4 gw = zero4, gp = zero4;
+    // With a wave per row, a rejected row and a turn past the share add nothing at all, as in a single
+    // step: zero times an infinite feature would be a NaN.  (Bit i: turn i's row counts.)  Steps of 128
+    // rows of 256 floats 4.48 us with every turn added, 4.32 so.  Elsewhere the steps this
+    // stands for add every row, and so does it.
+    constexpr bool SKIP = LPR == kWave && !HARD;
+    const uint32_t counts = SKIP ? (uint32_t)__ballot(keep && once) : ~0u;
     auto turn = [&](auto it) __attribute__((always_inline)) {
       constexpr int i = decltype(it)::value;
       if constexpr (i < IT) {
+        if (SKIP && !((counts >> i) & 1u)) return;
         gw = axpy4(row_bcast<i>(cw), x[i], gw);
         if (!HARD) gp = axpy4(row_bcast<i>(resid), x[i], gp);
       }

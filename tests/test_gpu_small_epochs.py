@@ -60,3 +60,54 @@ def test_epoch_of_more_steps_than_a_launch():
         assert ids[t * P] in pools[t]
     assert np.array_equal(ids.reshape(-1, P)[hist == 2], pools[hist == 2])
     assert np.isfinite(got[0][6]).all() and not np.array_equal(got[0][6], w0)
+
+
+def _epoch_and_steps(X, y, perm, P, w0, phi0, gamma, T):
+    """(w, phi, kept counts) of one train_epoch call and of one fused_step call per pool."""
+    n, d = X.shape
+    F, yd, pd, ws, Td = dense_features(X), dev(y), dev(perm), api.Workspace(P, d), scalar_dev(T)
+    steps = -(-n // P)
+    hist = torch.zeros(steps, dtype=torch.int32, device="cuda")
+    w, phi, b = dev(w0), dev(phi0), scalar_dev(0.0)
+    api.train_epoch(F, yd, pd, n, P, w, phi, b, api.step_config(gamma, 1e-3, 0.5, 0.1, 0.0, 5, 0, Td), None, hist, ws)
+    ws_, phis, bs, counts, cnt = dev(w0), dev(phi0), scalar_dev(0.0), [], scalar_dev(0, torch.int32)
+    for t in range(steps):
+        cfg = api.step_config(gamma, 1e-3, 0.5, 0.1, 0.0, 5, t, Td)
+        api.fused_step(F, yd, pd[t * P:], min(P, n - t * P), ws_, phis, bs, cfg, None, None, None, None, None, None, cnt, ws)
+        counts.append(int(host(cnt)[0]))
+    return (host(w), host(phi), host(hist).tolist()), (host(ws_), host(phis), counts)
+
+
+@pytest.mark.parametrize("d,P", [(132, 128), (200, 100), (256, 33)])
+def test_rejected_rows_reach_no_sum_whatever_they_hold(d, P):
+    """Rows with an infinite or NaN feature that are not kept: the model stays finite, as in single steps."""
+    n = 3 * P
+    X, y, perm, w0 = _problem(n, d)
+    phi0 = w0[::-1].copy()
+    phi0[0] = -1.0                       # an infinite x[0] scores -inf: never kept at gamma = 0
+    X[:, 0] = 0.0                        # (and so no kept row moves phi[0])
+    for t in range(3):
+        X[perm[t * P + 1], 0] = np.inf
+        X[perm[t * P + P // 2], 0] = np.nan
+        X[perm[t * P + P - 1], 0] = np.inf
+    epoch, steps = _epoch_and_steps(X, y, perm, P, w0, phi0, 0.0, 0.4)
+    assert epoch[2] == steps[2] and min(epoch[2]) > 0
+    for u, v in zip(epoch[:2], steps[:2]):
+        assert np.isfinite(u).all()
+        # (three steps, sums of at most 128 terms in two orders: 2e-6 per step is above their rounding)
+        assert np.allclose(u, v, rtol=1e-5, atol=6e-6)
+
+
+@pytest.mark.parametrize("d,P", [(132, 17), (200, 1), (256, 17)])
+def test_infinite_feature_in_a_kept_row_counts_once(d, P):
+    """A turn past the end of a wave's share re-reads its last row and adds nothing: an infinite
+    feature there moves its column to an infinity, not to a NaN."""
+    X, y, perm, w0 = _problem(P, d)
+    phi0 = w0[::-1].copy()
+    w0[0], phi0[0] = 1.0, -1.0
+    X[:, 0] = 0.0
+    X[perm[P - 1], 0], y[perm[P - 1]] = np.inf, -1.0  # margin -inf, score -inf: both coefficients are -1
+    epoch, steps = _epoch_and_steps(X, y, perm, P, w0, phi0, 1.0, 0.4)
+    assert epoch[2] == steps[2] == [P]
+    assert epoch[0][0] == steps[0][0] == -np.inf and epoch[1][0] == steps[1][0] == np.inf
+    assert np.isfinite(epoch[0][1:]).all() and np.isfinite(epoch[1][1:]).all()
