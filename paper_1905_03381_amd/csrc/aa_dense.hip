@@ -529,7 +529,8 @@ __global__ __launch_bounds__(NW * 64) void k_rows_once(const PassArgs a) {
 // is consumed as soon as it is there while rows r+1.. are still on their way.
 // Without gradient sums (MODE == kPool) it is the generator's half of k_boss_and_draw.
 // ANY: rows of any width (at least four floats), stride and address: read in pieces that start at
-// any float, the last one ending with the row, and summed in doubles, as the general kernels do.
+// any float, the last one ending with the row, and summed in doubles, and a coefficient of zero adds
+// nothing whatever the row holds, as in the general kernels.
 enum StepRows : int { kFullRows, kPartRows, kAnyRows };
 
 typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));  // (any float address)
@@ -745,7 +746,7 @@ __device__ __forceinline__ void step_rows(const PassArgs &a, int bid, int nblk, 
           if (POOL) keep = live && keep_decision(lane_read(u_l, src), g, a.gamma, a.one_minus_gamma);
         }
         const float yy = SVM ? lane_read(y_l, src) : 0.f;
-        if (GRAD && (HARD || keep)) {
+        if (GRAD && (HARD ? live : keep)) {
           if (SVM) {
             float dw = 0.f;
 #pragma unroll
@@ -755,16 +756,20 @@ __device__ __forceinline__ void step_rows(const PassArgs &a, int bid, int nblk, 
             loss = fmaxf(0.f, 1.f - marg);
             if (HARD) keep = live && loss > T;  // shrinking by the objective value itself
             const float cw = (keep && marg < 1.f) ? yy : 0.f;  // -d hinge / d margin, times y
+            if (!ANY || cw != 0.f) {  // (ANY: no zero times infinity, as in the general kernels)
 #pragma unroll
-            for (int v = 0; v < VPL; ++v) gw[v] = axpy4(cw, x[r][v], gw[v]);
+              for (int v = 0; v < VPL; ++v) gw[v] = axpy4(cw, x[r][v], gw[v]);
+            }
           } else {
             loss = lane_read(lin_l, src);
           }
           if (ASSIST) {
             const float z = loss > T ? 1.f : 0.f;    // label: Boss loss above the threshold
             const float resid = g - z;               // d cross-entropy / d logit (kept rows only)
+            if (!ANY || resid != 0.f) {
 #pragma unroll
-            for (int v = 0; v < VPL; ++v) gp[v] = axpy4(resid, x[r][v], gp[v]);
+              for (int v = 0; v < VPL; ++v) gp[v] = axpy4(resid, x[r][v], gp[v]);
+            }
             gb += resid;
           }
           if (keep) kept += 1;

@@ -99,3 +99,47 @@ def test_odd_rows_with_infinities_in_the_last_columns(ws, d):
     want = (X[rest].double().cpu() @ phi.double().cpu()).float().cuda()
     # (a sum of d terms of size 0.01: rounding below 1e-5)
     assert torch.all((logit[rest] - want).abs() <= 1e-5)
+
+
+def _one_step(X, y, w0, phi0, hard, gamma, T):
+    """w and phi (None with hard thresholds) after one whole step on all rows."""
+    n, d = X.shape
+    work, F, yd = api.Workspace(n, d), dense_features(X), dense.dev(y)
+    w, phi, cnt = dense.dev(w0), dense.dev(phi0), dense.scalar_dev(0, torch.int32)
+    if hard:
+        api.sk_step(F, yd, None, n, w, dense.scalar_dev(T), 0.0, 1.0, None, None, None, None, None, cnt, work)
+        return dense.host(w), None
+    cfg = api.step_config(gamma, 0.0, 1.0, 1.0, 0.0, 3, 0, dense.scalar_dev(T))
+    api.fused_step(F, yd, None, n, w, phi, None, cfg, None, None, None, None, None, None, cnt, work)
+    return dense.host(w), dense.host(phi)
+
+
+@pytest.mark.parametrize("d", [7, 130, 785, 1023, 1027, 4137, 9000])
+@pytest.mark.parametrize("hard", [False, True])
+@pytest.mark.parametrize("bad", [np.inf, np.nan])
+def test_rows_without_a_gradient_add_nothing(d, hard, bad):
+    """A row whose coefficients are zero (not kept, or kept with its margin met and its score right) adds
+    nothing, whatever it holds: the same model as with a large finite value in the place of the bad one."""
+    n, r = 21, dense.rng(d)
+    X = (r.standard_normal((n, d)) / np.sqrt(d)).astype(np.float32)
+    y = np.where(r.random(n) < 0.5, 1.0, -1.0).astype(np.float32)
+    w0, phi0 = r.standard_normal(d).astype(np.float32), r.standard_normal(d).astype(np.float32)
+    w0[0], phi0[0], X[:, 0] = 1.0, -1.0, 0.0
+    got = []
+    for value in (1e30, bad):  # margin beyond 1 and probability 0 (a NaN row is never kept: gamma < 1)
+        for row in (4, n - 1):
+            X[row, 0], y[row] = value, 1.0
+        got.append(_one_step(X, y, w0, phi0, hard, 0.0 if np.isnan(bad) else 1.0, 0.4))
+    assert np.isfinite(got[0][0]).all() and np.array_equal(got[0][0], got[1][0])
+    if not hard:
+        assert np.isfinite(got[0][1]).all() and np.array_equal(got[0][1], got[1][1])
+
+
+@pytest.mark.parametrize("d", [130, 132, 256, 1020, 1024, 1027])
+def test_infinite_feature_in_the_last_row_counts_once(d):
+    """A place past the last row re-reads it and adds nothing: an infinite feature there moves its
+    column to an infinity, not to a NaN."""
+    X = np.zeros((1, d), np.float32)
+    X[0, 0] = np.inf
+    w = _one_step(X, np.full(1, -1.0, np.float32), np.ones(d, np.float32), None, True, 0.0, 0.4)[0]
+    assert w[0] == -np.inf and np.array_equal(w[1:], np.ones(d - 1, np.float32))
