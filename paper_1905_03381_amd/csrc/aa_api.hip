@@ -192,8 +192,21 @@ size_t grad_bytes_for(const PassSpec &s) {
   if (use_fast(s))
     return (size_t)dense_pass_blocks(s.F->d, s.count_max, s.mode) * nvec *
            dense_d_pad(s.F->d) * sizeof(float);
-  // (what k_wide_pass needs, 256 partials of nvec rounded-up rows, is less than this)
+  // (what the other dense passes need, up to 256 partials of nvec rounded-up rows, is less than this,
+  // and where some of k_wide_pass's sums are doubles it takes no more blocks than this has room for)
   return general_acc_bytes(s.F->d, s.count_max);
+}
+
+// Blocks of the passes use_wide() takes.  With both vectors of more than 4096 columns the doubles among the
+// partial sums may leave room for fewer than wide_pass_blocks() asks for (182 of 256 at 8192 columns and
+// pools of up to 1365 rows, 204 at 4096 rows, all from 10,700 rows on).
+int32_t wide_blocks(const PassSpec &s) {
+  int32_t nblk = wide_pass_blocks(s.F->d, s.count_max);
+  const int nvec = ((s.mode & kSvm) ? 1 : 0) + ((s.mode & kAssist) ? 1 : 0);
+  if (nvec == 0) return nblk;
+  const size_t each = (size_t)nvec * wide_part_row(s.F->d, nvec) * sizeof(float);
+  const size_t room = general_acc_bytes(s.F->d, s.count_max) / each;
+  return (size_t)nblk < room ? nblk : (int32_t)room;
 }
 
 // What the kernels for dense rows in registers are told (wide: k_wide_pass).
@@ -204,6 +217,8 @@ PassArgs dense_args(const PassSpec &s, const Ws &ws, bool wide) {
   a.d4 = (s.F->d + 3) / 4;
   a.d = s.F->d;
   a.d_pad = wide ? wide_d_pad(s.F->d) : dense_d_pad(s.F->d);
+  const int nvec = ((s.mode & kSvm) ? 1 : 0) + ((s.mode & kAssist) ? 1 : 0);
+  a.part_row = wide ? wide_part_row(s.F->d, nvec) : a.d_pad;
   a.y = s.y;
   a.rows = s.rows;
   a.count_max = s.count_max;
@@ -242,7 +257,7 @@ hipError_t run_pass(const PassSpec &s, const Ws &ws, int32_t *nblk_out, hipStrea
   if (wide || use_fast(s)) {
     const PassArgs a = dense_args(s, ws, wide);
     if (wide) {
-      *nblk_out = wide_pass_blocks(s.F->d, s.count_max);
+      *nblk_out = wide_blocks(s);
       const Hook hook;
       return launch_wide_pass(a, s.mode, *nblk_out, st, hook.started, hook.stopped);
     }
@@ -340,6 +355,8 @@ hipError_t run_update(const PassSpec &s, const UpdateSpec &u, const Ws &ws, int3
     f.nvec = ((s.mode & kSvm) ? 1 : 0) + ((s.mode & kAssist) ? 1 : 0);
     f.d = s.F->d;
     f.d_pad = wide ? wide_d_pad(s.F->d) : dense_d_pad(s.F->d);
+    f.part_row = wide ? wide_part_row(s.F->d, f.nvec) : f.d_pad;
+    f.f64_from = f.part_row > f.d_pad ? kWideFp32Cols : f.d_pad;
     f.blk_cnt = ws.blk_cnt;
     f.blk_gb = ws.blk_gb;
     f.m_dev = pool ? nullptr : s.m_dev;

@@ -901,8 +901,11 @@ constexpr int kFinGroups = 256 / kFinCols4;    // partial groups per column (256
 // g, g + kFinGroups, ... in that order, the groups of a wave are folded with a fixed
 // butterfly, the four wave sums are added in wave order.  One memory round trip (every
 // load is requested before any is used) and one barrier.
+// TAIL64: the sums of the columns from a.f64_from on are doubles; a block's columns are all of one kind.
+template <bool TAIL64>
 __global__ __launch_bounds__(256) void k_finalize(const FinalizeArgs a) {
   __shared__ f4 s_acc[4][kFinCols4];
+  __shared__ f64x4 s_acc64[TAIL64 ? 4 : 1][kFinCols4];
   __shared__ int s_int[40];
   __shared__ float s_flt[8];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -952,15 +955,30 @@ __global__ __launch_bounds__(256) void k_finalize(const FinalizeArgs a) {
   for (int i = 0; i < 4; ++i) old[i] = model[min(k0 + i, a.d - 1)];
   const f4 zero = {0.f, 0.f, 0.f, 0.f};
   f4 acc = zero;
-  const f4 *p = reinterpret_cast<const f4 *>(a.partial) + (size_t)vec * row4 + col4;
-  const size_t stride = (size_t)a.nvec * row4;
-  for (int base = pg; base < nb; base += 8 * kFinGroups) {
-    f4 v[8];
+  const f4 *p = reinterpret_cast<const f4 *>(a.partial + (size_t)vec * a.part_row) + col4;
+  const size_t stride = (size_t)a.nvec * a.part_row / 4;
+  const bool tail = TAIL64 && k0 >= a.f64_from;          // (the same in the whole block)
+  f64x4 acc64 = {0., 0., 0., 0.};
+  if (tail) {
+    const f64x4 *p64 = reinterpret_cast<const f64x4 *>(a.partial + (size_t)vec * a.part_row + a.f64_from) +
+                       (k0 - a.f64_from) / 4;
+    for (int base = pg; base < nb; base += 8 * kFinGroups) {
+      f64x4 v[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) v[j] = p[(size_t)min(base + j * kFinGroups, nb - 1) * stride];
+      for (int j = 0; j < 8; ++j) v[j] = p64[(size_t)min(base + j * kFinGroups, nb - 1) * (stride / 2)];
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
-      if (base + j * kFinGroups < nb) acc += v[j];       // block order within the group
+      for (int j = 0; j < 8; ++j)
+        if (base + j * kFinGroups < nb) acc64 += v[j];
+    }
+  } else {
+    for (int base = pg; base < nb; base += 8 * kFinGroups) {
+      f4 v[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[j] = p[(size_t)min(base + j * kFinGroups, nb - 1) * stride];
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        if (base + j * kFinGroups < nb) acc += v[j];     // block order within the group
+    }
   }
   if (a.m_dev || tid >= nb) cnt_part = 0;
   if (!bias_block || tid >= nb) gb_part = 0.f;
@@ -980,6 +998,14 @@ __global__ __launch_bounds__(256) void k_finalize(const FinalizeArgs a) {
     acc.w += __shfl_xor(acc.w, off, kWave);
   }
   if (lane < kFinCols4) s_acc[wave][lane] = acc;
+  if (tail) {
+#pragma unroll
+    for (int off = kFinCols4; off < kWave; off <<= 1) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc64[i] += __shfl_xor(acc64[i], off, kWave);
+    }
+    if (lane < kFinCols4) s_acc64[TAIL64 ? wave : 0][lane] = acc64;
+  }
   cnt_part = wave_sum_int(cnt_part);
   gb_part = group_sum<kWave>(gb_part);
   if (lane == 0) {
@@ -1000,7 +1026,12 @@ __global__ __launch_bounds__(256) void k_finalize(const FinalizeArgs a) {
     const float inv_m = 1.f / (float)m;
     if (pg == 0) {
       const f4 g = (s_acc[0][c4] + s_acc[1][c4]) + (s_acc[2][c4] + s_acc[3][c4]);
-      const float gv[4] = {g.x, g.y, g.z, g.w};
+      float gv[4] = {g.x, g.y, g.z, g.w};
+      if constexpr (TAIL64) {
+        const f64x4 g64 = (s_acc64[0][c4] + s_acc64[1][c4]) + (s_acc64[2][c4] + s_acc64[3][c4]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) gv[i] = tail ? (float)g64[i] : gv[i];
+      }
       if (boss) {
         const float shrink = 1.f - lr * a.lambda;
         const float scale = lr * inv_m;
@@ -1292,7 +1323,10 @@ hipError_t launch_boss_and_draw(const PassArgs &boss, const PassArgs &gen, int32
 hipError_t launch_dense_finalize(const FinalizeArgs &a, hipStream_t st) {
   const int nred = a.d_pad / (4 * kFinCols4) * a.nvec;
   const int extra = a.flags ? compact_tiles(a.P) : 0;
-  hipLaunchKernelGGL(k_finalize, dim3(nred + extra), dim3(256), 0, st, a);
+  if (a.f64_from < a.d_pad)
+    hipLaunchKernelGGL(k_finalize<true>, dim3(nred + extra), dim3(256), 0, st, a);
+  else
+    hipLaunchKernelGGL(k_finalize<false>, dim3(nred + extra), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 

@@ -34,8 +34,9 @@ struct PassArgs {
   uint8_t *flags;         // pool: keep flags [P]
   float *loss_out;        // kSvm: loss per position (pool) or per row (kept); may be NULL
   const float *loss_in;   // kAssist without kSvm: Boss losses per row
-  float *partial;         // [nblk][nvec][d_pad]
-  int32_t d_pad;
+  float *partial;         // [nblk][nvec][part_row]
+  int32_t d_pad;          // padded width of a vector
+  int32_t part_row;       // floats of a block's sums of one vector (d_pad, more where some are doubles)
   int32_t *blk_cnt;       // [nblk] kept count per block (pool mode)
   float *blk_gb;          // [nblk] bias-gradient partial (kAssist)
   const int32_t *t_upd;   // optional update counter; block 0 snapshots it into *t_snap
@@ -66,6 +67,8 @@ inline int64_t dense_carry_capacity(int32_t nblk) { return (int64_t)nblk * kWave
 struct FinalizeArgs {
   const float *partial;
   int32_t nblk, nvec, d, d_pad;
+  int32_t part_row;        // floats of a block's sums of one vector
+  int32_t f64_from;        // the first column whose sums are doubles (a multiple of 32; d_pad: none)
   const int32_t *blk_cnt;  // pool mode: m = sum
   const float *blk_gb;
   const int32_t *m_dev;    // kept mode: m = min(*m_dev, m_max)

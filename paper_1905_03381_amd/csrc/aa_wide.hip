@@ -22,8 +22,13 @@ constexpr int kWideWaves = 8, kWideThreads = kWideWaves * kWave;
 // every load is a whole one, in bounds and without a condition.  Columns such a piece shares
 // with the one before are masked to zero.
 //
-// The gradient sums are doubles, rounded once per block (fp64 FMAs run at the fp32 rate here
-// and the pass waits for memory).  VPT pieces of R rows, twice, are in registers: 4 rows of
+// The gradient sums are doubles (fp64 FMAs run at the fp32 rate here and the pass waits for memory),
+// rounded once per block; with two vectors those of the columns from kWideFp32Cols on stay doubles
+// until the update kernel has added all blocks up.  That is what the general kernels keep of dense
+// rows: the LDS of a block there holds sums of 8192 columns of one vector or 4096 of two, which leave it as
+// floats, and everything past them is added in doubles.  (Whole steps with the doubles against all sums
+// rounded per block: d = 4137, 4096 rows 22.6 -> 23.4 us, d = 8000 35.2 -> 37.5, 512 rows 16.4 -> 19.3.)
+// VPT pieces of R rows, twice, are in registers: 4 rows of
 // 17 KB at d = 4137, so that about 130 KB of a compute unit's rows are on their way at a time.
 // Measured: epochs of 4 pools of 4096 rows (the general kernels' times in brackets, whose sums go
 // through LDS and sorted records): d = 2052 66 us (141), 4093 89 (232), 6145 116 (898), 8000 137
@@ -232,29 +237,32 @@ __global__ __launch_bounds__(kWideThreads)
   }
 
   if (GRAD) {
-    const int d_pad = a.d_pad;
-    float *const part = a.partial + (size_t)blockIdx.x * NVEC * d_pad;
+    const int row = a.part_row;
+    float *const part = a.partial + (size_t)blockIdx.x * NVEC * row;
 #pragma unroll
     for (int v = 0; v < VPT; ++v) {
+      constexpr int kPieces = kWideFp32Cols / (4 * kWideThreads);  // pieces of a thread before the doubles
       const int c = 4 * (v * kWideThreads + (int)threadIdx.x);
-      f4 tw = {0.f, 0.f, 0.f, 0.f}, tp = {0.f, 0.f, 0.f, 0.f};
+      auto put = [&](const double (&g)[4], float *to) __attribute__((always_inline)) {
+        if (NVEC == 2 && v >= kPieces) {
+          double *const out = reinterpret_cast<double *>(to + kWideFp32Cols) - kWideFp32Cols;
+          if (c + 4 <= a.d) {
+            *reinterpret_cast<f64x4 *>(out + c) = f64x4{g[0], g[1], g[2], g[3]};
+          } else {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        if (SVM) tw[i] = (float)gw[v][i];
-        if (ASSIST) tp[i] = (float)gp[v][i];
-      }
-      if (c + 4 <= a.d) {
-        if (SVM) *reinterpret_cast<f4 *>(part + c) = tw;
-        if (ASSIST) *reinterpret_cast<f4 *>(part + (SVM ? d_pad : 0) + c) = tp;
-      } else {
+            for (int i = 0; i < 4; ++i)
+              if (first[v] + i >= c) out[first[v] + i] = g[i];
+          }
+        } else if (c + 4 <= a.d) {
+          *reinterpret_cast<f4 *>(to + c) = f4{(float)g[0], (float)g[1], (float)g[2], (float)g[3]};
+        } else {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int k = first[v] + i;
-          if (k < c) continue;
-          if (SVM) part[k] = tw[i];
-          if (ASSIST) part[(SVM ? d_pad : 0) + k] = tp[i];
+          for (int i = 0; i < 4; ++i)
+            if (first[v] + i >= c) to[first[v] + i] = (float)g[i];
         }
-      }
+      };
+      if (SVM) put(gw[v], part);
+      if (ASSIST) put(gp[v], part + (SVM ? row : 0));
     }
     if (wave == 0) {  // (every wave counted the same)
 #pragma unroll
@@ -303,6 +311,11 @@ bool wide_rows_ok(const aa_features *F) {
 }
 
 int32_t wide_d_pad(int32_t d) { return (d + 31) / 32 * 32; }
+
+int32_t wide_part_row(int32_t d, int nvec) {
+  const int32_t pad = wide_d_pad(d);
+  return nvec == 2 && pad > kWideFp32Cols ? 2 * pad - kWideFp32Cols : pad;
+}
 
 // A block's partial sums are as long as a row per updated vector, written and read again, so few
 // rows per block are as much traffic for the sums as for the rows; few blocks leave compute units

@@ -17,6 +17,12 @@ bool wide_rows_ok(const aa_features *F);
 // Padded width (floats) of one gradient partial.
 int32_t wide_d_pad(int32_t d);
 
+// Passes that update both vectors leave a block's sums of the columns from this one on in doubles.
+constexpr int kWideFp32Cols = 4096;
+
+// Floats of a block's sums of one vector: the padded row, the doubles counting twice.
+int32_t wide_part_row(int32_t d, int nvec);
+
 int32_t wide_pass_blocks(int32_t d, int32_t count);
 
 hipError_t launch_wide_pass(const PassArgs &a, int mode, int32_t nblk, hipStream_t stream,

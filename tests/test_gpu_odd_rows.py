@@ -143,3 +143,19 @@ def test_infinite_feature_in_the_last_row_counts_once(d):
     X[0, 0] = np.inf
     w = _one_step(X, np.full(1, -1.0, np.float32), np.ones(d, np.float32), None, True, 0.0, 0.4)[0]
     assert w[0] == -np.inf and np.array_equal(w[1:], np.ones(d - 1, np.float32))
+
+
+@pytest.mark.parametrize("d", [4097, 4137, 6145, 8192])
+@pytest.mark.parametrize("P", [1024, 3000])
+def test_sums_past_4096_columns_are_rounded_once(d, P):
+    """Passes that update both vectors keep the sums of the columns from 4096 on in doubles until all
+    blocks are added up: a one beside terms of 2^24 that cancel between two blocks is not lost."""
+    X, cols = np.zeros((P, d), np.float32), np.unique([4096, 4096 + (d - 4096) // 2, d - 1])
+    for c in cols:
+        X[0, c], X[1, c], X[P - 1, c] = 2.0 ** 24, 1.0, -2.0 ** 24
+    zero = np.zeros(d, np.float32)
+    # (w = phi = 0: every margin is 0 and every score 1/2; T = 2 makes every label 0)
+    w, phi = _one_step(X, np.ones(P, np.float32), zero, zero, False, 1.0, 2.0)
+    inv = np.float32(1.0) / np.float32(P)
+    assert np.all(w[cols] == inv) and np.all(phi[cols] == -np.float32(0.5) * inv)
+    assert np.count_nonzero(w) == np.count_nonzero(phi) == cols.size
