@@ -534,6 +534,8 @@ __global__ __launch_bounds__(NW * 64) void k_rows_once(const PassArgs a) {
 enum StepRows : int { kFullRows, kPartRows, kAnyRows };
 
 typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));  // (any float address)
+typedef uint32_t u4u __attribute__((ext_vector_type(4), aligned(4)));
+
 template <int VPL, int MODE, int NW, int ROWS = kFullRows>
 struct StepLds {
   using Acc = std::conditional_t<ROWS == kAnyRows, f64x4, f4>;
@@ -585,8 +587,8 @@ __device__ __forceinline__ void step_rows(const PassArgs &a, int bid, int nblk, 
   // ---- Requests that depend on nothing, all unconditional: a load under a condition would
   // make every later wait for an older load a wait for everything (the pending counts of the
   // two paths are merged pessimistically), so absent inputs read a stand-in address (the
-  // start of a model vector, which always holds 132 floats) and indices are clamped; what was
-  // read for nothing is dropped by a select.
+  // first 16 bytes of a model vector: it holds four floats at least, at any float address with ANY)
+  // and indices are clamped; what was read for nothing is dropped by a select.
   const int32_t *stand_in = reinterpret_cast<const int32_t *>(model);
   const int in_group = min(lane, max(cnt, 1) - 1);
   const bool listed = a.rows != nullptr && cnt > 0;
@@ -598,9 +600,9 @@ __device__ __forceinline__ void step_rows(const PassArgs &a, int bid, int nblk, 
   const bool carry = POOL && GRAD && a.prev.flags != nullptr && bid * kWave < a.prev.P;
   const int cj0 = bid * kWave;     // this block places positions [cj0, cj0 + 64)
   const int n16 = carry ? (cj0 >> 4) : 0;  // 16-byte pieces of flags before them
-  const uint4 *p16 = n16 > 0 ? reinterpret_cast<const uint4 *>(a.prev.flags)
-                             : reinterpret_cast<const uint4 *>(model);
-  uint4 carry_v = p16[min((int)threadIdx.x, max(n16, 1) - 1)];
+  const u4u *p16 = n16 > 0 ? reinterpret_cast<const u4u *>(a.prev.flags)
+                           : reinterpret_cast<const u4u *>(model);
+  u4u carry_v = p16[min((int)threadIdx.x, max(n16, 1) - 1)];
   const int cpos = carry ? min(cj0 + lane, a.prev.P - 1) : 0;
   uint8_t carry_flag = (carry ? a.prev.flags : reinterpret_cast<const uint8_t *>(model))[cpos];
   int carry_id = ((carry && a.prev.idx) ? a.prev.idx : stand_in)[a.prev.idx ? cpos : 0];
@@ -639,7 +641,7 @@ __device__ __forceinline__ void step_rows(const PassArgs &a, int bid, int nblk, 
   if (carry && !a.prev.idx) carry_id = cj0 + lane;
   const unsigned long long carry_mask = __ballot(carry_flag != 0);
   for (int q = threadIdx.x + NT; q < n16; q += NT) {  // previous pools above 16 NT positions
-    const uint4 v = p16[q];
+    const u4u v = p16[q];
     carry_cnt += __popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w);
   }
 #pragma unroll

@@ -367,10 +367,12 @@ def _offset_by_4_bytes(a):
 
 
 @pytest.mark.parametrize("which", ["x", "w", "phi"])
-def test_pointers_aligned_to_4_bytes_only(ref, ws, which):
-    """x, w or phi 4-byte aligned but not 16-byte aligned: the calls take the general kernels
-    (no 128-bit loads) and still match the oracle: score, Boss step, whole step."""
-    n, d, P = 500, 1024, 333
+@pytest.mark.parametrize("d", [4, 1024])
+def test_pointers_aligned_to_4_bytes_only(ref, ws, which, d):
+    """x, w or phi 4-byte aligned but not 16-byte aligned: the calls take the kernels for rows at any
+    float address and still match the oracle: score, Boss step, whole step.  (Four floats: the model
+    vectors are no longer than one 16-byte piece.)"""
+    n, P = 500, 333
     X, y = make_dense(n, d, 111, unit=True)
     r = rng(112)
     w0 = (1.2 * r.standard_normal(d)).astype(np.float32)
