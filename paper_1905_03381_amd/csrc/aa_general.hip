@@ -845,7 +845,6 @@ __global__ __launch_bounds__(256) void k_prepare_general(float *p, size_t count,
 // per step, 4 / 8 / 16 waves: 73.4 / 68.2 / 69.6 us; pools of 8000 35.0 / 31.3 / 34.0.
 constexpr int kApplyWaves = 8, kApplyThreads = kApplyWaves * kWave;
 constexpr int kHeadCols = kApplyThreads / 16;
-static_assert(kGeneralGradBlocks <= kApplyThreads, "one per-block count of the pass per thread");
 
 typedef float f4v __attribute__((ext_vector_type(4), aligned(4)));  // (any float address)
 
@@ -893,7 +892,9 @@ struct Fold {
   }
 };
 
-// Kept count of the pass (and the sum of its bias gradients): one per-block value per thread.
+// Kept count of the pass (and the sum of its bias gradients): one per-block value per thread of
+// the first four waves.
+static_assert(kGeneralGradBlocks <= 4 * kWave && kApplyWaves >= 4, "pass_totals adds up four waves' counts");
 __device__ __forceinline__ int pass_totals(const ApplyArgs &a, int cnt, float gbs, int *s_m,
                                            float *s_g, float *gb_out) {
   const int t = threadIdx.x;
@@ -908,7 +909,7 @@ __device__ __forceinline__ int pass_totals(const ApplyArgs &a, int cnt, float gb
   }
   __syncthreads();
   *gb_out = (s_g[0] + s_g[1]) + (s_g[2] + s_g[3]);
-  const int m_pass = s_m[0] + s_m[1] + s_m[2] + s_m[3];  // (the counts are in the first four waves)
+  const int m_pass = s_m[0] + s_m[1] + s_m[2] + s_m[3];
   return a.m_dev ? min(max(*a.m_dev, 0), a.m_max) : m_pass;
 }
 
