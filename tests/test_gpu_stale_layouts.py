@@ -37,3 +37,21 @@ def test_batches_and_model(ref, n, d, P, k):
     tu = torch.zeros(1, dtype=torch.int32, device="cuda")
     api.train_epoch_stale(F, dev(y), dev(perm), n, P, k, w, phi, b, cfg, tu, None, None, ws, torch.cuda.Stream())
     assert np.array_equal(host(w), got[0]) and np.array_equal(host(phi), got[1]) and float(host(b)[0]) == got[2]
+
+
+def test_pools_beyond_direct_counting(ref):
+    """Above 2^18 candidates a drawn pool is compacted by launches of its own behind the update."""
+    n, d, P, k = 1000, 132, (1 << 18) + 5, 1
+    r = stale.rng(d)
+    X = r.standard_normal((n, d)).astype(np.float32)
+    X /= np.linalg.norm(X, axis=1, keepdims=True)
+    y = np.where(X @ r.standard_normal(d) > 0, 1.0, -1.0).astype(np.float32)
+    perm = r.integers(0, n, 2 * P + 9).astype(np.int32)  # (rows come up again and again)
+    w0, phi0 = np.zeros(d, np.float32), (0.5 * r.standard_normal(d)).astype(np.float32)
+    gamma, lam, lr0, T, lr_a, step0 = 0.05, 1e-4, 1.0, 0.9, 2.0, 0
+    for seed in range(11, 41):
+        want = ref.train_stale(ref.Features.dense(X), y, perm, P, w0, phi0, 0.2, gamma, seed, step0, lam, lr0, T, lr_a, k)
+        if all(clear_draws(ref, p, gamma, seed, step0 + s).all() for s, p in enumerate(want["prob"])):
+            break
+    got = stale._run_gpu(dense_features(X), y, perm, perm.size, P, d, k, gamma, seed, step0, lam, lr0, T, lr_a, w0, phi0, 0.2, True)
+    stale._compare(ref, got, want, P, gamma, seed, step0)
