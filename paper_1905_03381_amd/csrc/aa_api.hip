@@ -214,6 +214,7 @@ PassArgs dense_args(const PassSpec &s, const Ws &ws, bool wide) {
   PassArgs a{};
   a.x = s.F->x;
   a.ld = s.F->ld;
+  a.plain_loads = wide_plain_loads((size_t)s.F->n * (size_t)s.F->ld * sizeof(float));
   a.d4 = (s.F->d + 3) / 4;
   a.d = s.F->d;
   a.d_pad = wide ? wide_d_pad(s.F->d) : dense_d_pad(s.F->d);

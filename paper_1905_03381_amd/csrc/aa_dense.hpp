@@ -16,6 +16,7 @@ enum : int { kSvm = 1, kAssist = 2, kPool = 4, kHard = 8 };
 struct PassArgs {
   const float *x;
   int64_t ld;
+  bool plain_loads;       // rows are read with plain loads (k_wide_pass, scoring only)
   int32_t d4;             // pieces of four floats, rounded up
   int32_t d;
   const float *y;         // labels indexed by data-set row (kSvm)

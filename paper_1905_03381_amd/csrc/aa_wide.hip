@@ -35,7 +35,7 @@ constexpr int kWideWaves = 8, kWideThreads = kWideWaves * kWave;
 // (1488) = 3.8 TB/s of rows; the pass alone at d = 4137 19.3 us (53).  Scalars per row -- sigmoid,
 // draw, loss -- are worked out for all R rows at once, a row per eight lanes: done row by row in
 // every lane they took longer than the dot products (22.0 us).
-template <int VPT, int R, int MODE>
+template <int VPT, int R, int MODE, bool NT = true>
 __global__ __launch_bounds__(kWideThreads)
     __attribute__((amdgpu_waves_per_eu(2, 2))) void k_wide_pass(const PassArgs a) {
   constexpr bool POOL = (MODE & kPool) != 0;
@@ -115,7 +115,10 @@ __global__ __launch_bounds__(kWideThreads)
         const float *xr = a.x + (int64_t)row * a.ld;
 #pragma unroll
         for (int v = 0; v < VPT; ++v)
-          xb[r][v] = __builtin_nontemporal_load(reinterpret_cast<const f4u *>(xr + first[v]));
+          if (NT)
+            xb[r][v] = __builtin_nontemporal_load(reinterpret_cast<const f4u *>(xr + first[v]));
+          else
+            xb[r][v] = *reinterpret_cast<const f4u *>(xr + first[v]);
       }
     };
     auto consume = [&](int it, f4u (&xb)[R][VPT]) __attribute__((always_inline)) {
@@ -281,7 +284,10 @@ hipError_t launch_vpt(const PassArgs &a, int mode, int nblk, hipStream_t st, hip
   const dim3 grid(nblk), block(kWideThreads);
   switch (mode) {
     case kPool:
-      launch_stamped((k_wide_pass<VPT, R, kPool>), grid, block, st, e0, e1, a);
+      if (a.plain_loads)
+        launch_stamped((k_wide_pass<VPT, R, kPool, false>), grid, block, st, e0, e1, a);
+      else
+        launch_stamped((k_wide_pass<VPT, R, kPool>), grid, block, st, e0, e1, a);
       break;
     case kSvm:
       launch_stamped((k_wide_pass<VPT, R, kSvm>), grid, block, st, e0, e1, a);
@@ -322,6 +328,9 @@ int32_t wide_part_row(int32_t d, int nvec) {
 // idle.  Four rows a block up to half the compute units, eight beyond that.  Epochs of 4 pools at
 // d = 4137, one / four / eight rows a block: pools of 256 rows 53.7 / 43.8 / 48.8 us, of 500 55.9 /
 // 48.6 / 52.0, of 1000 59.2 / 59.2 / 56.7, of 1600 69.3 / 69.3 / 64.6 us.
+// Scoring leaves no sums, but takes the same blocks: with at most 1 / 2 / 4 / 8 of them per compute unit
+// 20,000 x 1027 took 17.0 / 19.0 / 24.5 / 32.5 us, 4096 x 4137 10.3 / 13.3 / 16.3 / 13.3, 65,536 x 31
+// 12.1 / 14.3 / 16.6 / 21.6: every block fetches the model and fills its pipeline anew.
 int32_t wide_pass_blocks(int32_t d, int32_t count) {
   if (d < kWideMinD) {  // a row per wave and block of eight
     const int32_t want = (int32_t)(((int64_t)count + 7) / 8);

@@ -159,3 +159,21 @@ def test_sums_past_4096_columns_are_rounded_once(d, P):
     inv = np.float32(1.0) / np.float32(P)
     assert np.all(w[cols] == inv) and np.all(phi[cols] == -np.float32(0.5) * inv)
     assert np.count_nonzero(w) == np.count_nonzero(phi) == cols.size
+
+
+@pytest.mark.parametrize("d", [1027, 2050, 4137, 8001])
+def test_scores_out_of_matrices_of_any_size(d):
+    """Scoring takes plain or non-temporal loads by the size of the whole matrix (76 and 256 MB are the
+    limits): the same bits from all of them, and the sum of the products."""
+    n, P = (1 << 26) // d + 300, 277
+    X = torch.empty(n, d, device="cuda").normal_(generator=torch.Generator(device="cuda").manual_seed(d))
+    phi = torch.randn(d, device="cuda", generator=torch.Generator(device="cuda").manual_seed(1)) / d ** 0.5
+    got = []
+    for rows in (X, X[:n // 2], X[:300]):  # 257 to 266, 128 to 133 and 1 to 10 MB
+        logit, prob = torch.zeros(P, device="cuda"), torch.zeros(P, device="cuda")
+        api.assistant_score(api.Features.dense(rows), None, P, phi, None, logit, prob)
+        got.append((logit, prob))
+    assert all(torch.equal(got[0][k], other[k]) for other in got[1:] for k in (0, 1))
+    want = X[:P].double().cpu() @ phi.double().cpu()
+    scale = X[:P].double().cpu().abs() @ phi.double().cpu().abs()
+    assert torch.all((got[0][0].cpu() - want).abs() <= 1e-5 * scale)
