@@ -153,7 +153,7 @@ __global__ __launch_bounds__(1024) void k_csr_rowptr(const GatherCsrArgs a) {
 }
 
 // Row pointers of many kept rows: entry count of every tile of 1024 rows, then the scan inside
-// each tile on top of the counts before it (beyond kSumTilesMax tiles those are scanned by a
+// each tile on top of the counts before it (beyond kCsrSumTilesMax tiles those are scanned by a
 // block in between).
 constexpr int kCsrTile = 1024;
 
@@ -374,7 +374,7 @@ hipError_t launch_gather_csr(const GatherCsrArgs &a, long long *tile_scratch, hi
   } else {
     const int ntiles = (a.max_rows + kCsrTile - 1) / kCsrTile;
     hipLaunchKernelGGL(k_csr_tile_sums, dim3(ntiles), dim3(kCsrTile), 0, st, a, tile_scratch);
-    if (ntiles > kSumTilesMax) {
+    if (ntiles > kCsrSumTilesMax) {
       hipLaunchKernelGGL(k_csr_scan_tiles, dim3(1), dim3(1024), 0, st, tile_scratch, ntiles);
       hipLaunchKernelGGL(k_csr_rowptr_tiles<true>, dim3(ntiles), dim3(kCsrTile), 0, st, a, tile_scratch);
     } else {

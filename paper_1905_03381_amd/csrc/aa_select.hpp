@@ -44,10 +44,12 @@ struct GatherCsrArgs {
 
 // Pools up to this size let every compaction tile count the flags before it directly.
 constexpr int kDirectCountMax = 1 << 18;
-// Up to this many tiles every block adds up the counts of the tiles before its own, at most 8 per
-// thread of the row-pointer scan and 32 of the compaction, instead of waiting for a launch of
-// one block that scans them (4.8 us; 1,000,000 candidates are 489 tiles).
-constexpr int kSumTilesMax = 8192;
+// Up to this many tiles every block adds up the counts of the tiles before its own instead of waiting
+// for a launch of one block that scans them; the counts read grow with the square of the tiles.
+// Whole calls, added up / scanned: keep flags of 500 tiles of 2048 12.3 / 14.0 us, 2000 22.8 / 24.7, 4000
+// 37.3 / 38.8, 6000 53.2 / 53.4, 8192 71.9 / 69.5; CSR assembly of 150 tiles of 1024 rows 14.3 / 16.5,
+// 2000 77.2 / 77.7, 3000 108.2 / 107.8, 8192 301 / 296.
+constexpr int kSumTilesMax = 4096, kCsrSumTilesMax = 2048;
 
 hipError_t launch_keep_flags(const KeepArgs &a, int source, hipStream_t stream);
 // Compact c.flags (c.tile_off is set here).  tile_off_scratch: P/2048 + 1 ints of workspace.

@@ -21,7 +21,8 @@ def _zeros(n, dtype=torch.int32):
     return torch.zeros(n, dtype=dtype, device="cuda")
 
 
-@pytest.mark.parametrize("P", [(1 << 18) + 1, 300 * 2048 + 5, 8192 * 2048, 8192 * 2048 + 1])
+@pytest.mark.parametrize("P", [(1 << 18) + 1, 300 * 2048 + 5, 4096 * 2048, 4096 * 2048 + 1, 8192 * 2048,
+                               8192 * 2048 + 1])
 def test_shrink_threshold_over_many_tiles(P):
     crit = torch.rand(P, generator=_gen(P), device="cuda")
     keep, pos, cnt = _zeros(P, torch.uint8), _zeros(P), _zeros(1)
@@ -31,7 +32,8 @@ def test_shrink_threshold_over_many_tiles(P):
     assert torch.equal(pos[:want.numel()], want) and not pos[want.numel():].any()
 
 
-@pytest.mark.parametrize("n,most", [(1025, 9), (5000, 140), (200_000, 70), (8192 * 1024, 3), (8192 * 1024 + 1025, 5)])
+@pytest.mark.parametrize("n,most", [(1025, 9), (5000, 140), (200_000, 70), (2048 * 1024, 5), (2048 * 1024 + 1, 5),
+                                    (8192 * 1024, 3), (8192 * 1024 + 1025, 5)])
 @pytest.mark.parametrize("ones", [False, True])
 def test_csr_assembly(n, most, ones):
     g = _gen(n)
