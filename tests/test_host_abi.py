@@ -86,3 +86,14 @@ def test_no_kernel_spills_registers():
     assert all("scratch" in v and "vgprs" in v for v in table.values())
     spilled = {k: v for k, v in table.items() if v["scratch"] > 0}
     assert not spilled, f"kernels with scratch: {spilled}"
+
+
+@pytest.mark.parametrize("missing", ["_raw_stream", "_device"])
+def test_stream_without_the_private_torch_calls(monkeypatch, missing):
+    """A torch without the private pair is asked for its Stream object."""
+    class Stream:
+        cuda_stream = 1234
+
+    monkeypatch.setattr(api, missing, None)
+    monkeypatch.setattr(api.torch.cuda, "current_stream", lambda: Stream)
+    assert api._stream() == 1234
