@@ -31,7 +31,7 @@ def make_dense(n, d, seed, ld=None, unit=False):
     return X, y
 
 
-# shapes: (n, d, ld, P) -- several register layouts, masked tails, the general kernels
+# shapes: (n, d, ld, P) -- several register layouts, masked tails, rows off 16 bytes, wide rows, the general kernels
 SCORE_SHAPES = [
     (300, 128, None, 256),      # tiny config: 32 lanes per row
     (700, 1024, None, 613),     # dense config row width, ragged pool
@@ -39,8 +39,8 @@ SCORE_SHAPES = [
     (300, 2048, None, 200),     # widest register layout
     (400, 36, None, 333),       # masked 16-lane layout
     (400, 200, 256, 400),       # padded rows (ld > d), masked lanes
-    (300, 130, None, 250),      # d % 4 != 0 -> general kernel
-    (200, 4100, None, 150),     # d > 2048 -> general kernel
+    (300, 130, None, 250),      # d % 4 != 0 -> the row-per-wave pass at any address
+    (200, 4100, None, 150),     # d > 2048 -> a block per row
     (120, 9000, None, 100),     # general kernel, thousands of columns past its LDS table
     (64, 1024, None, 1),        # single candidate
 ]
@@ -211,8 +211,8 @@ SGD_SHAPES = [
     (300, 2048, None, 77),
     (400, 36, None, 333),
     (400, 200, 256, 250),
-    (300, 130, None, 111),     # general kernel (atomics)
-    (200, 4100, None, 90),     # general kernel
+    (300, 130, None, 111),     # row per wave, any address
+    (200, 4100, None, 90),     # block per row
     (120, 9000, None, 100),    # general kernel, thousands of columns past its LDS table
     (64, 1024, None, 1),
 ]
@@ -309,7 +309,8 @@ def _check_state(ref_out, w, phi, b, Fh, ids_kept, y, w0, phi0, b0, lr, lam, lr_
     (700, 1024, None, 613, 0.0),     # no smoothing: the Assistant alone decides
     (700, 1024, None, 613, 0.5),
     (700, 1024, None, 613, 1.0),     # every candidate kept: the plain mini-batch step
-    (300, 130, None, 250, 1.0),      # the same through the general kernel
+    (300, 130, None, 250, 1.0),      # the same on rows off 16 bytes
+    (120, 9000, None, 100, 1.0),     # ... and through the general kernel
 ])
 def test_fused_step_matches_oracle_step(ref, ws, n, d, ld, P, gamma):
     X, y = make_dense(n, d, 61, ld, unit=True)
@@ -367,11 +368,11 @@ def _offset_by_4_bytes(a):
 
 
 @pytest.mark.parametrize("which", ["x", "w", "phi"])
-@pytest.mark.parametrize("d", [4, 1024])
+@pytest.mark.parametrize("d", [4, 1024, 1500, 9000])
 def test_pointers_aligned_to_4_bytes_only(ref, ws, which, d):
     """x, w or phi 4-byte aligned but not 16-byte aligned: the calls take the kernels for rows at any
     float address and still match the oracle: score, Boss step, whole step.  (Four floats: the model
-    vectors are no longer than one 16-byte piece.)"""
+    vectors are no longer than one 16-byte piece; 1500: a block per row; 9000: the general kernels.)"""
     n, P = 500, 333
     X, y = make_dense(n, d, 111, unit=True)
     r = rng(112)
@@ -468,8 +469,10 @@ def test_fused_step_empty_pool_and_nothing_kept(ref, ws):
 
 
 @pytest.mark.parametrize("n,d,P", [(3000, 1024, 2500),    # register-resident rows
-                                   (900, 130, 800),       # general kernel, all columns in its table
-                                   (700, 6000, 600)])     # general kernel: table, bins, accumulators
+                                   (900, 130, 800),       # row per wave, any address
+                                   (700, 6000, 600),      # block per row, sums in floats and doubles
+                                   (900, 3, 800),         # general kernel, all columns in its table
+                                   (700, 12_289, 600)])   # general kernel: table, bins, accumulators
 def test_fused_step_is_deterministic(n, d, P):
     X, y = make_dense(n, d, 91, unit=True)
     F = dense_features(X)
@@ -574,13 +577,13 @@ def test_train_epoch_matches_oracle_driver(ref, ws):
     assert 0 < min(counts2[:-1]) and max(counts2) < 256
 
 
-@pytest.mark.parametrize("d", [130, 4137])
+@pytest.mark.parametrize("d", [3, 130, 4137, 8193, 9001, 12_289])
 def test_train_epoch_on_general_dense_rows(ref, d):
-    """aa_train_epoch over dense rows that the register kernels do not take (d = 130; d = 4137:
-    more columns than the per-block table, so the last ones go through the column bins, and no
-    multiple of four): every step against the oracle step from the GPU's previous state, then
-    the epoch in one call bit for bit -- there the update kernel of a step leaves the workspace
-    ready for the next pass (d = 4137)."""
+    """aa_train_epoch over dense rows that the register layouts do not take (d = 130: a row per wave;
+    4137: a block per row; the general kernels with all columns in the per-block table at d = 3, and
+    with columns past it, which go through the column bins, from 8193 on): every step against the
+    oracle step from the GPU's previous state, then the epoch in one call bit for bit -- there the
+    update kernel of a general step leaves the workspace ready for the next pass."""
     from stepwise import check_epoch
     n, P = 1500, 256
     X, y = make_dense(n, d, 11, unit=True)

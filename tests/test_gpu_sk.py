@@ -1,5 +1,5 @@
 """GPU parity of the hard-threshold shrinking step (SK) against the oracle: dense register
-layouts, the general dense kernel, CSR rows, and the dense configuration at full pool size."""
+layouts, dense rows off them, the general dense kernel, CSR rows, and the dense configuration at full pool size."""
 import numpy as np
 import pytest
 import torch
@@ -84,8 +84,9 @@ DENSE_SHAPES = [
     (300, 2048, None, 200),
     (400, 36, None, 333),
     (400, 200, 256, 400),       # padded rows
-    (300, 130, None, 250),      # general kernel
-    (200, 4100, None, 150),     # general kernel
+    (300, 130, None, 250),      # row per wave, any address
+    (200, 4100, None, 150),     # block per row
+    (200, 12_289, None, 150),   # general kernel, columns past its table
     (64, 1024, None, 1),
     (40_000, 1024, None, 40_000),   # many rows per wave
 ]
@@ -168,6 +169,22 @@ def test_sk_epoch_matches_chained_oracle_steps(ref, ws):
                                 lam=lam, lr0=lr0, lr_a=0.0, T=T, ws=ws, hard=True)
     assert len(counts) == n // P and 0 < min(counts) and max(counts) < P
     assert state[3] == n // P
+
+
+@pytest.mark.parametrize("d", [3, 4137, 8195, 12_289])
+def test_sk_epoch_on_general_dense_rows(ref, d):
+    """aa_sk_epoch over dense rows of the general kernels (4137: of the pass before them): every step
+    against the oracle's, then the epoch in one call, where the update kernel leaves the workspace
+    ready, bit-identical to the step-wise run."""
+    from stepwise import check_epoch
+    n, P, r = 1000, 300, rng(d)
+    X = r.standard_normal((n, d)).astype(np.float32)
+    X /= np.linalg.norm(X, axis=1, keepdims=True)
+    y = np.where(X @ r.standard_normal(d) > 0, 1.0, -1.0).astype(np.float32)
+    perm, w0 = r.permutation(n).astype(np.int32), (0.8 * r.standard_normal(d)).astype(np.float32)
+    counts, state = check_epoch(ref, ref.Features.dense(X), dense_features(X), y, perm, n, P, w0, None, 0.0, gamma=0.0,
+                                seed=0, step0=0, lam=1e-3, lr0=0.5, lr_a=0.0, T=0.4, ws=api.Workspace(P, d), hard=True)
+    assert len(counts) == 4 and all(0 < m <= P for m in counts) and state[3] == 4
 
 
 def test_sk_epoch_on_csr_rows(ref):

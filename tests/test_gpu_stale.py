@@ -1,4 +1,4 @@
-"""GPU parity of the two-stream Boss / Assistant pipeline with a fixed staleness against the
+"""GPU parity of the stale Boss / Assistant pipeline (all on the Boss stream) against the
 oracle's schedule: every tick's batch bit for bit, the final model within tolerance."""
 import numpy as np
 import pytest
