@@ -108,7 +108,11 @@ int32_t aa_workspace_init(void *ws, size_t ws_bytes, void *stream);
  * hipEventElapsedTime(event_before, event_after) is the kernel's duration.  Both
  * are hipEvent_t handles created with timing enabled, owned by the caller, passed
  * as void*.  Two NULLs disarm.  Not for calls under stream capture.  Host state
- * only, not thread safe. */
+ * only, not thread safe.  An epoch over small pools, which otherwise runs all its
+ * steps in one launch, takes two launches a step while a hook is armed (the same
+ * batches, sums in another order): what is measured then is that pass.  A tick of
+ * aa_train_epoch_stale that scores a pool and runs the Boss in one launch counts as
+ * one row pass. */
 int32_t aa_profile_hook(void *event_before, void *event_after);
 
 /* The same for the next `count` row-pass launches, pair i around the i-th of

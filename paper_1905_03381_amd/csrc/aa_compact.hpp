@@ -1,13 +1,14 @@
 // Stable stream compaction of keep flags (the append order of Algorithm 1:
 // kept candidates stay in arrival order).
 //
-// A block compacts one tile of kCompactTile flags.  Each of its four waves owns
-// a contiguous 512-flag segment and walks it in eight 64-lane rounds: a wavefront
-// ballot turns the round's flags into a 64-bit mask, mbcnt on the mask ranks a
+// A block compacts one tile of kCompactTile flags.  Each of its waves (four, or
+// eight in the update kernel of the general path) owns a contiguous segment and
+// walks it in rounds of 64 lanes (eight of them, or four): a wavefront ballot turns the round's flags into a 64-bit mask, mbcnt on the mask ranks a
 // lane among the survivors of its round, popcounts of the masks give the wave's
-// total, and an LDS exchange of the four wave totals gives each wave its base.
-// The tile's own base is the number of flags set before it: either read from a
-// table of tile offsets or counted directly (popcount over the 0/1 bytes).
+// total, and an LDS exchange of the wave totals gives each wave its base.
+// The tile's own base is the number of flags set before it: read from a table of
+// tile offsets, added up from a table of tile counts, or counted directly
+// (popcount over the 0/1 bytes).
 #pragma once
 
 #include "aa_common.hpp"

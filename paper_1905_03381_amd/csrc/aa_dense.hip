@@ -247,35 +247,31 @@ __global__ __launch_bounds__(NW * 64)
       if (GRAD) {
         const float yy = SVM ? __shfl(y_l, li & 63, kWave) : 0.f;
         const float lin = (ASSIST && !SVM) ? __shfl(lin_l, li & 63, kWave) : 0.f;
-        bool any = true;
-        if (LPR == kWave) any = __builtin_amdgcn_readfirstlane((int)keep) != 0;
-        if (any) {
-          float loss = lin;
-          if (SVM) {
-            float dw = 0.f;
+        float loss = lin;
+        if (SVM) {
+          float dw = 0.f;
 #pragma unroll
-            for (int v = 0; v < VPL; ++v) dw = dot4(x[r][v], s_w[v * LPR + sub], dw);
-            dw = row_group_sum<LPR>(dw, lane);
-            const float marg = yy * dw;
-            loss = fmaxf(0.f, 1.f - marg);
-            if (HARD) {  // shrinking by the objective value itself
-              keep = live && loss > T;
-              if (sub == 0 && live && a.flags) a.flags[j] = keep ? 1 : 0;
-            }
-            if (sub == 0 && (HARD ? live : keep) && a.loss_out) a.loss_out[j] = loss;
-            const float cw = (keep && marg < 1.f) ? yy : 0.f;  // -d hinge / d margin, times y
-#pragma unroll
-            for (int v = 0; v < VPL; ++v) gw[v] = axpy4(cw, x[r][v], gw[v]);
+          for (int v = 0; v < VPL; ++v) dw = dot4(x[r][v], s_w[v * LPR + sub], dw);
+          dw = row_group_sum<LPR>(dw, lane);
+          const float marg = yy * dw;
+          loss = fmaxf(0.f, 1.f - marg);
+          if (HARD) {  // shrinking by the objective value itself
+            keep = live && loss > T;
+            if (sub == 0 && live && a.flags) a.flags[j] = keep ? 1 : 0;
           }
-          if (ASSIST) {
-            const float z = loss > T ? 1.f : 0.f;       // label: Boss loss above the threshold
-            const float resid = keep ? g - z : 0.f;     // d cross-entropy / d logit
+          if (sub == 0 && (HARD ? live : keep) && a.loss_out) a.loss_out[j] = loss;
+          const float cw = (keep && marg < 1.f) ? yy : 0.f;  // -d hinge / d margin, times y
 #pragma unroll
-            for (int v = 0; v < VPL; ++v) gp[v] = axpy4(resid, x[r][v], gp[v]);
-            if (sub == 0) gb += resid;
-          }
-          if (sub == 0 && keep) kept += 1;
+          for (int v = 0; v < VPL; ++v) gw[v] = axpy4(cw, x[r][v], gw[v]);
         }
+        if (ASSIST) {
+          const float z = loss > T ? 1.f : 0.f;       // label: Boss loss above the threshold
+          const float resid = keep ? g - z : 0.f;     // d cross-entropy / d logit
+#pragma unroll
+          for (int v = 0; v < VPL; ++v) gp[v] = axpy4(resid, x[r][v], gp[v]);
+          if (sub == 0) gb += resid;
+        }
+        if (sub == 0 && keep) kept += 1;
       }
     }
     // next rows: the same group of 64, or the next group
@@ -1194,6 +1190,9 @@ hipError_t launch_step_mode(const PassArgs &a, int mode, int nblk, hipStream_t s
   return hipGetLastError();
 }
 
+// Rows that fill the layout have kernels without masks: with those of the others d = 256, 40,000 rows took
+// 17.2 us per step instead of 16.8, d = 512, 16,384 13.1 / 12.4, d = 1024, 16,384 16.9 / 16.1 (262,144 the
+// same), d = 2048, 8192 17.9 / 17.1.
 template <int VPL, int NW, int RIF>
 hipError_t launch_step(const PassArgs &a, int mode, int nblk, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
   return a.d4 == kWave * VPL ? launch_step_mode<VPL, kFullRows, NW, RIF>(a, mode, nblk, st, e0, e1)
@@ -1286,8 +1285,11 @@ hipError_t launch_dense_pass(const PassArgs &a, int mode, int32_t d, int32_t nbl
 }
 
 // Rows of 4 to 1024 floats that are not laid out in 16-byte pieces.  In the general kernel every
-// element of theirs was an LDS atomic.  Per step at d = 785,
-// pools of 4000: 20.4 us there, 12.0 here; d = 999, 20,000: 60.7, 23.0; d = 131, 200: 12.7, 8.8.
+// element of theirs was an LDS atomic.  Per step of an epoch at d = 785, pools of 4000: 20.7 us there, 11.7
+// here; d = 999, 20,000: 61.5, 23.1; d = 131, 200: 12.8, 8.8.  Single steps of narrow rows, which leave most of a
+// wave without a piece: d = 5, 65,536 rows 44.0, 23.6; d = 31, 300 rows 13.7, 8.4, 16,384 19.3, 12.1, 200,000
+// 114, 60.  Blocks of eight waves with one row each, up to one block per compute unit: 1 to 16
+// rows a block are within 7 % from 64 to 4096 rows of 31 to 1023 floats, eight ahead or level.
 hipError_t launch_any_rows(const PassArgs &a, int mode, int32_t nblk, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
   if (a.d < 4 || a.d > 1024) return hipErrorInvalidValue;
   if (a.d <= 256) return launch_step_mode<1, kAnyRows, 8, 4>(a, mode, nblk, st, e0, e1);

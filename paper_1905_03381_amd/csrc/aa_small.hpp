@@ -21,7 +21,8 @@ struct SmallEpochArgs {
   float lambda, lr, lr_a, l2_a;
   int32_t *t_upd;
   int32_t *kept_hist;     // [steps] or NULL
-  // the batch of each step; pool t's ids and losses start at t * out_stride
+  // the batch of each step; pool t's ids start at t * ids_stride, its losses at t * loss_stride
+  // (0: every step writes the same place)
   int32_t *ids, *kept_pos;
   float *loss, *prob;
   uint8_t *flags;

@@ -218,7 +218,7 @@ def test_image_batch_generator_full_shape(ref):
 def test_threshold_assistant_update_equals_the_two_calls(d, ld, m, m_max):
     """aa_threshold_assistant_update against aa_threshold_update + aa_assistant_update on the
     same inputs, bit for bit, over three batches in a row (first batch sets the threshold, the
-    others move it): every register layout, the general kernel (d = 130) and a batch too large
+    others move it): every register layout, rows off 16 bytes (d = 130) and a batch too large
     for the in-pass median (both fall back to the two calls), ties among the losses, an empty
     batch."""
     r = rng(1000 * d + m)
