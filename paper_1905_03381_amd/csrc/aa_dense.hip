@@ -988,15 +988,16 @@ __global__ __launch_bounds__(256) void k_finalize(const FinalizeArgs a) {
   }
 
   // fold the groups of this wave (lanes that share a column), then the four waves
+  if (!tail) {
 #pragma unroll
-  for (int off = kFinCols4; off < kWave; off <<= 1) {
-    acc.x += __shfl_xor(acc.x, off, kWave);
-    acc.y += __shfl_xor(acc.y, off, kWave);
-    acc.z += __shfl_xor(acc.z, off, kWave);
-    acc.w += __shfl_xor(acc.w, off, kWave);
-  }
-  if (lane < kFinCols4) s_acc[wave][lane] = acc;
-  if (tail) {
+    for (int off = kFinCols4; off < kWave; off <<= 1) {
+      acc.x += __shfl_xor(acc.x, off, kWave);
+      acc.y += __shfl_xor(acc.y, off, kWave);
+      acc.z += __shfl_xor(acc.z, off, kWave);
+      acc.w += __shfl_xor(acc.w, off, kWave);
+    }
+    if (lane < kFinCols4) s_acc[wave][lane] = acc;
+  } else {
 #pragma unroll
     for (int off = kFinCols4; off < kWave; off <<= 1) {
 #pragma unroll
