@@ -162,13 +162,15 @@ __global__ __launch_bounds__(kWideThreads)
       const int my = min(lane >> 3, R - 1), li = it + my;
       const bool live = li < cnt && lane < 8 * R;
       const int src = min(li, cnt - 1);
+      // (read by every lane: a shuffle among some of them gets zero from the lanes left out)
+      const float u = POOL && !HARD ? __shfl(u_l, src, kWave) : 0.f;
       float g = 0.f, s = 0.f, loss = (ASSIST && !SVM) ? __shfl(lin_l, src, kWave) : 0.f;
       bool keep = live;
       if (NEED_PHI) {
         s = dot_of(my) + b;
         g = sigmoidf_(s);
         if (POOL && a.do_keep)
-          keep = live && keep_decision(__shfl(u_l, src, kWave), g, a.gamma, a.one_minus_gamma);
+          keep = live && keep_decision(u, g, a.gamma, a.one_minus_gamma);
       }
       float cw = 0.f, resid = 0.f;
       if (SVM) {

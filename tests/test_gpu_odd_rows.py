@@ -177,3 +177,31 @@ def test_scores_out_of_matrices_of_any_size(d):
     want = X[:P].double().cpu() @ phi.double().cpu()
     scale = X[:P].double().cpu().abs() @ phi.double().cpu().abs()
     assert torch.all((got[0][0].cpu() - want).abs() <= 1e-5 * scale)
+
+
+# rows of a block around the numbers of rows a batch of each layout works on at once (8, 4, 4 and 1 for
+# one to four pieces a thread) and around a group of 64
+@pytest.mark.parametrize("per_block", [4, 7, 8, 9, 16, 20, 31, 32, 40, 63, 64])
+@pytest.mark.parametrize("d", [5, 130, 132, 1000, 1025, 2049, 4097, 6145, 9000])
+def test_every_row_of_a_block_has_its_own_draw(ref, d, per_block):
+    """Keep flags against the scores that the same call returns and the uniforms of the definition, in the
+    scoring call and in the whole step."""
+    n, P, gamma, seed, step = 300, 256 * per_block + 100, 0.05, 9, 4
+    g = torch.Generator(device="cuda").manual_seed(d)
+    F = api.Features.dense(torch.randn(n, d, device="cuda", generator=g) / d ** 0.5)
+    idx = torch.randint(0, n, (P,), device="cuda", generator=g, dtype=torch.int32)
+    y = torch.ones(n, device="cuda")
+    w, phi, work = torch.zeros(d, device="cuda"), torch.randn(d, device="cuda", generator=g), api.Workspace(P, d)
+    u = torch.from_numpy(ref.uniforms(seed, step, P)).cuda().double()
+    for whole in (False, True):
+        prob, keep = torch.zeros(P, device="cuda"), torch.full((P,), 9, dtype=torch.uint8, device="cuda")
+        pos, cnt = torch.zeros(P, dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
+        if whole:
+            cfg = api.step_config(gamma, 0.0, 0.1, 0.1, 0.0, seed, step, dense.scalar_dev(0.4))
+            api.fused_step(F, y, idx, P, w, phi, None, cfg, None, prob, keep, pos, None, None, cnt, work)
+        else:
+            api.score_shrink(F, idx, P, phi, None, gamma, seed, step, None, prob, keep, pos, cnt, work)
+        p = gamma + (1.0 - gamma) * prob.double()
+        sure = (u - p).abs() > 1e-6
+        assert torch.equal(keep[sure].bool(), (u < p)[sure]) and int(cnt) == int(keep.sum())
+        assert torch.equal(pos[:int(cnt)].long(), torch.nonzero(keep).view(-1))
