@@ -701,6 +701,12 @@ __device__ __forceinline__ void step_rows(const PassArgs &a, int bid, int nblk, 
       *a.prev.kept_count = before + __popcll(mask);
   }
 
+  // ANY: a coefficient of zero adds no zero times infinity.  With hard thresholds, where it is every rejected
+  // row's, the row is replaced by zeros; kept rows are passed over by a branch.  (The other way round steps
+  // on 200,000 rows of 31 floats took 44.5 us instead of 39.3 and 64.2 instead of 62.5.)
+  auto added = [&](float coef, const f4 &row) __attribute__((always_inline)) {
+    return !(ANY && HARD) || coef != 0.f ? row : zero4;
+  };
   Acc gw[VPL], gp[VPL];
 #pragma unroll
   for (int v = 0; v < VPL; ++v) {
@@ -744,7 +750,7 @@ __device__ __forceinline__ void step_rows(const PassArgs &a, int bid, int nblk, 
           if (POOL) keep = live && keep_decision(lane_read(u_l, src), g, a.gamma, a.one_minus_gamma);
         }
         const float yy = SVM ? lane_read(y_l, src) : 0.f;
-        if (GRAD && (HARD ? live : keep)) {
+        if (GRAD && (HARD ? live || ANY : keep)) {
           if (SVM) {
             float dw = 0.f;
 #pragma unroll
@@ -754,9 +760,9 @@ __device__ __forceinline__ void step_rows(const PassArgs &a, int bid, int nblk, 
             loss = fmaxf(0.f, 1.f - marg);
             if (HARD) keep = live && loss > T;  // shrinking by the objective value itself
             const float cw = (keep && marg < 1.f) ? yy : 0.f;  // -d hinge / d margin, times y
-            if (!ANY || cw != 0.f) {  // (ANY: no zero times infinity, as in the general kernels)
+            if (!ANY || HARD || cw != 0.f) {
 #pragma unroll
-              for (int v = 0; v < VPL; ++v) gw[v] = axpy4(cw, x[r][v], gw[v]);
+              for (int v = 0; v < VPL; ++v) gw[v] = axpy4(cw, added(cw, x[r][v]), gw[v]);
             }
           } else {
             loss = lane_read(lin_l, src);
