@@ -362,7 +362,7 @@ __global__ __launch_bounds__(NW * 64) void k_rows_once(const PassArgs a) {
   const float *const model = SVM ? a.w : a.phi;
   f4 mw[SVM ? VPL : 1], mp[ASSIST ? VPL : 1];
 #pragma unroll
-  for (int v = 0; v < VPL; ++v) {  // (columns past the row meet zeros of the row)
+  for (int v = 0; v < VPL; ++v) {  // (columns past the row are cleared below, with the row's)
     const int c = min(v * LPR + sub, a.d4 - 1);
     if (SVM) mw[v] = reinterpret_cast<const f4 *>(a.w)[c];
     if (ASSIST) mp[v] = reinterpret_cast<const f4 *>(a.phi)[c];
@@ -453,8 +453,12 @@ __global__ __launch_bounds__(NW * 64) void k_rows_once(const PassArgs a) {
 
   if (a.d4 != ROW4) {
 #pragma unroll
-    for (int v = 0; v < VPL; ++v)
-      if (v * LPR + sub >= a.d4) x[v] = zero4;
+    for (int v = 0; v < VPL; ++v) {
+      if (v * LPR + sub < a.d4) continue;
+      x[v] = zero4;
+      if (SVM) mw[v] = zero4;
+      if (ASSIST) mp[v] = zero4;
+    }
   }
   float g = 0.f, loss = lin, cw = 0.f, resid = 0.f;
   if (ASSIST) {
@@ -643,6 +647,13 @@ __device__ __forceinline__ void step_rows(const PassArgs &a, int bid, int nblk, 
 #pragma unroll
   for (int q = 0; q < STG; ++q) {
     const int c = q * NT + threadIdx.x;
+    if (ANY) {  // (what the last piece shares with the one before it is zero in the row, and has to be here)
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        if (SVM && a.d - 4 + i < 4 * c) st_w[q][i] = 0.f;
+        if (NEED_PHI && a.d - 4 + i < 4 * c) st_p[q][i] = 0.f;
+      }
+    }
     if (c < ROW4) {  // (columns past the row: any finite value would do, the row is zero there)
       if (SVM) lds.w[c] = FULL || c < a.d4 ? st_w[q] : zero4;
       if (NEED_PHI) lds.phi[c] = FULL || c < a.d4 ? st_p[q] : zero4;

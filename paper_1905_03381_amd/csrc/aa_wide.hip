@@ -20,7 +20,7 @@ constexpr int kWideWaves = 8, kWideThreads = kWideWaves * kWave;
 // Thread t owns the 128-bit pieces t, t + 512, ... of a row.  The last piece of a row whose
 // width is not a multiple of four is read from d - 4 on and a piece past the end likewise:
 // every load is a whole one, in bounds and without a condition.  Columns such a piece shares
-// with the one before are masked to zero.
+// with the one before are masked to zero, in the rows and in the model.
 //
 // The gradient sums are doubles (fp64 FMAs run at the fp32 rate here and the pass waits for memory),
 // rounded once per block; with two vectors those of the columns from kWideFp32Cols on stay doubles
@@ -77,6 +77,11 @@ __global__ __launch_bounds__(kWideThreads)
   for (int v = 0; v < VPT; ++v) {
     if (SVM) mw[v] = *reinterpret_cast<const f4u *>(a.w + first[v]);
     if (NEED_PHI) mp[v] = *reinterpret_cast<const f4u *>(a.phi + first[v]);
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {  // (zero on both sides: the row's zero times an infinite entry would be a NaN)
+    if (SVM && !own[i]) mw[VPT - 1][i] = 0.f;
+    if (NEED_PHI && !own[i]) mp[VPT - 1][i] = 0.f;
   }
   const float b = (NEED_PHI && a.bias) ? *a.bias : 0.f;
   const float T = (ASSIST || HARD) ? *a.T : 0.f;

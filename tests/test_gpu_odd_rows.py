@@ -205,3 +205,22 @@ def test_every_row_of_a_block_has_its_own_draw(ref, d, per_block):
         sure = (u - p).abs() > 1e-6
         assert torch.equal(keep[sure].bool(), (u < p)[sure]) and int(cnt) == int(keep.sum())
         assert torch.equal(pos[:int(cnt)].long(), torch.nonzero(keep).view(-1))
+
+
+@pytest.mark.parametrize("d", [5, 7, 130, 785, 1023, 1027, 2050, 4097, 6147, 9001])
+@pytest.mark.parametrize("back", [1, 2, 3, 4, 5])
+def test_infinite_model_entries_in_the_last_columns(d, back):
+    """An infinite entry of the model among the last columns of an odd row, which are read twice, gives
+    infinite scores and losses with the signs of the features, as anywhere else."""
+    P = 9
+    X = torch.randn(P, d, generator=torch.Generator().manual_seed(d)).cuda()
+    v = torch.full((d,), 0.01, device="cuda")
+    v[d - back] = float("inf")
+    F, sign = api.Features.dense(X), torch.sign(X[:, d - back])
+    logit, prob = torch.zeros(P, device="cuda"), torch.zeros(P, device="cuda")
+    api.assistant_score(F, None, P, v, None, logit, prob)
+    assert torch.equal(logit, sign * float("inf"))
+    loss, cnt = torch.zeros(P, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
+    api.sk_step(F, torch.ones(P, device="cuda"), None, P, v.clone(), dense.scalar_dev(0.5), 0.0, 0.0, loss, None, None, None,
+                None, cnt, api.Workspace(P, d))
+    assert torch.equal(loss, torch.where(sign > 0, 0.0, float("inf"))) and int(cnt) == int((sign < 0).sum())

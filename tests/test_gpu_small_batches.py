@@ -47,3 +47,17 @@ def test_batch_median_beside_infinite_losses_and_rows(m):
     assert torch.isfinite(one[0]).all()
     # (a different room for the batch spreads it over other blocks: fp32 sums of m terms of size 1/m)
     assert torch.allclose(one[0], two[0], rtol=0, atol=1e-6) and torch.allclose(one[1], two[1], rtol=0, atol=1e-6)
+
+
+@pytest.mark.parametrize("d", [36, 100, 128, 200, 260, 1000, 1028])
+@pytest.mark.parametrize("m", [1, 9, 300])
+def test_infinite_model_entries_at_the_end_of_the_row(d, m):
+    """An infinite entry of w in the last columns gives infinite losses with the signs of the features: lanes
+    past the end of a row, which hold its last piece again, add nothing."""
+    X = torch.randn(m, d, generator=torch.Generator().manual_seed(d)).cuda()
+    w = torch.full((d,), 0.01, device="cuda")
+    w[d - 2] = float("inf")
+    sign, loss = torch.sign(X[:, d - 2]), torch.zeros(m, device="cuda")
+    api.svm_sgd_step(api.Features.dense(X), torch.ones(m, device="cuda"), None, torch.full((1,), m, dtype=torch.int32, device="cuda"),
+                     m, w, 0.0, 0.0, 0.0, loss, api.Workspace(m, d))
+    assert torch.equal(loss, torch.where(sign > 0, 0.0, float("inf")))
