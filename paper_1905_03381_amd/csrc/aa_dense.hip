@@ -1303,10 +1303,10 @@ hipError_t launch_dense_pass(const PassArgs &a, int mode, int32_t d, int32_t nbl
 }
 
 // Rows of 4 to 1024 floats that are not laid out in 16-byte pieces.  In the general kernel every
-// element of theirs was an LDS atomic.  Per step of an epoch at d = 785, pools of 4000: 20.7 us there, 11.7
-// here; d = 999, 20,000: 61.5, 23.1; d = 131, 200: 12.8, 8.8.  Single steps of narrow rows, which leave most of a
-// wave without a piece: d = 5, 65,536 rows 44.0, 23.6; d = 31, 300 rows 13.7, 8.4, 16,384 19.3, 12.1, 200,000
-// 114, 60.  Blocks of eight waves with one row each, up to one block per compute unit: 1 to 16
+// element of theirs was an LDS atomic.  Per step of an epoch at d = 785, pools of 4000: 20.7 us there, 11.2
+// here; d = 999, 20,000: 61.5, 22.4; d = 131, 200: 12.7, 8.7.  Single steps of narrow rows, which leave most of a
+// wave without a piece: d = 5, 65,536 rows 44.0, 24.3; d = 31, 300 rows 13.4, 8.4, 16,384 19.3, 11.9, 200,000
+// 114, 62.6.  Blocks of eight waves with one row each, up to one block per compute unit: 1 to 16
 // rows a block are within 7 % from 64 to 4096 rows of 31 to 1023 floats, eight ahead or level.
 hipError_t launch_any_rows(const PassArgs &a, int mode, int32_t nblk, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
   if (a.d < 4 || a.d > 1024) return hipErrorInvalidValue;

@@ -27,13 +27,13 @@ constexpr int kWideWaves = 8, kWideThreads = kWideWaves * kWave;
 // until the update kernel has added all blocks up.  That is what the general kernels keep of dense
 // rows: the LDS of a block there holds sums of 8192 columns of one vector or 4096 of two, which leave it as
 // floats, and everything past them is added in doubles.  (Whole steps with the doubles against all sums
-// rounded per block: d = 4137, 4096 rows 22.6 -> 23.4 us, d = 8000 35.2 -> 37.5, 512 rows 16.4 -> 19.3.)
+// rounded per block: d = 4137, 4096 rows 22.5 -> 22.9 us, d = 8000 34.7 -> 36.7, 512 rows 16.2 -> 18.7.)
 //
 // VPT pieces of R rows, twice, are in registers: 4 rows of 17 KB at d = 4137, so that about 130 KB of a
 // compute unit's rows are on their way at a time.  Measured: epochs of 4 pools of 4096 rows (the
-// general kernels' times in brackets, whose sums go through LDS and sorted records): d = 2052 67 us
-// (137), 4093 91 (223), 4137 100 (245), 6145 130 (859), 8000 151 (1709) = 3.5 TB/s of rows; the pass alone
-// at d = 4137 19.6 us (53).  Scalars per row -- sigmoid,
+// general kernels' times in brackets, whose sums go through LDS and sorted records): d = 2052 66 us
+// (138), 4093 90 (223), 4137 97 (245), 6145 126 (900), 8000 149 (1475) = 3.5 TB/s of rows; the pass alone
+// at d = 4137 19.4 us (53).  Scalars per row -- sigmoid,
 // draw, loss -- are worked out for all R rows at once, a row per eight lanes: done row by row in
 // every lane they took longer than the dot products (22.0 us).
 template <int VPT, int R, int MODE, bool NT = true>
@@ -334,9 +334,9 @@ int32_t wide_part_row(int32_t d, int nvec) {
 // A block's partial sums are as long as a row per updated vector, written and read again, so few
 // rows per block are as much traffic for the sums as for the rows; few blocks leave compute units
 // idle.  Four rows a block up to half the compute units, eight beyond that.  Whole steps, one / four /
-// eight / sixteen rows a block: d = 2047, 256 rows 10.5 / 8.9 / 8.7 / 10.3 us, 1000 rows 10.7 / 10.6 / 9.6 / 11.4;
-// d = 4137 14.3 / 10.9 / 13.0 / 16.3 and 15.0 / 14.8 / 14.4 / 17.3; d = 8000 20.1 / 15.1 / 16.9 / 22.5 and
-// 23.8 / 23.8 / 22.6 / 25.3; 4096 rows within 1 %.
+// eight / sixteen rows a block: d = 2047, 256 rows 10.5 / 8.9 / 8.6 / 10.1 us, 1000 rows 10.8 / 10.6 / 9.6 / 11.2;
+// d = 4137 13.9 / 10.6 / 12.4 / 15.8 and 14.6 / 14.3 / 13.7 / 16.4; d = 8000 20.0 / 15.0 / 16.6 / 21.0 and
+// 23.1 / 23.2 / 21.9 / 23.8; 4096 rows within 1 %.
 // Scoring leaves no sums, but takes the same blocks: with at most 1 / 2 / 4 / 8 of them per compute unit
 // 20,000 x 1027 took 17.0 / 19.0 / 24.5 / 32.5 us, 4096 x 4137 10.3 / 13.3 / 16.3 / 13.3, 65,536 x 31
 // 12.1 / 14.3 / 16.6 / 21.6: every block fetches the model and fills its pipeline anew.

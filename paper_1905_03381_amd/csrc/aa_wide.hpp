@@ -14,8 +14,8 @@ constexpr int kWideBlocks = 256;  // one per compute unit
 // Whether the scoring pass reads a matrix of that size with plain loads.  A matrix that stays in the
 // 256 MB memory-side cache from one pass to the next loses by non-temporal ones, unless it is so small
 // that the rest of the cache takes them too.  Every row scored again and again, plain / non-temporal
-// loads (the general kernel in brackets): 20,000 x 1027 (82 MB) 16.4 / 17.4 us (16.6), 60,000 x 1027
-// (246 MB) 40.5 / 47.4 (39.8), 30,000 x 2047 36.4 / 38.6 (35.5), 20,000 x 3000 36.2 / 36.6 (35.2), but 9000 x 2047
+// loads (the general kernel in brackets): 20,000 x 1027 (82 MB) 16.3 / 17.4 us (16.6), 60,000 x 1027
+// (246 MB) 39.7 / 47.4 (39.8), 30,000 x 2047 36.4 / 38.6 (35.5), 20,000 x 3000 35.0 / 36.6 (35.2), but 9000 x 2047
 // (74 MB) 13.3 / 12.4 (13.3) and 4096 x 4137 (68 MB) 11.7 / 10.8 (12.8); rows not seen before, out of 3 GB:
 // 20,000 x 1367 23.6 / 21.5 (24.2), 20,000 x 3000 44.4 / 39.8 (45.7).
 inline bool wide_plain_loads(size_t matrix_bytes) {
