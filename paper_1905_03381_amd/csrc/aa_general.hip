@@ -806,7 +806,8 @@ __global__ __launch_bounds__(kScoreTableThreads) void k_score_table(const GenArg
       const int li = __ffsll((long long)longer) - 1;
       longer &= longer - 1;
       const long long e0 = __shfl((long long)e_l.lo, li, kWave);
-      const int len = grp == 0 ? __shfl(len_l, li, kWave) : 0;
+      const int len_any = __shfl(len_l, li, kWave);  // (every lane takes part in the shuffle)
+      const int len = grp == 0 ? len_any : 0;
       const float u = __shfl(u_l, li, kWave);
       float dp = 0.f;
       for (int e = sub; e < len; e += GL) {  // (the order of a lane's additions is the loop's)
