@@ -26,6 +26,9 @@ namespace aa {
 
 namespace {
 
+typedef float f4v __attribute__((ext_vector_type(4), aligned(4)));  // (any float address)
+typedef int i4v __attribute__((ext_vector_type(4), aligned(4)));
+
 // Sum over aligned groups of WIDTH lanes, halves first.  For 16 lanes by rotations inside the row,
 // no trip through LDS: after each addition the values repeat with half the period, so rotating
 // by 8, 4, 2 and 1 adds the same pairs as exchanging with lane ^ 8, ^ 4, ^ 2 and ^ 1.
@@ -328,11 +331,52 @@ __global__ __launch_bounds__(1024) void k_rows_general(const GenArgs a) {
         }
         dot_entries(c0, x0);
       }
-      for (int e = sub + (KEEP ? GL * kUnroll : 0); e < len; e += GL * kUnroll) {
-        int c[kUnroll];
-        float xv[kUnroll];
-        load_entries(e, c, xv);
-        dot_entries(c, xv);
+      if constexpr (CSR && !GRAD) {
+        // four neighbouring entries a lane: one load per array for 4 GL entries.  The piece that ends
+        // with the row shares entries with the one before it, so that every load is a whole one inside
+        // the row (entries k < skip belong there); rows that end before the matrix's fourth
+        // entry have nothing to share with and are read one by one.
+        for (int e = 4 * sub; e < len; e += 8 * GL) {
+          i4v c[2] = {};
+          f4v xv[2] = {};
+#pragma unroll
+          for (int q = 0; q < 2; ++q) {
+            const int first = min(e + q * 4 * GL, len - 4);
+            if (e + q * 4 * GL < len && e0 + len >= 4) {
+              c[q] = *reinterpret_cast<const i4v *>(a.col + e0 + first);
+              if (a.val) xv[q] = *reinterpret_cast<const f4v *>(a.val + e0 + first);
+            }
+          }
+          if (e0 + len < 4) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+              if (k < 4 - len) continue;
+              c[0][k] = a.col[e0 + len - 4 + k];
+              xv[0][k] = a.val ? a.val[e0 + len - 4 + k] : 0.f;
+            }
+          }
+          float m[2][4];
+#pragma unroll
+          for (int q = 0; q < 2; ++q) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) m[q][k] = a.phi[k >= e + q * 4 * GL - (len - 4) ? c[q][k] : 0];
+          }
+#pragma unroll
+          for (int q = 0; q < 2; ++q) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+              const float added = __fmaf_rn(m[q][k], a.val ? xv[q][k] : 1.f, dp);
+              dp = k >= e + q * 4 * GL - (len - 4) ? added : dp;
+            }
+          }
+        }
+      } else {
+        for (int e = sub + (KEEP ? GL * kUnroll : 0); e < len; e += GL * kUnroll) {
+          int c[kUnroll];
+          float xv[kUnroll];
+          load_entries(e, c, xv);
+          dot_entries(c, xv);
+        }
       }
       float g = 0.f;
       bool keep = live;
@@ -593,24 +637,24 @@ __global__ __launch_bounds__(256) void k_zero_f32(float *p, size_t count) {
 
 // Scoring pass over CSR rows with the first kScoreTableCols entries of phi in LDS: one block of
 // 16 waves per compute unit loads them once and then walks its rows; only columns past the
-// table are gathered through the caches.  Pays when phi is too large for the vector L1 (a few
-// thousand floats) and the rows are many: the gathers of k_rows_general then miss the L1 and
-// pull a line from L2 for four bytes each.  Same outputs and the same order of additions per
-// row as k_rows_general<16, kPool, true>, so the two give the same bits.
-#ifndef AA_SCORE_TABLE_COLS
-#define AA_SCORE_TABLE_COLS 39936
-#endif
-constexpr int kScoreTableCols = AA_SCORE_TABLE_COLS;  // 156 KB of the 160 KB
+// table are gathered through the caches.  The gathers of k_rows_general go through the vector L1, which
+// serves a lane or so a cycle, and from a few thousand columns on miss it.  Same outputs and the same
+// order of additions per row as k_rows_general<16, kPool, true>, so the two give the same bits.
+// What bounds it: the vector memory path.  1,000,000 rows of 56 entries over 64,002 columns (448 MB),
+// per launch: 163 us with a 32-bit load per entry (16 loads and 8 gathers a step, a sigmoid per row and
+// group), 155 with one 128-bit load per array and half slot and the sigmoids of 64 rows at a time, 151 with
+// the requests going on across rounds.  With non-temporal loads it is 128, but the rows are then gone from
+// the memory-side cache and the copy of the kept rows that follows takes 126 instead of 97.
+constexpr int kScoreTableCols = 39936;  // 156 KB of the 160 KB
 constexpr int kScoreTableThreads = 1024;
-// Taken for pools of at least kScoreTableMinRows rows when phi is too large for the vector L1
-// to serve (more than kScoreTableMinCols columns) and the table holds at least half of it:
-// measured on 1,000,000 token-list rows over 64,002 columns 236 -> 161 us per launch; on
-// 65,536 rows of about 100 entries over 2^20 Zipf-distributed columns, where a quarter of the
-// entries lie past the table, k_rows_general stays ahead (34 us against 48).
-#ifndef AA_SCORE_TABLE_MIN_COLS
-#define AA_SCORE_TABLE_MIN_COLS 16384
-#endif
-constexpr int kScoreTableMinCols = AA_SCORE_TABLE_MIN_COLS, kScoreTableMinRows = 16384;
+// Taken for pools of at least kScoreTableMinRows rows over more than kScoreTableMinCols columns, and
+// for kScoreTableManyRows rows over fewer, when the table holds at least half of phi.  Whole batch
+// generator calls, k_rows_general / this: 1,000,000 rows over 16,002 columns 242 / 173 us, over 10,002
+// 347 / 276, over 4002 304 / 272; 200,000 over 4002 78.3 / 73.5; 100,000 over 4002 to 16,002 57 / 56.5, 54 /
+// 53, 58 / 59; 60,000 over 4002 49.8 / 52.0; 20,000 over 15,002 43.8 / 50.8.  On 65,536 rows of about
+// 100 entries over 2^20 Zipf-distributed columns, where a quarter of the entries lie past the
+// table, k_rows_general stays ahead (34 us against 48).
+constexpr int kScoreTableMinCols = 16384, kScoreTableMinRows = 16384, kScoreTableManyRows = 98304;
 constexpr int kScoreTableMaxCols = 2 * kScoreTableCols;
 
 // No load of the main loop sits behind a branch (a lane with nothing to read asks for an
@@ -624,9 +668,11 @@ template <bool VAL>
 __global__ __launch_bounds__(kScoreTableThreads) void k_score_table(const GenArgs a) {
   constexpr int GL = 16, G = kWave / GL, kUnroll = 8, kChunk = GL * kUnroll;
   __shared__ float s_phi[kScoreTableCols];
+  __shared__ float s_row[kScoreTableThreads / kWave][kWave];  // sums of a wave's round
   const int D = min(kScoreTableCols, a.d);
   for (int k = threadIdx.x; k < D; k += kScoreTableThreads) s_phi[k] = a.phi[k];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = kScoreTableThreads >> 6;
+  const int lane = threadIdx.x & 63, nw = kScoreTableThreads >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int grp = lane / GL, sub = lane % GL;
   const int total = a.count_max;
   const int nwaves = gridDim.x * nw, gwave = blockIdx.x * nw + wave;
@@ -640,8 +686,7 @@ __global__ __launch_bounds__(kScoreTableThreads) void k_score_table(const GenArg
 
   // Entries and cold columns are read through buffer resources: a lane with nothing to read
   // gives an offset past the resource's range, for which the hardware returns zero without a
-  // memory access -- no stand-in addresses, no masks where the values are used (a missing entry
-  // is column 0 with value 0, as in k_rows_general).  Offsets are 32 bits: rows whose entries
+  // memory access -- no stand-in addresses.  Offsets are 32 bits: rows whose entries
   // lie beyond kSpan bytes of the arrays take the walk after the loop.
   constexpr int kNone = (int)0x80000000;         // out of every resource's range
   constexpr long long kSpan = 0x7fffffffll / 4;  // entries within reach of a 32-bit byte offset
@@ -651,39 +696,44 @@ __global__ __launch_bounds__(kScoreTableThreads) void k_score_table(const GenArg
       const_cast<float *>(VAL ? a.val : a.phi), 0, kNone, 0x00020000);
   const __amdgpu_buffer_rsrc_t r_phi = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<float *>(a.phi), 0, a.d * 4, 0x00020000);
-  struct Slot {  // one chunk per lane group
-    int c[kUnroll];
-    float x[kUnroll];
+  struct Slot {  // two half chunks per lane group
+    i4v c[2];
+    f4v x[2];
     float far[kUnroll];
+    int skip[2];
   };
-  // One half of a slot: the kHalf turns from turn u0 on hold entries [e, e + kHalfChunk) of the
-  // row that starts at entry e0 and has len entries.
-  constexpr int kHalf = kUnroll / 2, kHalfChunk = GL * kHalf;
-  auto request_half = [&](int e0, int len, int e, int u0, Slot &t) __attribute__((always_inline)) {
-#pragma unroll
-    for (int u = 0; u < kHalf; ++u) {
-      const int eu = e + sub + u * GL;
-      const int off = eu < len ? (e0 + eu) * 4 : kNone;
-      t.c[u0 + u] = __builtin_amdgcn_raw_buffer_load_b32(r_col, off, 0, 0);
-      if (VAL)
-        t.x[u0 + u] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(r_val, off, 0, 0));
-      else
-        t.x[u0 + u] = eu < len ? 1.f : 0.f;
-    }
+  // Half h of a slot: entries [e, e + kHalfChunk) of the row that starts at entry e0 and has len
+  // entries, four neighbours a lane.  The piece that ends with the row shares entries with the one
+  // before it, so that every load is a whole one inside the row; entries k < skip belong there.
+  constexpr int kHalfChunk = GL * 4;
+  static_assert(kUnroll == 8, "two pieces of four");
+  auto request_half = [&](int e0, int len, int e, int h, Slot &t) __attribute__((always_inline)) {
+    const int first = e + 4 * sub, last = len - 4;
+    t.skip[h] = first - last;
+    const int off = first < len ? (e0 + min(first, last)) * 4 : kNone;
+    t.c[h] = __builtin_bit_cast(i4v, __builtin_amdgcn_raw_buffer_load_b128(r_col, off, 0, 0));
+    if (VAL) t.x[h] = __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(r_val, off, 0, 0));
   };
   auto gather = [&](Slot &t) __attribute__((always_inline)) {  // columns past the table
 #pragma unroll
-    for (int u = 0; u < kUnroll; ++u)
-      t.far[u] = __int_as_float(
-          __builtin_amdgcn_raw_buffer_load_b32(r_phi, t.c[u] >= D ? t.c[u] * 4 : kNone, 0, 0));
+    for (int u = 0; u < kUnroll; ++u) {
+      const int c = t.c[u / 4][u % 4];
+      
+      t.far[u] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(r_phi, c >= D ? c * 4 : kNone, 0, 0));
+
+    }
   };
-  auto dot_half = [&](const Slot &t, int u0, float dp) __attribute__((always_inline)) {
-    float near[kHalf];
+  auto dot_half = [&](const Slot &t, int h, float dp) __attribute__((always_inline)) {
+    float near[4];
 #pragma unroll
-    for (int u = 0; u < kHalf; ++u) near[u] = s_phi[min(t.c[u0 + u], D - 1)];
+    for (int k = 0; k < 4; ++k) near[k] = s_phi[min(t.c[h][k], D - 1)];
+
 #pragma unroll
-    for (int u = 0; u < kHalf; ++u)
-      dp = __fmaf_rn(t.c[u0 + u] >= D ? t.far[u0 + u] : near[u], t.x[u0 + u], dp);
+    for (int k = 0; k < 4; ++k) {
+      const float m = t.c[h][k] >= D ? t.far[4 * h + k] : near[k];
+      const float added = VAL ? __fmaf_rn(m, t.x[h][k], dp) : dp + m;
+      dp = k >= t.skip[h] ? added : dp;
+    }
     return dp;
   };
   auto emit = [&](int j, float dp, float u) __attribute__((always_inline)) {
@@ -716,83 +766,112 @@ __global__ __launch_bounds__(kScoreTableThreads) void k_score_table(const GenArg
 
   // A step gives every group of 16 lanes two half slots of 64 entries: both chunks of one row of
   // 65 to 128 entries, or the only chunks of two rows of up to 64.  Per round the wave's 64 rows
-  // are put in that order -- the longer rows, then the shorter ones, each class in pool order --
-  // with one ds_permute per value, so half slot h belongs to sorted row h / 2 (chunk h % 2) while
-  // h < 2 M and to sorted row h - M after that (M = number of longer rows).
-  constexpr int kAhead = 3;  // steps in flight; slot (it % kAhead) holds step it of a round
-  Slot t[kAhead];
-  for (int base = lo; base < hi; base += kWave) {
-    const float u_l = a.do_keep ? keep_uniform(a.key, (uint32_t)(base + lane)) : 2.f;
+  // are put in that order -- the M longer rows, then the S shorter ones, each class in pool order --
+  // with one ds_permute per value.  Unit u of a round (group u % 4 of step u / 4) is sorted row u and,
+  // from M on, sorted row u + SH beside it (SH = half of S): neighbouring groups read neighbouring rows.
+  constexpr int kAhead = 3;  // steps in flight
+  struct Round {
+    int base;               // its first pool position
+    int M, SH, rows, steps; // (at least kAhead steps, so that requests are one round ahead at most)
+    unsigned long long here;  // rows that take part
+    int e0, len, src;       // of sorted row `lane`: first entry, entries, place in pool order
+  };
+  // (the next 64 rows' extents are in `cur`; those of the round after and the row ids of the one
+  // after that go out here, loads that wait for nothing)
+  auto make_round = [&](int base) __attribute__((always_inline)) {
+    Round r;
+    r.base = base;
     const bool valid = base + lane < hi;
     int len_cur = valid ? (int)(cur.hi - cur.lo) : 0;
-    if (cur.hi > kSpan) len_cur = kChunk + 1;  // (out of reach: a row for the walk after the loop)
+    // (out of reach, or no four entries up to the row's end: a row for the walk after the loop)
+    if (cur.hi > kSpan || (len_cur > 0 && cur.hi < 4)) len_cur = kChunk + 1;
     any_longer = any_longer || (valid && len_cur > kChunk);
     const bool two = valid && len_cur > kHalfChunk && len_cur <= kChunk;
     const bool one = valid && len_cur <= kHalfChunk;
     const unsigned long long m_two = __ballot(two), m_one = __ballot(one);
-    const int M = __popcll(m_two), S = __popcll(m_one), H = 2 * M + S;
+    const int S = __popcll(m_one);
+    r.M = __popcll(m_two);
+    r.SH = (S + 1) / 2;
+    r.rows = r.M + S;
+    r.steps = max(kAhead, (r.M + r.SH + G - 1) / G);
+    r.here = m_two | m_one;
     auto rank_in = [&](unsigned long long mask) __attribute__((always_inline)) {
       return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
                                             __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
     };
-    const int dest = two ? rank_in(m_two) : one ? M + rank_in(m_one) : M + S + rank_in(~(m_two | m_one));
-    const int e0_s = __builtin_amdgcn_ds_permute(dest * 4, (int)cur.lo);
-    const int len_s = __builtin_amdgcn_ds_permute(dest * 4, len_cur);
-    const int src_s = __builtin_amdgcn_ds_permute(dest * 4, lane);
-    const float u_s = __int_as_float(__builtin_amdgcn_ds_permute(dest * 4, __float_as_int(u_l)));
-    const int nsteps = (H + 2 * G - 1) / (2 * G);
-    // half slots (A, B) of this lane's group in step `it`: sorted row and first entry of each
-    auto halves = [&](int it, int *rowA, int *rowB, bool *same) __attribute__((always_inline)) {
-      const int hA = 2 * (it * G + grp), hB = hA + 1;
-      *same = hB < 2 * M;
-      *rowA = hA < 2 * M ? (hA >> 1) : hA - M;
-      *rowB = *same ? *rowA : hB - M;
-      if (hA >= H) *rowA = -1;
-      if (hB >= H) *rowB = -1;
-    };
-    auto request_step = [&](int it, Slot &s) __attribute__((always_inline)) {
-      int rowA, rowB;
-      bool same;
-      halves(it, &rowA, &rowB, &same);
-      const int e0A = __shfl(e0_s, max(rowA, 0), kWave), lenA = __shfl(len_s, max(rowA, 0), kWave);
-      const int e0B = __shfl(e0_s, max(rowB, 0), kWave), lenB = __shfl(len_s, max(rowB, 0), kWave);
-      request_half(e0A, rowA >= 0 ? min(lenA, kHalfChunk) : 0, 0, 0, s);
-      request_half(e0B, rowB >= 0 ? (same ? lenB : min(lenB, kHalfChunk)) : 0, same ? kHalfChunk : 0,
-                   kHalf, s);
-    };
-    auto finish_step = [&](int it, float dpA, float dpB) __attribute__((always_inline)) {
-      int rowA, rowB;
-      bool same;
-      halves(it, &rowA, &rowB, &same);
-      dpA = gsum<GL>(dpA);
-      dpB = gsum<GL>(dpB);
-      const int jA = base + __shfl(src_s, max(rowA, 0), kWave), jB = base + __shfl(src_s, max(rowB, 0), kWave);
-      const float uA = __shfl(u_s, max(rowA, 0), kWave), uB = __shfl(u_s, max(rowB, 0), kWave);
-      if (sub == 0 && rowA >= 0 && !same) emit(jA, dpA, uA);
-      if (sub == 0 && rowB >= 0) emit(jB, dpB, uB);
-    };
-    // the extents of the next round and the row ids of the one after go out ahead of this
-    // round's entries: the only loads of a round that wait for nothing
-    const Extent coming = extent(base + 2 * kWave + lane, id_after);
+    const int dest = two ? rank_in(m_two) : one ? r.M + rank_in(m_one) : r.rows + rank_in(~r.here);
+    r.e0 = __builtin_amdgcn_ds_permute(dest * 4, (int)cur.lo);
+    r.len = __builtin_amdgcn_ds_permute(dest * 4, len_cur);
+    r.src = __builtin_amdgcn_ds_permute(dest * 4, lane);
+    cur = next;
+    next = extent(base + 2 * kWave + lane, id_after);
     id_after = row_id(base + 3 * kWave + lane);
+    return r;
+  };
+  // sorted rows of this lane's group in step `it` (-1: none); *same: both halves are one row's
+  auto halves = [&](const Round &r, int it, int *rowA, int *rowB, bool *same) __attribute__((always_inline)) {
+    const int u = it * G + grp;
+    *same = u < r.M;
+    *rowA = u < r.M + r.SH ? u : -1;
+    *rowB = *same ? u : (u < r.M + r.SH && u + r.SH < r.rows ? u + r.SH : -1);
+  };
+  auto request_step = [&](const Round &r, int it, Slot &s) __attribute__((always_inline)) {
+    int rowA, rowB;
+    bool same;
+    halves(r, it, &rowA, &rowB, &same);
+    const int e0A = __shfl(r.e0, max(rowA, 0), kWave), lenA = __shfl(r.len, max(rowA, 0), kWave);
+    const int e0B = __shfl(r.e0, max(rowB, 0), kWave), lenB = __shfl(r.len, max(rowB, 0), kWave);
+    request_half(e0A, rowA >= 0 ? lenA : 0, 0, 0, s);
+    request_half(e0B, rowB >= 0 ? lenB : 0, same ? kHalfChunk : 0, 1, s);
+  };
+
+  Slot t[kAhead];
+  if (lo < hi) {
+    // `ask` is the round whose entries are being requested, `use` the one whose rows are added up,
+    // kAhead steps behind: the requests go on across the end of a round.
+    Round ask = make_round(lo);
+    Round use = ask;
+    int asked = 0, used = 0;
 #pragma unroll
-    for (int p = 0; p < kAhead; ++p) request_step(p, t[p]);
+    for (int p = 0; p < kAhead; ++p) request_step(ask, asked++, t[p]);
     gather(t[0]);
-    // (whole turns of the three slots: the steps past the last one hold nothing and load nothing)
+    bool more = true;
 #pragma unroll 1
-    for (int it0 = 0; it0 < nsteps; it0 += kAhead) {
+    while (more) {
 #pragma unroll
       for (int p = 0; p < kAhead; ++p) {
-        gather(t[(p + 1) % kAhead]);  // step it + 1: its entries were requested two steps ago
-        const int hB = 2 * ((it0 + p) * G + grp) + 1;
-        const float dpA = dot_half(t[p], 0, 0.f);
-        const float dpB = dot_half(t[p], kHalf, hB < 2 * M ? dpA : 0.f);  // (one row: its sum goes on)
-        request_step(it0 + p + kAhead, t[p]);
-        finish_step(it0 + p, dpA, dpB);
+        gather(t[(p + 1) % kAhead]);  // the next step: its entries were requested two steps ago
+        int rowA, rowB;
+        bool same;
+        halves(use, used, &rowA, &rowB, &same);
+        float dpA = dot_half(t[p], 0, 0.f);
+        float dpB = dot_half(t[p], 1, same ? dpA : 0.f);  // (one row: its sum goes on)
+        if (asked == ask.steps && ask.base + kWave < hi) {
+          ask = make_round(ask.base + kWave);
+          asked = 0;
+        }
+        request_step(ask, asked, t[p]);  // (past the last round: nothing)
+        ++asked;
+        dpA = gsum<GL>(dpA);
+        dpB = gsum<GL>(dpB);
+        const int atA = __shfl(use.src, max(rowA, 0), kWave), atB = __shfl(use.src, max(rowB, 0), kWave);
+        if (sub == 0 && rowA >= 0 && !same) s_row[wave][atA] = dpA;
+        if (sub == 0 && rowB >= 0) s_row[wave][atB] = dpB;
+        if (++used == use.steps) {
+          // the round's rows, one a lane: what follows from the sums costs as much for 64 rows as for
+          // four, and the stores are whole lines
+          __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+          const int j = use.base + lane;
+          const float u = a.do_keep ? keep_uniform(a.key, (uint32_t)j) : 2.f;
+          if ((use.here >> lane) & 1ull) emit(j, s_row[wave][lane], u);
+          __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+          more = use.base + kWave < hi;
+          if (!more) break;
+          use = ask;
+          used = 0;
+        }
       }
     }
-    cur = next;
-    next = coming;
   }
   if (__ballot(any_longer) == 0ull) return;
   // rows of more than one chunk, one after the other in the wave's first lane group
@@ -801,7 +880,7 @@ __global__ __launch_bounds__(kScoreTableThreads) void k_score_table(const GenArg
     const Extent e_l = extent(j_l, row_id(j_l));
     const int len_l = j_l < hi ? (int)(e_l.hi - e_l.lo) : 0;
     const float u_l = a.do_keep ? keep_uniform(a.key, (uint32_t)j_l) : 2.f;
-    unsigned long long longer = __ballot(len_l > kChunk || (j_l < hi && e_l.hi > kSpan));
+    unsigned long long longer = __ballot(len_l > kChunk || (j_l < hi && e_l.hi > kSpan) || (len_l > 0 && e_l.hi < 4));
     while (longer != 0ull) {
       const int li = __ffsll((long long)longer) - 1;
       longer &= longer - 1;
@@ -810,10 +889,12 @@ __global__ __launch_bounds__(kScoreTableThreads) void k_score_table(const GenArg
       const int len = grp == 0 ? len_any : 0;
       const float u = __shfl(u_l, li, kWave);
       float dp = 0.f;
-      for (int e = sub; e < len; e += GL) {  // (the order of a lane's additions is the loop's)
-        const int c = a.col[e0 + e];
-        const float xv = VAL ? a.val[e0 + e] : 1.f;
-        dp = __fmaf_rn(c < D ? s_phi[c] : a.phi[c], xv, dp);
+      for (int e = 4 * sub; e < len; e += kHalfChunk) {  // (the order of a lane's additions is the loop's)
+        for (int k = e; k < min(e + 4, len); ++k) {
+          const int c = a.col[e0 + k];
+          const float m = c < D ? s_phi[c] : a.phi[c];
+          dp = VAL ? __fmaf_rn(m, a.val[e0 + k], dp) : dp + m;
+        }
       }
       dp = gsum<GL>(dp);
       if (lane == 0) emit(base + li, dp, u);
@@ -846,8 +927,6 @@ __global__ __launch_bounds__(256) void k_prepare_general(float *p, size_t count,
 // per step, 4 / 8 / 16 waves: 73.4 / 68.2 / 69.6 us; pools of 8000 35.0 / 31.3 / 34.0.
 constexpr int kApplyWaves = 8, kApplyThreads = kApplyWaves * kWave;
 constexpr int kHeadCols = kApplyThreads / 16;
-
-typedef float f4v __attribute__((ext_vector_type(4), aligned(4)));  // (any float address)
 
 // The update of one column from its gradient sums (m == 0: the model stays).
 struct Fold {
@@ -1206,8 +1285,8 @@ int32_t general_pass_blocks(int32_t count, bool csr, int mode) {
 
 hipError_t launch_general_pass(const GenArgs &a, int mode, bool csr, int32_t nblk,
                                hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
-  if (csr && mode == kPool && a.d > kScoreTableMinCols && a.d <= kScoreTableMaxCols &&
-      a.count_max >= kScoreTableMinRows) {
+  if (csr && mode == kPool && a.d <= kScoreTableMaxCols &&
+      a.count_max >= (a.d > kScoreTableMinCols ? kScoreTableMinRows : kScoreTableManyRows)) {
     if (a.val)
       launch_stamped(k_score_table<true>, dim3(kGeneralGradBlocks), dim3(kScoreTableThreads), st, e0, e1, a);
     else

@@ -105,6 +105,30 @@ def test_csr_score_large_pool_equals_small_pools(ref, ws, ones, indexed):
     assert m == int(k.sum()) and np.array_equal(host(pos)[:m], np.flatnonzero(k))
 
 
+@pytest.mark.parametrize("ones", [True, False])
+@pytest.mark.parametrize("P", [5_000, 98_304 + 37])
+def test_csr_score_row_ends(ref, ones, P):
+    """Rows are read four entries at a time, the last piece ending with the row: rows of every length
+    around the pieces (0 to 9, 61 to 68, 125 to 133 entries), the shortest first, where nothing lies before
+    them in the matrix -- through the general kernel (5000 rows) and through the one with phi in
+    LDS, which takes over at 98,304 rows of so few columns.  No row holds column 0, whose model entry
+    is infinite: what a piece shares with another row or entry must not count."""
+    lens = np.tile(np.r_[1, 1, 0, 0:10, 61:69, 125:134, 5, 3, 2], P // 33 + 1)[:P]
+    r, d = rng(43), 3000
+    rowptr = np.zeros(P + 1, dtype=np.int64)
+    np.cumsum(lens, out=rowptr[1:])
+    col = r.integers(1, d, size=int(rowptr[-1])).astype(np.int32)
+    val = None if ones else (r.standard_normal(col.size) / 10.0).astype(np.float32)
+    phi = r.standard_normal(d).astype(np.float32)
+    Fh = ref.Features.csr(rowptr, col, val, d)
+    ref_logit, ref_prob = ref.assistant_score(Fh, None, P, phi, bias=0.2)
+    scale = abs_dot_scale(Fh, np.arange(P), phi)
+    phi[0] = np.inf
+    logit, prob = torch.zeros(P, device="cuda"), torch.zeros(P, device="cuda")
+    api.assistant_score(csr_features(rowptr, col, val, d), None, P, dev(phi), scalar_dev(0.2), logit, prob)
+    assert_logit_prob(host(logit), host(prob), ref_logit, ref_prob, scale, bias=0.2)
+
+
 def test_csr_all_ones_values(ref, ws):
     """Token lists: val == NULL means every entry is 1; repeated tokens add."""
     rowptr, col, val, len_s, len_t, d = synth.sentence_pairs(n=5000, vocab=2000)
