@@ -48,9 +48,9 @@ struct Ws {
   size_t total;
 };
 
-// General kernels: a header (scalars, bin fill counts), the two dense accumulators, the
-// model vectors as (w, phi) pairs, the per-block sums of the first columns, then the record
-// bins of the other columns.
+// General kernels: a header (scalars, bin and block record counts), the two dense accumulators, the
+// model vectors as (w, phi) pairs, the per-block sums of the first columns, then the records of
+// the other columns and where each bin's runs of the late ones start.
 size_t general_pairs_offset(int32_t d) {  // (w, phi) pairs of the columns, indexed by column
   return align_up(general_clear_floats(d) * sizeof(float), 256);
 }
@@ -60,8 +60,11 @@ size_t general_part_offset(int32_t d) {
 size_t general_bins_offset(int32_t d) {
   return general_part_offset(d) + align_up(general_part_floats(d) * sizeof(float), 256);
 }
+size_t general_runs_offset(int32_t d, int32_t count_max) {
+  return general_bins_offset(d) + general_record_capacity(count_max) * kRecordWordBytes;
+}
 size_t general_acc_bytes(int32_t d, int32_t count_max) {
-  return general_bins_offset(d) + general_record_capacity(count_max) * sizeof(TailRecord);
+  return general_bins_offset(d) + general_record_capacity(count_max) * kRecordBytes;
 }
 
 Ws carve(void *ws, size_t grad_bytes, int32_t P, bool epoch_outputs = false) {
@@ -314,16 +317,16 @@ hipError_t run_pass(const PassSpec &s, const Ws &ws, int32_t *nblk_out, hipStrea
   a.acc_p = a.acc_w + s.F->d;
   a.part = reinterpret_cast<float *>(ws.grad + general_part_offset(s.F->d));
   a.head = general_head_columns(s.F->d, nvec, csr);
-  a.wp = (nvec == 2 && s.F->d > a.head)
-             ? reinterpret_cast<const float2 *>(ws.grad + general_pairs_offset(s.F->d))
-             : nullptr;
-  a.bin_fill = reinterpret_cast<unsigned long long *>(acc + 16);
-  a.bins = reinterpret_cast<TailRecord *>(ws.grad + general_bins_offset(s.F->d));
-  a.plan = general_bin_plan(s.F->d, a.head, nvec, s.count_max);
-  a.t_upd = s.t_upd;
+  a.wp = nvec == 2 ? reinterpret_cast<const float2 *>(ws.grad + general_pairs_offset(s.F->d)) : nullptr;
+  a.bin_fill = reinterpret_cast<unsigned *>(acc + 16);
+  a.blk_late = reinterpret_cast<int32_t *>(acc + 16 + kMaxBins);
+  a.recs = reinterpret_cast<int32_t *>(ws.grad + general_bins_offset(s.F->d));
+  a.runs = reinterpret_cast<int32_t *>(ws.grad + general_runs_offset(s.F->d, s.count_max));
+    a.t_upd = s.t_upd;
   a.t_snap = ws.ctl + kCtlUpdateSnapshot;
   const int32_t nblk = general_pass_blocks(s.count_max, csr, s.mode);
   *nblk_out = nblk;
+  a.plan = general_bin_plan(s.F->d, a.head, nvec, s.count_max, nblk);
   const Hook hook;
   return launch_general_pass(a, s.mode, csr, nblk, st, hook.started, hook.stopped);
 }
@@ -398,9 +401,11 @@ hipError_t run_update(const PassSpec &s, const UpdateSpec &u, const Ws &ws, int3
   p.part = reinterpret_cast<const float *>(ws.grad + general_part_offset(s.F->d));
   p.nvec = ((s.mode & kSvm) ? 1 : 0) + ((s.mode & kAssist) ? 1 : 0);
   p.head = general_head_columns(s.F->d, p.nvec, s.F->layout == AA_CSR);
-  p.bin_fill = reinterpret_cast<unsigned long long *>(acc + 16);
-  p.bins = reinterpret_cast<const TailRecord *>(ws.grad + general_bins_offset(s.F->d));
-  p.plan = general_bin_plan(s.F->d, p.head, p.nvec, s.count_max);
+  p.bin_fill = reinterpret_cast<unsigned *>(acc + 16);
+  p.blk_late = reinterpret_cast<const int32_t *>(acc + 16 + kMaxBins);
+  p.recs = reinterpret_cast<const int32_t *>(ws.grad + general_bins_offset(s.F->d));
+  p.runs = reinterpret_cast<const int32_t *>(ws.grad + general_runs_offset(s.F->d, s.count_max));
+  p.plan = general_bin_plan(s.F->d, p.head, p.nvec, s.count_max, nblk);
   p.t_upd = u.t_upd;
   p.t_snap = ws.ctl + kCtlUpdateSnapshot;
   p.keep_ready = (u.keep_ready && p.plan.nb > 0) ? 1 : 0;

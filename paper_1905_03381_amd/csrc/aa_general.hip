@@ -12,13 +12,15 @@
 //  * any other column may claim one of a few thousand hashed LDS slots, first come
 //    first served (a hot column outside the first ones -- a bias-like feature at the
 //    end, the head of a second vocabulary -- comes early and keeps its slot);
-//  * entries that find their slot taken are collected as records in LDS and written,
-//    sorted by column bin, into per-bin arrays, and so are the hashed slots at the
-//    end; the block that owns a bin in the second kernel sums its records in LDS.
-//    One integer atomic per block, bin and flush reserves the space.  The buffer is
-//    emptied whenever the block finds it half full after 8 rows per wave;
-//  * only what does not fit (records beyond the LDS buffer or a bin's capacity, or
+//  * entries that find their slots taken, and in the end the hashed slots, become records
+//    that are sorted by column bin: the block that owns a bin in the second kernel sums its
+//    records in LDS.  A block's first records stay in LDS until it is done and go to the
+//    bins' arrays (one integer atomic per block and bin reserves the space); the others
+//    are written out as they come and sorted in pieces at the end;
+//  * only what does not fit (records beyond a block's room or a bin's capacity, or
 //    more columns than the bins can cover) is added to dense accumulators in HBM.
+#include <type_traits>
+
 #include "aa_compact.hpp"
 #include "aa_general.hpp"
 
@@ -47,20 +49,24 @@ __device__ __forceinline__ float gsum(float v) {
 
 // Per-block LDS: kDirect* slots for columns 0..kDirect*-1 (one sum per updated vector) and as
 // many entries of the model vectors themselves, kHashed* slots with a column tag each, and a
-// buffer of kRecords* records.  About 154 KB: one block of 16 waves per compute unit.
+// block's first kRecords* records.  About 150 KB: one block of 16 waves per compute unit.
 // The sums are doubles: on MI355X `ds_add_f32` retires about one lane every three cycles,
 // `ds_add_f64` three lanes a cycle (measured, scattered addresses), and the sums come out
 // closer to exact.
-constexpr int kDirectTwoVec = 3072, kHashedTwoVec = 1024, kRecordsTwoVec = 5120;
-// (dense rows keep the older split: with the sizes above their kernels need more registers
-// than a block of 1024 threads has, and a dense row fills the table before anything else)
-constexpr int kDirectTwoVecDense = 4096, kRecordsTwoVecDense = 3072;
-constexpr int kDirectOneVec = 8192, kHashedOneVec = 2048, kRecordsOneVec = 4096;
+constexpr int kDirectTwoVec = 3072, kHashedTwoVec = 1024;
+constexpr int kDirectTwoVecDense = 4096, kHashedTwoVecDense = 1024;
+constexpr int kDirectOneVec = 8192, kHashedOneVec = 2048;
 constexpr int kGradThreads = 1024, kPoolThreads = 256;
-constexpr int kCheckRows = 8;  // rows per wave between two looks at the record buffer (4: 2 to 4 % slower, 16: the buffer overflows)
+constexpr int kClaimRows = 16;  // rows per wave from which a column of every row that lost its slot would show
 
 __device__ __forceinline__ int bin_of(int c, int head, const BinPlan &p) {
   return ((c - head) >> p.group_log2) & (p.nb - 1);
+}
+
+// The set of two hashed slots a column may have.
+template <int H>
+__device__ __forceinline__ int hashed_set(int c, int salt) {
+  return (c ^ (c >> 11) ^ salt) & (H / 2 - 1);
 }
 
 // Adds one entry's terms to the dense accumulators in HBM (the path of last resort).  They
@@ -78,136 +84,56 @@ __device__ __forceinline__ void add_global(const GenArgs &a, int c, double ta, d
   }
 }
 
-// Empties the block's record buffer -- and with HASHED its hashed slots -- into the bins.
-// Whole block; the caller has put a barrier between the last append and this call.
-// Which columns win a hashed slot depends on the order in which the waves arrive, so a slot's
-// sum must leave the block without rounding: it goes out as a record of its own kind that
-// carries the double itself (one per updated vector).  The bin owner adds every record of a
-// column in doubles, so a column's total does not depend on how its entries were split
-// between slots and records.
-template <int R, int H, bool SVM, bool ASSIST, bool HASHED>
-__device__ __forceinline__ void flush_records(const GenArgs &a, int head, const int *s_rc,
-                                              const float *s_ra, const float *s_rb, int *s_nrec,
-                                              const int *s_tag, const double *s_ha,
-                                              const double *s_hb, int *s_hist, int *s_base) {
-  constexpr int kVec = (SVM && ASSIST) ? 2 : 1;
-  constexpr int kPerR = R / kGradThreads, kPerH = HASHED ? kVec * H / kGradThreads : 0;
-  constexpr int kPer = kPerR + kPerH;
-  // the kind of the q-th record of a thread: 0 two float terms, 1 + v the double of vector v
-  auto kind_of = [](int q) { return q < kPerR ? 0 : 1 + ((q - kPerR) * kGradThreads) / H; };
-  static_assert(R % kGradThreads == 0 && H % kGradThreads == 0, "whole turns of the block");
-  const int n = min(*s_nrec, R);
-  const int nb = a.plan.nb;
-  for (int t = threadIdx.x; t < nb; t += blockDim.x) s_hist[t] = 0;
-  __syncthreads();
-  // The q-th record of this thread: its column (-1: none) and its second and third words.
-  // (Read from LDS again after the places are known rather than kept in registers across the
-  // two barriers: only the ranks stay.)
-  auto record = [&](int q, int &wa, int &wb) __attribute__((always_inline)) {
-    const int i = threadIdx.x + q * kGradThreads;
-    int c = -1;
-    wa = wb = 0;
-    if (q < kPerR) {
-      if (i < n) {
-        c = s_rc[i];
-        wa = __float_as_int(s_ra[i]);
-        if (SVM && ASSIST) wb = __float_as_int(s_rb[i]);
-      }
-    } else {
-      const int slot = (i - R) & (H - 1);
-      c = s_tag[slot];
-      if (c >= 0) {
-        const double v = kind_of(q) == 1 ? s_ha[slot] : s_hb[slot];
-        wa = __double2loint(v);
-        wb = __double2hiint(v);
-        if (v == 0.0) c = -1;
-      }
-    }
-    return c;
-  };
-  int rank[kPer];
-#pragma unroll
-  for (int q = 0; q < kPer; ++q) {
-    int wa, wb;
-    const int c = record(q, wa, wb);
-    rank[q] = c >= 0 ? atomicAdd(s_hist + bin_of(c, head, a.plan), 1) : 0;
-  }
-  __syncthreads();
-  for (int t = threadIdx.x; t < nb; t += blockDim.x) {
-    const int h = s_hist[t];
-    // (64-bit fill counts: they keep counting past the capacity; the base is clamped to it)
-    s_base[t] = h > 0 ? (int)min(atomicAdd(a.bin_fill + t, (unsigned long long)h),
-                                 (unsigned long long)a.plan.cap)
-                      : 0;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int q = 0; q < kPer; ++q) {
-    int wa, wb;
-    const int c = record(q, wa, wb);
-    if (c < 0) continue;
-    const int bin = bin_of(c, head, a.plan);
-    const int pos = s_base[bin] + rank[q];
-    const int kind = kind_of(q);
-    if (pos < a.plan.cap) {
-      TailRecord r;
-      r.col = c;
-      r.a = wa;
-      r.b = wb;
-      r.kind = kind;
-      a.bins[(size_t)bin * a.plan.cap + pos] = r;
-    } else if (kind == 0) {
-      add_global<SVM, ASSIST>(a, c, __int_as_float(wa), __int_as_float(wb));
-    } else {
-      const double v = __hiloint2double(wb, wa);
-      add_global<SVM, ASSIST>(a, c, kind == 1 ? v : 0.0, kind == 1 ? 0.0 : v);
-    }
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) *s_nrec = 0;
-  __syncthreads();
-}
-
+// A gradient pass.  A group of GL lanes walks a row's entries twice: for the dot products, and with the
+// row's coefficients for the sums.  One block of 16 waves per compute unit (LDS); nothing in the row loop
+// makes the waves of a block wait for each other.
+// What bounds it: on short rows over a wide vocabulary the instructions per entry (walk, LDS sums,
+// records), on long sparse rows the gathers of columns that are not in LDS.  The records used to meet in
+// an LDS buffer that the block looked at, and emptied, together every eight rows of a wave:
+// 55 % of the wave cycles were waits.  Now those that the buffer has no room for go to memory as they
+// come, and the block sorts all of them by bin once, at the end.
 template <int GL, int MODE, bool CSR>
-__global__ __launch_bounds__(1024) void k_rows_general(const GenArgs a) {
+__global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
   constexpr bool POOL = (MODE & kPool) != 0;
   constexpr bool SVM = (MODE & kSvm) != 0;
   constexpr bool ASSIST = (MODE & kAssist) != 0;
   constexpr bool HARD = (MODE & kHard) != 0;  // keep by the row's own loss, no Assistant
-  constexpr bool GRAD = SVM || ASSIST;
   constexpr bool NEED_PHI = (POOL && !HARD) || ASSIST;
-  constexpr int G = kWave / GL;
+  constexpr int G = kWave / GL, kWaves = kGradThreads / kWave;
   constexpr int NVEC = (SVM ? 1 : 0) + (ASSIST ? 1 : 0);
-  constexpr int D = NVEC == 2 ? (CSR ? kDirectTwoVec : kDirectTwoVecDense) : kDirectOneVec;  // slots 0..D-1: column = slot
-  constexpr int H = NVEC == 2 ? kHashedTwoVec : kHashedOneVec;  // hashed slots
-  constexpr int R = NVEC == 2 ? (CSR ? kRecordsTwoVec : kRecordsTwoVecDense) : kRecordsOneVec;  // record buffer
-  __shared__ double s_sum[GRAD ? NVEC * D : 1];
-  __shared__ float s_model[GRAD ? NVEC * D : 1];  // the first D entries of w and / or phi
-  __shared__ int s_tag[GRAD ? H : 1];
-  __shared__ double s_hs[GRAD ? NVEC * H : 1];
-  __shared__ int s_rc[GRAD ? R : 1];
-  __shared__ float s_rt[GRAD ? NVEC * R : 1];
-  __shared__ int s_hist[GRAD ? kMaxBins : 1], s_base[GRAD ? kMaxBins : 1];
+  constexpr bool TWO = NVEC == 2;
+  constexpr int D = TWO ? (CSR ? kDirectTwoVec : kDirectTwoVecDense) : kDirectOneVec;  // slots 0..D-1: column = slot
+  constexpr int H = TWO ? (CSR ? kHashedTwoVec : kHashedTwoVecDense) : kHashedOneVec;  // hashed slots, two to a set
+  constexpr int RW = TWO ? 3 : 2, C = TWO ? kSortTwoVec : kSortOneVec;
+  constexpr int R = TWO ? (CSR ? kRecordsTwoVec : kRecordsTwoVecDense) : kRecordsOneVec;  // records held in LDS
+  // LDS: the sums (slots, then hashed slots; per vector), the first D entries of the model, the hashed
+  // slots' columns, the first records; at the end the same memory holds a piece of records being sorted
+  constexpr int kSumBytes = 8 * NVEC * (D + H), kModelBytes = 4 * NVEC * D, kTagBytes = 4 * H;
+  constexpr int kHeldBytes = 4 * RW * R, kSortBytes = 4 * RW * C;
+  constexpr int kTableBytes = kSumBytes + kModelBytes + kTagBytes + kHeldBytes;
+  __shared__ __attribute__((aligned(16))) char s_mem[kTableBytes > kSortBytes ? kTableBytes : kSortBytes];
+  __shared__ __attribute__((aligned(16))) int s_hist[kMaxBins], s_base[kMaxBins];
   __shared__ int s_nrec;
-  __shared__ int s_cnt[16];
-  __shared__ float s_gb[16];
-  double *const s_w = s_sum, *const s_p = s_sum + (SVM ? D : 0);
-  const float *const s_mw = s_model, *const s_mp = s_model + (SVM ? D : 0);
-  float *const s_ra = s_rt, *const s_rb = s_rt + (NVEC == 2 ? R : 0);
-  double *const s_ha = s_hs, *const s_hb = s_hs + (NVEC == 2 ? H : 0);
-  const bool binned = GRAD && a.plan.nb > 0;
-  const int salt = (int)((blockIdx.x * 0x9E3779B1u) >> 19) & (H - 1);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  __shared__ int s_cnt[kWaves];
+  __shared__ float s_gb[kWaves];
+  double *const s_sum = reinterpret_cast<double *>(s_mem);  // [vector][D + H]
+  float *const s_model = reinterpret_cast<float *>(s_mem + kSumBytes);  // one vector: [D]; two: pairs
+  int *const s_tag = reinterpret_cast<int *>(s_mem + kSumBytes + kModelBytes);
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int *const s_held = reinterpret_cast<int *>(s_mem + kSumBytes + kModelBytes + kTagBytes);
+  const bool binned = a.plan.nb > 0;
+  const int salt = (int)((blockIdx.x * 0x9E3779B1u) >> 19);
   const int grp = lane / GL, sub = lane % GL;
 
   int total = a.count_max;
   if (!POOL && a.m_dev) total = min(max(*a.m_dev, 0), a.count_max);
-  const int nwaves = gridDim.x * nw, gwave = blockIdx.x * nw + wave;
+  const int nwaves = gridDim.x * kWaves, gwave = blockIdx.x * kWaves + wave;
   const int per = total / nwaves, rem = total % nwaves;
   const int lo = gwave * per + min(gwave, rem);
   const int hi = lo + per + (gwave < rem ? 1 : 0);
 
-  // One row per lane, 64 rows per round: id, extent, label, draw, incoming loss.
+  // One row per lane, 64 rows per round: extent, label, draw, incoming loss.
   struct RowInfo {
     long long e0;
     int len;
@@ -215,8 +141,7 @@ __global__ __launch_bounds__(1024) void k_rows_general(const GenArgs a) {
   };
   auto load_rows = [&](int round) {
     RowInfo r{0, 0, 0.f, 2.f, 0.f};
-    const int base = lo + round * kWave;
-    const int j_l = base + lane;
+    const int j_l = lo + round * kWave + lane;
     if (j_l < hi) {
       const int row_l = a.rows ? a.rows[j_l] : j_l;
       if (CSR) {
@@ -232,59 +157,598 @@ __global__ __launch_bounds__(1024) void k_rows_general(const GenArgs a) {
     }
     return r;
   };
-  if (GRAD) {
-    for (int k = threadIdx.x; k < NVEC * D; k += blockDim.x) s_sum[k] = 0.0;
-    for (int k = threadIdx.x; k < min(D, a.d); k += blockDim.x) {
-      if (SVM) s_model[k] = a.w[k];
-      if (ASSIST) s_model[(SVM ? D : 0) + k] = a.phi[k];
+  RowInfo first_rows;
+  {  // (the model's loads go out together, and the first rows' behind them)
+    float mw[D / kGradThreads], mp[D / kGradThreads];
+#pragma unroll
+    for (int i = 0; i < D / kGradThreads; ++i) {
+      const int k = min((int)threadIdx.x + i * kGradThreads, a.d - 1);
+      if (SVM) mw[i] = a.w[k];
+      if (ASSIST) mp[i] = a.phi[k];
     }
-    for (int k = threadIdx.x; k < H; k += blockDim.x) s_tag[k] = -1;
-    for (int k = threadIdx.x; k < NVEC * H; k += blockDim.x) s_hs[k] = 0.0;
-    if (threadIdx.x == 0) s_nrec = 0;
-    __syncthreads();
+    first_rows = load_rows(0);
+    for (int k = threadIdx.x; k < NVEC * (D + H); k += kGradThreads) s_sum[k] = 0.0;
+#pragma unroll
+    for (int i = 0; i < D / kGradThreads; ++i) {
+      const int k = threadIdx.x + i * kGradThreads;
+      if (SVM) s_model[TWO ? 2 * k : k] = mw[i];
+      if (ASSIST) s_model[TWO ? 2 * k + 1 : k] = mp[i];
+    }
   }
-  if (GRAD && a.t_upd && blockIdx.x == 0 && threadIdx.x == 0) *a.t_snap = *a.t_upd;
+  for (int k = threadIdx.x; k < H; k += kGradThreads) s_tag[k] = -1;
+  if (threadIdx.x == 0) s_nrec = 0;
+  __syncthreads();
+  if (a.t_upd && blockIdx.x == 0 && threadIdx.x == 0) *a.t_snap = *a.t_upd;
 
   const float b = (NEED_PHI && a.bias) ? *a.bias : 0.f;
   const float T = (ASSIST || HARD) ? *a.T : 0.f;
   float gb = 0.f;
   int kept = 0;
+  const int held = binned ? R : 0, cap = held + (binned ? a.plan.pieces * a.plan.piece : 0);
+  int32_t *const late = a.recs + (size_t)a.plan.nb * a.plan.bin_cap * RW;  // records that LDS has no room for
+  auto piece_at = [&](int piece) { return late + ((size_t)piece * gridDim.x + blockIdx.x) * a.plan.piece * RW; };
+  // N records a lane, those with `want`; all lanes take part.  A block's first `held` records stay in LDS until the
+  // end, the others go to where they will be sorted.
+  auto append = [&](auto n_const, const bool *want, const int *c, const float *ta, const float *tb)
+                    __attribute__((always_inline)) {
+    constexpr int N = decltype(n_const)::value;
+    int total = 0;
+#pragma unroll
+    for (int k = 0; k < N; ++k) total += __popcll(__ballot(want[k]));
+    if (total == 0) return;
+    int first = 0;
+    if (lane == 0) first = atomicAdd(&s_nrec, total);
+    first = __builtin_amdgcn_readfirstlane(first);
+    int pos[N];
+#pragma unroll
+    for (int k = 0, next = first; k < N; ++k) {
+      const unsigned long long mask = __ballot(want[k]);
+      pos[k] = next + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                                     __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+      next += __popcll(mask);
+    }
+    if (first < held) {
+#pragma unroll
+      for (int k = 0; k < N; ++k) {
+        if (want[k] && pos[k] < held) {
+          s_held[pos[k] * RW] = c[k];
+          s_held[pos[k] * RW + 1] = __float_as_int(ta[k]);
+          if (TWO) s_held[pos[k] * RW + RW - 1] = __float_as_int(tb[k]);
+        }
+      }
+    }
+    if (first + total > held && first < cap && cap > held) {
+      // (a lane's records lie in one piece or in it and the next: with several, one is longer than 64 N)
+      static_assert(kSortTwoVec / 2 > 8 * kWave && kSortOneVec / 2 > 8 * kWave, "at most one boundary");
+      const int from = max(first - held, 0);
+      const int piece = from >= a.plan.piece ? (int)((unsigned)from / (unsigned)a.plan.piece) : 0;
+      int32_t *const here = piece_at(piece), *const after = piece_at(piece + 1);
+#pragma unroll
+      for (int k = 0; k < N; ++k) {
+        if (want[k] && pos[k] >= held && pos[k] < cap) {
+          const int i = pos[k] - held - piece * a.plan.piece;
+          int32_t *const dst = i < a.plan.piece ? here + i * RW : after + (i - a.plan.piece) * RW;
+          dst[0] = c[k];
+          dst[1] = __float_as_int(ta[k]);
+          if (TWO) dst[RW - 1] = __float_as_int(tb[k]);
+        }
+      }
+    }
+    if (first + total > cap) {
+      // (one copy of what adds to the accumulators: copies behind every entry cost hundreds of scalar registers
+      // parked in vector ones)
+#pragma unroll 1
+      for (int k = 0; k < N; ++k) {
+        int ck = c[0];
+        float tak = ta[0], tbk = tb[0];
+        bool out = want[0] && pos[0] >= cap;
+#pragma unroll
+        for (int i = 1; i < N; ++i) {
+          ck = i == k ? c[i] : ck;
+          tak = i == k ? ta[i] : tak;
+          tbk = i == k ? tb[i] : tbk;
+          out = i == k ? want[i] && pos[i] >= cap : out;
+        }
+        if (out) add_global<SVM, ASSIST>(a, ck, tak, tbk);
+      }
+    }
+  };
 
-  // every wave of the grid makes the same number of rounds, so that a block can meet between them
+  // Entries are read through buffer resources: a lane with nothing to read gives an offset past the
+  // resource's range, for which the hardware returns zero without a memory access.  No load of the row loop
+  // sits behind a branch then, and the next unit's entries stay in flight while this one's gathers are waited for
+  // (with exec-masked loads every wait was for everything in flight).
+  constexpr int kNone = (int)0x80000000;         // out of every resource's range
+  constexpr long long kSpan = 0x7fffffffll / 4;  // entries within reach of a 32-bit byte offset
+  const __amdgpu_buffer_rsrc_t r_col = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<int32_t *>(CSR ? a.col : nullptr), 0, CSR ? kNone : 0, 0x00020000);
+  const __amdgpu_buffer_rsrc_t r_val = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<float *>(CSR && a.val ? a.val : a.T), 0, CSR && a.val ? kNone : 0, 0x00020000);
   const int rows_max = per + (rem > 0 ? 1 : 0);
   const int rounds = (rows_max + kWave - 1) / kWave;
   for (int round = 0; round < rounds; ++round) {
     const int base = lo + round * kWave;
     const int cnt = max(0, min(kWave, hi - base));
-    const RowInfo ri = load_rows(round);  // (ahead of the LDS set-up these loads only delay it: measured)
-    const long long e0_l = ri.e0;
-    const int len_l = ri.len;
-    const float y_l = ri.y, u_l = ri.u, lin_l = ri.lin;
-    // the same trip count in every wave of the block (rows past a wave's own count are idle)
-    const int iters = (max(0, min(kWave, rows_max - round * kWave)) + G - 1) / G;
-    constexpr int kUnroll = 8;
-    constexpr bool KEEP = GRAD && CSR;  // (dense rows here are long: nothing worth keeping)
-    // entries e, e + GL, ... of the row that starts at entry e0 and has len entries
-    auto load_entries_at = [&](long long e0, int len, int e, int *c, float *xv) {
+    const RowInfo ri = round == 0 ? first_rows : load_rows(round);
+    long long e0_l = ri.e0;
+    int len_l = ri.len, src_l = lane;
+    float y_l = ri.y, u_l = ri.u, lin_l = ri.lin;
+    constexpr int kPiece = 4 * GL;  // entries of a row that its lanes read with one load
+    // A unit, the work of a lane group at a time, is a row of up to two pieces and whatever follows (the first M
+    // places), or two rows of one piece, which then share the chain of round trips (1,000,000 sentence pairs:
+    // pass 151 us with a row at a time, 138 with two).
+    int M = cnt;
+    if constexpr (CSR) {
+      const bool whole = lane < cnt && (len_l > kPiece || (len_l > 0 && (e0_l + len_l < 4 || e0_l + len_l > kSpan)));
+      const unsigned long long m_whole = __ballot(whole), mine = whole ? m_whole : ~m_whole;
+      M = __popcll(m_whole);
+      const int first_short = M;
+      // (few rows leave lane groups idle in pairs, and a unit without a second piece costs half: one update over 5000
+      // sentence pairs 18.6 us paired, 17.8 not)
+      if (cnt <= G) M = cnt;
+      const int to = 4 * ((whole ? 0 : first_short) + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mine >> 32),
+                                                                          __builtin_amdgcn_mbcnt_lo((uint32_t)mine, 0u)));
+      auto put = [&](int v) { return __builtin_amdgcn_ds_permute(to, v); };
+      const int e_lo = put((int)(uint32_t)e0_l), e_hi = put((int)(e0_l >> 32));
+      e0_l = ((long long)e_hi << 32) | (uint32_t)e_lo;
+      len_l = put(len_l);
+      src_l = put(lane);
+      if (SVM) y_l = __int_as_float(put(__float_as_int(y_l)));
+      if (POOL) u_l = __int_as_float(put(__float_as_int(u_l)));
+      if (ASSIST && !SVM) lin_l = __int_as_float(put(__float_as_int(lin_l)));
+    }
+    const int units = M + (cnt - M + 1) / 2;  // (lanes without a row have the last places)
+    const int iters = (units + G - 1) / G;
+    // place of a unit's row in slot 0 or 1
+    auto place = [&](int unit, int slot) { return unit < M ? unit : 2 * unit - M + slot; };
+    // The unit's two pieces, four neighbouring entries a lane and piece.  The piece that ends with
+    // a row shares entries with the one before it, so that every load is a whole one inside the
+    // row; entries k < skip belong there.  A row that ends before the matrix's fourth entry has nothing
+    // to share with: it is left to the walk one by one, and so is one past the reach of a 32-bit offset.
+    struct Pieces {
+      i4v c[2];
+      f4v x[2];
+      int skip[2];  // (4 and more: nothing here)
+    };
+    auto quick_len = [&](long long e0, int len) { return e0 + len >= 4 && e0 + len <= kSpan ? min(len, 2 * kPiece) : 0; };
+    auto request = [&](int it, Pieces &p) __attribute__((always_inline)) {
+      const int unit = it * G + grp;
+      int off[2];
 #pragma unroll
-      for (int u = 0; u < kUnroll; ++u) {
-        const int eu = e + u * GL;
-        const bool in = eu < len;
-        c[u] = CSR ? (in ? a.col[e0 + eu] : 0) : (in ? eu : 0);
-        xv[u] = in ? (CSR ? (a.val ? a.val[e0 + eu] : 1.f) : a.x[e0 + eu]) : 0.f;
+      for (int q = 0; q < 2; ++q) {
+        const int at = place(unit, q);
+        const long long e0 = __shfl(e0_l, min(at, kWave - 1), kWave);
+        const int len_any = __shfl(len_l, min(at, kWave - 1), kWave);
+        const int len = at < cnt ? len_any : 0, last = len - 4;
+        const int e = 4 * sub + (q == 1 && unit < M ? kPiece : 0);
+        const bool here = e < quick_len(e0, len);
+        off[q] = here ? ((int)e0 + min(e, last)) * 4 : kNone;
+        p.skip[q] = here ? e - last : 4;
+      }
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        p.c[q] = __builtin_bit_cast(i4v, __builtin_amdgcn_raw_buffer_load_b128(r_col, off[q], 0, 0));
+        p.x[q] = __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(r_val, off[q], 0, 0));
       }
     };
-    // The first kUnroll entries per lane of the NEXT group of rows are requested while this
-    // group's terms are scattered, so that a group's walk starts with its entries at hand.
-    int cn[KEEP ? kUnroll : 1];
-    float xn[KEEP ? kUnroll : 1];
-    auto prefetch_group = [&](int it) {
-      const int li = min(it * G + grp, kWave - 1);
-      const long long e0 = __shfl(e0_l, li, kWave);
-      const int len = __shfl(len_l, li, kWave);
-      load_entries_at(e0, it * G + grp < cnt ? len : 0, sub, cn, xn);
-    };
-    if (KEEP && iters > 0) prefetch_group(0);
+    Pieces ahead;
+    if (CSR && iters > 0) request(0, ahead);
+    if (CSR && round == 0 && per >= kClaimRows) {
+      // A column that every row has must find a hashed slot: the columns of the block's first row get theirs
+      // before the waves race for them (left to the race, the two length columns of the translation batches lost it
+      // in one block of ten, whose entries then met in one bin: update kernel 21 -> 134 us).
+      if (wave == 0 && grp == 0) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          const int c = ahead.c[k / 4][k % 4];
+          if (k % 4 >= ahead.skip[k / 4] && (k < 4 || M > 0) && c >= D) {
+            int *const tags = s_tag + 2 * hashed_set<H>(c, salt);
+            const int old = atomicCAS(tags, -1, c);
+            if (old != -1 && old != c) atomicCAS(tags + 1, -1, c);
+          }
+        }
+      }
+      __syncthreads();
+    }
+    for (int it = 0; it < iters; ++it) {
+      const int unit = it * G + grp;
+      const bool pair = unit >= M;
+      // Row scalars are worked out by the lanes of a row: even lanes have the row in slot 0, odd ones slot 1.
+      const int at = place(unit, sub & 1), at_safe = min(at, kWave - 1);
+      const bool live = at < cnt, teller = live && (sub == 0 || (sub == 1 && pair));
+      const int j = base + (CSR ? __shfl(src_l, at_safe, kWave) : at_safe);
+      const float u = __shfl(u_l, at_safe, kWave);
+      const float yy = __shfl(y_l, at_safe, kWave);
+      const float lin = __shfl(lin_l, at_safe, kWave);
+      const long long e0 = __shfl(e0_l, at_safe, kWave);
+      const int len_any = __shfl(len_l, at_safe, kWave);
+      // what is left of a row of its own after the first two pieces is walked entry by entry
+      const int len = live && !pair ? len_any : 0;
+      const int slow = CSR ? quick_len(e0, len) : 0;
+      float dp[2] = {0.f, 0.f}, dw[2] = {0.f, 0.f};
+      // Shares of the dot products.  The columns that are not in LDS are gathered without a
+      // branch (an entry with nothing to fetch asks for column 0), so that the gathers leave together.
+      auto gather = [&](auto n_const, const int *c, float2 *far) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < decltype(n_const)::value; ++k) far[k] = make_float2(0.f, 0.f);
+        if (a.d <= D) return;  // (no such columns: a round trip less)
+#pragma unroll
+        for (int k = 0; k < decltype(n_const)::value; ++k) {
+          const int cf = c[k] >= D ? c[k] : 0;
+          if (TWO)
+            far[k] = a.wp[cf];  // both values of the column with one gather
+          else
+            far[k].x = (ASSIST ? a.phi : a.w)[cf];
+        }
+      };
+      auto dot_entries = [&](auto n_const, const int *c, const float *xv, const float2 *far, const bool *in,
+                             int q) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < decltype(n_const)::value; ++k) {
+          const int cn = min(c[k], D - 1);
+          float mw, mp;
+          if (TWO) {
+            const float2 near = reinterpret_cast<const float2 *>(s_model)[cn];
+            mw = c[k] >= D ? far[k].x : near.x;
+            mp = c[k] >= D ? far[k].y : near.y;
+          } else {
+            mw = mp = c[k] >= D ? far[k].x : s_model[cn];
+          }
+          if (SVM) dw[q] = in[k] ? __fmaf_rn(mw, xv[k], dw[q]) : dw[q];
+          if (NEED_PHI) dp[q] = in[k] ? __fmaf_rn(mp, xv[k], dp[q]) : dp[q];
+        }
+      };
+      Pieces cur;
+      bool second = false;  // anything in slot 1
+      if constexpr (CSR) {
+        cur = ahead;
+        asm volatile("" : "+v"(cur.c[0]), "+v"(cur.c[1]), "+v"(cur.x[0]), "+v"(cur.x[1]));  // (waited for here)
+        int c[8];
+        float xv[8];
+        bool in[8];
+        float2 far[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) c[k] = cur.c[k / 4][k % 4];
+        gather(std::integral_constant<int, 8>{}, c, far);
+        __builtin_amdgcn_sched_barrier(0);
+        request(it + 1, ahead);  // (past the last unit: no accesses)
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          xv[k] = a.val ? cur.x[k / 4][k % 4] : 1.f;
+          in[k] = k % 4 >= cur.skip[k / 4];
+        }
+        dot_entries(std::integral_constant<int, 4>{}, c, xv, far, in, 0);
+        second = __ballot(cur.skip[1] < 4) != 0ull;
+        if (second) dot_entries(std::integral_constant<int, 4>{}, c + 4, xv + 4, far + 4, in + 4, 1);
+      }
+      constexpr int kRest = CSR && TWO ? 4 : 8;  // (eight: more registers than there are)
+      for (int eb = slow + sub; eb < len; eb += kRest * GL) {
+        int c[kRest];
+        float xv[kRest];
+        bool in[kRest];
+        float2 far[kRest];
+#pragma unroll
+        for (int k = 0; k < kRest; ++k) {
+          const int e = eb + k * GL;
+          in[k] = e < len;
+          c[k] = in[k] ? (CSR ? a.col[e0 + e] : e) : 0;
+          xv[k] = in[k] ? (CSR ? (a.val ? a.val[e0 + e] : 1.f) : a.x[e0 + e]) : 0.f;
+        }
+        gather(std::integral_constant<int, kRest>{}, c, far);
+        dot_entries(std::integral_constant<int, kRest>{}, c, xv, far, in, 0);
+      }
+      // the sums of this lane's slot
+      auto own = [&](float v0, float v1) __attribute__((always_inline)) {
+        if (!CSR) return gsum<GL>(v0);
+        v0 = gsum<GL>(v0);
+        v1 = gsum<GL>(v1);
+        return pair ? ((sub & 1) ? v1 : v0) : v0 + v1;
+      };
+      float g = 0.f;
+      bool keep = live;
+      if (NEED_PHI) {
+        const float s = own(dp[0], dp[1]) + b;
+        g = sigmoidf_(s);
+        if (POOL) {
+          if (a.do_keep) keep = live && keep_decision(u, g, a.gamma, a.one_minus_gamma);
+          if (teller) {
+            if (a.logit) a.logit[j] = s;
+            if (a.prob) a.prob[j] = g;
+            if (a.flags) a.flags[j] = keep ? 1 : 0;
+          }
+        }
+      }
+      float loss = lin, cw_own = 0.f, resid_own = 0.f;
+      if (SVM) {
+        const float marg = yy * own(dw[0], dw[1]);
+        loss = fmaxf(0.f, 1.f - marg);
+        if (HARD) {  // shrinking by the objective value itself
+          keep = live && loss > T;
+          if (teller && a.flags) a.flags[j] = keep ? 1 : 0;
+        }
+        if (teller && (HARD || keep) && a.loss_out) a.loss_out[j] = loss;
+        cw_own = (keep && marg < 1.f) ? yy : 0.f;
+      }
+      if (ASSIST) {
+        const float z = loss > T ? 1.f : 0.f;
+        resid_own = keep ? g - z : 0.f;
+        if (teller) gb += resid_own;
+      }
+      if (teller && keep) kept += 1;
+      // the coefficients of both slots' rows, in every lane (quad_perm 0,0,2,2 and 1,1,3,3)
+      const float cw[2] = {dpp_move<0xA0>(cw_own), dpp_move<0xF5>(cw_own)};
+      const float resid[2] = {dpp_move<0xA0>(resid_own), dpp_move<0xF5>(resid_own)};
+      const bool contrib[2] = {cw[0] != 0.f || resid[0] != 0.f, cw[1] != 0.f || resid[1] != 0.f};
+      // Second walk.  A column's sum is its slot's, or that of the hashed slot that holds it; an entry that
+      // finds neither leaves as a record.  N entries of a lane together (column -1: none): their tag reads
+      // are in flight at once.
+      auto scatter = [&](auto n_const, const int *c, const float *xv, int slot) __attribute__((always_inline)) {
+        constexpr int N = decltype(n_const)::value;
+        int2 tag[N];
+        int at_sum[N];
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+          at_sum[k] = c[k] >= D ? 2 * hashed_set<H>(c[k], salt) : 0;
+          tag[k] = *reinterpret_cast<const int2 *>(s_tag + at_sum[k]);
+        }
+        bool claim = false;
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+          const bool found = tag[k].x == c[k] || tag[k].y == c[k];
+          claim = claim || (c[k] >= D && !found && (tag[k].x == -1 || tag[k].y == -1));
+        }
+        if (__ballot(claim) != 0ull) {  // (rare after the first rows)
+#pragma unroll
+          for (int k = 0; k < N; ++k) {
+            if (c[k] >= D && tag[k].x != c[k] && tag[k].y != c[k]) {  // (a tag changes once, from -1 to its column)
+              int *const tags = s_tag + at_sum[k];
+              if (tag[k].x == -1) {
+                const int old = atomicCAS(tags, -1, c[k]);
+                tag[k].x = old == -1 ? c[k] : old;
+              }
+              if (tag[k].x != c[k] && tag[k].y == -1) {
+                const int old = atomicCAS(tags + 1, -1, c[k]);
+                tag[k].y = old == -1 ? c[k] : old;
+              }
+            }
+          }
+        }
+        bool miss[N];
+        float ta[N], tb[N];
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+          const int q = slot + k / 4, hashed = tag[k].x == c[k] ? D + at_sum[k] : tag[k].y == c[k] ? D + at_sum[k] + 1 : -1;
+          const int at = c[k] < D ? c[k] : hashed;
+          miss[k] = c[k] >= D && at < 0;
+          ta[k] = SVM ? (cw[q] != 0.f ? cw[q] * xv[k] : 0.f) : resid[q] * xv[k];
+          tb[k] = TWO ? (resid[q] != 0.f ? resid[q] * xv[k] : 0.f) : 0.f;
+          if (at >= 0) {
+            if (!TWO || cw[q] != 0.f) unsafeAtomicAdd(s_sum + at, (double)ta[k]);
+            if (TWO && resid[q] != 0.f) unsafeAtomicAdd(s_sum + (D + H) + at, (double)tb[k]);
+          }
+        }
+        append(n_const, miss, c, ta, tb);
+      };
+      if constexpr (CSR) {
+        int c[8];
+        float xv[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          c[k] = contrib[k / 4] && k % 4 >= cur.skip[k / 4] ? cur.c[k / 4][k % 4] : -1;
+          xv[k] = a.val ? cur.x[k / 4][k % 4] : 1.f;
+        }
+        if (!TWO && second) {
+          scatter(std::integral_constant<int, 8>{}, c, xv, 0);
+        } else {  // (two vectors: eight at once are more registers than there are)
+          scatter(std::integral_constant<int, 4>{}, c, xv, 0);
+          if (TWO && second) scatter(std::integral_constant<int, 4>{}, c + 4, xv + 4, 1);
+        }
+      }
+      // entries beyond; the wave's groups step together
+      int steps_len = contrib[0] ? len - slow : 0;
+#pragma unroll
+      for (int off = GL; off < kWave; off <<= 1) steps_len = max(steps_len, __shfl_xor(steps_len, off, kWave));
+      steps_len = __builtin_amdgcn_readfirstlane(steps_len);  // (what follows is the wave's then: scalar counts)
+      for (int eb = 0; eb < steps_len; eb += GL) {
+        const int e = slow + eb + sub;
+        int c = -1;
+        float xv = 0.f;
+        if (contrib[0] && e < len) {
+          c = CSR ? a.col[e0 + e] : e;
+          xv = CSR ? (a.val ? a.val[e0 + e] : 1.f) : a.x[e0 + e];
+        }
+        scatter(std::integral_constant<int, 1>{}, &c, &xv, 0);
+      }
+    }
+  }
+
+  // kept count and bias-gradient sum of the block: wave sums, then wave order (one store per
+  // block; thousands of waves adding to one address would run one after the other)
+  int kw = kept;
+  float gbw = gb;
+#pragma unroll
+  for (int off = kWave / 2; off > 0; off >>= 1) {
+    kw += __shfl_xor(kw, off, kWave);
+    gbw += __shfl_xor(gbw, off, kWave);
+  }
+  if (lane == 0) {
+    s_cnt[wave] = kw;
+    s_gb[wave] = gbw;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int kb = 0;
+    float gbb = 0.f;
+    for (int i = 0; i < kWaves; ++i) {
+      kb += s_cnt[i];
+      gbb += s_gb[i];
+    }
+    a.blk_cnt[blockIdx.x] = kb;
+    a.blk_gb[blockIdx.x] = gbb;
+  }
+  // The hashed slots.  Which columns won one depends on the order in which the waves arrived, so a
+  // slot's sum must leave the block without rounding: as up to three records, floats that add up
+  // to the double exactly (24 bits each; the sums are multiples of the smallest float).
+  static_assert(H % kGradThreads == 0, "whole turns of the block");
+  for (int turn = 0; turn < H / kGradThreads; ++turn) {
+    const int k = turn * kGradThreads + threadIdx.x;
+    int c = s_tag[k];
+    double va = s_sum[D + k], vb = TWO ? s_sum[(D + H) + D + k] : 0.0;
+    if (c >= 0 && !(fabs(va) <= 3e38 && fabs(vb) <= 3e38)) {  // (no float for it, or no number)
+      add_global<SVM, ASSIST>(a, c, va, vb);
+      c = -1;
+    }
+    bool want[3];
+    int cols[3];
+    float ta[3], tb[3];
+#pragma unroll
+    for (int part = 0; part < 3; ++part) {
+      ta[part] = (float)va;
+      tb[part] = (float)vb;
+      va -= (double)ta[part];
+      vb -= (double)tb[part];
+      cols[part] = c;
+      want[part] = c >= 0 && (ta[part] != 0.f || tb[part] != 0.f);
+    }
+    append(std::integral_constant<int, 3>{}, want, cols, ta, tb);
+  }
+  // the first columns: this block's sums, zeros included
+  float *const mine = a.part + (size_t)blockIdx.x * NVEC * a.head;
+  for (int k = threadIdx.x; k < a.head; k += kGradThreads) {
+    mine[k] = (float)s_sum[k];
+    if (TWO) mine[a.head + k] = (float)s_sum[(D + H) + k];
+  }
+  if (!binned) return;
+  __syncthreads();
+  // The records in LDS go to the bins, a run per bin (one integer atomic per block and bin reserves the space).
+  const int n = min(s_nrec, cap);
+  {
+    const int m = min(n, held);
+    constexpr int kPer = R / kGradThreads;
+    static_assert(R % kGradThreads == 0, "whole turns of the block");
+    if (threadIdx.x < kMaxBins) s_hist[threadIdx.x] = 0;
+    __syncthreads();
+    int rank[kPer];
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      const int i = threadIdx.x + q * kGradThreads;
+      rank[q] = i < m ? atomicAdd(s_hist + bin_of(s_held[i * RW], D, a.plan), 1) : 0;
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < a.plan.nb) {
+      const int h = s_hist[threadIdx.x];
+      s_base[threadIdx.x] = h > 0 ? (int)atomicAdd(a.bin_fill + threadIdx.x, (unsigned)h) : 0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      const int i = threadIdx.x + q * kGradThreads;
+      if (i >= m) continue;
+      int r[RW];
+#pragma unroll
+      for (int w = 0; w < RW; ++w) r[w] = s_held[i * RW + w];
+      const int bin = bin_of(r[0], D, a.plan), pos = s_base[bin] + rank[q];
+      if (pos < a.plan.bin_cap) {
+        int32_t *const dst = a.recs + ((size_t)bin * a.plan.bin_cap + pos) * RW;
+#pragma unroll
+        for (int w = 0; w < RW; ++w) dst[w] = r[w];
+      } else {
+        add_global<SVM, ASSIST>(a, r[0], __int_as_float(r[1]), TWO ? __int_as_float(r[RW - 1]) : 0.f);
+      }
+    }
+  }
+  // The others, a piece (at most C) at a time, sorted by bin: a counting sort by way of LDS, back to where they
+  // were.  The owner of a bin finds its records of a piece as one run (start, count).
+  const int beyond = max(n - held, 0);
+  if (threadIdx.x == 0) a.blk_late[blockIdx.x] = beyond;
+  int *const s_rec = reinterpret_cast<int *>(s_mem);
+  constexpr int kPer = C / kGradThreads;
+  for (int piece = 0; piece * a.plan.piece < beyond; ++piece) {
+    int32_t *const src = piece_at(piece);
+    const int m = min(a.plan.piece, beyond - piece * a.plan.piece);
+    __syncthreads();  // (everybody is done with what the memory held before)
+    if (threadIdx.x < kMaxBins) s_hist[threadIdx.x] = 0;
+    int r[kPer][RW], rank[kPer];
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      if (q * kGradThreads >= m) break;  // (the same for the whole block)
+      const int i = min((int)threadIdx.x + q * kGradThreads, m - 1);
+#pragma unroll
+      for (int w = 0; w < RW; ++w) r[q][w] = src[(size_t)i * RW + w];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      if (q * kGradThreads >= m) break;
+      rank[q] = 0;
+      if ((int)threadIdx.x + q * kGradThreads < m) rank[q] = atomicAdd(s_hist + bin_of(r[q][0], D, a.plan), 1);
+    }
+    __syncthreads();
+    if (wave == 0) {  // four bins a lane
+      static_assert(kMaxBins == 4 * kWave, "one wave scans the bins");
+      const int4 h = reinterpret_cast<const int4 *>(s_hist)[lane];
+      const int mine = h.x + h.y + h.z + h.w;
+      int before = mine;
+#pragma unroll
+      for (int off = 1; off < kWave; off <<= 1) {
+        const int v = __shfl_up(before, off, kWave);
+        if (lane >= off) before += v;
+      }
+      before -= mine;
+      reinterpret_cast<int4 *>(s_base)[lane] = make_int4(before, before + h.x, before + h.x + h.y, before + h.x + h.y + h.z);
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < a.plan.nb)
+      a.runs[((size_t)threadIdx.x * a.plan.pieces + piece) * gridDim.x + blockIdx.x] =
+          s_base[threadIdx.x] | (s_hist[threadIdx.x] << 16);
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      if (q * kGradThreads >= m) break;
+      if ((int)threadIdx.x + q * kGradThreads < m) {
+        const int pos = s_base[bin_of(r[q][0], D, a.plan)] + rank[q];
+#pragma unroll
+        for (int w = 0; w < RW; ++w) s_rec[pos * RW + w] = r[q][w];
+      }
+    }
+    __syncthreads();
+    // whole 128-bit words (a piece is a multiple of four records)
+    for (int i = threadIdx.x; 4 * i < m * RW; i += kGradThreads)
+      reinterpret_cast<int4 *>(src)[i] = reinterpret_cast<const int4 *>(s_rec)[i];
+  }
+}
+
+// The scoring pass: the stored entries of a row by GL lanes, phi through the caches.
+template <int GL, bool CSR>
+__global__ __launch_bounds__(kPoolThreads) void k_rows_general(const GenArgs a) {
+  constexpr int G = kWave / GL, kUnroll = 8;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  const int grp = lane / GL, sub = lane % GL;
+  const int total = a.count_max;
+  const int nwaves = gridDim.x * nw, gwave = blockIdx.x * nw + wave;
+  const int per = total / nwaves, rem = total % nwaves;
+  const int lo = gwave * per + min(gwave, rem);
+  const int hi = lo + per + (gwave < rem ? 1 : 0);
+  const float b = a.bias ? *a.bias : 0.f;
+  for (int base = lo; base < hi; base += kWave) {
+    const int cnt = min(kWave, hi - base);
+    // one row per lane, 64 rows per round: extent, draw
+    long long e0_l = 0;
+    int len_l = 0;
+    float u_l = 2.f;
+    if (lane < cnt) {
+      const int j_l = base + lane;
+      const int row_l = a.rows ? a.rows[j_l] : j_l;
+      if (CSR) {
+        e0_l = a.rowptr[row_l];
+        len_l = (int)(a.rowptr[row_l + 1] - e0_l);
+      } else {
+        e0_l = (long long)row_l * a.ld;
+        len_l = a.d;
+      }
+      if (a.do_keep) u_l = keep_uniform(a.key, (uint32_t)j_l);
+    }
+    const int iters = (cnt + G - 1) / G;
     for (int it = 0; it < iters; ++it) {
       const int li = it * G + grp;
       const bool live = li < cnt;
@@ -293,45 +757,8 @@ __global__ __launch_bounds__(1024) void k_rows_general(const GenArgs a) {
       const int len_any = __shfl(len_l, li, kWave);  // every lane takes part in the shuffle
       const int len = live ? len_any : 0;
       const float u = __shfl(u_l, li, kWave);
-      const float yy = __shfl(y_l, li, kWave);
-      const float lin = __shfl(lin_l, li, kWave);
-      float dp = 0.f, dw = 0.f;
-      // kUnroll entries per lane at a time: their column and value loads leave together, then
-      // the model gathers that depend on the columns (the chain that bounds this loop)
-      int c0[kUnroll];  // the first kUnroll entries of the lane stay in registers for the second walk
-      float x0[kUnroll];
-      auto load_entries = [&](int e, int *c, float *xv) { load_entries_at(e0, len, e, c, xv); };
-      auto dot_entries = [&](const int *c, const float *xv) {
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-          if (GRAD) {  // the first columns of the model are in LDS
-            const bool near = c[u] < D;
-            if (SVM && ASSIST) {  // past the table: both values of the column with one gather
-              float2 far = make_float2(0.f, 0.f);
-              if (!near) far = a.wp[c[u]];
-              dw = __fmaf_rn(near ? s_mw[c[u]] : far.x, xv[u], dw);
-              dp = __fmaf_rn(near ? s_mp[c[u]] : far.y, xv[u], dp);
-            } else {
-              if (NEED_PHI) {
-                const float pv = ASSIST ? (near ? s_mp[c[u]] : a.phi[c[u]]) : a.phi[c[u]];
-                dp = __fmaf_rn(pv, xv[u], dp);
-              }
-              if (SVM) dw = __fmaf_rn(near ? s_mw[c[u]] : a.w[c[u]], xv[u], dw);
-            }
-          } else {
-            if (NEED_PHI) dp = __fmaf_rn(a.phi[c[u]], xv[u], dp);
-          }
-        }
-      };
-      if (KEEP) {
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-          c0[u] = cn[u];
-          x0[u] = xn[u];
-        }
-        dot_entries(c0, x0);
-      }
-      if constexpr (CSR && !GRAD) {
+      float dp = 0.f;
+      if constexpr (CSR) {
         // four neighbouring entries a lane: one load per array for 4 GL entries.  The piece that ends
         // with the row shares entries with the one before it, so that every load is a whole one inside
         // the row (entries k < skip belong there); rows that end before the matrix's fourth
@@ -371,257 +798,23 @@ __global__ __launch_bounds__(1024) void k_rows_general(const GenArgs a) {
           }
         }
       } else {
-        for (int e = sub + (KEEP ? GL * kUnroll : 0); e < len; e += GL * kUnroll) {
-          int c[kUnroll];
+        for (int e = sub; e < len; e += GL * kUnroll) {
           float xv[kUnroll];
-          load_entries(e, c, xv);
-          dot_entries(c, xv);
+#pragma unroll
+          for (int u = 0; u < kUnroll; ++u) xv[u] = e + u * GL < len ? a.x[e0 + e + u * GL] : 0.f;
+#pragma unroll
+          for (int u = 0; u < kUnroll; ++u) dp = __fmaf_rn(a.phi[e + u * GL < len ? e + u * GL : 0], xv[u], dp);
         }
       }
-      float g = 0.f;
-      bool keep = live;
-      if (NEED_PHI) {
-        dp = gsum<GL>(dp);
-        const float s = dp + b;
-        g = sigmoidf_(s);
-        if (POOL) {
-          if (a.do_keep) keep = live && keep_decision(u, g, a.gamma, a.one_minus_gamma);
-          if (sub == 0 && live) {
-            if (a.logit) a.logit[j] = s;
-            if (a.prob) a.prob[j] = g;
-            if (a.flags) a.flags[j] = keep ? 1 : 0;
-          }
-        }
+      dp = gsum<GL>(dp);
+      const float s = dp + b;
+      const float g = sigmoidf_(s);
+      const bool keep = live && (!a.do_keep || keep_decision(u, g, a.gamma, a.one_minus_gamma));
+      if (sub == 0 && live) {
+        if (a.logit) a.logit[j] = s;
+        if (a.prob) a.prob[j] = g;
+        if (a.flags) a.flags[j] = keep ? 1 : 0;
       }
-      if (GRAD) {
-        float loss = lin;
-        float cw = 0.f, resid = 0.f;
-        if (SVM) {
-          dw = gsum<GL>(dw);
-          const float marg = yy * dw;
-          loss = fmaxf(0.f, 1.f - marg);
-          if (HARD) {  // shrinking by the objective value itself
-            keep = live && loss > T;
-            if (sub == 0 && live && a.flags) a.flags[j] = keep ? 1 : 0;
-          }
-          if (sub == 0 && (HARD ? live : keep) && a.loss_out) a.loss_out[j] = loss;
-          cw = (keep && marg < 1.f) ? yy : 0.f;
-        }
-        if (ASSIST) {
-          const float z = loss > T ? 1.f : 0.f;
-          resid = keep ? g - z : 0.f;
-          if (sub == 0) gb += resid;
-        }
-        if (sub == 0 && keep) kept += 1;
-        if (KEEP && it + 1 < iters) prefetch_group(it + 1);
-        // second walk: the wave's groups step together, so that lanes with an entry outside the
-        // table can reserve their places in the record buffer with one LDS atomic per step
-        const bool contrib = cw != 0.f || resid != 0.f;
-        int steps_len = contrib ? len : 0;
-#pragma unroll
-        for (int off = GL; off < kWave; off <<= 1)
-          steps_len = max(steps_len, __shfl_xor(steps_len, off, kWave));
-        auto scatter = [&](bool active, int c, float xv) {
-          const float ta = SVM ? cw * xv : resid * xv, tb = resid * xv;
-          if (active && c < D) {
-            if (SVM && cw != 0.f) unsafeAtomicAdd(s_w + c, (double)(cw * xv));
-            if (ASSIST && resid != 0.f) unsafeAtomicAdd(s_p + c, (double)(resid * xv));
-          }
-          bool tail = active && c >= D;
-          if (tail) {  // the column's hashed slot, if it is free or already the column's
-            // (a tag changes once, from -1 to its column: a plain read settles most cases)
-            auto owner_of = [&](int slot) {
-              int t = s_tag[slot];
-              if (t == -1) {
-                const int old = atomicCAS(s_tag + slot, -1, c);
-                t = old == -1 ? c : old;
-              }
-              return t;
-            };
-            int h = (c ^ (c >> 11) ^ salt) & (H - 1);
-            int owner = owner_of(h);
-            if (owner != c) {  // second try, elsewhere in the table
-              h = (h ^ (H / 2) ^ (c >> 5)) & (H - 1);
-              owner = owner_of(h);
-            }
-            if (owner == c) {
-              if (SVM && cw != 0.f) unsafeAtomicAdd(s_ha + h, (double)ta);
-              if (ASSIST && resid != 0.f) unsafeAtomicAdd((SVM ? s_hb : s_ha) + h, (double)tb);
-              tail = false;
-            }
-          }
-          if (binned) {
-            const unsigned long long mask = __ballot(tail);
-            if (mask != 0ull) {
-              const int leader = __ffsll((long long)mask) - 1;
-              int first = 0;
-              if (lane == leader) first = atomicAdd(&s_nrec, __popcll(mask));
-              first = __shfl(first, leader, kWave);
-              if (tail) {
-                const int pos = first + (int)__builtin_amdgcn_mbcnt_hi(
-                                            (uint32_t)(mask >> 32),
-                                            __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-                if ((unsigned)pos < (unsigned)R) {
-                  s_rc[pos] = c;
-                  s_ra[pos] = ta;
-                  if (NVEC == 2) s_rb[pos] = tb;
-                } else {
-                  add_global<SVM, ASSIST>(a, c, ta, tb);
-                }
-              }
-            }
-          } else if (tail) {
-            add_global<SVM, ASSIST>(a, c, ta, tb);
-          }
-                };
-        if (KEEP) {
-          // The entries held in registers go through the same stations as `scatter` above, but
-          // kBatch of a lane together: their tag reads are in flight at once, then the claims,
-          // then the second probes, and the wave reserves its places in the record buffer once
-          // -- a handful of LDS round trips per batch, not per entry.  (All kUnroll together
-          // cost more registers than there are.)
-          constexpr int kBatch = 4;
-#pragma unroll
-          for (int u0 = 0; u0 < kUnroll; u0 += kBatch) {
-            if (u0 * GL >= steps_len) break;  // (no row of the wave reaches this far)
-            bool tl[kBatch];    // entry still on its way to a hashed slot or a record
-            int slot[kBatch];   // hashed slot it is looking at
-            int seen[kBatch];   // the tag found there
-#pragma unroll
-            for (int k = 0; k < kBatch; ++k) {
-              const int u = u0 + k;
-              const bool active = contrib && sub + u * GL < len;
-              const int c = c0[u];
-              if (active && c < D) {
-                if (SVM && cw != 0.f) unsafeAtomicAdd(s_w + c, (double)(cw * x0[u]));
-                if (ASSIST && resid != 0.f) unsafeAtomicAdd(s_p + c, (double)(resid * x0[u]));
-              }
-              tl[k] = active && c >= D;
-              slot[k] = (c ^ (c >> 11) ^ salt) & (H - 1);
-              seen[k] = tl[k] ? s_tag[slot[k]] : 0;
-            }
-            auto claim = [&](int k) {  // (a tag changes once, from -1 to its column)
-              if (tl[k] && seen[k] == -1) {
-                const int old = atomicCAS(s_tag + slot[k], -1, c0[u0 + k]);
-                seen[k] = old == -1 ? c0[u0 + k] : old;
-              }
-            };
-#pragma unroll
-            for (int k = 0; k < kBatch; ++k) claim(k);
-#pragma unroll
-            for (int k = 0; k < kBatch; ++k) {  // second try, elsewhere in the table
-              if (tl[k] && seen[k] != c0[u0 + k]) {
-                slot[k] = (slot[k] ^ (H / 2) ^ (c0[u0 + k] >> 5)) & (H - 1);
-                seen[k] = s_tag[slot[k]];
-              }
-            }
-#pragma unroll
-            for (int k = 0; k < kBatch; ++k) claim(k);
-            int n_tail = 0;
-#pragma unroll
-            for (int k = 0; k < kBatch; ++k) {
-              const int u = u0 + k;
-              if (tl[k] && seen[k] == c0[u]) {
-                const float ta = SVM ? cw * x0[u] : resid * x0[u], tb = resid * x0[u];
-                if (SVM && cw != 0.f) unsafeAtomicAdd(s_ha + slot[k], (double)ta);
-                if (ASSIST && resid != 0.f) unsafeAtomicAdd((SVM ? s_hb : s_ha) + slot[k], (double)tb);
-                tl[k] = false;
-              }
-              n_tail += __popcll(__ballot(tl[k]));
-            }
-            if (n_tail > 0) {  // (the same in every lane)
-              int first = 0;
-              if (binned) {
-                if (lane == 0) first = atomicAdd(&s_nrec, n_tail);
-                first = __shfl(first, 0, kWave);
-              }
-#pragma unroll
-              for (int k = 0; k < kBatch; ++k) {
-                const int u = u0 + k;
-                const unsigned long long mask = __ballot(tl[k]);
-                if (tl[k]) {
-                  const float ta = SVM ? cw * x0[u] : resid * x0[u], tb = resid * x0[u];
-                  const int pos = first + (int)__builtin_amdgcn_mbcnt_hi(
-                                              (uint32_t)(mask >> 32),
-                                              __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-                  if (binned && (unsigned)pos < (unsigned)R) {
-                    s_rc[pos] = c0[u];
-                    s_ra[pos] = ta;
-                    if (NVEC == 2) s_rb[pos] = tb;
-                  } else {
-                    add_global<SVM, ASSIST>(a, c0[u], ta, tb);
-                  }
-                }
-                first += __popcll(mask);
-              }
-            }
-          }
-        }
-        for (int eb = KEEP ? GL * kUnroll : 0; eb < steps_len; eb += GL) {
-          const int e = eb + sub;
-          const bool active = contrib && e < len;
-          int c = 0;
-          float xv = 0.f;
-          if (active) {
-            c = CSR ? a.col[e0 + e] : e;
-            xv = CSR ? (a.val ? a.val[e0 + e] : 1.f) : a.x[e0 + e];
-          }
-          scatter(active, c, xv);
-        }
-        // every kCheckRows rows per wave the block looks at its record buffer together
-        if (binned && ((it + 1) * G) % kCheckRows == 0 && (it + 1 < iters || round + 1 < rounds)) {
-          __syncthreads();
-          const int fill = s_nrec;
-          __syncthreads();
-          if (fill > R / 2)
-            flush_records<R, H, SVM, ASSIST, false>(a, D, s_rc, s_ra, s_rb, &s_nrec, s_tag, s_ha,
-                                                    s_hb, s_hist, s_base);
-        }
-      }
-    }
-  }
-
-  if (GRAD) {
-    // kept count and bias-gradient sum of the block: wave sums, then wave order (one store per
-    // block; thousands of waves adding to one address would run one after the other)
-    int kw = kept;
-    float gbw = gb;
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) {
-      kw += __shfl_xor(kw, off, kWave);
-      gbw += __shfl_xor(gbw, off, kWave);
-    }
-    if (lane == 0) {
-      s_cnt[wave] = kw;
-      s_gb[wave] = gbw;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      int kb = 0;
-      float gbb = 0.f;
-      for (int i = 0; i < nw; ++i) {
-        kb += s_cnt[i];
-        gbb += s_gb[i];
-      }
-      a.blk_cnt[blockIdx.x] = kb;
-      a.blk_gb[blockIdx.x] = gbb;
-    }
-    if (binned) {
-      flush_records<R, H, SVM, ASSIST, true>(a, D, s_rc, s_ra, s_rb, &s_nrec, s_tag, s_ha, s_hb,
-                                             s_hist, s_base);
-    } else {
-      for (int k = threadIdx.x; k < H; k += blockDim.x) {
-        const int c = s_tag[k];
-        if (c >= 0)
-          add_global<SVM, ASSIST>(a, c, s_ha[k], (SVM && ASSIST) ? s_hb[k] : 0.0);
-      }
-    }
-    // the first columns: this block's sums, zeros included, as plain stores -- the last thing a
-    // wave does, so that nothing waits for them (a barrier after them would)
-    float *const mine = a.part + (size_t)blockIdx.x * NVEC * a.head;
-    for (int k = threadIdx.x; k < a.head; k += blockDim.x) {
-      if (SVM) mine[k] = (float)s_w[k];
-      if (ASSIST) mine[(SVM ? a.head : 0) + k] = (float)s_p[k];
     }
   }
 }
@@ -639,7 +832,7 @@ __global__ __launch_bounds__(256) void k_zero_f32(float *p, size_t count) {
 // 16 waves per compute unit loads them once and then walks its rows; only columns past the
 // table are gathered through the caches.  The gathers of k_rows_general go through the vector L1, which
 // serves a lane or so a cycle, and from a few thousand columns on miss it.  Same outputs and the same
-// order of additions per row as k_rows_general<16, kPool, true>, so the two give the same bits.
+// order of additions per row as k_rows_general<16, true>, so the two give the same bits.
 // What bounds it: the vector memory path.  1,000,000 rows of 56 entries over 64,002 columns (448 MB),
 // per launch: 163 us with a 32-bit load per entry (16 loads and 8 gathers a step, a sigmoid per row and
 // group), 155 with one 128-bit load per array and half slot and the sigmoids of 64 rows at a time, 151 with
@@ -974,7 +1167,7 @@ struct Fold {
 
 // Kept count of the pass (and the sum of its bias gradients): one per-block value per thread of
 // the first four waves.
-static_assert(kGeneralGradBlocks <= 4 * kWave && kApplyWaves >= 4, "pass_totals adds up four waves' counts");
+static_assert(kGeneralGradBlocks == 4 * kWave && kApplyWaves >= 4, "pass_totals adds up four waves' counts");
 __device__ __forceinline__ int pass_totals(const ApplyArgs &a, int cnt, float gbs, int *s_m,
                                            float *s_g, float *gb_out) {
   const int t = threadIdx.x;
@@ -1003,32 +1196,74 @@ __device__ __forceinline__ int bin_column(int k, int bin, const ApplyArgs &a) {
   return a.head + (((((k >> gl) << a.plan.nb_log2) | bin) << gl) | (k & ((1 << gl) - 1)));
 }
 
+// The records of a bin that did not fit into a block's LDS: a run in every sorted piece of every block.
+// Sixteen lanes read a run, four runs of a lane group in flight together, two records a lane of each.
+template <int RW, class Add>
+__device__ __forceinline__ void late_records(const ApplyArgs &a, int bin, int n_mine, int *s_run, int pieces, Add add) {
+  constexpr int kGroups = kApplyThreads / 16, kRuns = 4;
+  const int tid = threadIdx.x, grp = tid / 16, sub = tid % 16, nblk = a.nblk_pass;
+  const int32_t *const runs = a.runs + (size_t)bin * a.plan.pieces * nblk;
+  const int32_t *const late = a.recs + (size_t)a.plan.nb * a.plan.bin_cap * RW;
+  for (int piece = 0; piece < pieces; ++piece) {
+    __syncthreads();
+    if (tid < kGeneralGradBlocks) s_run[tid] = piece * a.plan.piece < n_mine ? runs[(size_t)piece * nblk + tid] : 0;
+    __syncthreads();
+    for (int b0 = grp; b0 < nblk; b0 += kRuns * kGroups) {
+      int cnt[kRuns], longest = 0;
+      const int32_t *at[kRuns];
+#pragma unroll
+      for (int i = 0; i < kRuns; ++i) {
+        const int blk = min(b0 + i * kGroups, kGeneralGradBlocks - 1), run = s_run[blk];
+        cnt[i] = b0 + i * kGroups < nblk ? run >> 16 : 0;
+        longest = max(longest, cnt[i]);
+        at[i] = late + (((size_t)piece * nblk + min(blk, nblk - 1)) * a.plan.piece + (cnt[i] > 0 ? run & 0xffff : 0)) * RW;
+      }
+      // (Every load is unconditional: a load under a condition makes the compiler wait for all loads in flight
+      // where the paths join.  An index past the end is clamped and the value then not used.)
+      for (int j = sub; j - sub < longest; j += 32) {
+        int r[2 * kRuns][RW];
+#pragma unroll
+        for (int i = 0; i < 2 * kRuns; ++i) {
+          const int k = max(min(j + 16 * (i & 1), cnt[i / 2] - 1), 0);
+#pragma unroll
+          for (int w = 0; w < RW; ++w) r[i][w] = at[i / 2][k * RW + w];
+        }
+#pragma unroll
+        for (int i = 0; i < 2 * kRuns; ++i)
+          if (j + 16 * (i & 1) < cnt[i / 2]) add(r[i]);
+      }
+    }
+  }
+}
+
 // The block that owns a bin.  Everything it needs from memory (the first records and columns
 // per thread, in registers) is requested before anything is used: one round trip, not five.
+template <int RW>
 __device__ __forceinline__ void apply_bin(const ApplyArgs &a, int bin, double *s_bin, int *s_m,
-                                          float *s_g) {
+                                          float *s_g, int *s_run, int *s_late) {
   // per thread: kRec records per batch (the first batch is requested before the bin's fill count
   // is known: 1024 records a bin; with 4096, small pools read megabytes of stale ones); kCol runs
   // of four columns (a bin's columns come in groups of at least four neighbours) --
   // 4 * kCol * kApplyThreads covers any bin of a pass that updates two vectors, and half of the
   // largest bin of one that updates one
   constexpr int kRec = 2, kCol = 2;
-  const int tid = threadIdx.x, cols = a.plan.cols, cap = a.plan.cap;
+  const int tid = threadIdx.x, cols = a.plan.cols, cap = a.plan.bin_cap;
   const int cnt = tid < a.nblk_pass ? a.blk_cnt[tid] : 0;
-  const int fill = (int)min(a.bin_fill[bin], (unsigned long long)cap);
+  const int n_mine = tid < a.nblk_pass ? a.blk_late[tid] : 0;
+  const int n = (int)min(a.bin_fill[bin], (unsigned)cap);
   const int acc_used = a.acc_used[bin];
-  const TailRecord *rec = a.bins + (size_t)bin * cap;
-  // records, four words each; two register sets, so that the loads of the next batch are in
-  // flight while this one is added up
-  int4 r0[kRec], r1[kRec];
+  const int32_t *const rec = a.recs + (size_t)bin * cap * RW;
+  // two register sets, so that the loads of the next batch are in flight while this one is added up
+  int r0[kRec][RW], r1[kRec][RW];
   constexpr int kBatch = kRec * kApplyThreads;
   // (Every load below is unconditional: a load under a condition makes the compiler wait for
   // all loads in flight where the paths join, and the requests would go out one at a time.
   // An index past the end is clamped to the last record, whose value is then not used.)
-  auto load_batch = [&](int4 *__restrict__ r, int base, int last) __attribute__((always_inline)) {
+  auto load_batch = [&](int (*__restrict__ r)[RW], int base, int last) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < kRec; ++u)
-      r[u] = *reinterpret_cast<const int4 *>(rec + min(base + tid + u * kApplyThreads, last));
+#pragma unroll
+      for (int w = 0; w < RW; ++w) r[u][w] = rec[(size_t)min(base + tid + u * kApplyThreads, last) * RW + w];
   };
   load_batch(r0, 0, cap - 1);  // past the fill count: stale, in bounds, not used
   int col[kCol];   // first column of the run, -1: none, or not all four exist (the model's end)
@@ -1052,21 +1287,22 @@ __device__ __forceinline__ void apply_bin(const ApplyArgs &a, int bin, double *s
   while (copies < 16 && 2 * copies * span <= kBinColsMax) copies *= 2;
   double *const s_mine = s_bin + (tid & (copies - 1)) * span;
   for (int k = tid; k < copies * span; k += kApplyThreads) s_bin[k] = 0.0;
+  if (tid < kGeneralGradBlocks) {
+    int most = n_mine;
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) most = max(most, __shfl_xor(most, off, kWave));
+    if ((tid & 63) == 0) s_late[tid >> 6] = most;
+  }
   float gb_unused;
   const int m = pass_totals(a, cnt, 0.f, s_m, s_g, &gb_unused);  // barrier: the sums are zero
   const Fold fold(a, m);
-  const int n = min(fill, cap);
-  auto add = [&](const int4 &r) {  // (x: column, y and z: the terms, w: the record's kind)
-    const int k = bin_local(r.x, a);
-    if (r.w == 0) {
-      const float ta = __int_as_float(r.y), tb = __int_as_float(r.z);
-      if (ta != 0.f) unsafeAtomicAdd(s_mine + k, (double)ta);
-      if (a.nvec == 2 && tb != 0.f) unsafeAtomicAdd(s_mine + cols + k, (double)tb);
-    } else {  // a hashed slot's sum: the double of one vector
-      unsafeAtomicAdd(s_mine + (r.w == 2 ? cols : 0) + k, __hiloint2double(r.z, r.y));
-    }
+  auto add = [&](const int *r) __attribute__((always_inline)) {
+    const int k = bin_local(r[0], a);
+    const float ta = __int_as_float(r[1]), tb = __int_as_float(r[RW - 1]);
+    if (ta != 0.f) unsafeAtomicAdd(s_mine + k, (double)ta);
+    if (RW == 3 && tb != 0.f) unsafeAtomicAdd(s_mine + cols + k, (double)tb);
   };
-  auto add_batch = [&](const int4 *r, int base) __attribute__((always_inline)) {
+  auto add_batch = [&](const int (*r)[RW], int base) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < kRec; ++u)
       if (base + tid + u * kApplyThreads < n) add(r[u]);
@@ -1077,6 +1313,8 @@ __device__ __forceinline__ void apply_bin(const ApplyArgs &a, int bin, double *s
     load_batch(r0, base + 2 * kBatch, n - 1);
     add_batch(r1, base + kBatch);
   }
+  const int most = max(max(s_late[0], s_late[1]), max(s_late[2], s_late[3]));
+  if (most > 0) late_records<RW>(a, bin, n_mine, s_run, (most + a.plan.piece - 1) / a.plan.piece, add);
   __syncthreads();
   auto sum_of = [&](int k) {  // over the copies, in order
     double v = 0.0;
@@ -1159,7 +1397,7 @@ __device__ __forceinline__ void apply_bin(const ApplyArgs &a, int bin, double *s
     }
   }
   if (a.keep_ready && tid == 0) {  // (read at the top; the next pass counts from zero)
-    a.bin_fill[bin] = 0ull;
+    a.bin_fill[bin] = 0u;
     a.acc_used[bin] = 0;
   }
 }
@@ -1170,6 +1408,7 @@ __global__ __launch_bounds__(kApplyThreads) void k_apply_general(const ApplyArgs
   __shared__ int s_m[kApplyWaves];
   __shared__ float s_g[kApplyWaves];
   __shared__ double s_bin[kBinColsMax + 1];  // (+1: the odd stride of a single copy)
+  __shared__ int s_run[kGeneralGradBlocks], s_late[kGeneralGradBlocks / kWave];
   // roles by block number: the other columns first (the bin owners have the longest way to
   // go), then the first columns, then the compaction tiles
   const int bid = (int)blockIdx.x, hb = bid - nrest;
@@ -1188,7 +1427,10 @@ __global__ __launch_bounds__(kApplyThreads) void k_apply_general(const ApplyArgs
     return;
   }
   if (bid < nrest && a.plan.nb > 0) {  // nrest == nb
-    apply_bin(a, bid, s_bin, s_m, s_g);
+    if (a.nvec == 2)
+      apply_bin<3>(a, bid, s_bin, s_m, s_g, s_run, s_late);
+    else
+      apply_bin<2>(a, bid, s_bin, s_m, s_g, s_run, s_late);
     return;
   }
   const int t = threadIdx.x;
@@ -1245,22 +1487,22 @@ hipError_t launch_gl(const GenArgs &a, int mode, int nblk, hipStream_t st, hipEv
   const dim3 grid(nblk), block(mode == kPool ? kPoolThreads : kGradThreads);
   switch (mode) {
     case kPool:
-      launch_stamped((k_rows_general<GL, kPool, CSR>), grid, block, st, e0, e1, a);
+      launch_stamped((k_rows_general<GL, CSR>), grid, block, st, e0, e1, a);
       break;
     case kSvm:
-      launch_stamped((k_rows_general<GL, kSvm, CSR>), grid, block, st, e0, e1, a);
+      launch_stamped((k_rows_grad<GL, kSvm, CSR>), grid, block, st, e0, e1, a);
       break;
     case kAssist:
-      launch_stamped((k_rows_general<GL, kAssist, CSR>), grid, block, st, e0, e1, a);
+      launch_stamped((k_rows_grad<GL, kAssist, CSR>), grid, block, st, e0, e1, a);
       break;
     case kSvm | kAssist:
-      launch_stamped((k_rows_general<GL, kSvm | kAssist, CSR>), grid, block, st, e0, e1, a);
+      launch_stamped((k_rows_grad<GL, kSvm | kAssist, CSR>), grid, block, st, e0, e1, a);
       break;
     case kPool | kSvm | kAssist:
-      launch_stamped((k_rows_general<GL, kPool | kSvm | kAssist, CSR>), grid, block, st, e0, e1, a);
+      launch_stamped((k_rows_grad<GL, kPool | kSvm | kAssist, CSR>), grid, block, st, e0, e1, a);
       break;
     case kPool | kSvm | kHard:
-      launch_stamped((k_rows_general<GL, kPool | kSvm | kHard, CSR>), grid, block, st, e0, e1, a);
+      launch_stamped((k_rows_grad<GL, kPool | kSvm | kHard, CSR>), grid, block, st, e0, e1, a);
       break;
     default:
       return hipErrorInvalidValue;
@@ -1321,7 +1563,7 @@ hipError_t launch_zero_f32(float *p, size_t count, hipStream_t st) {
 }
 
 bool general_keeps_ready(int32_t d, int nvec, bool csr) {
-  return general_bin_plan(d, general_head_columns(d, nvec, csr), nvec, 1).nb > 0;
+  return general_bin_plan(d, general_head_columns(d, nvec, csr), nvec, 1, 1).nb > 0;
 }
 
 int32_t general_head_columns(int32_t d, int nvec, bool csr) {

@@ -6,40 +6,43 @@
 
 namespace aa {
 
-// What leaves a block of a gradient pass for a column without a slot in its LDS table.
-// kind 0: one stored entry of a kept row -- a and b hold, as float bits, its terms of the (up
-// to two) gradient sums (two updated vectors: a -> w, b -> phi; one: a -> that vector).
-// kind 1, 2: the sum a hashed slot collected for the first / second updated vector -- a and b
-// hold the low and high word of the double.
-struct __attribute__((aligned(16))) TailRecord {
-  int32_t col;
-  int32_t a, b;
-  int32_t kind;
-};
+// What leaves a block of a gradient pass for a column without a slot in its LDS table: records of two
+// words (column, term) when one vector is updated, of three (column, term for w, term for phi) when both
+// are.  The first kRecords* of a block stay in its LDS and go to the bins at the end.  Those that find no room
+// there ("late" ones) are written out as they come and in the end sorted by bin, in pieces of at most
+// kSort* (what LDS holds); the first pieces of all blocks lie side by side, then the second ones.
+constexpr int kRecordsTwoVec = 5120, kRecordsTwoVecDense = 2048, kRecordsOneVec = 4096;
+constexpr int kSortOneVec = 16384, kSortTwoVec = 12288;
 
 // Columns from `head` on are dealt to nb bins (a power of two, 0: no binning) in groups of
 // 2^group_log2: group g = (col - head) >> group_log2 goes to bin g % nb, where it is group
-// g / nb; a bin spans `cols` columns in all and holds up to `cap` records.  A group is 16
+// g / nb; a bin spans `cols` columns in all.  A group is 16
 // columns (one 64-byte line of a model vector) when there are many columns, so that the
 // owners read and write the model in whole lines; with fewer columns that traffic is small
 // beside the records', and groups of 4 spread a run of frequent neighbouring columns (the
 // head of a vocabulary, say) over four times as many bins -- the bin with the most records
 // sets the update kernel's time.
+// A bin has room for `bin_cap` records, a block of the pass for `pieces` pieces of `piece` late ones
+// (multiples of four).
 struct BinPlan {
-  int32_t nb, nb_log2, cols, cap, group_log2;
+  int32_t nb, nb_log2, cols, bin_cap, piece, pieces, group_log2;
 };
 constexpr int kMaxBins = 256;
 constexpr int kBinGroupLog2 = 4, kBinFineGroupLog2 = 2;
 constexpr int64_t kBinFineColsMax = 1 << 18;  // groups of 4 up to this many binned columns
 constexpr int kBinColsMax = 8192;  // LDS floats of a bin's owner in the update kernel
-// Records the bins hold in all: 48 per candidate (the sparse configuration needs about 26),
+// Records the blocks of a pass have room for in all: 48 per candidate (the sparse configuration needs about 26),
 // at least 65,536, at most 2^27 (2 GiB); what does not fit goes to the accumulators.
 inline size_t general_record_capacity(int32_t count_max) {
   const size_t want = 48 * (size_t)(count_max > 0 ? count_max : 0);
   return want < 65536 ? 65536 : (want > ((size_t)1 << 27) ? ((size_t)1 << 27) : want);
 }
-inline BinPlan general_bin_plan(int32_t d, int32_t head, int nvec, int32_t count_max) {
-  BinPlan p{0, 0, 0, 0, kBinGroupLog2};
+// The workspace has 16 bytes per record of that capacity: 12 for records (the bins one and a half times what the
+// blocks' LDS holds, but at most three quarters; late records the rest), the others for the runs (nb * pieces words per
+// block, each piece of several more than 4096 records).
+constexpr size_t kRecordBytes = 16, kRecordWordBytes = 12;
+inline BinPlan general_bin_plan(int32_t d, int32_t head, int nvec, int32_t count_max, int32_t nblk) {
+  BinPlan p{0, 0, 0, 0, 0, 0, kBinGroupLog2};
   const int gl = (int64_t)d - head <= kBinFineColsMax ? kBinFineGroupLog2 : kBinGroupLog2;
   const int64_t group = (int64_t)1 << gl;
   const int64_t groups = ((int64_t)d - head + group - 1) / group;
@@ -55,7 +58,15 @@ inline BinPlan general_bin_plan(int32_t d, int32_t head, int nvec, int32_t count
   p.nb_log2 = lg;
   p.group_log2 = gl;
   p.cols = (int32_t)cols;
-  p.cap = (int32_t)(general_record_capacity(count_max) / nb);
+  const int64_t all = general_record_capacity(count_max) * kRecordWordBytes / (nvec == 2 ? 12 : 8);
+  const int64_t in_lds = (int64_t)nblk * (nvec == 2 ? kRecordsTwoVec : kRecordsOneVec);
+  int64_t binned = in_lds + in_lds / 2 > 49152 ? in_lds + in_lds / 2 : 49152;
+  if (binned > all / 4 * 3) binned = all / 4 * 3;
+  p.bin_cap = (int32_t)(binned / nb) & ~3;
+  const int32_t each = (int32_t)((all - binned) / nblk), most = nvec == 2 ? kSortTwoVec : kSortOneVec;
+  p.pieces = (each + most - 1) / most;
+  if (each < 256) p.pieces = 0;  // (not worth a piece)
+  p.piece = p.pieces > 0 ? (each / p.pieces) & ~3 : 0;
   return p;
 }
 
@@ -84,8 +95,8 @@ struct GenArgs {
   float *loss_out;
   const float *loss_in;
   // (w[c], phi[c]) side by side for the columns past `head`, indexed by column: one gather
-  // brings both values of a column that is not in LDS (written before the pass; NULL unless
-  // the pass updates both vectors)
+  // brings both values of a column that is not in LDS (written before the pass; element 0 is always
+  // readable; NULL unless the pass updates both vectors)
   const float2 *wp;
   // atomic accumulators (zeroed before the pass); with bins, acc_used[bin] (zeroed too) is set
   // by whoever adds to a column of that bin
@@ -99,10 +110,14 @@ struct GenArgs {
   // written whole by every block of a gradient pass (no clearing needed)
   float *part;
   int32_t head;
-  // entries of the other columns leave a block as records, sorted into bins by column
-  // (see BinPlan); fill[bin] counts the records offered to a bin, zeroed before the pass
-  TailRecord *bins;
-  unsigned long long *bin_fill;
+  // entries of the other columns leave a block as records (see BinPlan): recs[bin * bin_cap + i], with the
+  // bin's count in bin_fill (zeroed before the pass); behind the bins the late ones of block and piece p,
+  // [(p * blocks + block) * piece + i], with a bin's run (start | count << 16) in
+  // runs[(bin * pieces + p) * blocks + block] and the block's count in blk_late
+  int32_t *recs;
+  int32_t *runs;
+  unsigned *bin_fill;
+  int32_t *blk_late;
   BinPlan plan;
   // optional device-side update counter (step size lr / sqrt(t)): block 0 of a gradient pass
   // copies it to *t_snap, which the update kernel reads (the counter itself changes there)
@@ -116,8 +131,8 @@ int32_t general_head_columns(int32_t d, int nvec, bool csr);
 // Whether the update kernel can leave the workspace ready for the next pass (see ApplyArgs).
 bool general_keeps_ready(int32_t d, int nvec, bool csr);
 constexpr int kGeneralGradBlocks = 256;
-// floats ahead of the accumulators: 16 scalars, the 64-bit fill counts of the bins, then one
-// flag per bin (an even count in all: the accumulators behind it are doubles)
+// floats ahead of the accumulators: 16 scalars, the fill counts of the bins, the blocks' counts of late
+// records, then one flag per bin (an even count in all: the accumulators behind it are doubles)
 constexpr int kGeneralHeader = 16 + 3 * kMaxBins;
 // floats the header and the two accumulators of d doubles take
 inline size_t general_clear_floats(int32_t d) { return kGeneralHeader + 4 * (size_t)d; }
@@ -146,8 +161,10 @@ struct ApplyArgs {
   float *bias;
   const float *part;  // per-block sums of the first `head` columns (see GenArgs)
   int32_t head, nvec, nblk_pass;
-  const TailRecord *bins;  // records of the other columns (see GenArgs)
-  unsigned long long *bin_fill;
+  const int32_t *recs;  // records of the other columns (see GenArgs)
+  const int32_t *runs;
+  unsigned *bin_fill;
+  const int32_t *blk_late;
   BinPlan plan;
   float lambda, lr, lr_a, l2_a;
   int32_t *t_upd;          // optional update counter: the Boss step size is lr / sqrt(updates so far)

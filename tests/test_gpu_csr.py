@@ -659,3 +659,39 @@ def test_csr_updates_at_the_edges_of_the_column_bins(ref, d):
     r = rng(900 + d % 1000)
     _check_csr_updates(ref, r, d, 2000, "hot_tail", 20, 60, True)
     _check_csr_updates(ref, r, d, 300, "uniform", 1, 12, False)
+
+
+@pytest.mark.parametrize("n,d,kind,lo,hi,with_val", [
+    (40_000, 60_000, "uniform", 40, 90, True),     # two rows a unit and rows of their own; late records in one piece
+    (20_000, 300_000, "uniform", 100, 200, True),  # late records in several pieces; rows past two pieces
+    (30_000, 9000, "hot_tail", 0, 5, False),       # empty rows, rows that end before the matrix's fourth entry
+    (30_000, 4000, "zipf", 63, 65, True),          # both sides of one piece; no column outside the table
+    (24_000, 70_000, "hot_tail", 127, 129, False), # both sides of two pieces
+    (70, 200_000, "uniform", 900, 1100, True)])    # two blocks whose records need every piece there is
+def test_csr_updates_pieces_pairs_and_late_records(ref, n, d, kind, lo, hi, with_val):
+    """Row lengths around the pieces of 64 entries, enough rows per wave for two rows a unit, and
+    records beyond what a block's LDS holds (all rows chosen, or nearly)."""
+    _check_csr_updates(ref, rng(n + d), d, n, kind, lo, hi, with_val)
+
+
+def test_csr_hashed_sum_beyond_float_range():
+    """A column past the table whose sum no float holds, and one whose sum is no number: the column's total
+    is rounded once (to an infinity, a NaN), and nothing else is touched by it."""
+    n, d, big, nan = 64, 9000, 8999, 8995
+    cols = np.stack([np.full(n, 5), np.full(n, nan), np.full(n, big)], axis=1).astype(np.int32)
+    vals = np.stack([np.ones(n), np.ones(n), np.full(n, 3e38)], axis=1).astype(np.float32)
+    vals[3, 1] = np.nan
+    F = csr_features(np.arange(0, 3 * n + 1, 3, dtype=np.int64), cols.ravel(), vals.ravel(), d)
+    phi, b = torch.zeros(d, device="cuda"), scalar_dev(0.0)
+    keep = [i for i in range(n) if i != 3]
+    ws = api.Workspace(n, d)
+    api.assistant_update(F, dev(np.array(keep, np.int32)), scalar_dev(n - 1, torch.int32), n - 1,
+                         torch.zeros(n - 1, device="cuda"), scalar_dev(1.0), phi, b, 1.0, 0.0, ws)
+    got = host(phi)
+    assert got[big] == -np.inf and np.isclose(got[5], -0.5) and np.isclose(got[nan], -0.5)
+    assert np.count_nonzero(got) == 3 and np.isclose(float(host(b)[0]), -0.5)
+    phi.zero_()
+    api.assistant_update(F, None, scalar_dev(n, torch.int32), n, torch.zeros(n, device="cuda"), scalar_dev(1.0),
+                         phi, b, 1.0, 0.0, ws)
+    got = host(phi)
+    assert np.isnan(got[[5, nan, big]]).all() and np.count_nonzero(got) == 3   # (row 3's residual is a NaN)
