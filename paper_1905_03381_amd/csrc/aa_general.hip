@@ -31,6 +31,12 @@ namespace {
 typedef float f4v __attribute__((ext_vector_type(4), aligned(4)));  // (any float address)
 typedef int i4v __attribute__((ext_vector_type(4), aligned(4)));
 
+// v moved by a DPP control.
+template <int CTRL>
+__device__ __forceinline__ float dpp_move(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+
 // Sum over aligned groups of WIDTH lanes, halves first.  For 16 lanes by rotations inside the row,
 // no trip through LDS: after each addition the values repeat with half the period, so rotating
 // by 8, 4, 2 and 1 adds the same pairs as exchanging with lane ^ 8, ^ 4, ^ 2 and ^ 1.
@@ -139,11 +145,14 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
     int len;
     float y, u, lin;
   };
-  auto load_rows = [&](int round) {
+  auto row_id = [&](int round) {
+    const int j_l = lo + round * kWave + lane;
+    return j_l < hi && a.rows ? a.rows[j_l] : j_l;
+  };
+  auto load_rows = [&](int round, int row_l) {
     RowInfo r{0, 0, 0.f, 2.f, 0.f};
     const int j_l = lo + round * kWave + lane;
     if (j_l < hi) {
-      const int row_l = a.rows ? a.rows[j_l] : j_l;
       if (CSR) {
         r.e0 = a.rowptr[row_l];
         r.len = (int)(a.rowptr[row_l + 1] - r.e0);
@@ -166,8 +175,13 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
       if (SVM) mw[i] = a.w[k];
       if (ASSIST) mp[i] = a.phi[k];
     }
-    first_rows = load_rows(0);
+    int id = row_id(0);
+    __builtin_amdgcn_sched_barrier(0);
     for (int k = threadIdx.x; k < NVEC * (D + H); k += kGradThreads) s_sum[k] = 0.0;
+    for (int k = threadIdx.x; k < H; k += kGradThreads) s_tag[k] = -1;
+    if (threadIdx.x == 0) s_nrec = 0;
+    __builtin_amdgcn_sched_barrier(0);
+    first_rows = load_rows(0, id);
 #pragma unroll
     for (int i = 0; i < D / kGradThreads; ++i) {
       const int k = threadIdx.x + i * kGradThreads;
@@ -175,8 +189,6 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
       if (ASSIST) s_model[TWO ? 2 * k + 1 : k] = mp[i];
     }
   }
-  for (int k = threadIdx.x; k < H; k += kGradThreads) s_tag[k] = -1;
-  if (threadIdx.x == 0) s_nrec = 0;
   __syncthreads();
   if (a.t_upd && blockIdx.x == 0 && threadIdx.x == 0) *a.t_snap = *a.t_upd;
 
@@ -269,7 +281,7 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
   for (int round = 0; round < rounds; ++round) {
     const int base = lo + round * kWave;
     const int cnt = max(0, min(kWave, hi - base));
-    const RowInfo ri = round == 0 ? first_rows : load_rows(round);
+    const RowInfo ri = round == 0 ? first_rows : load_rows(round, row_id(round));
     long long e0_l = ri.e0;
     int len_l = ri.len, src_l = lane;
     float y_l = ri.y, u_l = ri.u, lin_l = ri.lin;
