@@ -867,8 +867,8 @@ constexpr int kScoreTableMaxCols = 2 * kScoreTableCols;
 // waits the compiler places count the loads in flight exactly and never drain them: the
 // entries of the row groups one and two steps ahead and the cold-column gathers of the next
 // group stay outstanding while the current group is added up, and the row extents arrive a
-// round (64 rows) ahead, the row ids two rounds.  Rows longer than one chunk (128 entries) are
-// rare in data this kernel is for; they are skipped in the loop and walked afterwards.
+// round (64 rows) ahead, the row ids two rounds.  Rows longer than one chunk (128 entries)
+// are skipped in the loop and walked afterwards, a lane group each.
 template <bool VAL>
 __global__ __launch_bounds__(kScoreTableThreads) void k_score_table(const GenArgs a) {
   constexpr int GL = 16, G = kWave / GL, kUnroll = 8, kChunk = GL * kUnroll;
@@ -964,7 +964,8 @@ __global__ __launch_bounds__(kScoreTableThreads) void k_score_table(const GenArg
     e.hi = a.rowptr[row + 1];
     return e;
   };
-  Extent cur = extent(lo + lane, row_id(lo + lane));
+  const Extent first_rows = extent(lo + lane, row_id(lo + lane));
+  Extent cur = first_rows;
   Extent next = extent(lo + kWave + lane, row_id(lo + kWave + lane));
   int id_after = row_id(lo + 2 * kWave + lane);
   bool any_longer = false;
@@ -1079,31 +1080,81 @@ __global__ __launch_bounds__(kScoreTableThreads) void k_score_table(const GenArg
     }
   }
   if (__ballot(any_longer) == 0ull) return;
-  // rows of more than one chunk, one after the other in the wave's first lane group
+  // Rows of more than one chunk or out of reach: a row a lane group, chunk after chunk in the order above, with
+  // 64-bit addresses; the requests go on across the ends of rows here too.  100,000 rows of 200 entries, one row of a
+  // wave at a time and entry by entry / so / k_rows_general: over 512 columns 132 / 30.7 / 29.6 us, over 2000
+  // 134 / 31.1 / 31.5, over 10,000 136 / 33.0 / 40.3, over 50,000 165 / 39.9 / 145.
   for (int base = lo; base < hi; base += kWave) {
     const int j_l = base + lane;
-    const Extent e_l = extent(j_l, row_id(j_l));
+    const Extent e_l = base == lo ? first_rows : extent(j_l, row_id(j_l));
     const int len_l = j_l < hi ? (int)(e_l.hi - e_l.lo) : 0;
-    const float u_l = a.do_keep ? keep_uniform(a.key, (uint32_t)j_l) : 2.f;
-    unsigned long long longer = __ballot(len_l > kChunk || (j_l < hi && e_l.hi > kSpan) || (len_l > 0 && e_l.hi < 4));
-    while (longer != 0ull) {
-      const int li = __ffsll((long long)longer) - 1;
-      longer &= longer - 1;
-      const long long e0 = __shfl((long long)e_l.lo, li, kWave);
-      const int len_any = __shfl(len_l, li, kWave);  // (every lane takes part in the shuffle)
-      const int len = grp == 0 ? len_any : 0;
-      const float u = __shfl(u_l, li, kWave);
+    const bool early = len_l > 0 && e_l.hi < 4;  // (ends before the matrix's fourth entry: one by one)
+    const bool mine = !early && (len_l > kChunk || (j_l < hi && e_l.hi > kSpan));
+    const unsigned long long m_mine = __ballot(mine);
+    if (__ballot(mine || early) == 0ull) continue;
+    if (early) {
       float dp = 0.f;
-      for (int e = 4 * sub; e < len; e += kHalfChunk) {  // (the order of a lane's additions is the loop's)
-        for (int k = e; k < min(e + 4, len); ++k) {
-          const int c = a.col[e0 + k];
-          const float m = c < D ? s_phi[c] : a.phi[c];
-          dp = VAL ? __fmaf_rn(m, a.val[e0 + k], dp) : dp + m;
+      for (int k = 0; k < len_l; ++k) {
+        const int c = a.col[e_l.lo + k];
+        const float m = c < D ? s_phi[c] : a.phi[c];
+        dp = VAL ? __fmaf_rn(m, a.val[e_l.lo + k], dp) : dp + m;
+      }
+      s_row[wave][lane] = dp;
+    }
+    const int n = __popcll(m_mine);
+    if (n > 0) {
+      const unsigned long long m_same = mine ? m_mine : ~m_mine;
+      const int to = 4 * ((mine ? 0 : n) + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m_same >> 32),
+                                                                    __builtin_amdgcn_mbcnt_lo((uint32_t)m_same, 0u)));
+      const int lo_s = __builtin_amdgcn_ds_permute(to, (int)(uint32_t)e_l.lo);
+      const int hi_s = __builtin_amdgcn_ds_permute(to, (int)(e_l.lo >> 32));
+      const int len_s = __builtin_amdgcn_ds_permute(to, len_l), src_s = __builtin_amdgcn_ds_permute(to, lane);
+      // a group's next chunk: sorted row and first entry
+      int at = grp, e = 0;
+      // (what: twice the chunk's row, plus one for the row's last; -1 past the last row.  A lane with nothing
+      // to read gets the matrix's first entries -- there are four: some row here ends behind them.)
+      auto request_chunk = [&](Slot &s, int *what) __attribute__((always_inline)) {
+        const int from = min(at, kWave - 1);
+        const long long e0 = ((long long)__shfl(hi_s, from, kWave) << 32) | (uint32_t)__shfl(lo_s, from, kWave);
+        const int len_any = __shfl(len_s, from, kWave), len = at < n ? len_any : 0;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int first = e + h * kHalfChunk + 4 * sub, last = len - 4;
+          const long long off = first < len ? e0 + min(first, last) : 0;
+          s.skip[h] = first - last;
+          s.c[h] = *reinterpret_cast<const i4v *>(a.col + off);
+          if (VAL) s.x[h] = *reinterpret_cast<const f4v *>(a.val + off);
+        }
+        const bool ends = e + kChunk >= len;
+        *what = at < n ? 2 * at + (ends ? 1 : 0) : -1;
+        at = at < n && ends ? at + G : at;
+        e = ends ? 0 : e + kChunk;
+      };
+      int what[kAhead];
+#pragma unroll
+      for (int p = 0; p < kAhead; ++p) request_chunk(t[p], &what[p]);
+      gather(t[0]);
+      float dp = 0.f;
+#pragma unroll 1
+      while (__ballot(what[0] >= 0) != 0ull) {
+#pragma unroll
+        for (int p = 0; p < kAhead; ++p) {
+          gather(t[(p + 1) % kAhead]);
+          dp = dot_half(t[p], 0, dp);
+          dp = dot_half(t[p], 1, dp);
+          const int done = what[p];
+          request_chunk(t[p], &what[p]);
+          const float sum = gsum<GL>(dp);
+          const int place = __shfl(src_s, max(done, 0) >> 1, kWave);
+          const bool ends = done >= 0 && (done & 1);
+          if (ends && sub == 0) s_row[wave][place] = sum;
+          dp = ends ? 0.f : dp;
         }
       }
-      dp = gsum<GL>(dp);
-      if (lane == 0) emit(base + li, dp, u);
     }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    if (mine || early) emit(j_l, s_row[wave][lane], a.do_keep ? keep_uniform(a.key, (uint32_t)j_l) : 2.f);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   }
 }
 

@@ -129,6 +129,48 @@ def test_csr_score_row_ends(ref, ones, P):
     assert_logit_prob(host(logit), host(prob), ref_logit, ref_prob, scale, bias=0.2)
 
 
+def _device_time(call, n=10):
+    """Shortest of five runs of n calls, in milliseconds."""
+    call()
+    best = float("inf")
+    for _ in range(5):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(n):
+            call()
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b))
+    return best
+
+
+@pytest.mark.parametrize("ones", [True, False])
+def test_csr_score_long_rows_in_a_large_pool(ref, ones):
+    """Rows of more than 128 entries (up to 700) in a pool that the kernel with phi in LDS takes: the bits of the
+    general kernel's scores of the halves, and about their time (four times that when such rows were walked
+    one by one)."""
+    P, d = 98_304, 2000
+    r = rng(47)
+    lens = r.integers(129, 400, size=P)
+    lens[::1000] = r.integers(400, 701, size=lens[::1000].size)
+    rowptr = np.zeros(P + 1, dtype=np.int64)
+    np.cumsum(lens, out=rowptr[1:])
+    col = r.integers(0, d, size=int(rowptr[-1])).astype(np.int32)
+    val = None if ones else (r.standard_normal(col.size) / 16.0).astype(np.float32)
+    F, phi, bias = csr_features(rowptr, col, val, d), dev(r.standard_normal(d).astype(np.float32)), scalar_dev(0.2)
+    out = [torch.zeros(P, device="cuda") for _ in range(4)]
+    ids = torch.arange(P, dtype=torch.int32, device="cuda")
+    half = P // 2
+
+    def halves():
+        for lo in (0, half):
+            api.assistant_score(F, ids[lo:], half, phi, bias, out[2][lo:], out[3][lo:])
+    whole = _device_time(lambda: api.assistant_score(F, ids, P, phi, bias, out[0], out[1]))
+    split = _device_time(halves)
+    assert np.array_equal(host(out[0]), host(out[2])) and np.array_equal(host(out[1]), host(out[3]))
+    assert whole < 1.5 * split, (whole, split)
+
+
 def test_csr_all_ones_values(ref, ws):
     """Token lists: val == NULL means every entry is 1; repeated tokens add."""
     rowptr, col, val, len_s, len_t, d = synth.sentence_pairs(n=5000, vocab=2000)
