@@ -374,7 +374,7 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
       const float lin = __shfl(lin_l, at_safe, kWave);
       const long long e0 = __shfl(e0_l, at_safe, kWave);
       const int len_any = __shfl(len_l, at_safe, kWave);
-      // what is left of a row of its own after the first two pieces is walked entry by entry
+      // what is left of a row of its own after the first two pieces
       const int len = live && !pair ? len_any : 0;
       const int slow = CSR ? quick_len(e0, len) : 0;
       float dp[2] = {0.f, 0.f}, dw[2] = {0.f, 0.f};
@@ -431,31 +431,61 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
           in[k] = k % 4 >= cur.skip[k / 4];
         }
         dot_entries(std::integral_constant<int, 4>{}, c, xv, far, in, 0);
+        dp[1] = pair ? 0.f : dp[0];  // (one row: its sums go on, in the order of the scoring kernels)
+        dw[1] = pair ? 0.f : dw[0];
         second = __ballot(cur.skip[1] < 4) != 0ull;
         if (second) dot_entries(std::integral_constant<int, 4>{}, c + 4, xv + 4, far + 4, in + 4, 1);
       }
       constexpr int kRest = CSR && TWO ? 4 : 8;  // (eight: more registers than there are)
-      for (int eb = slow + sub; eb < len; eb += kRest * GL) {
+      for (int eb = CSR ? slow + 4 * sub : sub; eb < len; eb += kRest * GL) {
         int c[kRest];
         float xv[kRest];
         bool in[kRest];
         float2 far[kRest];
+        if constexpr (CSR) {  // four neighbours a lane here too
+          i4v cq[kRest / 4] = {};
+          f4v xq[kRest / 4] = {};
+          if (e0 + len >= 4) {
 #pragma unroll
-        for (int k = 0; k < kRest; ++k) {
-          const int e = eb + k * GL;
-          in[k] = e < len;
-          c[k] = in[k] ? (CSR ? a.col[e0 + e] : e) : 0;
-          xv[k] = in[k] ? (CSR ? (a.val ? a.val[e0 + e] : 1.f) : a.x[e0 + e]) : 0.f;
+            for (int q = 0; q < kRest / 4; ++q) {
+              const int first = min(eb + q * kPiece, len - 4);
+              if (eb + q * kPiece < len) {
+                cq[q] = *reinterpret_cast<const i4v *>(a.col + e0 + first);
+                if (a.val) xq[q] = *reinterpret_cast<const f4v *>(a.val + e0 + first);
+              }
+            }
+          } else {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+              if (k < 4 - len) continue;
+              cq[0][k] = a.col[e0 + len - 4 + k];
+              if (a.val) xq[0][k] = a.val[e0 + len - 4 + k];
+            }
+          }
+#pragma unroll
+          for (int k = 0; k < kRest; ++k) {
+            in[k] = k % 4 >= eb + k / 4 * kPiece - (len - 4);
+            c[k] = cq[k / 4][k % 4];
+            xv[k] = a.val ? xq[k / 4][k % 4] : 1.f;
+          }
+        } else {
+#pragma unroll
+          for (int k = 0; k < kRest; ++k) {
+            const int e = eb + k * GL;
+            in[k] = e < len;
+            c[k] = in[k] ? e : 0;
+            xv[k] = in[k] ? a.x[e0 + e] : 0.f;
+          }
         }
         gather(std::integral_constant<int, kRest>{}, c, far);
-        dot_entries(std::integral_constant<int, kRest>{}, c, xv, far, in, 0);
+        dot_entries(std::integral_constant<int, kRest>{}, c, xv, far, in, CSR ? 1 : 0);
       }
       // the sums of this lane's slot
       auto own = [&](float v0, float v1) __attribute__((always_inline)) {
         if (!CSR) return gsum<GL>(v0);
         v0 = gsum<GL>(v0);
         v1 = gsum<GL>(v1);
-        return pair ? ((sub & 1) ? v1 : v0) : v0 + v1;
+        return pair && !(sub & 1) ? v0 : v1;
       };
       float g = 0.f;
       bool keep = live;

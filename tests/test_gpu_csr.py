@@ -287,6 +287,37 @@ def test_csr_fused_step(ref, ws, sparse):
                         "phi")
 
 
+@pytest.mark.parametrize("ones", [True, False])
+@pytest.mark.parametrize("d", [3000, 20_000, 300_000])
+def test_csr_fused_scores_have_the_bits_of_separate_ones(d, ones):
+    """The whole-step pass and the scoring kernels add a row's terms in the same order (20,000 columns: the kernel
+    with phi in LDS): same logits, probabilities and draws for rows on both sides of 64 and 128 entries,
+    long ones, and short ones at the matrix's start, before fewer and more rows than a wave's lane groups."""
+    n = 20_000
+    r = rng(53)
+    lens = np.where(r.random(n) < 0.5, r.integers(0, 70, size=n), r.integers(60, 300, size=n))
+    lens[:4] = 1, 1, 0, 1
+    rowptr = np.zeros(n + 1, dtype=np.int64)
+    np.cumsum(lens, out=rowptr[1:])
+    col = r.integers(0, d, size=int(rowptr[-1])).astype(np.int32)
+    val = None if ones else (r.standard_normal(col.size) / 8.0).astype(np.float32)
+    F = csr_features(rowptr, col, val, d)
+    y, idx = dev(np.where(r.random(n) < 0.5, -1.0, 1.0).astype(np.float32)), dev(r.permutation(n).astype(np.int32))
+    phi = dev((r.standard_normal(d) / (8.0 if ones else 1.0)).astype(np.float32))
+    cfg = api.step_config(0.1, 1e-3, 0.5, 0.3, 0.0, 7, 2, scalar_dev(0.1))
+    for P, ids in ((n, idx), (300, idx), (40, None)):
+        ws = api.Workspace(P, d)
+        got = [torch.zeros(P, device="cuda") for _ in range(5)]
+        keep = [torch.zeros(P, dtype=torch.uint8, device="cuda") for _ in range(2)]
+        pos, kept = (torch.zeros(P, dtype=torch.int32, device="cuda") for _ in range(2))
+        cnt = torch.zeros(1, dtype=torch.int32, device="cuda")
+        api.score_shrink(F, ids, P, phi, scalar_dev(-0.2), 0.1, 7, 2, got[0], got[1], keep[0], pos, cnt, ws)
+        api.fused_step(F, y, ids, P, torch.zeros(d, device="cuda"), phi.clone(), scalar_dev(-0.2), cfg, got[2], got[3],
+                       keep[1], pos, kept, got[4], cnt, ws)
+        assert np.array_equal(host(got[0]), host(got[2])) and np.array_equal(host(got[1]), host(got[3]))
+        assert np.array_equal(host(keep[0]), host(keep[1]))
+
+
 def _bits(t):
     return host(t).view(np.uint32).copy()
 
