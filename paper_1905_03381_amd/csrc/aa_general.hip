@@ -1290,26 +1290,46 @@ __device__ __forceinline__ int bin_column(int k, int bin, const ApplyArgs &a) {
 }
 
 // The records of a bin that did not fit into a block's LDS: a run in every sorted piece of every block.
-// Sixteen lanes read a run, four runs of a lane group in flight together, two records a lane of each.
+// Sixteen lanes read a run, four runs of a lane group in flight together, two records a lane of each.  What a run has
+// beyond four times the average (of 64 runs, and beyond kShortRun) the whole block reads, run after run: a frequent
+// column that found no slot in one block makes one run of thousands, which sixteen lanes walked alone (256 rows of
+// 60 entries in one bin, 65,280 rows of two anywhere: update 184 -> 63 us).
 template <int RW, class Add>
-__device__ __forceinline__ void late_records(const ApplyArgs &a, int bin, int n_mine, int *s_run, int pieces, Add add) {
-  constexpr int kGroups = kApplyThreads / 16, kRuns = 4;
+__device__ __forceinline__ void late_records(const ApplyArgs &a, int bin, int n_mine, int *s_run, int *s_limit,
+                                             unsigned long long *s_long, int pieces, Add add) {
+  constexpr int kGroups = kApplyThreads / 16, kRuns = 4, kShortRun = 128;
   const int tid = threadIdx.x, grp = tid / 16, sub = tid % 16, nblk = a.nblk_pass;
   const int32_t *const runs = a.runs + (size_t)bin * a.plan.pieces * nblk;
   const int32_t *const late = a.recs + (size_t)a.plan.nb * a.plan.bin_cap * RW;
   for (int piece = 0; piece < pieces; ++piece) {
     __syncthreads();
-    if (tid < kGeneralGradBlocks) s_run[tid] = piece * a.plan.piece < n_mine ? runs[(size_t)piece * nblk + tid] : 0;
+    if (tid < kGeneralGradBlocks) {
+      const int run = piece * a.plan.piece < n_mine ? runs[(size_t)piece * nblk + tid] : 0;
+      s_run[tid] = run;
+      int sum = run >> 16;
+#pragma unroll
+      for (int off = kWave / 2; off > 0; off >>= 1) sum += __shfl_xor(sum, off, kWave);
+      const int limit = max(kShortRun, sum / (kWave / 4));
+      const unsigned long long is_long = __ballot((run >> 16) > limit);
+      if ((tid & 63) == 0) {
+        s_limit[tid >> 6] = limit;
+        s_long[tid >> 6] = is_long;
+      }
+    }
     __syncthreads();
+    auto run_at = [&](int blk) {
+      return late + (((size_t)piece * nblk + min(blk, nblk - 1)) * a.plan.piece + (s_run[blk] & 0xffff)) * RW;
+    };
     for (int b0 = grp; b0 < nblk; b0 += kRuns * kGroups) {
       int cnt[kRuns], longest = 0;
       const int32_t *at[kRuns];
 #pragma unroll
       for (int i = 0; i < kRuns; ++i) {
-        const int blk = min(b0 + i * kGroups, kGeneralGradBlocks - 1), run = s_run[blk];
-        cnt[i] = b0 + i * kGroups < nblk ? run >> 16 : 0;
+        const int blk = min(b0 + i * kGroups, kGeneralGradBlocks - 1);
+        cnt[i] = min(s_run[blk] >> 16, s_limit[blk / kWave]);
+        if (b0 + i * kGroups >= nblk) cnt[i] = 0;
         longest = max(longest, cnt[i]);
-        at[i] = late + (((size_t)piece * nblk + min(blk, nblk - 1)) * a.plan.piece + (cnt[i] > 0 ? run & 0xffff : 0)) * RW;
+        at[i] = cnt[i] > 0 ? run_at(blk) : late;
       }
       // (Every load is unconditional: a load under a condition makes the compiler wait for all loads in flight
       // where the paths join.  An index past the end is clamped and the value then not used.)
@@ -1326,6 +1346,25 @@ __device__ __forceinline__ void late_records(const ApplyArgs &a, int bin, int n_
           if (j + 16 * (i & 1) < cnt[i / 2]) add(r[i]);
       }
     }
+    for (int w = 0; w < kGeneralGradBlocks / kWave; ++w) {
+      for (unsigned long long m = s_long[w]; m != 0ull; m &= m - 1) {
+        const int blk = w * kWave + __ffsll((long long)m) - 1, cnt = s_run[blk] >> 16;
+        const int32_t *const run = run_at(blk);
+        constexpr int kTurns = 4;
+        for (int j = s_limit[w] + tid; j - tid < cnt; j += kTurns * kApplyThreads) {
+          int r[kTurns][RW];
+#pragma unroll
+          for (int i = 0; i < kTurns; ++i) {
+            const int k = min(j + i * kApplyThreads, cnt - 1);
+#pragma unroll
+            for (int v = 0; v < RW; ++v) r[i][v] = run[k * RW + v];
+          }
+#pragma unroll
+          for (int i = 0; i < kTurns; ++i)
+            if (j + i * kApplyThreads < cnt) add(r[i]);
+        }
+      }
+    }
   }
 }
 
@@ -1333,7 +1372,8 @@ __device__ __forceinline__ void late_records(const ApplyArgs &a, int bin, int n_
 // per thread, in registers) is requested before anything is used: one round trip, not five.
 template <int RW>
 __device__ __forceinline__ void apply_bin(const ApplyArgs &a, int bin, double *s_bin, int *s_m,
-                                          float *s_g, int *s_run, int *s_late) {
+                                          float *s_g, int *s_run, int *s_late,
+                                          unsigned long long *s_long) {
   // per thread: kRec records per batch (the first batch is requested before the bin's fill count
   // is known: 1024 records a bin; with 4096, small pools read megabytes of stale ones); kCol runs
   // of four columns (a bin's columns come in groups of at least four neighbours) --
@@ -1407,7 +1447,7 @@ __device__ __forceinline__ void apply_bin(const ApplyArgs &a, int bin, double *s
     add_batch(r1, base + kBatch);
   }
   const int most = max(max(s_late[0], s_late[1]), max(s_late[2], s_late[3]));
-  if (most > 0) late_records<RW>(a, bin, n_mine, s_run, (most + a.plan.piece - 1) / a.plan.piece, add);
+  if (most > 0) late_records<RW>(a, bin, n_mine, s_run, s_late, s_long, (most + a.plan.piece - 1) / a.plan.piece, add);
   __syncthreads();
   auto sum_of = [&](int k) {  // over the copies, in order
     double v = 0.0;
@@ -1502,6 +1542,7 @@ __global__ __launch_bounds__(kApplyThreads) void k_apply_general(const ApplyArgs
   __shared__ float s_g[kApplyWaves];
   __shared__ double s_bin[kBinColsMax + 1];  // (+1: the odd stride of a single copy)
   __shared__ int s_run[kGeneralGradBlocks], s_late[kGeneralGradBlocks / kWave];
+  __shared__ unsigned long long s_long[kGeneralGradBlocks / kWave];
   // roles by block number: the other columns first (the bin owners have the longest way to
   // go), then the first columns, then the compaction tiles
   const int bid = (int)blockIdx.x, hb = bid - nrest;
@@ -1521,9 +1562,9 @@ __global__ __launch_bounds__(kApplyThreads) void k_apply_general(const ApplyArgs
   }
   if (bid < nrest && a.plan.nb > 0) {  // nrest == nb
     if (a.nvec == 2)
-      apply_bin<3>(a, bid, s_bin, s_m, s_g, s_run, s_late);
+      apply_bin<3>(a, bid, s_bin, s_m, s_g, s_run, s_late, s_long);
     else
-      apply_bin<2>(a, bid, s_bin, s_m, s_g, s_run, s_late);
+      apply_bin<2>(a, bid, s_bin, s_m, s_g, s_run, s_late, s_long);
     return;
   }
   const int t = threadIdx.x;

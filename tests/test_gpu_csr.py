@@ -747,6 +747,31 @@ def test_csr_updates_pieces_pairs_and_late_records(ref, n, d, kind, lo, hi, with
     _check_csr_updates(ref, rng(n + d), d, n, kind, lo, hi, with_val)
 
 
+def test_csr_records_of_one_block_in_one_bin():
+    """The rows of one block of the pass have all their columns in one column bin, far more than a block has hashed slots:
+    its records are one run of thousands.  The sums are right, and the update takes about as long as with the
+    same rows spread over all columns (twice to three times when sixteen lanes read such a run alone)."""
+    n, d, per, few = 65_536, 1_500_000, 60, 2
+    r = rng(67)
+    lens = np.where(np.arange(n) < 256, per, few)
+    rowptr = np.zeros(n + 1, dtype=np.int64)
+    np.cumsum(lens, out=rowptr[1:])
+    nnz, head = int(rowptr[-1]), 256 * per
+    spread = r.integers(8192, d, size=nnz)
+    one_bin = spread.copy()
+    one_bin[:head] = 8192 + 16 * 256 * r.integers(0, 360, size=head) + r.integers(0, 16, size=head)
+    ws, loss, T = api.Workspace(n, d), torch.full((n,), 0.7, device="cuda"), scalar_dev(0.5)
+    m, times = scalar_dev(n, torch.int32), {}
+    for name, col in (("spread", spread), ("one bin", one_bin)):
+        F = csr_features(rowptr, col.astype(np.int32), None, d)
+        phi, b = torch.zeros(d, device="cuda"), scalar_dev(0.0)
+        api.assistant_update(F, None, m, n, loss, T, phi, b, 1.0, 0.0, ws)
+        # g = 1/2, z = 1: every entry moves its column by 1 / (2 n), exactly
+        assert np.array_equal(host(phi), (np.bincount(col, minlength=d) / (2.0 * n)).astype(np.float32))
+        times[name] = _device_time(lambda: api.assistant_update(F, None, m, n, loss, T, phi, b, 0.0, 0.0, ws))
+    assert times["one bin"] < 1.5 * times["spread"], times
+
+
 def test_csr_hashed_sum_beyond_float_range():
     """A column past the table whose sum no float holds, and one whose sum is no number: the column's total
     is rounded once (to an infinity, a NaN), and nothing else is touched by it."""
