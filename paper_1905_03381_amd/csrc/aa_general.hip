@@ -119,7 +119,7 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
   constexpr int kTableBytes = kSumBytes + kModelBytes + kTagBytes + kHeldBytes;
   __shared__ __attribute__((aligned(16))) char s_mem[kTableBytes > kSortBytes ? kTableBytes : kSortBytes];
   __shared__ __attribute__((aligned(16))) int s_hist[kMaxBins], s_base[kMaxBins];
-  __shared__ int s_nrec;
+  __shared__ int s_nrec, s_more;
   __shared__ int s_cnt[kWaves];
   __shared__ float s_gb[kWaves];
   double *const s_sum = reinterpret_cast<double *>(s_mem);  // [vector][D + H]
@@ -179,7 +179,7 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
     __builtin_amdgcn_sched_barrier(0);
     for (int k = threadIdx.x; k < NVEC * (D + H); k += kGradThreads) s_sum[k] = 0.0;
     for (int k = threadIdx.x; k < H; k += kGradThreads) s_tag[k] = -1;
-    if (threadIdx.x == 0) s_nrec = 0;
+    if (threadIdx.x == 0) s_nrec = s_more = 0;
     __builtin_amdgcn_sched_barrier(0);
     first_rows = load_rows(0, id);
 #pragma unroll
@@ -663,8 +663,10 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
   }
   if (!binned) return;
   __syncthreads();
-  // The records in LDS go to the bins, a run per bin (one integer atomic per block and bin reserves the space).
+  // The records in LDS go to the bins, a run per bin (one integer atomic per block and bin reserves the space); one
+  // that finds its bin full joins the late ones.
   const int n = min(s_nrec, cap);
+  int beyond = max(n - held, 0);
   {
     const int m = min(n, held);
     constexpr int kPer = R / kGradThreads;
@@ -696,13 +698,22 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
 #pragma unroll
         for (int w = 0; w < RW; ++w) dst[w] = r[w];
       } else {
-        add_global<SVM, ASSIST>(a, r[0], __int_as_float(r[1]), TWO ? __int_as_float(r[RW - 1]) : 0.f);
+        const int i = beyond + atomicAdd(&s_more, 1);
+        if (i < cap - held) {
+          const int piece = (int)((unsigned)i / (unsigned)a.plan.piece);
+          int32_t *const dst = piece_at(piece) + (i - piece * a.plan.piece) * RW;
+#pragma unroll
+          for (int w = 0; w < RW; ++w) dst[w] = r[w];
+        } else {
+          add_global<SVM, ASSIST>(a, r[0], __int_as_float(r[1]), TWO ? __int_as_float(r[RW - 1]) : 0.f);
+        }
       }
     }
+    __syncthreads();
+    beyond = min(beyond + s_more, cap - held);
   }
   // The others, a piece (at most C) at a time, sorted by bin: a counting sort by way of LDS, back to where they
   // were.  The owner of a bin finds its records of a piece as one run (start, count).
-  const int beyond = max(n - held, 0);
   if (threadIdx.x == 0) a.blk_late[blockIdx.x] = beyond;
   int *const s_rec = reinterpret_cast<int *>(s_mem);
   constexpr int kPer = C / kGradThreads;

@@ -31,16 +31,19 @@ constexpr int kMaxBins = 256;
 constexpr int kBinGroupLog2 = 4, kBinFineGroupLog2 = 2;
 constexpr int64_t kBinFineColsMax = 1 << 18;  // groups of 4 up to this many binned columns
 constexpr int kBinColsMax = 8192;  // LDS floats of a bin's owner in the update kernel
-// Records the blocks of a pass have room for in all: 48 per candidate (the sparse configuration needs about 26),
-// at least 65,536, at most 2^27 (2 GiB); what does not fit goes to the accumulators.
+// Records of 16 bytes the workspace has room for: 48 per candidate, at least 65,536, at most 2^27 (2 GiB); of records
+// of a pass over two vectors that is 56 per candidate, over one 84 (the sparse configuration needs about 26); what
+// does not fit goes to the accumulators.
 inline size_t general_record_capacity(int32_t count_max) {
   const size_t want = 48 * (size_t)(count_max > 0 ? count_max : 0);
   return want < 65536 ? 65536 : (want > ((size_t)1 << 27) ? ((size_t)1 << 27) : want);
 }
-// The workspace has 16 bytes per record of that capacity: 12 for records (the bins one and a half times what the
-// blocks' LDS holds, but at most three quarters; late records the rest), the others for the runs (nb * pieces words per
-// block, each piece of several more than 4096 records).
-constexpr size_t kRecordBytes = 16, kRecordWordBytes = 12;
+// The workspace has 16 bytes per record of that capacity.  14 are for records: the bins take one and a quarter times what
+// the blocks' LDS holds, but at most seven eighths (late room is a block's own: with smaller bins the blocks that finish
+// last would find all of them full), late records, among them those that find their bin full, the rest.  Two are
+// for the runs (nb * pieces words per block: 64 bytes a candidate where a block has 16 rows, and beyond 256 blocks a
+// kilobyte for a piece, which is longer than 6000 records if there are several).
+constexpr size_t kRecordBytes = 16, kRecordWordBytes = 14;
 inline BinPlan general_bin_plan(int32_t d, int32_t head, int nvec, int32_t count_max, int32_t nblk) {
   BinPlan p{0, 0, 0, 0, 0, 0, kBinGroupLog2};
   const int gl = (int64_t)d - head <= kBinFineColsMax ? kBinFineGroupLog2 : kBinGroupLog2;
@@ -60,12 +63,11 @@ inline BinPlan general_bin_plan(int32_t d, int32_t head, int nvec, int32_t count
   p.cols = (int32_t)cols;
   const int64_t all = general_record_capacity(count_max) * kRecordWordBytes / (nvec == 2 ? 12 : 8);
   const int64_t in_lds = (int64_t)nblk * (nvec == 2 ? kRecordsTwoVec : kRecordsOneVec);
-  int64_t binned = in_lds + in_lds / 2 > 49152 ? in_lds + in_lds / 2 : 49152;
-  if (binned > all / 4 * 3) binned = all / 4 * 3;
+  int64_t binned = in_lds + in_lds / 4 > 49152 ? in_lds + in_lds / 4 : 49152;
+  if (binned > all / 8 * 7) binned = all / 8 * 7;
   p.bin_cap = (int32_t)(binned / nb) & ~3;
   const int32_t each = (int32_t)((all - binned) / nblk), most = nvec == 2 ? kSortTwoVec : kSortOneVec;
   p.pieces = (each + most - 1) / most;
-  if (each < 256) p.pieces = 0;  // (not worth a piece)
   p.piece = p.pieces > 0 ? (each / p.pieces) & ~3 : 0;
   return p;
 }

@@ -772,6 +772,35 @@ def test_csr_records_of_one_block_in_one_bin():
     assert times["one bin"] < 1.5 * times["spread"], times
 
 
+def _bins_with_accumulators(ws):
+    """Column bins of the last pass of which an entry found no room as a record (flags behind the 16 scalars and the
+    two tables of 256 counts that open the general kernels' part of the workspace)."""
+    first = ws.ptr - ws.buf.data_ptr() + 256 + 2 * 4 * 1024 + 256 + 4 * (16 + 512)
+    return int(np.count_nonzero(host(ws.buf)[first:first + 4 * 256].view(np.int32)))
+
+
+def test_csr_records_that_find_their_bin_full():
+    """48 records a candidate, evenly spread: there is room for all of them.  A record whose bin is full joins its block's late
+    ones: nothing is left to the atomics on the accumulators, and the sums are right."""
+    r = rng(71)
+    n, per, d = 16_384, 48, 60_000  # (1 / 2n is exact)
+    col = r.integers(8192, d, size=n * per)
+    rowptr = np.arange(0, n * per + 1, per, dtype=np.int64)
+    F, ws = csr_features(rowptr, col.astype(np.int32), None, d), api.Workspace(n, d)
+    m, y, loss = scalar_dev(n, torch.int32), dev(np.ones(n, np.float32)), torch.full((n,), 0.7, device="cuda")
+    want = (np.bincount(col, minlength=d) / (2.0 * n)).astype(np.float32)
+    phi, b = torch.zeros(d, device="cuda"), scalar_dev(0.0)
+    api.assistant_update(F, None, m, n, loss, scalar_dev(0.5), phi, b, 1.0, 0.0, ws)  # (g = 1/2, z = 1)
+    assert _bins_with_accumulators(ws) == 0 and np.array_equal(host(phi), want)
+    w = torch.zeros(d, device="cuda")
+    phi.zero_()
+    b.zero_()
+    cfg = api.step_config(0.0, 0.0, 0.5, 1.0, 0.0, 1, 0, scalar_dev(0.5))
+    api.boss_assistant_step(F, y, None, m, n, w, phi, b, cfg, loss, ws)               # (margin 0, loss 1)
+    assert _bins_with_accumulators(ws) == 0
+    assert np.array_equal(host(phi), want) and np.array_equal(host(w), want)
+
+
 def test_csr_hashed_sum_beyond_float_range():
     """A column past the table whose sum no float holds, and one whose sum is no number: the column's total
     is rounded once (to an infinity, a NaN), and nothing else is touched by it."""
