@@ -625,7 +625,7 @@ def test_csr_fused_step_more_columns_than_the_bins_cover(ref):
 
 def _check_csr_updates(ref, r, d, n, kind, lo, hi, with_val, misalign=False):
     """Boss step, Assistant update and both in one pass on random CSR rows of `lo` to `hi`
-    entries against the oracle (columns uniform, Zipf-like or hot at the end of the range).
+    entries against the oracle (columns uniform, Zipf-like, hot at the end of the range, or every 512 columns).
     misalign: the model vectors start 4 bytes past a 16-byte boundary."""
     def model(a):  # device copy of a model vector
         if not misalign:
@@ -643,6 +643,8 @@ def _check_csr_updates(ref, r, d, n, kind, lo, hi, with_val, misalign=False):
         col = r.integers(0, d, size=nnz)
     elif kind == "zipf":
         col = np.minimum(r.pareto(1.1, size=nnz).astype(np.int64), d - 1)
+    elif kind == "fields":  # fields of 512 columns, each with a default in half of its entries
+        col = 512 * r.integers(0, d // 512, size=nnz) + np.where(r.random(nnz) < 0.5, 0, r.integers(0, 512, size=nnz))
     else:  # a few very hot columns at the end of the range
         col = np.where(r.random(nnz) < 0.5, d - 1 - r.integers(0, min(3, d), size=nnz),
                        r.integers(0, d, size=nnz))
@@ -747,6 +749,38 @@ def test_csr_updates_pieces_pairs_and_late_records(ref, n, d, kind, lo, hi, with
     _check_csr_updates(ref, rng(n + d), d, n, kind, lo, hi, with_val)
 
 
+@pytest.mark.parametrize("d", [80 * 512, 20 * 512])
+def test_csr_updates_frequent_columns_512_apart(ref, d):
+    """Fields padded to 512 columns, each with a frequent default: columns 512, 1024, 2048 ... apart past the table
+    compete for the hashed slots."""
+    _check_csr_updates(ref, rng(512 + d), d, 6000, "fields", 40, 100, True)
+
+
+def test_csr_frequent_columns_512_apart_take_no_longer():
+    """A whole step over rows of 80 fields takes about as long with fields of 512 columns as with fields of 1000 (3.6 times
+    when frequent columns a power of two apart lost their hashed slots to each other in every block)."""
+    n, fields = 65_536, 80
+    r = rng(61)
+    field, other = np.arange(n * fields) % fields, r.random(n * fields)
+    default = r.random(n * fields) < 0.5
+    val = (r.standard_normal(n * fields) / 9.0).astype(np.float32)
+    y, idx = dev(np.where(r.random(n) < 0.5, -1.0, 1.0).astype(np.float32)), dev(r.permutation(n).astype(np.int32))
+    cfg = api.step_config(0.1, 0.0, 1e-7, 1e-7, 0.0, 3, 1, scalar_dev(0.5))
+    times = {}
+    for width in (512, 1000):
+        d = fields * width
+        col = (field * width + np.where(default, 0, (other * width).astype(np.int64))).astype(np.int32)
+        F = csr_features(np.arange(0, n * fields + 1, fields, dtype=np.int64), col, val, d)
+        w, phi, b = (dev((0.1 * r.standard_normal(k)).astype(np.float32)) for k in (d, d, 1))
+        ws = api.Workspace(n, d)
+        prob, loss = torch.zeros(n, device="cuda"), torch.zeros(n, device="cuda")
+        keep = torch.zeros(n, dtype=torch.uint8, device="cuda")
+        pos, ids, cnt = (torch.zeros(k, dtype=torch.int32, device="cuda") for k in (n, n, 1))
+        times[width] = _device_time(lambda: api.fused_step(F, y, idx, n, w, phi, b, cfg, None, prob, keep, pos, ids, loss,
+                                                           cnt, ws))
+    assert times[512] < 1.7 * times[1000], times
+
+
 def test_csr_records_of_one_block_in_one_bin():
     """The rows of one block of the pass have all their columns in one column bin, far more than a block has hashed slots:
     its records are one run of thousands.  The sums are right, and the update takes about as long as with the
@@ -779,12 +813,17 @@ def _bins_with_accumulators(ws):
     return int(np.count_nonzero(host(ws.buf)[first:first + 4 * 256].view(np.int32)))
 
 
-def test_csr_records_that_find_their_bin_full():
-    """48 records a candidate, evenly spread: there is room for all of them.  A record whose bin is full joins its block's late
+@pytest.mark.parametrize("kind", ["uniform", "fields"])
+def test_csr_records_that_find_their_bin_full(ref, kind):
+    """48 records a candidate, evenly spread: more than the bins have places, fewer than there is room for; and fields of
+    512 columns, whose frequent columns all lie in two bins.  A record whose bin is full joins its block's late
     ones: nothing is left to the atomics on the accumulators, and the sums are right."""
     r = rng(71)
-    n, per, d = 16_384, 48, 60_000  # (1 / 2n is exact)
-    col = r.integers(8192, d, size=n * per)
+    n, per, d = (16_384, 48, 60_000) if kind == "uniform" else (32_768, 40, 80 * 512)  # (1 / 2n is exact)
+    if kind == "uniform":
+        col = r.integers(8192, d, size=n * per)
+    else:
+        col = 512 * r.integers(16, 80, size=n * per) + np.where(r.random(n * per) < 0.5, 0, r.integers(0, 512, size=n * per))
     rowptr = np.arange(0, n * per + 1, per, dtype=np.int64)
     F, ws = csr_features(rowptr, col.astype(np.int32), None, d), api.Workspace(n, d)
     m, y, loss = scalar_dev(n, torch.int32), dev(np.ones(n, np.float32)), torch.full((n,), 0.7, device="cuda")
