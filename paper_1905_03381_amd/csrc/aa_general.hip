@@ -66,7 +66,8 @@ constexpr int kGradThreads = 1024, kPoolThreads = 256;
 constexpr int kClaimRows = 16;  // rows per wave from which a column of every row that lost its slot would show
 
 __device__ __forceinline__ int bin_of(int c, int head, const BinPlan &p) {
-  return ((c - head) >> p.group_log2) & (p.nb - 1);
+  const int g = (c - head) >> p.group_log2;
+  return (g + (g >> p.nb_log2) * kBinTurn) & (p.nb - 1);
 }
 
 // The set of two hashed slots a column may have.  A run of H neighbouring columns past the table fills the sets evenly;
@@ -1303,7 +1304,8 @@ __device__ __forceinline__ int bin_local(int col, const ApplyArgs &a) {
 
 __device__ __forceinline__ int bin_column(int k, int bin, const ApplyArgs &a) {
   const int gl = a.plan.group_log2;
-  return a.head + (((((k >> gl) << a.plan.nb_log2) | bin) << gl) | (k & ((1 << gl) - 1)));
+  const int turn = k >> gl, g = (turn << a.plan.nb_log2) | ((bin - turn * kBinTurn) & (a.plan.nb - 1));
+  return a.head + ((g << gl) | (k & ((1 << gl) - 1)));
 }
 
 // The records of a bin that did not fit into a block's LDS: a run in every sorted piece of every block.

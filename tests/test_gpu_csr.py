@@ -756,9 +756,10 @@ def test_csr_updates_frequent_columns_512_apart(ref, d):
     _check_csr_updates(ref, rng(512 + d), d, 6000, "fields", 40, 100, True)
 
 
-def test_csr_frequent_columns_512_apart_take_no_longer():
-    """A whole step over rows of 80 fields takes about as long with fields of 512 columns as with fields of 1000 (3.6 times
-    when frequent columns a power of two apart lost their hashed slots to each other in every block)."""
+def test_csr_frequent_columns_a_power_of_two_apart_take_no_longer():
+    """A whole step over rows of 80 fields takes about as long with fields of 512 or 1024 columns as with fields of 1000 (3.6
+    and 2.2 times when frequent columns a power of two apart lost their hashed slots to each other in every
+    block; 1.3 and 1.6 times when the records of their slots all met in two bins or one)."""
     n, fields = 65_536, 80
     r = rng(61)
     field, other = np.arange(n * fields) % fields, r.random(n * fields)
@@ -767,7 +768,7 @@ def test_csr_frequent_columns_512_apart_take_no_longer():
     y, idx = dev(np.where(r.random(n) < 0.5, -1.0, 1.0).astype(np.float32)), dev(r.permutation(n).astype(np.int32))
     cfg = api.step_config(0.1, 0.0, 1e-7, 1e-7, 0.0, 3, 1, scalar_dev(0.5))
     times = {}
-    for width in (512, 1000):
+    for width in (512, 1024, 1000):
         d = fields * width
         col = (field * width + np.where(default, 0, (other * width).astype(np.int64))).astype(np.int32)
         F = csr_features(np.arange(0, n * fields + 1, fields, dtype=np.int64), col, val, d)
@@ -778,7 +779,7 @@ def test_csr_frequent_columns_512_apart_take_no_longer():
         pos, ids, cnt = (torch.zeros(k, dtype=torch.int32, device="cuda") for k in (n, n, 1))
         times[width] = _device_time(lambda: api.fused_step(F, y, idx, n, w, phi, b, cfg, None, prob, keep, pos, ids, loss,
                                                            cnt, ws))
-    assert times[512] < 1.7 * times[1000], times
+    assert max(times[512], times[1024]) < 1.3 * times[1000], times
 
 
 def test_csr_records_of_one_block_in_one_bin():
@@ -815,8 +816,8 @@ def _bins_with_accumulators(ws):
 
 @pytest.mark.parametrize("kind", ["uniform", "fields"])
 def test_csr_records_that_find_their_bin_full(ref, kind):
-    """48 records a candidate, evenly spread: more than the bins have places, fewer than there is room for; and fields of
-    512 columns, whose frequent columns all lie in two bins.  A record whose bin is full joins its block's late
+    """48 records a candidate, evenly spread: there is room for all of them; and fields of 512 columns, each with a frequent
+    one.  A record whose bin is full joins its block's late
     ones: nothing is left to the atomics on the accumulators, and the sums are right."""
     r = rng(71)
     n, per, d = (16_384, 48, 60_000) if kind == "uniform" else (32_768, 40, 80 * 512)  # (1 / 2n is exact)
