@@ -387,10 +387,10 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
       float dp[2] = {0.f, 0.f}, dw[2] = {0.f, 0.f};
       // Shares of the dot products.  The columns that are not in LDS are gathered without a
       // branch (an entry with nothing to fetch asks for column 0), so that the gathers leave together.
-      auto gather = [&](auto n_const, const int *c, float2 *far) __attribute__((always_inline)) {
+      auto gather = [&](auto n_const, const int *c, float2 *far, bool all_near) __attribute__((always_inline)) {
 #pragma unroll
         for (int k = 0; k < decltype(n_const)::value; ++k) far[k] = make_float2(0.f, 0.f);
-        if (a.d <= D) return;  // (no such columns: a round trip less)
+        if (all_near) return;  // (no such columns: a round trip less)
 #pragma unroll
         for (int k = 0; k < decltype(n_const)::value; ++k) {
           const int cf = c[k] >= D ? c[k] : 0;
@@ -428,7 +428,7 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
         float2 far[8];
 #pragma unroll
         for (int k = 0; k < 8; ++k) c[k] = cur.c[k / 4][k % 4];
-        gather(std::integral_constant<int, 8>{}, c, far);
+        gather(std::integral_constant<int, 8>{}, c, far, a.d <= D);
         __builtin_amdgcn_sched_barrier(0);
         request(it + 1, ahead);  // (past the last unit: no accesses)
         __builtin_amdgcn_sched_barrier(0);
@@ -444,7 +444,7 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
         if (second) dot_entries(std::integral_constant<int, 4>{}, c + 4, xv + 4, far + 4, in + 4, 1);
       }
       constexpr int kRest = CSR && TWO ? 4 : 8;  // (eight: more registers than there are)
-      for (int eb = CSR ? slow + 4 * sub : sub; eb < len; eb += kRest * GL) {
+      auto walk = [&](int eb, bool all_near) __attribute__((always_inline)) {
         int c[kRest];
         float xv[kRest];
         bool in[kRest];
@@ -484,8 +484,16 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
             xv[k] = in[k] ? a.x[e0 + e] : 0.f;
           }
         }
-        gather(std::integral_constant<int, kRest>{}, c, far);
+        gather(std::integral_constant<int, kRest>{}, c, far, all_near);
         dot_entries(std::integral_constant<int, kRest>{}, c, xv, far, in, CSR ? 1 : 0);
+      };
+      if constexpr (CSR) {
+        for (int eb = slow + 4 * sub; eb < len; eb += kRest * GL) walk(eb, a.d <= D);
+      } else {  // (first the columns that are in LDS)
+        static_assert(CSR || D % (kRest * GL) == 0, "no turn on both sides");
+        int eb = sub;
+        for (; eb < min(len, D); eb += kRest * GL) walk(eb, true);
+        for (; eb < len; eb += kRest * GL) walk(eb, false);
       }
       // the sums of this lane's slot
       auto own = [&](float v0, float v1) __attribute__((always_inline)) {
@@ -532,8 +540,27 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
       // Second walk.  A column's sum is its slot's, or that of the hashed slot that holds it; an entry that
       // finds neither leaves as a record.  N entries of a lane together (column -1: none): their tag reads
       // are in flight at once.
-      auto scatter = [&](auto n_const, const int *c, const float *xv, int slot) __attribute__((always_inline)) {
+      auto scatter = [&](auto n_const, const int *c, const float *xv, int slot, bool all_near) __attribute__((always_inline)) {
         constexpr int N = decltype(n_const)::value;
+        auto terms = [&](int k, float *ta, float *tb) __attribute__((always_inline)) {
+          const int q = slot + k / 4;
+          *ta = SVM ? (cw[q] != 0.f ? cw[q] * xv[k] : 0.f) : resid[q] * xv[k];
+          *tb = TWO ? (resid[q] != 0.f ? resid[q] * xv[k] : 0.f) : 0.f;
+        };
+        auto add_at = [&](int k, int at, float ta, float tb) __attribute__((always_inline)) {
+          const int q = slot + k / 4;
+          if (!TWO || cw[q] != 0.f) unsafeAtomicAdd(s_sum + at, (double)ta);
+          if (TWO && resid[q] != 0.f) unsafeAtomicAdd(s_sum + (D + H) + at, (double)tb);
+        };
+        if (all_near) {  // (every column has its slot)
+#pragma unroll
+          for (int k = 0; k < N; ++k) {
+            float ta, tb;
+            terms(k, &ta, &tb);
+            if (c[k] >= 0) add_at(k, c[k], ta, tb);
+          }
+          return;
+        }
         int2 tag[N];
         int at_sum[N];
 #pragma unroll
@@ -567,15 +594,11 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
         float ta[N], tb[N];
 #pragma unroll
         for (int k = 0; k < N; ++k) {
-          const int q = slot + k / 4, hashed = tag[k].x == c[k] ? D + at_sum[k] : tag[k].y == c[k] ? D + at_sum[k] + 1 : -1;
+          const int hashed = tag[k].x == c[k] ? D + at_sum[k] : tag[k].y == c[k] ? D + at_sum[k] + 1 : -1;
           const int at = c[k] < D ? c[k] : hashed;
           miss[k] = c[k] >= D && at < 0;
-          ta[k] = SVM ? (cw[q] != 0.f ? cw[q] * xv[k] : 0.f) : resid[q] * xv[k];
-          tb[k] = TWO ? (resid[q] != 0.f ? resid[q] * xv[k] : 0.f) : 0.f;
-          if (at >= 0) {
-            if (!TWO || cw[q] != 0.f) unsafeAtomicAdd(s_sum + at, (double)ta[k]);
-            if (TWO && resid[q] != 0.f) unsafeAtomicAdd(s_sum + (D + H) + at, (double)tb[k]);
-          }
+          terms(k, &ta[k], &tb[k]);
+          if (at >= 0) add_at(k, at, ta[k], tb[k]);
         }
         append(n_const, miss, c, ta, tb);
       };
@@ -588,10 +611,10 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
           xv[k] = a.val ? cur.x[k / 4][k % 4] : 1.f;
         }
         if (!TWO && second) {
-          scatter(std::integral_constant<int, 8>{}, c, xv, 0);
+          scatter(std::integral_constant<int, 8>{}, c, xv, 0, a.d <= D);
         } else {  // (two vectors: eight at once are more registers than there are)
-          scatter(std::integral_constant<int, 4>{}, c, xv, 0);
-          if (TWO && second) scatter(std::integral_constant<int, 4>{}, c + 4, xv + 4, 1);
+          scatter(std::integral_constant<int, 4>{}, c, xv, 0, a.d <= D);
+          if (TWO && second) scatter(std::integral_constant<int, 4>{}, c + 4, xv + 4, 1, a.d <= D);
         }
       }
       // entries beyond; the wave's groups step together
@@ -599,7 +622,7 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
 #pragma unroll
       for (int off = GL; off < kWave; off <<= 1) steps_len = max(steps_len, __shfl_xor(steps_len, off, kWave));
       steps_len = __builtin_amdgcn_readfirstlane(steps_len);  // (what follows is the wave's then: scalar counts)
-      for (int eb = 0; eb < steps_len; eb += GL) {
+      auto walk_again = [&](int eb, bool all_near) __attribute__((always_inline)) {
         const int e = slow + eb + sub;
         int c = -1;
         float xv = 0.f;
@@ -607,7 +630,14 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
           c = CSR ? a.col[e0 + e] : e;
           xv = CSR ? (a.val ? a.val[e0 + e] : 1.f) : a.x[e0 + e];
         }
-        scatter(std::integral_constant<int, 1>{}, &c, &xv, 0);
+        scatter(std::integral_constant<int, 1>{}, &c, &xv, 0, all_near);
+      };
+      if constexpr (CSR) {
+        for (int eb = 0; eb < steps_len; eb += GL) walk_again(eb, a.d <= D);
+      } else {
+        int eb = 0;
+        for (; eb < min(steps_len, D); eb += GL) walk_again(eb, true);
+        for (; eb < steps_len; eb += GL) walk_again(eb, false);
       }
     }
   }
