@@ -59,11 +59,11 @@ def test_csr_score_and_fused_keep(ref, ws, sparse):
 @pytest.mark.parametrize("ones", [False, True])
 @pytest.mark.parametrize("indexed", [True, False])
 def test_csr_score_large_pool_equals_small_pools(ref, ws, ones, indexed):
-    """Pools of 16,384 rows and more over 16,385 to 79,872 columns are scored by the kernel that
-    keeps the head of phi in LDS, smaller ones by the general kernel: both add a row's terms in
+    """Pools of 16,384 rows and more over 16,385 to 79,872 columns (and of 98,304 and more over fewer) are scored by the
+    kernel that keeps the head of phi in LDS, smaller ones by the general kernel: both add a row's terms in
     the same order, so one pool of 25,001 rows and the same rows in pools of 9000 give the same
     bits -- and the oracle's values.  Rows of 0 to 260 entries: half of them exceed the 128
-    entries of the first kernel's main loop and take its separate walk; a fifth of the
+    entries of the first kernel's main loop and take its walk over long rows; a fifth of the
     columns lie past its table."""
     n, d, P = 30_000, 50_000, 25_001
     r = rng(41)
@@ -506,9 +506,9 @@ def _col_abs_sum_sp(Fh, ids, d):
 @pytest.mark.parametrize("n,nnz_lo,nnz_hi", [(300_000, 8, 16), (3000, 500, 700)])
 def test_csr_updates_uniform_columns(ref, n, nnz_lo, nnz_hi):
     """Columns uniform over d = 2^18: nearly every entry falls outside the per-block table.
-    300,000 short rows: every block makes two rounds and empties its entry buffer many times.
-    3000 rows of about 600 entries: the entries of four rows per wave overflow the buffer, and
-    the bins (48 records per candidate) overflow too, so the excess goes to the accumulators."""
+    300,000 short rows: every block makes two rounds, and most of its records are late ones.
+    3000 rows of about 600 entries: the records of four rows per wave are more than a block's LDS,
+    the bins and its late room hold (84 per candidate), so the excess goes to the accumulators."""
     r = rng(21)
     d, m = 1 << 18, n
     rowptr, col, val = _uniform_csr(r, n, d, nnz_lo, nnz_hi)
@@ -550,7 +550,7 @@ def test_csr_updates_uniform_columns(ref, n, nnz_lo, nnz_hi):
 
 def test_train_epoch_with_overflowing_bins(ref):
     """aa_train_epoch over rows of about 600 entries with columns uniform over d = 2^18: in every
-    step the record buffer and the bins overflow into the accumulators.  One step per call
+    step the records overflow LDS, the bins and the late room into the accumulators.  One step per call
     (each call prepares the workspace itself) is held to the oracle step at the single-step
     tolerances; then the epoch in one call, where from the second step on no launch prepares
     the workspace -- the update kernel of the step before has cleared what it read and has
@@ -623,10 +623,28 @@ def test_csr_fused_step_more_columns_than_the_bins_cover(ref):
                         "phi")
 
 
-def _check_csr_updates(ref, r, d, n, kind, lo, hi, with_val, misalign=False):
+def _workspace_counts(ws, table):
+    """Table 0 (records offered to a bin), 1 (late records of a block) or 2 (bins whose accumulators were used) of the last
+    pass: 256 integers each behind the 16 scalars that open the general kernels' part of the workspace."""
+    first = ws.ptr - ws.buf.data_ptr() + 256 + 2 * 4 * 1024 + 256 + 4 * (16 + 256 * table)
+    return host(ws.buf[first:first + 4 * 256]).view(np.int32)
+
+
+def _late_records(ws):
+    return _workspace_counts(ws, 1)
+
+
+def _bins_with_accumulators(ws):
+    """Bins of the last pass of which an entry found no room as a record."""
+    return int(np.count_nonzero(_workspace_counts(ws, 2)))
+
+
+def _check_csr_updates(ref, r, d, n, kind, lo, hi, with_val, misalign=False, all_rows=False, late=(0, 0)):
     """Boss step, Assistant update and both in one pass on random CSR rows of `lo` to `hi`
     entries against the oracle (columns uniform, Zipf-like, hot at the end of the range, or every 512 columns).
-    misalign: the model vectors start 4 bytes past a 16-byte boundary."""
+    misalign: the model vectors start 4 bytes past a 16-byte boundary.  all_rows: every row is chosen (a random
+    number of them otherwise).  late: a block of the pass over one vector (all rows contribute) / over two has
+    more late records than this."""
     def model(a):  # device copy of a model vector
         if not misalign:
             return dev(a)
@@ -654,6 +672,7 @@ def _check_csr_updates(ref, r, d, n, kind, lo, hi, with_val, misalign=False):
     w0 = (0.3 * r.standard_normal(d)).astype(np.float32)
     phi0 = (0.3 * r.standard_normal(d)).astype(np.float32)
     m = int(r.integers(1, n + 1))
+    m = n if all_rows else m
     rows = r.permutation(n)[:m].astype(np.int32)
     tag = f"d={d} n={n} m={m} nnz={nnz} {kind}"
     Fh = ref.Features.csr(rowptr, col, val, d)
@@ -679,6 +698,7 @@ def _check_csr_updates(ref, r, d, n, kind, lo, hi, with_val, misalign=False):
     phi, b = model(phi0), scalar_dev(b0)
     api.assistant_update(F, dev(rows), scalar_dev(m, torch.int32), m, dev(loss_ref),
                          scalar_dev(T), phi, b, lr_a, 0.0, ws)
+    assert not late[0] or _late_records(ws).max() > late[0], tag
     absx = np.asarray(Sa[rows].sum(axis=0)).ravel()
     assert_close_scaled(host(phi), phi_ref, np.abs(phi0.astype(np.float64)) + lr_a / m * absx,
                         "phi " + tag)
@@ -690,6 +710,7 @@ def _check_csr_updates(ref, r, d, n, kind, lo, hi, with_val, misalign=False):
     cfg = api.step_config(0.0, lam, lr, lr_a, 0.0, 1, 0, Tt)
     api.boss_assistant_step(F, dev(y), dev(rows), scalar_dev(m, torch.int32), m, w, phi, b, cfg,
                             loss, ws)
+    assert not late[1] or _late_records(ws).max() > late[1], tag
     assert_close_scaled(host(w), w_ref, np.abs(w0.astype(np.float64)) + lr / m * absx_w,
                         "w (one pass) " + tag, atol=lr / m * akink)
     on_T = np.abs(loss_ref.astype(np.float64) - T) <= RTOL * Sdot
@@ -736,17 +757,18 @@ def test_csr_updates_at_the_edges_of_the_column_bins(ref, d):
     _check_csr_updates(ref, r, d, 300, "uniform", 1, 12, False)
 
 
-@pytest.mark.parametrize("n,d,kind,lo,hi,with_val", [
-    (40_000, 60_000, "uniform", 40, 90, True),     # two rows a unit and rows of their own; late records in one piece
-    (20_000, 300_000, "uniform", 100, 200, True),  # late records in several pieces; rows past two pieces
-    (30_000, 9000, "hot_tail", 0, 5, False),       # empty rows, rows that end before the matrix's fourth entry
-    (30_000, 4000, "zipf", 63, 65, True),          # both sides of one piece; no column outside the table
-    (24_000, 70_000, "hot_tail", 127, 129, False), # both sides of two pieces
-    (70, 200_000, "uniform", 900, 1100, True)])    # two blocks whose records need every piece there is
-def test_csr_updates_pieces_pairs_and_late_records(ref, n, d, kind, lo, hi, with_val):
-    """Row lengths around the pieces of 64 entries, enough rows per wave for two rows a unit, and
-    records beyond what a block's LDS holds (all rows chosen, or nearly)."""
-    _check_csr_updates(ref, rng(n + d), d, n, kind, lo, hi, with_val)
+@pytest.mark.parametrize("n,d,kind,lo,hi,with_val,late", [
+    (40_000, 60_000, "uniform", 40, 90, True, (4000, 2000)),      # two rows a unit and rows of their own
+    (40_000, 9000, "hot_tail", 0, 5, False, (0, 0)),              # empty rows, and some before the matrix's fourth entry
+    (40_000, 4000, "zipf", 63, 65, True, (0, 0)),                 # both sides of one piece of 64 entries
+    (30_000, 70_000, "hot_tail", 127, 129, False, (0, 0)),        # both sides of two
+    (20_000, 300_000, "uniform", 100, 200, True, (1000, 400)),    # rows past two pieces, no late room left
+    (64, 200_000, "uniform", 380, 420, True, (16_384, 12_288)),   # one block, several sorted pieces
+    (110_000, 300_000, "uniform", 42, 46, True, (0, 12_288))])    # 256 blocks, two sorted pieces
+def test_csr_updates_pieces_pairs_and_late_records(ref, n, d, kind, lo, hi, with_val, late):
+    """All rows chosen.  30,000 rows are at least seven a wave, more than it has lane groups: short rows go two to a unit.
+    Records beyond a block's LDS are late ones, sorted by bin in pieces of at most 16,384 (one vector) and 12,288 (two)."""
+    _check_csr_updates(ref, rng(n + d), d, n, kind, lo, hi, with_val, all_rows=True, late=late)
 
 
 @pytest.mark.parametrize("d", [80 * 512, 20 * 512])
@@ -807,13 +829,6 @@ def test_csr_records_of_one_block_in_one_bin():
     assert times["one bin"] < 1.5 * times["spread"], times
 
 
-def _bins_with_accumulators(ws):
-    """Column bins of the last pass of which an entry found no room as a record (flags behind the 16 scalars and the
-    two tables of 256 counts that open the general kernels' part of the workspace)."""
-    first = ws.ptr - ws.buf.data_ptr() + 256 + 2 * 4 * 1024 + 256 + 4 * (16 + 512)
-    return int(np.count_nonzero(host(ws.buf)[first:first + 4 * 256].view(np.int32)))
-
-
 @pytest.mark.parametrize("kind", ["uniform", "fields"])
 def test_csr_records_that_find_their_bin_full(ref, kind):
     """48 records a candidate, evenly spread: there is room for all of them; and fields of 512 columns, each with a frequent
@@ -839,6 +854,57 @@ def test_csr_records_that_find_their_bin_full(ref, kind):
     api.boss_assistant_step(F, y, None, m, n, w, phi, b, cfg, loss, ws)               # (margin 0, loss 1)
     assert _bins_with_accumulators(ws) == 0
     assert np.array_equal(host(phi), want) and np.array_equal(host(w), want)
+
+
+@pytest.mark.parametrize("ones", [True, False])
+def test_csr_rows_past_two_to_the_29_entries(ref, ones):
+    """Rows on both sides of entry 2^29, where 32-bit byte offsets end, behind a row of half a thousand million entries that is
+    not chosen: scores (general kernel; 20,000 pool places over these columns: the one with phi in LDS) and updates have
+    the bits of the same rows in a matrix of their own, and the oracle's values."""
+    r = rng(73)
+    n, d = 400, 20_000
+    lens = np.where(r.random(n) < 0.5, r.integers(0, 70, size=n), r.integers(60, 300, size=n))
+    own = np.zeros(n + 1, dtype=np.int64)
+    np.cumsum(lens, out=own[1:])
+    nnz, skipped = int(own[-1]), (1 << 29) - int(own[n // 2]) - 3
+    col = r.integers(0, d, size=nnz).astype(np.int32)
+    val = None if ones else (r.standard_normal(nnz) / 8.0).astype(np.float32)
+    far_col = torch.zeros(skipped + nnz, dtype=torch.int32, device="cuda")
+    far_col[skipped:] = dev(col)
+    far_val = None
+    if not ones:
+        far_val = torch.zeros(skipped + nnz, dtype=torch.float32, device="cuda")
+        far_val[skipped:] = dev(val)
+    near = csr_features(own, col, val, d)
+    far = api.Features.csr(dev(np.r_[0, own + skipped]), far_col, far_val, d)  # (row k + 1 is the other's row k)
+    phi0 = (r.standard_normal(d) / 8.0).astype(np.float32)
+    w0 = (r.standard_normal(d) / 8.0).astype(np.float32)
+    y = np.where(r.random(n) < 0.5, -1.0, 1.0).astype(np.float32)
+    Fh = ref.Features.csr(own, col, val, d)
+    ws, got = api.Workspace(n, d), {}
+    for name, F, shift in (("near", near, 0), ("far", far, 1)):
+        out = []
+        for P in (n, 20_000):
+            ids = dev((np.arange(P) % n + shift).astype(np.int32))
+            out += [torch.zeros(P, device="cuda"), torch.zeros(P, device="cuda")]
+            api.assistant_score(F, ids, P, dev(phi0), scalar_dev(0.1), out[-2], out[-1])
+        ids, m = dev((np.arange(n) + shift).astype(np.int32)), scalar_dev(n, torch.int32)
+        yd = dev(np.r_[np.zeros(shift, np.float32), y])
+        w, phi, b, loss = dev(w0), dev(phi0), scalar_dev(0.1), torch.zeros(n, device="cuda")
+        cfg = api.step_config(0.0, 1e-3, 0.7, 0.5, 0.0, 1, 0, scalar_dev(0.4))
+        api.boss_assistant_step(F, yd, ids, m, n, w, phi, b, cfg, loss, ws)
+        w1 = dev(w0)
+        api.svm_sgd_step(F, yd, ids, m, n, w1, 1e-3, 0.7, 0.0, loss, ws)
+        got[name] = [host(t).copy() for t in out + [w, phi, b, loss, w1]]
+    for x, z in zip(got["near"], got["far"]):
+        assert np.array_equal(x, z)
+    ref_logit, ref_prob = ref.assistant_score(Fh, None, n, phi0, bias=0.1)
+    assert_logit_prob(got["far"][0], got["far"][1], ref_logit, ref_prob, abs_dot_scale(Fh, np.arange(n), phi0), bias=0.1)
+    assert np.array_equal(got["far"][2], np.resize(got["far"][0], 20_000))
+    w_ref, loss_ref = ref.svm_sgd_step(Fh, y, np.arange(n, dtype=np.int32), n, w0, 1e-3, 0.7)
+    assert_close_scaled(got["far"][7], loss_ref, abs_dot_scale(Fh, np.arange(n), w0), "loss", atol=1e-6)
+    scale = np.abs(w0.astype(np.float64)) + 0.7 / n * _col_abs_sum(Fh, np.arange(n), d)
+    assert_close_scaled(got["far"][8], w_ref, scale, "w")
 
 
 def test_csr_hashed_sum_beyond_float_range():
