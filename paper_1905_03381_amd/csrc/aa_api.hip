@@ -322,7 +322,7 @@ hipError_t run_pass(const PassSpec &s, const Ws &ws, int32_t *nblk_out, hipStrea
   a.blk_late = reinterpret_cast<int32_t *>(acc + 16 + kMaxBins);
   a.recs = reinterpret_cast<int32_t *>(ws.grad + general_bins_offset(s.F->d));
   a.runs = reinterpret_cast<int32_t *>(ws.grad + general_runs_offset(s.F->d, s.count_max));
-    a.t_upd = s.t_upd;
+  a.t_upd = s.t_upd;
   a.t_snap = ws.ctl + kCtlUpdateSnapshot;
   const int32_t nblk = general_pass_blocks(s.count_max, csr, s.mode);
   *nblk_out = nblk;

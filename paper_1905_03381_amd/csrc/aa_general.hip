@@ -16,9 +16,10 @@
 //    that are sorted by column bin: the block that owns a bin in the second kernel sums its
 //    records in LDS.  A block's first records stay in LDS until it is done and go to the
 //    bins' arrays (one integer atomic per block and bin reserves the space); the others
-//    are written out as they come and sorted in pieces at the end;
-//  * only what does not fit (records beyond a block's room or a bin's capacity, or
-//    more columns than the bins can cover) is added to dense accumulators in HBM.
+//    are written out as they come, those that find their bin full join them, and they are
+//    sorted in pieces at the end;
+//  * only what does not fit (records beyond a block's room, or more columns than the
+//    bins can cover) is added to dense accumulators in HBM.
 #include <type_traits>
 
 #include "aa_compact.hpp"
@@ -73,7 +74,7 @@ __device__ __forceinline__ int bin_of(int c, int head, const BinPlan &p) {
 // The set of two hashed slots a column may have.  A run of H neighbouring columns past the table fills the sets evenly;
 // columns a power of two apart go to different sets, and which of them meet depends on the block.  (With
 // c ^ c >> 11 the frequent columns of fields padded to 512 columns met in every block, four to a set: whole step over
-// 65,536 rows of 80 such fields 245 us, now 94; fields of 1000 columns 68 and 71.)
+// 65,536 rows of 80 such fields 245 us, now 72; fields of 1000 columns 68 and 70.)
 template <int H>
 __device__ __forceinline__ int hashed_set(int c, int factor) {
   constexpr int kLog2 = H == 2048 ? 10 : 9;
@@ -214,12 +215,12 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
   auto append = [&](auto n_const, const bool *want, const int *c, const float *ta, const float *tb)
                     __attribute__((always_inline)) {
     constexpr int N = decltype(n_const)::value;
-    int total = 0;
+    int count = 0;
 #pragma unroll
-    for (int k = 0; k < N; ++k) total += __popcll(__ballot(want[k]));
-    if (total == 0) return;
+    for (int k = 0; k < N; ++k) count += __popcll(__ballot(want[k]));
+    if (count == 0) return;
     int first = 0;
-    if (lane == 0) first = atomicAdd(&s_nrec, total);
+    if (lane == 0) first = atomicAdd(&s_nrec, count);
     first = __builtin_amdgcn_readfirstlane(first);
     int pos[N];
 #pragma unroll
@@ -239,7 +240,7 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
         }
       }
     }
-    if (first + total > held && first < cap && cap > held) {
+    if (first + count > held && first < cap && cap > held) {
       // (a lane's records lie in one piece or in it and the next: with several, one is longer than 64 N)
       static_assert(kSortTwoVec / 2 > 8 * kWave && kSortOneVec / 2 > 8 * kWave, "at most one boundary");
       const int from = max(first - held, 0);
@@ -256,7 +257,7 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
         }
       }
     }
-    if (first + total > cap) {
+    if (first + count > cap) {
       // (one copy of what adds to the accumulators: copies behind every entry cost hundreds of scalar registers
       // parked in vector ones)
 #pragma unroll 1
@@ -940,9 +941,11 @@ constexpr int kScoreTableThreads = 1024;
 // for kScoreTableManyRows rows over fewer, when the table holds at least half of phi.  Whole batch
 // generator calls, k_rows_general / this: 1,000,000 rows over 16,002 columns 242 / 173 us, over 10,002
 // 347 / 276, over 4002 304 / 272; 200,000 over 4002 78.3 / 73.5; 100,000 over 4002 to 16,002 57 / 56.5, 54 /
-// 53, 58 / 59; 60,000 over 4002 49.8 / 52.0; 20,000 over 15,002 43.8 / 50.8.  On 65,536 rows of about
-// 100 entries over 2^20 Zipf-distributed columns, where a quarter of the entries lie past the
-// table, k_rows_general stays ahead (34 us against 48).
+// 53, 58 / 59; 60,000 over 4002 49.8 / 52.0; 20,000 over 15,002 43.8 / 50.8.  Scoring calls alone, 100,000 rows
+// of 40 to 72 entries: over 64 columns 14.0 / 12.6, 512 14.3 / 12.6, 2000 14.4 / 12.6, 8002 15.2 / 14.2, 16,002 16.1 /
+// 16.2; 1,000,000: over 64 122 / 97, 2000 129 / 96, 16,002 195 / 102; of 4 to 20 entries over 64 to 2000 54.5 / 40.7.
+// On 65,536 rows of about 100 entries over 2^20 Zipf-distributed columns, where a quarter of the entries lie
+// past the table, k_rows_general stays ahead (34 us against 48).
 constexpr int kScoreTableMinCols = 16384, kScoreTableMinRows = 16384, kScoreTableManyRows = 98304;
 constexpr int kScoreTableMaxCols = 2 * kScoreTableCols;
 
@@ -1007,16 +1010,13 @@ __global__ __launch_bounds__(kScoreTableThreads) void k_score_table(const GenArg
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
       const int c = t.c[u / 4][u % 4];
-      
       t.far[u] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(r_phi, c >= D ? c * 4 : kNone, 0, 0));
-
     }
   };
   auto dot_half = [&](const Slot &t, int h, float dp) __attribute__((always_inline)) {
     float near[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) near[k] = s_phi[min(t.c[h][k], D - 1)];
-
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const float m = t.c[h][k] >= D ? t.far[4 * h + k] : near[k];

@@ -9,7 +9,7 @@ namespace aa {
 // What leaves a block of a gradient pass for a column without a slot in its LDS table: records of two
 // words (column, term) when one vector is updated, of three (column, term for w, term for phi) when both
 // are.  The first kRecords* of a block stay in its LDS and go to the bins at the end.  Those that find no room
-// there ("late" ones) are written out as they come and in the end sorted by bin, in pieces of at most
+// there, or their bin full ("late" ones), are written out as they come and in the end sorted by bin, in pieces of at most
 // kSort* (what LDS holds); the first pieces of all blocks lie side by side, then the second ones.
 constexpr int kRecordsTwoVec = 5120, kRecordsTwoVecDense = 2048, kRecordsOneVec = 4096;
 constexpr int kSortOneVec = 16384, kSortTwoVec = 12288;
