@@ -408,18 +408,26 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
                              int q) __attribute__((always_inline)) {
         constexpr int N = decltype(n_const)::value;
         // (the entries that are in LDS are read together, and ahead of the chain of additions: left to the compiler each
-        // is read and waited for behind a branch of its own, inside the chain.  65,536 rows of about 100 entries over 2^20
-        // columns 52 -> 51 us a pass, 20,000 over 200,000 25.3 -> 24.7)
-        float2 near[N];
-#pragma unroll
-        for (int k = 0; k < N; ++k) {
+        // is read and waited for behind a branch of its own, inside the chain.  An epoch over 2^20 columns, about 100 entries a
+        // row, 41.9 -> 40.8 us a pass, 20,000 rows over 200,000 25.3 -> 24.7; not for dense rows, where all columns of a turn
+        // are on one side: step over 16,384 of 9000 709 us, with this 773)
+        auto in_lds = [&](int k) __attribute__((always_inline)) {
           const int cn = min(c[k], D - 1);
-          near[k] = TWO ? reinterpret_cast<const float2 *>(s_model)[cn] : make_float2(s_model[cn], 0.f);
+          return TWO ? reinterpret_cast<const float2 *>(s_model)[cn] : make_float2(s_model[cn], 0.f);
+        };
+        float2 near[N];
+        if constexpr (CSR) {
+#pragma unroll
+          for (int k = 0; k < N; ++k) near[k] = in_lds(k);
+#pragma unroll
+          for (int k = 0; k < N; ++k) {
+            asm volatile("" : "+v"(near[k].x));
+            if (TWO) asm volatile("" : "+v"(near[k].y));
+          }
         }
 #pragma unroll
-        for (int k = 0; k < N; ++k) asm volatile("" : "+v"(near[k].x), "+v"(near[k].y));
-#pragma unroll
         for (int k = 0; k < N; ++k) {
+          if constexpr (!CSR) near[k] = in_lds(k);
           const float mw = c[k] >= D ? far[k].x : near[k].x;
           const float mp = TWO ? (c[k] >= D ? far[k].y : near[k].y) : mw;
           if (SVM) dw[q] = in[k] ? __fmaf_rn(mw, xv[k], dw[q]) : dw[q];
