@@ -31,6 +31,8 @@ namespace {
 
 typedef float f4v __attribute__((ext_vector_type(4), aligned(4)));  // (any float address)
 typedef int i4v __attribute__((ext_vector_type(4), aligned(4)));
+typedef unsigned u2v __attribute__((ext_vector_type(2)));
+typedef unsigned u3v __attribute__((ext_vector_type(3)));
 
 // v moved by a DPP control.
 template <int CTRL>
@@ -105,8 +107,14 @@ __device__ __forceinline__ void add_global(const GenArgs &a, int c, double ta, d
 // an LDS buffer that the block looked at, and emptied, together every eight rows of a wave:
 // 55 % of the wave cycles were waits.  Now those that the buffer has no room for go to memory as they
 // come, and the block sorts all of them by bin once, at the end.
-template <int GL, int MODE, bool CSR>
+// An entry cost about 96 vector instructions; 25.8 M of them over 64,002 columns kept a pass at 58 % of its issue
+// cycles.  Lane sets in scalar registers, one sum's address instead of two branches, no division a record, row extents
+// clipped once a round and record stores without a branch leave 62: the update over 460,000 sentence pairs 170.4 ->
+// 157.1 us, an epoch of four pools of 65,536 rows over 2^20 columns 233.3 -> 228.3.
+// NEAR: every column is in the table; no tags, records and gathers.
+template <int GL, int MODE, bool CSR, bool NEAR>
 __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
+  static_assert(CSR || !NEAR, "dense rows choose turn by turn");
   constexpr bool POOL = (MODE & kPool) != 0;
   constexpr bool SVM = (MODE & kSvm) != 0;
   constexpr bool ASSIST = (MODE & kAssist) != 0;
@@ -126,12 +134,12 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
   constexpr int kTableBytes = kSumBytes + kModelBytes + kTagBytes + kHeldBytes;
   __shared__ __attribute__((aligned(16))) char s_mem[kTableBytes > kSortBytes ? kTableBytes : kSortBytes];
   __shared__ __attribute__((aligned(16))) int s_hist[kMaxBins], s_base[kMaxBins];
-  __shared__ int s_nrec, s_more, s_next;
+  __shared__ int s_nrec[1], s_more, s_next;
   __shared__ int s_cnt[kWaves];
   __shared__ float s_gb[kWaves];
-  double *const s_sum = reinterpret_cast<double *>(s_mem);  // [vector][D + H]
-  float *const s_model = reinterpret_cast<float *>(s_mem + kSumBytes);  // one vector: [D]; two: pairs
-  int *const s_tag = reinterpret_cast<int *>(s_mem + kSumBytes + kModelBytes);
+  int *const s_tag = reinterpret_cast<int *>(s_mem);  // (in front: an access's own offset has 16 bits)
+  double *const s_sum = reinterpret_cast<double *>(s_mem + kTagBytes);  // [vector][D + H]
+  float *const s_model = reinterpret_cast<float *>(s_mem + kTagBytes + kSumBytes);  // one vector: [D]; two: pairs
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int *const s_held = reinterpret_cast<int *>(s_mem + kSumBytes + kModelBytes + kTagBytes);
@@ -185,12 +193,12 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
     int id = row_id(0);
     __builtin_amdgcn_sched_barrier(0);
     // (no more than the model has columns for: one vector of 3000, 8192 rows of 56 entries 15.4 -> 14.4 us)
-    const int used = a.d <= D ? a.d : D + H;
+    const int used = NEAR || a.d <= D ? a.d : D + H;
 #pragma unroll
     for (int v = 0; v < NVEC; ++v)
       for (int k = threadIdx.x; k < used; k += kGradThreads) s_sum[v * (D + H) + k] = 0.0;
-    for (int k = threadIdx.x; a.d > D && k < H; k += kGradThreads) s_tag[k] = -1;
-    if (threadIdx.x == 0) s_nrec = s_more = s_next = 0;
+    for (int k = threadIdx.x; !NEAR && a.d > D && k < H; k += kGradThreads) s_tag[k] = -1;
+    if (threadIdx.x == 0) s_nrec[0] = s_more = s_next = 0;
     __builtin_amdgcn_sched_barrier(0);
     first_rows = load_rows(0, id);
 #pragma unroll
@@ -210,52 +218,84 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
   const int held = binned ? R : 0, cap = held + (binned ? a.plan.pieces * a.plan.piece : 0);
   int32_t *const late = a.recs + (size_t)a.plan.nb * a.plan.bin_cap * RW;  // records that LDS has no room for
   auto piece_at = [&](int piece) { return late + ((size_t)piece * gridDim.x + blockIdx.x) * a.plan.piece * RW; };
-  // N records a lane, those with `want`; all lanes take part.  A block's first `held` records stay in LDS until the
-  // end, the others go to where they will be sorted.
-  auto append = [&](auto n_const, const bool *want, const int *c, const float *ta, const float *tb)
-                    __attribute__((always_inline)) {
+  // Late records are stored through a buffer resource: a lane without one gives an offset out of range, and the store
+  // needs no branch.  Loads and stores share one counter here: behind a store under a condition the wait for the next
+  // unit's entries, requested before it, would be a wait for its acknowledgement, too.
+  constexpr int kNone = (int)0x80000000;  // out of every resource's range
+  const __amdgpu_buffer_rsrc_t r_late = __builtin_amdgcn_make_buffer_rsrc(late, 0, binned ? kNone : 0, 0x00020000);
+  // the piece that the wave's last records went to: places from piece_lo to piece_hi, byte offset of place 0
+  const int piece_len = a.plan.piece;
+  int piece_lo = held, piece_hi = held, piece_off = 0;
+  auto piece_of_place = [&](int place) { return (int)((unsigned)(place - held) / (unsigned)piece_len); };
+  auto offset_of = [&](int piece) {
+    return (int)((((unsigned)piece * gridDim.x + blockIdx.x - (unsigned)piece) * (unsigned)piece_len - (unsigned)held) * (4u * RW));
+  };
+  // Places for N records a lane, those of the lanes in want[k]; all lanes take part.  A block's first `held` records stay
+  // in LDS until the end, the others go to where they will be sorted: off[k] is what their store is given.
+  // (Lane sets are masks in scalar registers throughout: as booleans that cross a branch they are a vector register
+  // and three instructions each.)
+  auto place_records = [&](auto n_const, const uint64_t *want, const int *c, const float *ta, const float *tb, int *off)
+                           __attribute__((always_inline)) {
     constexpr int N = decltype(n_const)::value;
     int count = 0;
 #pragma unroll
-    for (int k = 0; k < N; ++k) count += __popcll(__ballot(want[k]));
+    for (int k = 0; k < N; ++k) count += __popcll(want[k]);
+#pragma unroll
+    for (int k = 0; k < N; ++k) off[k] = kNone;
     if (count == 0) return;
     int first = 0;
-    if (lane == 0) first = atomicAdd(&s_nrec, count);
+    {
+      int at = 0;
+      asm volatile("" : "+v"(at));  // (one lane adds: nothing to combine)
+      if (lane == 0) first = atomicAdd(s_nrec + at, count);
+    }
     first = __builtin_amdgcn_readfirstlane(first);
     int pos[N];
 #pragma unroll
     for (int k = 0, next = first; k < N; ++k) {
-      const unsigned long long mask = __ballot(want[k]);
-      pos[k] = next + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
-                                                     __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-      next += __popcll(mask);
+      pos[k] = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(want[k] >> 32),
+                                              __builtin_amdgcn_mbcnt_lo((uint32_t)want[k], (uint32_t)next));
+      next += __popcll(want[k]);
     }
-    if (first < held) {
+    if (first >= piece_hi && first < cap) {  // (on to the piece that `first` lies in)
+      const int piece = piece_of_place(first);
+      piece_lo = held + piece * piece_len;
+      piece_hi = min(piece_lo + piece_len, cap);
+      piece_off = offset_of(piece);
+    }
+    if (first >= piece_lo && first + count <= piece_hi) {
 #pragma unroll
       for (int k = 0; k < N; ++k) {
-        if (want[k] && pos[k] < held) {
+        const int o = pos[k] * (4 * RW) + piece_off;
+        off[k] = __builtin_amdgcn_inverse_ballot_w64(want[k]) ? o : kNone;
+      }
+      return;
+    }
+    if (first + count <= held) {
+#pragma unroll
+      for (int k = 0; k < N; ++k) {
+        if (__builtin_amdgcn_inverse_ballot_w64(want[k])) {
           s_held[pos[k] * RW] = c[k];
           s_held[pos[k] * RW + 1] = __float_as_int(ta[k]);
           if (TWO) s_held[pos[k] * RW + RW - 1] = __float_as_int(tb[k]);
         }
       }
+      return;
     }
-    if (first + count > held && first < cap && cap > held) {
-      // (a lane's records lie in one piece or in it and the next: with several, one is longer than 64 N)
-      static_assert(kSortTwoVec / 2 > 8 * kWave && kSortOneVec / 2 > 8 * kWave, "at most one boundary");
-      const int from = max(first - held, 0);
-      const int piece = from >= a.plan.piece ? (int)((unsigned)from / (unsigned)a.plan.piece) : 0;
-      int32_t *const here = piece_at(piece), *const after = piece_at(piece + 1);
+    // on both sides of a boundary, or beyond the block's room
+    // (a lane's records lie in one piece or in it and the next: with several, one is longer than 64 N)
+    static_assert(kSortTwoVec / 2 > 8 * kWave && kSortOneVec / 2 > 8 * kWave, "at most one boundary");
+    const int piece = first < cap && max(first, held) < cap && cap > held ? piece_of_place(max(first, held)) : 0;
+    const int ends = held + (piece + 1) * piece_len, off_here = offset_of(piece), off_next = offset_of(piece + 1);
 #pragma unroll
-      for (int k = 0; k < N; ++k) {
-        if (want[k] && pos[k] >= held && pos[k] < cap) {
-          const int i = pos[k] - held - piece * a.plan.piece;
-          int32_t *const dst = i < a.plan.piece ? here + i * RW : after + (i - a.plan.piece) * RW;
-          dst[0] = c[k];
-          dst[1] = __float_as_int(ta[k]);
-          if (TWO) dst[RW - 1] = __float_as_int(tb[k]);
-        }
+    for (int k = 0; k < N; ++k) {
+      const bool mine = __builtin_amdgcn_inverse_ballot_w64(want[k]);
+      if (mine && pos[k] < held) {
+        s_held[pos[k] * RW] = c[k];
+        s_held[pos[k] * RW + 1] = __float_as_int(ta[k]);
+        if (TWO) s_held[pos[k] * RW + RW - 1] = __float_as_int(tb[k]);
       }
+      if (mine && pos[k] >= held && pos[k] < cap) off[k] = pos[k] * (4 * RW) + (pos[k] < ends ? off_here : off_next);
     }
     if (first + count > cap) {
       // (one copy of what adds to the accumulators: copies behind every entry cost hundreds of scalar registers
@@ -264,27 +304,49 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
       for (int k = 0; k < N; ++k) {
         int ck = c[0];
         float tak = ta[0], tbk = tb[0];
-        bool out = want[0] && pos[0] >= cap;
+        bool out = __builtin_amdgcn_inverse_ballot_w64(want[0]) && pos[0] >= cap;
 #pragma unroll
         for (int i = 1; i < N; ++i) {
           ck = i == k ? c[i] : ck;
           tak = i == k ? ta[i] : tak;
           tbk = i == k ? tb[i] : tbk;
-          out = i == k ? want[i] && pos[i] >= cap : out;
+          out = i == k ? __builtin_amdgcn_inverse_ballot_w64(want[i]) && pos[i] >= cap : out;
         }
         if (out) add_global<SVM, ASSIST>(a, ck, tak, tbk);
       }
     }
+  };
+  auto store_records = [&](auto n_const, const int *c, const float *ta, const float *tb, const int *off)
+                           __attribute__((always_inline)) {
+#pragma unroll
+    for (int k = 0; k < decltype(n_const)::value; ++k) {
+      if constexpr (TWO)
+        __builtin_amdgcn_raw_buffer_store_b96(u3v{(unsigned)c[k], __float_as_uint(ta[k]), __float_as_uint(tb[k])}, r_late,
+                                              off[k], 0, 0);
+      else
+        __builtin_amdgcn_raw_buffer_store_b64(u2v{(unsigned)c[k], __float_as_uint(ta[k])}, r_late, off[k], 0, 0);
+    }
+  };
+  auto append = [&](auto n_const, const uint64_t *want, const int *c, const float *ta, const float *tb)
+                    __attribute__((always_inline)) {
+    int off[decltype(n_const)::value];
+    place_records(n_const, want, c, ta, tb, off);
+    store_records(n_const, c, ta, tb, off);
   };
 
   // Entries are read through buffer resources: a lane with nothing to read gives an offset past the
   // resource's range, for which the hardware returns zero without a memory access.  No load of the row loop
   // sits behind a branch then, and the next unit's entries stay in flight while this one's gathers are waited for
   // (with exec-masked loads every wait was for everything in flight).
-  constexpr int kNone = (int)0x80000000;         // out of every resource's range
   constexpr long long kSpan = 0x7fffffffll / 4;  // entries within reach of a 32-bit byte offset
   const __amdgpu_buffer_rsrc_t r_col = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<int32_t *>(CSR ? a.col : nullptr), 0, CSR ? kNone : 0, 0x00020000);
+  // (the model past the table, where a 32-bit offset reaches all of it)
+  constexpr int kColBytes = TWO ? 8 : 4;
+  const bool reach = a.d <= (int)(0x7fffffffu / kColBytes);
+  const void *const far_src = TWO ? (const void *)a.wp : (const void *)(ASSIST ? a.phi : a.w);
+  const __amdgpu_buffer_rsrc_t r_far = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(far_src), 0,
+                                                                       CSR && reach ? a.d * kColBytes : 0, 0x00020000);
   const __amdgpu_buffer_rsrc_t r_val = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<float *>(CSR && a.val ? a.val : a.T), 0, CSR && a.val ? kNone : 0, 0x00020000);
   const int rows_max = per + (rem > 0 ? 1 : 0);
@@ -322,8 +384,6 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
     }
     const int units = M + (cnt - M + 1) / 2;  // (lanes without a row have the last places)
     const int iters = (units + G - 1) / G;
-    // place of a unit's row in slot 0 or 1
-    auto place = [&](int unit, int slot) { return unit < M ? unit : 2 * unit - M + slot; };
     // The unit's two pieces, four neighbouring entries a lane and piece.  The piece that ends with
     // a row shares entries with the one before it, so that every load is a whole one inside the
     // row; entries k < skip belong there.  A row that ends before the matrix's fourth entry has nothing
@@ -332,21 +392,26 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
       i4v c[2];
       f4v x[2];
       int skip[2];  // (4 and more: nothing here)
+      int at;       // place of the row whose scalars this lane works out: even lanes slot 0, odd ones slot 1
     };
     auto quick_len = [&](long long e0, int len) { return e0 + len >= 4 && e0 + len <= kSpan ? min(len, 2 * kPiece) : 0; };
+    const int quick_l = CSR ? quick_len(e0_l, len_l) : 0, first_l = (int)e0_l;
+    const bool rest = !CSR || __ballot(len_l > quick_l) != 0ull;  // (anything in the wave's rows past the pieces)
     auto request = [&](int it, Pieces &p) __attribute__((always_inline)) {
       const int unit = it * G + grp;
+      const bool pair = unit >= M;
+      const int at0 = pair ? 2 * unit - M : unit, at1 = pair ? at0 + 1 : at0;
+      p.at = (sub & 1) ? at1 : at0;
       int off[2];
 #pragma unroll
       for (int q = 0; q < 2; ++q) {
-        const int at = place(unit, q);
-        const long long e0 = __shfl(e0_l, min(at, kWave - 1), kWave);
-        const int len_any = __shfl(len_l, min(at, kWave - 1), kWave);
+        const int at = q == 0 ? at0 : at1;
+        const int e0 = __builtin_amdgcn_ds_bpermute(4 * at, first_l);
+        const int len_any = __builtin_amdgcn_ds_bpermute(4 * at, quick_l);
         const int len = at < cnt ? len_any : 0, last = len - 4;
-        const int e = 4 * sub + (q == 1 && unit < M ? kPiece : 0);
-        const bool here = e < quick_len(e0, len);
-        off[q] = here ? ((int)e0 + min(e, last)) * 4 : kNone;
-        p.skip[q] = here ? e - last : 4;
+        const int e = q == 1 && !pair ? 4 * sub + kPiece : 4 * sub;
+        off[q] = e < len ? (e0 + min(e, last)) * 4 : kNone;
+        p.skip[q] = e - last;
       }
 #pragma unroll
       for (int q = 0; q < 2; ++q) {
@@ -356,7 +421,7 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
     };
     Pieces ahead;
     if (CSR && iters > 0) request(0, ahead);
-    if (CSR && round == 0 && per >= kClaimRows) {
+    if (CSR && !NEAR && round == 0 && per >= kClaimRows) {
       // A column that every row has must find a hashed slot: the columns of the block's first row get theirs
       // before the waves race for them (left to the race, the two length columns of the translation batches lost it
       // in one block of ten, whose entries then met in one bin: update kernel 21 -> 134 us).
@@ -373,38 +438,66 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
       }
       __syncthreads();
     }
+    if constexpr (CSR && !NEAR) {  // (as many stores behind the first request as behind the others, see r_late)
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        int none = kNone;
+        asm volatile("" : "+v"(none));  // (not one for all)
+        store_records(std::integral_constant<int, 1>{}, &lane, &b, &b, &none);
+      }
+    }
     for (int it = 0; it < iters; ++it) {
       const int unit = it * G + grp;
       const bool pair = unit >= M;
       // Row scalars are worked out by the lanes of a row: even lanes have the row in slot 0, odd ones slot 1.
-      const int at = place(unit, sub & 1), at_safe = min(at, kWave - 1);
+      const int at = CSR ? ahead.at : unit;
       const bool live = at < cnt, teller = live && (sub == 0 || (sub == 1 && pair));
-      const int j = base + (CSR ? __shfl(src_l, at_safe, kWave) : at_safe);
-      const float u = __shfl(u_l, at_safe, kWave);
-      const float yy = __shfl(y_l, at_safe, kWave);
-      const float lin = __shfl(lin_l, at_safe, kWave);
-      const long long e0 = __shfl(e0_l, at_safe, kWave);
-      const int len_any = __shfl(len_l, at_safe, kWave);
+      auto of_row = [&](int v) { return __builtin_amdgcn_ds_bpermute(4 * at, v); };
+      const int j = base + (CSR ? of_row(src_l) : at);
+      const float u = POOL ? __int_as_float(of_row(__float_as_int(u_l))) : 0.f;
+      const float yy = SVM ? __int_as_float(of_row(__float_as_int(y_l))) : 0.f;
+      const float lin = ASSIST && !SVM ? __int_as_float(of_row(__float_as_int(lin_l))) : 0.f;
       // what is left of a row of its own after the first two pieces
-      const int len = live && !pair ? len_any : 0;
-      const int slow = CSR ? quick_len(e0, len) : 0;
+      long long e0 = 0;
+      int len = 0, slow = 0;
+      if (rest) {
+        e0 = ((long long)of_row((int)(e0_l >> 32)) << 32) | (uint32_t)of_row((int)(uint32_t)e0_l);
+        const int len_any = of_row(len_l);
+        len = live && !pair ? len_any : 0;
+        slow = CSR ? quick_len(e0, len) : 0;
+      }
       float dp[2] = {0.f, 0.f}, dw[2] = {0.f, 0.f};
       // Shares of the dot products.  The columns that are not in LDS are gathered without a
-      // branch (an entry with nothing to fetch asks for column 0), so that the gathers leave together.
+      // branch (an entry with nothing to fetch asks for nothing), so that the gathers leave together.
+      // Column -1: no entry.
       auto gather = [&](auto n_const, const int *c, float2 *far, bool all_near) __attribute__((always_inline)) {
+        constexpr int N = decltype(n_const)::value;
 #pragma unroll
-        for (int k = 0; k < decltype(n_const)::value; ++k) far[k] = make_float2(0.f, 0.f);
+        for (int k = 0; k < N; ++k) far[k] = make_float2(0.f, 0.f);
         if (all_near) return;  // (no such columns: a round trip less)
+        if (CSR && reach) {
 #pragma unroll
-        for (int k = 0; k < decltype(n_const)::value; ++k) {
+          for (int k = 0; k < N; ++k) {
+            const int off = c[k] >= D ? c[k] * kColBytes : kNone;
+            if (TWO) {
+              const u2v v = __builtin_bit_cast(u2v, __builtin_amdgcn_raw_buffer_load_b64(r_far, off, 0, 0));
+              far[k] = make_float2(__uint_as_float(v.x), __uint_as_float(v.y));  // both values with one gather
+            } else {
+              far[k].x = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r_far, off, 0, 0));
+            }
+          }
+          return;
+        }
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
           const int cf = c[k] >= D ? c[k] : 0;
           if (TWO)
-            far[k] = a.wp[cf];  // both values of the column with one gather
+            far[k] = a.wp[cf];
           else
             far[k].x = (ASSIST ? a.phi : a.w)[cf];
         }
       };
-      auto dot_entries = [&](auto n_const, const int *c, const float *xv, const float2 *far, const bool *in,
+      auto dot_entries = [&](auto n_const, const int *c, const float *xv, const float2 *far,
                              int q) __attribute__((always_inline)) {
         constexpr int N = decltype(n_const)::value;
         // (the entries that are in LDS are read together, and ahead of the chain of additions: left to the compiler each
@@ -412,7 +505,7 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
         // row, 41.9 -> 40.8 us a pass, 20,000 rows over 200,000 25.3 -> 24.7; not for dense rows, where all columns of a turn
         // are on one side: step over 16,384 of 9000 709 us, with this 773)
         auto in_lds = [&](int k) __attribute__((always_inline)) {
-          const int cn = min(c[k], D - 1);
+          const int cn = NEAR ? max(c[k], 0) : min(max(c[k], 0), D - 1);
           return TWO ? reinterpret_cast<const float2 *>(s_model)[cn] : make_float2(s_model[cn], 0.f);
         };
         float2 near[N];
@@ -428,43 +521,43 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
 #pragma unroll
         for (int k = 0; k < N; ++k) {
           if constexpr (!CSR) near[k] = in_lds(k);
-          const float mw = c[k] >= D ? far[k].x : near[k].x;
-          const float mp = TWO ? (c[k] >= D ? far[k].y : near[k].y) : mw;
-          if (SVM) dw[q] = in[k] ? __fmaf_rn(mw, xv[k], dw[q]) : dw[q];
-          if (NEED_PHI) dp[q] = in[k] ? __fmaf_rn(mp, xv[k], dp[q]) : dp[q];
+          const bool in = c[k] >= 0;
+          const float mw = !NEAR && c[k] >= D ? far[k].x : near[k].x;
+          const float mp = TWO ? (!NEAR && c[k] >= D ? far[k].y : near[k].y) : mw;
+          if (SVM) dw[q] = in ? __fmaf_rn(mw, xv[k], dw[q]) : dw[q];
+          if (NEED_PHI) dp[q] = in ? __fmaf_rn(mp, xv[k], dp[q]) : dp[q];
         }
       };
-      Pieces cur;
+      int c_unit[8];
+      float x_unit[8];
       bool second = false;  // anything in slot 1
       if constexpr (CSR) {
-        cur = ahead;
+        Pieces cur = ahead;
         asm volatile("" : "+v"(cur.c[0]), "+v"(cur.c[1]), "+v"(cur.x[0]), "+v"(cur.x[1]));  // (waited for here)
-        int c[8];
-        float xv[8];
-        bool in[8];
-        float2 far[8];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) c[k] = cur.c[k / 4][k % 4];
-        gather(std::integral_constant<int, 8>{}, c, far, a.d <= D);
+        for (int k = 0; k < 8; ++k) {
+          c_unit[k] = k % 4 >= cur.skip[k / 4] ? cur.c[k / 4][k % 4] : -1;
+          x_unit[k] = cur.x[k / 4][k % 4];
+        }
+        float2 far[8];
+        gather(std::integral_constant<int, 8>{}, c_unit, far, NEAR);
         __builtin_amdgcn_sched_barrier(0);
         request(it + 1, ahead);  // (past the last unit: no accesses)
         __builtin_amdgcn_sched_barrier(0);
+        if (!a.val) {
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          xv[k] = a.val ? cur.x[k / 4][k % 4] : 1.f;
-          in[k] = k % 4 >= cur.skip[k / 4];
+          for (int k = 0; k < 8; ++k) x_unit[k] = 1.f;
         }
-        dot_entries(std::integral_constant<int, 4>{}, c, xv, far, in, 0);
+        dot_entries(std::integral_constant<int, 4>{}, c_unit, x_unit, far, 0);
         dp[1] = pair ? 0.f : dp[0];  // (one row: its sums go on, in the order of the scoring kernels)
         dw[1] = pair ? 0.f : dw[0];
         second = __ballot(cur.skip[1] < 4) != 0ull;
-        if (second) dot_entries(std::integral_constant<int, 4>{}, c + 4, xv + 4, far + 4, in + 4, 1);
+        if (second) dot_entries(std::integral_constant<int, 4>{}, c_unit + 4, x_unit + 4, far + 4, 1);
       }
       constexpr int kRest = CSR && TWO ? 4 : 8;  // (eight: more registers than there are)
       auto walk = [&](int eb, bool all_near) __attribute__((always_inline)) {
         int c[kRest];
         float xv[kRest];
-        bool in[kRest];
         float2 far[kRest];
         if constexpr (CSR) {  // four neighbours a lane here too
           i4v cq[kRest / 4] = {};
@@ -488,24 +581,23 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
           }
 #pragma unroll
           for (int k = 0; k < kRest; ++k) {
-            in[k] = k % 4 >= eb + k / 4 * kPiece - (len - 4);
-            c[k] = cq[k / 4][k % 4];
+            c[k] = k % 4 >= eb + k / 4 * kPiece - (len - 4) ? cq[k / 4][k % 4] : -1;
             xv[k] = a.val ? xq[k / 4][k % 4] : 1.f;
           }
         } else {
 #pragma unroll
           for (int k = 0; k < kRest; ++k) {
             const int e = eb + k * GL;
-            in[k] = e < len;
-            c[k] = in[k] ? e : 0;
-            xv[k] = in[k] ? a.x[e0 + e] : 0.f;
+            c[k] = e < len ? e : -1;
+            xv[k] = e < len ? a.x[e0 + e] : 0.f;
           }
         }
         gather(std::integral_constant<int, kRest>{}, c, far, all_near);
-        dot_entries(std::integral_constant<int, kRest>{}, c, xv, far, in, CSR ? 1 : 0);
+        dot_entries(std::integral_constant<int, kRest>{}, c, xv, far, CSR ? 1 : 0);
       };
       if constexpr (CSR) {
-        for (int eb = slow + 4 * sub; eb < len; eb += kRest * GL) walk(eb, a.d <= D);
+        if (rest)
+          for (int eb = slow + 4 * sub; eb < len; eb += kRest * GL) walk(eb, NEAR);
       } else {  // (first the columns that are in LDS)
         static_assert(CSR || D % (kRest * GL) == 0, "no turn on both sides");
         int eb = sub;
@@ -517,6 +609,7 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
         if (!CSR) return gsum<GL>(v0);
         v0 = gsum<GL>(v0);
         v1 = gsum<GL>(v1);
+        asm volatile("" : "+v"(v0), "+v"(v1));  // (both there: a choice, not a branch)
         return pair && !(sub & 1) ? v0 : v1;
       };
       float g = 0.f;
@@ -553,49 +646,55 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
       // the coefficients of both slots' rows, in every lane (quad_perm 0,0,2,2 and 1,1,3,3)
       const float cw[2] = {dpp_move<0xA0>(cw_own), dpp_move<0xF5>(cw_own)};
       const float resid[2] = {dpp_move<0xA0>(resid_own), dpp_move<0xF5>(resid_own)};
-      const bool contrib[2] = {cw[0] != 0.f || resid[0] != 0.f, cw[1] != 0.f || resid[1] != 0.f};
       // Second walk.  A column's sum is its slot's, or that of the hashed slot that holds it; an entry that
       // finds neither leaves as a record.  N entries of a lane together (column -1: none): their tag reads
       // are in flight at once.
-      auto scatter = [&](auto n_const, const int *c, const float *xv, int slot, bool all_near) __attribute__((always_inline)) {
+      const bool has_w[2] = {SVM && cw[0] != 0.f, SVM && cw[1] != 0.f};
+      const bool has_p[2] = {ASSIST && resid[0] != 0.f, ASSIST && resid[1] != 0.f};
+      const uint64_t contrib[2] = {__ballot(has_w[0] || has_p[0]), __ballot(has_w[1] || has_p[1])};
+      auto add_at = [&](int q, int at, float ta, float tb) __attribute__((always_inline)) {  // (at: byte offset)
+        double *const to = reinterpret_cast<double *>(reinterpret_cast<char *>(s_sum) + at);
+        if (!TWO || has_w[q]) unsafeAtomicAdd(to, (double)ta);
+        if (TWO && has_p[q]) unsafeAtomicAdd(to + (D + H), (double)tb);
+      };
+      auto scatter = [&](auto n_const, const int *c, const float *xv, int slot, bool all_near, uint64_t *miss, float *ta,
+                         float *tb) __attribute__((always_inline)) {
         constexpr int N = decltype(n_const)::value;
-        auto terms = [&](int k, float *ta, float *tb) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
           const int q = slot + k / 4;
-          *ta = SVM ? (cw[q] != 0.f ? cw[q] * xv[k] : 0.f) : resid[q] * xv[k];
-          *tb = TWO ? (resid[q] != 0.f ? resid[q] * xv[k] : 0.f) : 0.f;
-        };
-        auto add_at = [&](int k, int at, float ta, float tb) __attribute__((always_inline)) {
-          const int q = slot + k / 4;
-          if (!TWO || cw[q] != 0.f) unsafeAtomicAdd(s_sum + at, (double)ta);
-          if (TWO && resid[q] != 0.f) unsafeAtomicAdd(s_sum + (D + H) + at, (double)tb);
-        };
+          ta[k] = SVM ? (has_w[q] ? cw[q] * xv[k] : 0.f) : resid[q] * xv[k];
+          tb[k] = TWO ? (has_p[q] ? resid[q] * xv[k] : 0.f) : 0.f;
+          miss[k] = 0;
+        }
         if (all_near) {  // (every column has its slot)
 #pragma unroll
-          for (int k = 0; k < N; ++k) {
-            float ta, tb;
-            terms(k, &ta, &tb);
-            if (c[k] >= 0) add_at(k, c[k], ta, tb);
-          }
+          for (int k = 0; k < N; ++k)
+            if (__builtin_amdgcn_inverse_ballot_w64(contrib[slot + k / 4] & __ballot(c[k] >= 0)))
+              add_at(slot + k / 4, 8 * c[k], ta[k], tb[k]);
           return;
         }
         int2 tag[N];
-        int at_sum[N];
+        int set[N];  // byte offset of the set's tags
 #pragma unroll
         for (int k = 0; k < N; ++k) {
-          at_sum[k] = c[k] >= D ? 2 * hashed_set<H>(c[k], factor) : 0;
-          tag[k] = *reinterpret_cast<const int2 *>(s_tag + at_sum[k]);
+          set[k] = 8 * hashed_set<H>(c[k], factor);
+          tag[k] = *reinterpret_cast<const int2 *>(reinterpret_cast<const char *>(s_tag) + set[k]);
         }
-        bool claim = false;
+        uint64_t far[N], first_is[N], second_is[N], claim = 0;
 #pragma unroll
         for (int k = 0; k < N; ++k) {
-          const bool found = tag[k].x == c[k] || tag[k].y == c[k];
-          claim = claim || (c[k] >= D && !found && (tag[k].x == -1 || tag[k].y == -1));
+          far[k] = contrib[slot + k / 4] & __ballot(c[k] >= D);
+          first_is[k] = __ballot(tag[k].x == c[k]);
+          second_is[k] = __ballot(tag[k].y == c[k]);
+          claim |= far[k] & ~(first_is[k] | second_is[k]) & __ballot(tag[k].y == -1);  // (the second of a set is taken last)
         }
-        if (__ballot(claim) != 0ull) {  // (rare after the first rows)
+        if (claim != 0ull) {  // (rare after the first rows)
 #pragma unroll
           for (int k = 0; k < N; ++k) {
-            if (c[k] >= D && tag[k].x != c[k] && tag[k].y != c[k]) {  // (a tag changes once, from -1 to its column)
-              int *const tags = s_tag + at_sum[k];
+            if (__builtin_amdgcn_inverse_ballot_w64(far[k] & ~(first_is[k] | second_is[k]))) {
+              // (a tag changes once, from -1 to its column)
+              int *const tags = reinterpret_cast<int *>(reinterpret_cast<char *>(s_tag) + set[k]);
               if (tag[k].x == -1) {
                 const int old = atomicCAS(tags, -1, c[k]);
                 tag[k].x = old == -1 ? c[k] : old;
@@ -605,58 +704,79 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
                 tag[k].y = old == -1 ? c[k] : old;
               }
             }
+            first_is[k] = __ballot(tag[k].x == c[k]);
+            second_is[k] = __ballot(tag[k].y == c[k]);
           }
         }
-        bool miss[N];
-        float ta[N], tb[N];
 #pragma unroll
         for (int k = 0; k < N; ++k) {
-          const int hashed = tag[k].x == c[k] ? D + at_sum[k] : tag[k].y == c[k] ? D + at_sum[k] + 1 : -1;
-          const int at = c[k] < D ? c[k] : hashed;
-          miss[k] = c[k] >= D && at < 0;
-          terms(k, &ta[k], &tb[k]);
-          if (at >= 0) add_at(k, at, ta[k], tb[k]);
+          int in_set = 2 * set[k] + 8 * D + (__builtin_amdgcn_inverse_ballot_w64(second_is[k]) ? 8 : 0);
+          asm volatile("" : "+v"(in_set));  // (one address, one addition: not a branch for either)
+          const int at = c[k] >= D ? in_set : 8 * c[k];
+          const uint64_t near = contrib[slot + k / 4] & __ballot((unsigned)c[k] < (unsigned)D);
+          const uint64_t has = first_is[k] | second_is[k];
+          miss[k] = far[k] & ~has;
+          if (__builtin_amdgcn_inverse_ballot_w64(near | (far[k] & has))) add_at(slot + k / 4, at, ta[k], tb[k]);
         }
-        append(n_const, miss, c, ta, tb);
       };
       if constexpr (CSR) {
-        int c[8];
-        float xv[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          c[k] = contrib[k / 4] && k % 4 >= cur.skip[k / 4] ? cur.c[k / 4][k % 4] : -1;
-          xv[k] = a.val ? cur.x[k / 4][k % 4] : 1.f;
-        }
         // (two vectors: eight at once are more registers than there are; one vector, four at once: update over 460,000
         // sentence pairs 171 us, with eight 168, over 1000 rows of 56 entries 20.3 and 21.1)
-        if (!TWO && second) {
-          scatter(std::integral_constant<int, 8>{}, c, xv, 0, a.d <= D);
+        uint64_t miss[8];
+        float ta[8], tb[8];
+        if constexpr (!TWO) {
+          int off[8] = {kNone, kNone, kNone, kNone, kNone, kNone, kNone, kNone};
+          if (second) {
+            scatter(std::integral_constant<int, 8>{}, c_unit, x_unit, 0, NEAR, miss, ta, tb);
+            if (!NEAR) place_records(std::integral_constant<int, 8>{}, miss, c_unit, ta, tb, off);
+          } else {
+            scatter(std::integral_constant<int, 4>{}, c_unit, x_unit, 0, NEAR, miss, ta, tb);
+            if (!NEAR) place_records(std::integral_constant<int, 4>{}, miss, c_unit, ta, tb, off);
+#pragma unroll
+            for (int k = 4; k < 8; ++k) ta[k] = tb[k] = 0.f;
+          }
+          if (!NEAR) store_records(std::integral_constant<int, 8>{}, c_unit, ta, tb, off);
         } else {
-          scatter(std::integral_constant<int, 4>{}, c, xv, 0, a.d <= D);
-          if (TWO && second) scatter(std::integral_constant<int, 4>{}, c + 4, xv + 4, 1, a.d <= D);
+          int off[4];
+          scatter(std::integral_constant<int, 4>{}, c_unit, x_unit, 0, NEAR, miss, ta, tb);
+          if (!NEAR) {
+            place_records(std::integral_constant<int, 4>{}, miss, c_unit, ta, tb, off);
+            store_records(std::integral_constant<int, 4>{}, c_unit, ta, tb, off);
+          }
+#pragma unroll
+          for (int k = 0; k < 4; ++k) off[k] = kNone;
+          if (second) {
+            scatter(std::integral_constant<int, 4>{}, c_unit + 4, x_unit + 4, 1, NEAR, miss, ta, tb);
+            if (!NEAR) place_records(std::integral_constant<int, 4>{}, miss, c_unit + 4, ta, tb, off);
+          }
+          if (!NEAR) store_records(std::integral_constant<int, 4>{}, c_unit + 4, ta, tb, off);
         }
       }
       // entries beyond; the wave's groups step together
-      int steps_len = contrib[0] ? len - slow : 0;
+      if (rest) {
+        int steps_len = has_w[0] || has_p[0] ? len - slow : 0;
 #pragma unroll
-      for (int off = GL; off < kWave; off <<= 1) steps_len = max(steps_len, __shfl_xor(steps_len, off, kWave));
-      steps_len = __builtin_amdgcn_readfirstlane(steps_len);  // (what follows is the wave's then: scalar counts)
-      auto walk_again = [&](int eb, bool all_near) __attribute__((always_inline)) {
-        const int e = slow + eb + sub;
-        int c = -1;
-        float xv = 0.f;
-        if (contrib[0] && e < len) {
-          c = CSR ? a.col[e0 + e] : e;
-          xv = CSR ? (a.val ? a.val[e0 + e] : 1.f) : a.x[e0 + e];
+        for (int off = GL; off < kWave; off <<= 1) steps_len = max(steps_len, __shfl_xor(steps_len, off, kWave));
+        steps_len = __builtin_amdgcn_readfirstlane(steps_len);  // (what follows is the wave's then: scalar counts)
+        auto walk_again = [&](int eb, bool all_near) __attribute__((always_inline)) {
+          const int e = slow + eb + sub;
+          int c = -1;
+          float xv = 0.f, ta, tb;
+          uint64_t miss;
+          if ((has_w[0] || has_p[0]) && e < len) {
+            c = CSR ? a.col[e0 + e] : e;
+            xv = CSR ? (a.val ? a.val[e0 + e] : 1.f) : a.x[e0 + e];
+          }
+          scatter(std::integral_constant<int, 1>{}, &c, &xv, 0, all_near, &miss, &ta, &tb);
+          if (!all_near) append(std::integral_constant<int, 1>{}, &miss, &c, &ta, &tb);
+        };
+        if constexpr (CSR) {
+          for (int eb = 0; eb < steps_len; eb += GL) walk_again(eb, NEAR);
+        } else {
+          int eb = 0;
+          for (; eb < min(steps_len, D); eb += GL) walk_again(eb, true);
+          for (; eb < steps_len; eb += GL) walk_again(eb, false);
         }
-        scatter(std::integral_constant<int, 1>{}, &c, &xv, 0, all_near);
-      };
-      if constexpr (CSR) {
-        for (int eb = 0; eb < steps_len; eb += GL) walk_again(eb, a.d <= D);
-      } else {
-        int eb = 0;
-        for (; eb < min(steps_len, D); eb += GL) walk_again(eb, true);
-        for (; eb < steps_len; eb += GL) walk_again(eb, false);
       }
     }
   }
@@ -689,7 +809,7 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
   // slot's sum must leave the block without rounding: as up to three records, floats that add up
   // to the double exactly (24 bits each; the sums are multiples of the smallest float).
   static_assert(H % kGradThreads == 0, "whole turns of the block");
-  for (int turn = 0; a.d > D && turn < H / kGradThreads; ++turn) {
+  for (int turn = 0; !NEAR && a.d > D && turn < H / kGradThreads; ++turn) {
     const int k = turn * kGradThreads + threadIdx.x;
     int c = s_tag[k];
     double va = s_sum[D + k], vb = TWO ? s_sum[(D + H) + D + k] : 0.0;
@@ -697,7 +817,7 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
       add_global<SVM, ASSIST>(a, c, va, vb);
       c = -1;
     }
-    bool want[3];
+    uint64_t want[3];
     int cols[3];
     float ta[3], tb[3];
 #pragma unroll
@@ -707,7 +827,7 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
       va -= (double)ta[part];
       vb -= (double)tb[part];
       cols[part] = c;
-      want[part] = c >= 0 && (ta[part] != 0.f || tb[part] != 0.f);
+      want[part] = __ballot(c >= 0 && (ta[part] != 0.f || tb[part] != 0.f));
     }
     append(std::integral_constant<int, 3>{}, want, cols, ta, tb);
   }
@@ -717,11 +837,11 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
     mine[k] = (float)s_sum[k];
     if (TWO) mine[a.head + k] = (float)s_sum[(D + H) + k];
   }
-  if (!binned) return;
+  if (NEAR || !binned) return;
   __syncthreads();
   // The records in LDS go to the bins, a run per bin (one integer atomic per block and bin reserves the space); one
   // that finds its bin full joins the late ones.
-  const int n = min(s_nrec, cap);
+  const int n = min(s_nrec[0], cap);
   int beyond = max(n - held, 0);
   {
     const int m = min(n, held);
@@ -1683,28 +1803,40 @@ __global__ __launch_bounds__(kApplyThreads) void k_apply_general(const ApplyArgs
   }
 }
 
+// A model that fits a gradient pass's table takes kernels without tags, records and gathers.
+template <int GL, bool CSR, int MODE>
+void launch_grad(const GenArgs &a, int nblk, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
+  constexpr bool TWO = (MODE & kSvm) != 0 && (MODE & kAssist) != 0;
+  if constexpr (CSR) {
+    if (a.d <= (TWO ? kDirectTwoVec : kDirectOneVec)) {
+      launch_stamped((k_rows_grad<GL, MODE, true, true>), dim3(nblk), dim3(kGradThreads), st, e0, e1, a);
+      return;
+    }
+  }
+  launch_stamped((k_rows_grad<GL, MODE, CSR, false>), dim3(nblk), dim3(kGradThreads), st, e0, e1, a);
+}
+
 template <int GL, bool CSR>
 hipError_t launch_gl(const GenArgs &a, int mode, int nblk, hipStream_t st, hipEvent_t e0,
                      hipEvent_t e1) {
-  const dim3 grid(nblk), block(mode == kPool ? kPoolThreads : kGradThreads);
   switch (mode) {
     case kPool:
-      launch_stamped((k_rows_general<GL, CSR>), grid, block, st, e0, e1, a);
+      launch_stamped((k_rows_general<GL, CSR>), dim3(nblk), dim3(kPoolThreads), st, e0, e1, a);
       break;
     case kSvm:
-      launch_stamped((k_rows_grad<GL, kSvm, CSR>), grid, block, st, e0, e1, a);
+      launch_grad<GL, CSR, kSvm>(a, nblk, st, e0, e1);
       break;
     case kAssist:
-      launch_stamped((k_rows_grad<GL, kAssist, CSR>), grid, block, st, e0, e1, a);
+      launch_grad<GL, CSR, kAssist>(a, nblk, st, e0, e1);
       break;
     case kSvm | kAssist:
-      launch_stamped((k_rows_grad<GL, kSvm | kAssist, CSR>), grid, block, st, e0, e1, a);
+      launch_grad<GL, CSR, kSvm | kAssist>(a, nblk, st, e0, e1);
       break;
     case kPool | kSvm | kAssist:
-      launch_stamped((k_rows_grad<GL, kPool | kSvm | kAssist, CSR>), grid, block, st, e0, e1, a);
+      launch_grad<GL, CSR, kPool | kSvm | kAssist>(a, nblk, st, e0, e1);
       break;
     case kPool | kSvm | kHard:
-      launch_stamped((k_rows_grad<GL, kPool | kSvm | kHard, CSR>), grid, block, st, e0, e1, a);
+      launch_grad<GL, CSR, kPool | kSvm | kHard>(a, nblk, st, e0, e1);
       break;
     default:
       return hipErrorInvalidValue;
