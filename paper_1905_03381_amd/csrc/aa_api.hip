@@ -28,6 +28,7 @@ namespace {
 
 constexpr int kCtlUpdateSnapshot = 0;  // control word: update counter before the running step
 constexpr int kCtlThresholdNext = 1;   // control word: the running threshold a pass worked out (a float)
+constexpr int kCtlTeamShut = 2;        // control word: see k_team_reset
 
 struct Ws {
   char *base;
@@ -1188,7 +1189,7 @@ static int32_t epoch_impl(const aa_features *F, const float *y, const int32_t *p
   probe.count_max = P;
   // (armed timing hooks stand for one launch per step)
   if (g_hook_left == 0 && use_fast(probe) && small_epoch_ok(F->d, F->ld, P)) {
-    const Ws w_small = carve(ws, grad_bytes_for(probe), P, true);
+    Ws w_small = carve(ws, grad_bytes_for(probe), P, true);
     if (int32_t rc = check_ws(ws, ws_bytes, w_small.total)) return rc;
     SmallEpochArgs a{};
     a.x = F->x;
@@ -1211,6 +1212,14 @@ static int32_t epoch_impl(const aa_features *F, const float *y, const int32_t *p
     a.lr_a = cfg->lr_a;
     a.l2_a = cfg->l2_a;
     a.t_upd = t_upd;
+    // (a workspace without room for the team's words has one block do the epoch)
+    const size_t sums = grad_bytes_for(probe), words = small_epoch_words_bytes();
+    const Ws w_team = carve(ws, words > sums ? words : sums, P, true);
+    if (check_ws(ws, ws_bytes, w_team.total) == AA_OK) {
+      w_small = w_team;
+      a.words = reinterpret_cast<uint64_t *>(w_team.grad);
+      a.shut = w_team.ctl + kCtlTeamShut;
+    }
     a.kept_pos = w_small.kept_pos;
     a.prob = hard ? nullptr : w_small.prob;
     a.flags = w_small.flags;

@@ -1,10 +1,24 @@
-// Epochs over small pools: one block of 16 waves runs the steps one after the other.
+// Epochs over small pools: 16 waves run the steps one after the other, in one block or in a team of four.
 //
 // A pool of 256 rows of 128 floats is 128 KB: a step of two launches spends its 9 us on two kernel
 // boundaries and on chains of round trips, not on reading.  Here the model stays in LDS, the
 // next pool's rows are requested into a second set of registers while this one's are used, and
 // nothing waits for another compute unit.  What bounds it then: one compute unit's share of the
 // memory system (about 28 bytes per ns) for pools near the limit, the waves' arithmetic below.
+//
+// In a team every wave has a SIMD to itself (nearly), and four compute units read: an epoch of 40 pools of 256 x 128
+// 192 -> 118 us.  The waves' gradient sums, added up by fours in each block, then go through memory, each in a
+// 64-bit word with the step's number beside it, stored and read with relaxed device-scope atomics: a reader takes a word
+// whose number is the step's and asks again otherwise, so nothing has to be ordered or counted.  (Four blocks that read
+// 256 words of each other: 0.7 to 1.0 us a round; every wave's sums without the additions, four times the words, 3.)
+// Every block adds all sums up, in the order of the single block, and updates a model of its own: the same bits.  A word
+// has two places, for odd and even steps: a block writes step t + 2's sums when it has read all of step t + 1's, which the
+// others wrote after they had read step t's.  Waves of their own do the reading: loads return in order, and a wave with
+// the next rows on their way would wait for those first.
+// The blocks of a team have to run at once.  k_team_reset clears words and gate ahead of the launch; a block counts
+// itself in, the last one opens the gate, and nobody publishes before it is open.  A block that has waited past its
+// limit shuts the gate for good; all of them leave then, and the launch behind, which has nothing to do otherwise, does the
+// epoch with one block.
 #include "aa_small.hpp"
 
 namespace aa {
@@ -12,6 +26,38 @@ namespace aa {
 namespace {
 
 constexpr int kSmallWaves = 16, kSmallTurns = 8;
+constexpr int kTeamBlocks = 4, kTeamWaves = kSmallWaves / kTeamBlocks;  // row waves of a block, and as many others
+constexpr int kGateWords = 16;  // 64-bit words in front: blocks that are there, state of the gate
+constexpr int kTeamExtra = 16;  // words behind a block's sums: its waves' kept rows (a byte each), bias gradient, nothing
+enum Gate : int { kGateOpen = 1, kGateShut = 2, kGateLost = 3 };
+// 100 MHz ticks: until the gate opens (some milliseconds, different from call to call), and for a word once it is
+// (whoever is waited for runs then: this ends a wait that could not end otherwise)
+constexpr long long kGateTicks = 200000, kWordTicks = 200000000;
+
+constexpr size_t team_words(int cols) { return kGateWords + 2 * (size_t)kTeamBlocks * (cols + kTeamExtra); }
+
+__device__ __forceinline__ uint64_t word_of(uint32_t v, int tag) { return ((uint64_t)(uint32_t)tag << 32) | v; }
+__device__ __forceinline__ uint64_t load_word(const uint64_t *p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void store_word(uint64_t *p, uint64_t v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ int tag_of(uint64_t w) { return (int)(w >> 32); }
+__device__ __forceinline__ float value_of(uint64_t w) { return __uint_as_float((uint32_t)w); }
+__device__ __forceinline__ int load_gate(const int32_t *state) {
+  return __hip_atomic_load(state, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void move_gate(int32_t *state, int to) {
+  int closed = 0;
+  __hip_atomic_compare_exchange_strong(state, &closed, to, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// (a control word of kGateShut has one block do the epochs: for tests)
+__global__ __launch_bounds__(256) void k_team_reset(uint64_t *words, int count, const int32_t *shut) {
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < count; i += gridDim.x * blockDim.x)
+    words[i] = i == 0 && *shut == kGateShut ? (uint64_t)kGateShut << 32 : 0;
+}
 
 // lane I of every 16, in all 16
 template <int I>
@@ -24,12 +70,96 @@ struct Turn {
   static constexpr int value = I;
 };
 
+// What a wave works out from its rows of a pool.
+struct RowSums {
+  float g, loss, gb;  // (g and loss: lane i of every 16 (of LPR) for turn i's row, i < 8)
+  bool keep;
+  int kept;
+  f4 gw, gp;          // the sums of this lane's columns, in all lane groups
+};
+
+// The rows' part of a step: x: the wave's turns; `own`: the lane holds columns; cnt rows; u_of(i): row i's draw.
+template <int LPR, bool HARD, int IT, class Draw>
+__device__ __forceinline__ RowSums small_rows(const SmallEpochArgs &a, f4 (&x)[IT], float y, bool own, const f4 &mw,
+                                              const f4 &mp, float b, float T, int cnt, Draw u_of) {
+  constexpr int G = kWave / LPR;
+  const f4 zero4 = {0.f, 0.f, 0.f, 0.f};
+  const int lane = threadIdx.x & 63, sub = lane % LPR;
+  RowSums out;
+  // dot products: turn it's in lane it (Assistant) and lane 8 + it (Boss) of every 16
+  float v = 0.f;
+#pragma unroll
+  for (int it = 0; it < IT; ++it) {
+    if (!own) x[it] = zero4;
+    if (!HARD) {
+      const float dp = row_group_sum<16>(dot4(x[it], mp, 0.f), lane);
+      v = (lane & 15) == it ? dp : v;
+    }
+    const float dw = row_group_sum<16>(dot4(x[it], mw, 0.f), lane);
+    v = (lane & 15) == 8 + it ? dw : v;
+  }
+  if (LPR >= 32) v += __shfl_xor(v, 16, kWave);
+  if (LPR >= 64) v += __shfl_xor(v, 32, kWave);
+  const float other = __shfl_xor(v, 8, kWave);
+  const float dot_p = (lane & 8) ? other : v, dot_w = (lane & 8) ? v : other;
+
+  // lane `it` (and 8 + it) of every 16 goes on with row it * G + grp
+  int me = lane;
+  asm volatile("" : "+v"(me));  // (worked out here, not kept in a register across the steps)
+  const int li = (me & 7) * G + me / LPR;
+  const bool live = li < cnt;
+  const float yy = __shfl(y, li & 63, kWave);
+  out.g = 0.f;
+  out.keep = live;
+  if (!HARD) {
+    out.g = sigmoidf_(dot_p + b);
+    const float u = u_of(li);  // (every lane takes part)
+    out.keep = live && keep_decision(u, out.g, a.gamma, a.one_minus_gamma);
+  }
+  const float marg = yy * dot_w;
+  out.loss = fmaxf(0.f, 1.f - marg);
+  if (HARD) out.keep = live && out.loss > T;  // shrinking by the objective value itself
+  const float cw = (out.keep && marg < 1.f) ? yy : 0.f;  // -d hinge / d margin, times y
+  const float resid = !HARD && out.keep ? out.g - (out.loss > T ? 1.f : 0.f) : 0.f;  // label: Boss loss above T
+  const bool once = sub < 8;  // (the lanes that stand for a row)
+  out.kept = __popcll(__ballot(out.keep && once));
+  out.gb = HARD ? 0.f : row_group_sum<kWave>(once ? resid : 0.f, lane);
+
+  f4 gw = zero4, gp = zero4;
+  // With a wave per row, a rejected row and a turn past the share add nothing at all, as in a single
+  // step: zero times an infinite feature would be a NaN.  (Bit i: turn i's row counts.)  Steps of 128
+  // rows of 256 floats 4.48 us with every turn added, 4.32 so.  Elsewhere the steps this
+  // stands for add every row, and so does it.
+  constexpr bool SKIP = LPR == kWave && !HARD;
+  const uint32_t counts = SKIP ? (uint32_t)__ballot(out.keep && once) : ~0u;
+  auto turn = [&](auto it) __attribute__((always_inline)) {
+    constexpr int i = decltype(it)::value;
+    if constexpr (i < IT) {
+      if (SKIP && !((counts >> i) & 1u)) return;
+      gw = axpy4(row_bcast<i>(cw), x[i], gw);
+      if (!HARD) gp = axpy4(row_bcast<i>(resid), x[i], gp);
+    }
+  };
+  turn(Turn<0>{}), turn(Turn<1>{}), turn(Turn<2>{}), turn(Turn<3>{});
+  turn(Turn<4>{}), turn(Turn<5>{}), turn(Turn<6>{}), turn(Turn<7>{});
+  if (LPR < kWave) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      gw[i] = fold_groups<LPR>(gw[i]);
+      if (!HARD) gp[i] = fold_groups<LPR>(gp[i]);
+    }
+  }
+  out.gw = gw;
+  out.gp = gp;
+  return out;
+}
+
 // LPR lanes hold a row (up to 4 LPR floats), a wave takes up to IT (at most kSmallTurns) turns of 64 / LPR rows.
 // Per row only the 128-bit products run in all lanes; a turn's two dot products end in one lane
 // of every 16 and what follows from them (sigmoid, draw, loss, coefficients) is worked out for
 // all rows of the wave at once.
-// Per step, two launches / this: 256 rows of 128 floats 9.0 / 4.8 us (hard thresholds 8.0 / 3.1),
-// 100 of 64 9.0 / 3.2 (7.8 / 2.0), 20 of 256 9.1 / 2.7 (7.8 / 1.5).  The limit is what the
+// Per step, two launches / this (a team is faster, see launch_team): 256 rows of 128 floats 9.0 / 4.8 us (hard
+// thresholds 8.0 / 3.1), 100 of 64 9.0 / 3.2 (7.8 / 2.0), 20 of 256 9.1 / 2.7 (7.8 / 1.5).  The limit is what the
 // registers hold twice, 128 KB of rows; past it a compute unit's reads alone take as long as the
 // two launches.
 template <int LPR, bool HARD, int IT>
@@ -45,9 +175,9 @@ __global__ __launch_bounds__(kSmallWaves * 64)
   __shared__ float s_gb[NW];
   __shared__ float s_u[2][HARD ? 1 : kRows];  // draws of this step and the next
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (a.words && load_gate(reinterpret_cast<const int32_t *>(a.words) + 1) != kGateShut) return;  // (the team did it)
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int grp = lane / LPR, sub = lane % LPR;
-  const f4 zero4 = {0.f, 0.f, 0.f, 0.f};
   const int piece = min(sub, a.d4 - 1);  // (lanes past the row re-read its last piece and are masked)
   const bool own = sub < a.d4;
 
@@ -137,68 +267,13 @@ __global__ __launch_bounds__(kSmallWaves * 64)
     request(t + 1, id_next, xn, yn);
     const f4 mw = s_model[0][sub], mp = s_model[NVEC - 1][sub];
 
-    // dot products: turn it's in lane it (Assistant) and lane 8 + it (Boss) of every 16
-    float v = 0.f;
-#pragma unroll
-    for (int it = 0; it < IT; ++it) {
-      if (!own) x[it] = zero4;
-      if (!HARD) {
-        const float dp = row_group_sum<16>(dot4(x[it], mp, 0.f), lane);
-        v = (lane & 15) == it ? dp : v;
-      }
-      const float dw = row_group_sum<16>(dot4(x[it], mw, 0.f), lane);
-      v = (lane & 15) == 8 + it ? dw : v;
-    }
-    if (LPR >= 32) v += __shfl_xor(v, 16, kWave);
-    if (LPR >= 64) v += __shfl_xor(v, 32, kWave);
-    const float other = __shfl_xor(v, 8, kWave);
-    const float dot_p = (lane & 8) ? other : v, dot_w = (lane & 8) ? v : other;
-
-    // lane `it` (and 8 + it) of every 16 goes on with row it * G + grp
-    int me = lane;
-    asm volatile("" : "+v"(me));  // (as below)
-    const int li = (me & 7) * G + me / LPR;
-    const bool live = li < sh.cnt;
-    const float yy = __shfl(y, li & 63, kWave);
-    float g = 0.f;
-    bool keep = live;
-    if (!HARD) {
-      g = sigmoidf_(dot_p + b);
-      keep = live && keep_decision(s_u[t & 1][min(sh.lo + li, kRows - 1)], g, a.gamma, a.one_minus_gamma);
-    }
-    const float marg = yy * dot_w;
-    const float loss = fmaxf(0.f, 1.f - marg);
-    if (HARD) keep = live && loss > T;  // shrinking by the objective value itself
-    const float cw = (keep && marg < 1.f) ? yy : 0.f;  // -d hinge / d margin, times y
-    const float resid = !HARD && keep ? g - (loss > T ? 1.f : 0.f) : 0.f;  // label: Boss loss above T
-    const bool once = sub < 8;  // (the lanes that stand for a row)
-    const int kept = __popcll(__ballot(keep && once));
-    const float gb = HARD ? 0.f : row_group_sum<kWave>(once ? resid : 0.f, lane);
-
-    f4 gw = zero4, gp = zero4;
-    // With a wave per row, a rejected row and a turn past the share add nothing at all, as in a single
-    // step: zero times an infinite feature would be a NaN.  (Bit i: turn i's row counts.)  Steps of 128
-    // rows of 256 floats 4.48 us with every turn added, 4.32 so.  Elsewhere the steps this
-    // stands for add every row, and so does it.
-    constexpr bool SKIP = LPR == kWave && !HARD;
-    const uint32_t counts = SKIP ? (uint32_t)__ballot(keep && once) : ~0u;
-    auto turn = [&](auto it) __attribute__((always_inline)) {
-      constexpr int i = decltype(it)::value;
-      if constexpr (i < IT) {
-        if (SKIP && !((counts >> i) & 1u)) return;
-        gw = axpy4(row_bcast<i>(cw), x[i], gw);
-        if (!HARD) gp = axpy4(row_bcast<i>(resid), x[i], gp);
-      }
-    };
-    turn(Turn<0>{}), turn(Turn<1>{}), turn(Turn<2>{}), turn(Turn<3>{});
-    turn(Turn<4>{}), turn(Turn<5>{}), turn(Turn<6>{}), turn(Turn<7>{});
-    if (LPR < kWave) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        gw[i] = fold_groups<LPR>(gw[i]);
-        if (!HARD) gp[i] = fold_groups<LPR>(gp[i]);
-      }
-    }
+    const RowSums rs = small_rows<LPR, HARD, IT>(a, x, y, own, mw, mp, b, T, sh.cnt, [&](int li) __attribute__((always_inline)) {
+      return s_u[t & 1][min(sh.lo + li, kRows - 1)];
+    });
+    const bool keep = rs.keep;
+    const float loss = rs.loss, g = rs.g, gb = rs.gb;
+    const int kept = rs.kept;
+    const f4 gw = rs.gw, gp = rs.gp;
     if (lane < LPR) {
       s_red[wave][0][lane] = gw;
       if (!HARD) s_red[wave][NVEC - 1][lane] = gp;
@@ -212,12 +287,14 @@ __global__ __launch_bounds__(kSmallWaves * 64)
 
     int m = 0, before = 0;
     float gbs = 0.f;
+    float four = 0.f;  // (four waves, then the fours: the order of a team)
 #pragma unroll
     for (int i = 0; i < NW; ++i) {
       const int c = s_cnt[i];
       before += i < wave ? c : 0;
       m += c;
-      gbs += s_gb[i];
+      four = i % kTeamWaves == 0 ? s_gb[i] : four + s_gb[i];
+      if (i % kTeamWaves == kTeamWaves - 1) gbs += four;
     }
     m = __builtin_amdgcn_readfirstlane(m);
     before = __builtin_amdgcn_readfirstlane(before);
@@ -228,9 +305,13 @@ __global__ __launch_bounds__(kSmallWaves * 64)
       const float lr = a.t_upd ? a.lr / sqrtf((float)t_now) : a.lr;
       if (column) {
         const float *red = reinterpret_cast<const float *>(s_red);
-        float gsum = 0.f;
+        float gsum = 0.f, four = 0.f;
 #pragma unroll
-        for (int i = 0; i < NW; ++i) gsum += red[(i * NVEC + vec) * ROW + col];
+        for (int i = 0; i < NW; ++i) {
+          const float r = red[(i * NVEC + vec) * ROW + col];
+          four = i % kTeamWaves == 0 ? r : four + r;
+          if (i % kTeamWaves == kTeamWaves - 1) gsum += four;
+        }
         if (vec == 0)
           mine = __fmaf_rn(lr * inv_m, gsum, (1.f - lr * a.lambda) * mine);
         else
@@ -275,17 +356,307 @@ __global__ __launch_bounds__(kSmallWaves * 64)
   }
 }
 
+// The same in a team: waves 0 to 3 of a block are row waves (of the 16: 4 blockIdx.x + wave), the others read what all
+// blocks have published, update the model and hand it over at the second barrier of a step.
+// What bounds it, 256 rows of 128 floats, 2.9 us a step: the chain of dot products, coefficients and sums of a wave's eight turns
+// (0.9), the words' way to the other blocks and back (1.1), the update (0.3), barriers; meanwhile a row wave stores the
+// last step's outputs, requests rows two steps ahead and draws (1.4).
+template <int LPR, bool HARD, int IT>
+__global__ __launch_bounds__(2 * kTeamWaves * 64)
+    __attribute__((amdgpu_waves_per_eu(2, 2))) void k_team_epoch(const SmallEpochArgs a) {
+  constexpr int NW = kSmallWaves, G = kWave / LPR, ROW = 4 * LPR, NVEC = HARD ? 1 : 2, COLS = NVEC * ROW;
+  constexpr int NT = kTeamWaves * 64, PER = (COLS + NT - 1) / NT;  // readers, columns of a reader
+  constexpr int kStride = COLS + kTeamExtra;
+  constexpr int kTeamNap = PER == 1 ? 6 : 1;  // between requests for words, in 64 cycles: 0 to 12 within 3 % for one column a reader
+  __shared__ f4 s_model[NVEC][LPR], s_red[kTeamWaves][NVEC][LPR];
+  __shared__ int s_before[2][kTeamWaves], s_kept[kTeamWaves], s_state;
+  __shared__ float s_b, s_gb[kTeamWaves];
+  const int tid = threadIdx.x, lane = tid & 63, in_block = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int32_t *const gate = reinterpret_cast<int32_t *>(a.words);
+  if (tid < COLS) {
+    const int col = tid % ROW;
+    reinterpret_cast<float *>(s_model)[tid] = col < a.d ? (tid < ROW ? a.w : a.phi)[col] : 0.f;
+  }
+  auto pool_rows = [&](int t) { return (int)min((int64_t)a.P, a.n_perm - (int64_t)t * a.P); };
+
+  if (in_block < kTeamWaves) {
+    const int wave = blockIdx.x * kTeamWaves + in_block, grp = lane / LPR, sub = lane % LPR;
+    const int piece = min(sub, a.d4 - 1);  // (lanes past the row re-read its last piece and are masked)
+    const bool own = sub < a.d4;
+    const float T = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(*a.T)));
+    struct Share {
+      int lo, cnt;
+    };
+    auto share_of = [&](int t) {  // as in k_small_epoch
+      const int total = pool_rows(t), per = (total + NW - 1) / NW, lo = min(wave * per, total);
+      return Share{lo, min(per, total - lo)};
+    };
+    auto load_ids = [&](int t) {
+      t = min(t, a.steps - 1);
+      const Share s = share_of(t);
+      return a.perm[(int64_t)t * a.P + min(s.lo + min(lane, max(s.cnt, 1) - 1), pool_rows(t) - 1)];
+    };
+    auto request = [&](int t, int id, f4 (&x)[IT], float &y) __attribute__((always_inline)) {
+      const int last = max(share_of(min(t, a.steps - 1)).cnt, 1) - 1;
+      y = a.y[id];
+#pragma unroll
+      for (int it = 0; it < IT; ++it) {
+        const int row = __shfl(id, min(it * G + grp, last), kWave);
+        x[it] = reinterpret_cast<const f4 *>(a.x + (uint64_t)(uint32_t)row * (uint32_t)a.ld)[piece];
+      }
+    };
+    auto draw_of = [&](int t) __attribute__((always_inline)) {  // (a wave has fewer rows than lanes)
+      const uint64_t st = a.step + (uint64_t)t;
+      const int lo = share_of(min(t, a.steps - 1)).lo;
+      return HARD ? 2.f : keep_uniform(DrawKey{a.k0, a.k1, (uint32_t)st, (uint32_t)(st >> 32)}, (uint32_t)(lo + lane));
+    };
+    // outputs of the step before, one row per lane
+    int o_lo = 0, o_cnt = 0, o_id = 0;
+    bool o_keep = false;
+    float o_loss = 0.f, o_prob = 0.f;
+    int32_t *ids = a.ids;
+    float *losses = a.loss;
+    auto put = [&](int before) __attribute__((always_inline)) {  // (before: kept rows ahead of this wave's)
+      const unsigned long long mask = __ballot(o_keep);
+      if (lane < o_cnt) {
+        const int j = o_lo + lane;
+        if (!HARD && a.prob) a.prob[j] = o_prob;
+        if (a.flags) a.flags[j] = o_keep ? 1 : 0;
+        if (o_keep) {
+          const int pos = before + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                                                  __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+          if (a.kept_pos) a.kept_pos[pos] = j;
+          if (ids) ids[pos] = o_id;
+          if (losses) losses[pos] = o_loss;
+        }
+      }
+    };
+    // (rows two steps ahead, in the registers of the pool just done; ids three)
+    int id0 = load_ids(0), id1 = load_ids(1), id2 = load_ids(2);
+    f4 xa[IT], xb[IT];
+    float ya, yb, u = draw_of(0);
+    request(0, id0, xa, ya);
+    request(1, id1, xb, yb);
+    __syncthreads();
+    if (s_state != kGateOpen) return;
+    auto step = [&](int t, f4 (&x)[IT], float &y) __attribute__((always_inline)) {
+      const Share sh = share_of(t);
+      const f4 mw = s_model[0][sub], mp = s_model[NVEC - 1][sub];
+      const RowSums rs = small_rows<LPR, HARD, IT>(a, x, y, own, mw, mp, s_b, T, sh.cnt, [&](int li) __attribute__((always_inline)) {
+        return __shfl(u, li & 63, kWave);
+      });
+      if (lane < LPR) {
+        s_red[in_block][0][lane] = rs.gw;
+        if (!HARD) s_red[in_block][NVEC - 1][lane] = rs.gp;
+      }
+      if (lane == 0) {
+        s_kept[in_block] = rs.kept;
+        s_gb[in_block] = rs.gb;
+      }
+      __syncthreads();
+      if (t > 0) {
+        put(s_before[(t - 1) & 1][in_block]);
+        if (ids) ids += a.ids_stride;
+        if (losses) losses += a.loss_stride;
+      }
+      // row `lane` of the wave: what lane (its turn) of its group worked out
+      int here = lane;
+      asm volatile("" : "+v"(here));
+      const int from = (here % G) * LPR + ((here / G) & 7);
+      o_keep = __shfl(rs.keep ? 1 : 0, from, kWave) != 0 && lane < sh.cnt;
+      o_loss = __shfl(rs.loss, from, kWave);
+      o_prob = __shfl(rs.g, from, kWave);
+      o_lo = sh.lo;
+      o_cnt = sh.cnt;
+      o_id = id0;
+      request(t + 2, id2, x, y);
+      id0 = id1;
+      id1 = id2;
+      id2 = load_ids(t + 3);
+      u = draw_of(t + 1);
+      __syncthreads();
+    };
+    for (int t = 0; t < a.steps; t += 2) {
+      step(t, xa, ya);
+      if (t + 1 < a.steps) step(t + 1, xb, yb);
+    }
+    put(s_before[(a.steps - 1) & 1][in_block]);
+  } else {
+    const int rt = tid - NT;
+    bool lost = false;  // a wait has passed its limit: no more waits
+    float b = !HARD && a.bias ? *a.bias : 0.f;
+    int t_now = a.t_upd ? *a.t_upd : 0;
+    float mine[PER];
+#pragma unroll
+    for (int p = 0; p < PER; ++p) {
+      const int c = min(rt + p * NT, COLS - 1), col = c % ROW;
+      mine[p] = col < a.d ? (c < ROW ? a.w : a.phi)[col] : 0.f;
+    }
+    if (rt == 0) {
+      s_b = b;
+      if (__hip_atomic_fetch_add(gate, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == kTeamBlocks - 1)
+        move_gate(gate + 1, kGateOpen);
+      const long long since = wall_clock64(), limit = kGateTicks * (1 + ((since >> 4) & 7));
+      int state;
+      while ((state = load_gate(gate + 1)) == 0)
+        if (wall_clock64() - since > limit) move_gate(gate + 1, kGateShut);
+      s_state = state;
+    }
+    __syncthreads();
+    if (s_state != kGateOpen) return;
+    for (int t = 0; t < a.steps; ++t) {
+      const int tag = t + 1;
+      uint64_t *const words = a.words + kGateWords + (size_t)(t & 1) * kTeamBlocks * kStride;
+      __syncthreads();  // the row waves' sums are in LDS
+      {
+        uint64_t *const to = words + blockIdx.x * kStride;
+        const float *const red = reinterpret_cast<const float *>(s_red);
+#pragma unroll
+        for (int p = 0; p < PER; ++p) {
+          const int c = rt + p * NT;
+          if (c >= COLS) break;
+          float four = red[c];
+#pragma unroll
+          for (int i = 1; i < kTeamWaves; ++i) four += red[i * COLS + c];
+          store_word(to + c, word_of(__float_as_uint(four), tag));
+        }
+        if (rt < 2) {
+          uint32_t kept = 0;
+          float four = s_gb[0];
+#pragma unroll
+          for (int i = 0; i < kTeamWaves; ++i) kept |= (uint32_t)s_kept[i] << (8 * i);
+#pragma unroll
+          for (int i = 1; i < kTeamWaves; ++i) four += s_gb[i];
+          store_word(to + COLS + rt, word_of(rt == 0 ? kept : __float_as_uint(four), tag));
+        }
+      }
+      // (what does not depend on them, while they are on their way)
+      const float lr = a.t_upd ? a.lr / sqrtf((float)(t_now + 1)) : a.lr;
+      float base[PER];
+#pragma unroll
+      for (int p = 0; p < PER; ++p) base[p] = (1.f - lr * a.lambda) * mine[p];
+      // All blocks' kept rows (lane i < 4: block i's) and bias gradients (lane 4 + i), and the sums of this thread's
+      // columns.  Two requests are on their way, a little apart: the words come between 0.4 and 1 us after the block's
+      // own, and a request takes 0.8.
+      struct Words {
+        uint64_t v[PER][kTeamBlocks], e;
+      } first, second;
+      auto request = [&](Words &w) __attribute__((always_inline)) {
+        const uint64_t *from = words;  // (worked out anew in every turn)
+        asm volatile("" : "+s"(from));
+        w.e = load_word(from + (lane & 3) * kStride + COLS + ((lane >> 2) & 1));
+#pragma unroll
+        for (int p = 0; p < PER; ++p)
+#pragma unroll
+          for (int i = 0; i < kTeamBlocks; ++i) w.v[p][i] = load_word(from + i * kStride + min(rt + p * NT, COLS - 1));
+      };
+      auto there = [&](const Words &w) __attribute__((always_inline)) {
+        bool ok = tag_of(w.e) == tag;
+#pragma unroll
+        for (int p = 0; p < PER; ++p)
+#pragma unroll
+          for (int i = 0; i < kTeamBlocks; ++i) ok = ok && tag_of(w.v[p][i]) == tag;
+        return lost || __ballot(!ok) == 0ull;
+      };
+      __builtin_amdgcn_s_sleep(kTeamNap);
+      request(first);
+      const long long since = wall_clock64();
+      for (;;) {
+        __builtin_amdgcn_s_sleep(kTeamNap);
+        request(second);
+        if (there(first)) break;
+        __builtin_amdgcn_s_sleep(kTeamNap);
+        request(first);
+        if (there(second)) {
+          first = second;
+          break;
+        }
+        if (wall_clock64() - since > kWordTicks) {
+          lost = true;
+          __hip_atomic_store(gate + 1, (int)kGateLost, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+      }
+      int m = 0, before = 0;
+      float gbs = 0.f;
+      const float ev = value_of(first.e);
+#pragma unroll
+      for (int i = 0; i < kTeamBlocks; ++i) {
+        const uint32_t four = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)first.e, i);
+#pragma unroll
+        for (int w = 0; w < kTeamWaves; ++w) {
+          const int c = (four >> (8 * w)) & 0xff;
+          m += c;
+          before += i * kTeamWaves + w < (int)blockIdx.x * kTeamWaves + rt ? c : 0;
+        }
+        gbs += lane_read(ev, 4 + i);
+      }
+      if (m > 0) {
+        const float inv_m = 1.f / (float)m;
+        ++t_now;
+#pragma unroll
+        for (int p = 0; p < PER; ++p) {
+          const int c = rt + p * NT;
+          if (c >= COLS || c % ROW >= a.d) continue;
+          float gsum = 0.f;
+#pragma unroll
+          for (int i = 0; i < kTeamBlocks; ++i) gsum += value_of(first.v[p][i]);
+          if (c < ROW)
+            mine[p] = __fmaf_rn(lr * inv_m, gsum, base[p]);
+          else
+            mine[p] = mine[p] - a.lr_a * __fmaf_rn(a.l2_a, mine[p], gsum * inv_m);
+          reinterpret_cast<float *>(s_model)[c] = mine[p];
+        }
+        if (!HARD && a.bias) b = b - a.lr_a * (gbs * inv_m);
+      }
+      if (rt < kTeamWaves) s_before[t & 1][rt] = before;
+      if (rt == 0) {
+        s_b = b;
+        if (blockIdx.x == 0 && a.kept_hist) a.kept_hist[t] = m;
+      }
+      __syncthreads();
+    }
+    if (blockIdx.x == 0) {
+      const bool void_ = load_gate(gate + 1) == kGateLost;  // (nothing here can be trusted, and it shows)
+      for (int c = rt; c < COLS; c += NT) {
+        const int col = c % ROW;
+        if (col < a.d)
+          (c < ROW ? a.w : a.phi)[col] = void_ ? __int_as_float(0x7fc00000) : reinterpret_cast<const float *>(s_model)[c];
+      }
+      if (rt == 0) {
+        if (!HARD && a.bias) *a.bias = void_ ? __int_as_float(0x7fc00000) : b;
+        if (a.t_upd) *a.t_upd = t_now;
+      }
+    }
+  }
+}
+
+// A team where its exchange costs less than the turns it spares, and over enough steps to make up for its two launches
+// more (5 us).  Microseconds a step, one block / team (40 steps, the launches included): two turns a wave, 64 of 128
+// 3.04 / 2.40, 100 of 64 3.17 / 2.80, 32 of 256 2.89 / 3.06, with hard thresholds 64 of 128 2.00 / 2.09; four, 128 of 128
+// 3.60 / 2.60 (2.28 / 2.06), 64 of 256 3.39 / 3.19 (2.22 / 2.12); eight, 256 of 128 4.82 / 2.96 (3.05 / 2.36), 512 of 64
+// 5.16 / 3.33 (3.31 / 2.41), 128 of 256 4.66 / 3.74 (2.99 / 2.30).
+template <int LPR, bool HARD, int IT>
+hipError_t launch_team(SmallEpochArgs a, hipStream_t st) {
+  bool team = false;
+  if constexpr (IT > 2 || (!HARD && LPR < kWave)) {
+    team = a.words != nullptr && a.steps * IT >= 4 * kSmallTurns;
+    if (team) {
+      const int count = (int)team_words((HARD ? 1 : 2) * 4 * LPR);
+      hipLaunchKernelGGL(k_team_reset, dim3(16), dim3(256), 0, st, a.words, count, a.shut);
+      hipLaunchKernelGGL((k_team_epoch<LPR, HARD, IT>), dim3(kTeamBlocks), dim3(2 * kTeamWaves * 64), 0, st, a);
+    }
+  }
+  if (!team) a.words = nullptr;
+  hipLaunchKernelGGL((k_small_epoch<LPR, HARD, IT>), dim3(1), dim3(kSmallWaves * 64), 0, st, a);
+  return hipGetLastError();
+}
+
 template <int LPR, bool HARD>
 hipError_t launch_turns(const SmallEpochArgs &a, hipStream_t st) {
-  const dim3 grid(1), block(kSmallWaves * 64);
   const int per_turn = kSmallWaves * (kWave / LPR);
-  if (a.P <= 2 * per_turn)
-    hipLaunchKernelGGL((k_small_epoch<LPR, HARD, 2>), grid, block, 0, st, a);
-  else if (a.P <= 4 * per_turn)
-    hipLaunchKernelGGL((k_small_epoch<LPR, HARD, 4>), grid, block, 0, st, a);
-  else
-    hipLaunchKernelGGL((k_small_epoch<LPR, HARD, kSmallTurns>), grid, block, 0, st, a);
-  return hipGetLastError();
+  if (a.P <= 2 * per_turn) return launch_team<LPR, HARD, 2>(a, st);
+  if (a.P <= 4 * per_turn) return launch_team<LPR, HARD, 4>(a, st);
+  return launch_team<LPR, HARD, kSmallTurns>(a, st);
 }
 
 template <int LPR>
@@ -300,6 +671,8 @@ int lanes_per_row(int32_t d) { return d <= 64 ? 16 : d <= 128 ? 32 : 64; }
 bool small_epoch_ok(int32_t d, int64_t ld, int32_t P) {
   return d <= 256 && ld <= 0x7fffffff && P <= kSmallWaves * kSmallTurns * (kWave / lanes_per_row(d));
 }
+
+size_t small_epoch_words_bytes() { return team_words(2 * 4 * kWave) * sizeof(uint64_t); }
 
 hipError_t launch_small_epoch(const SmallEpochArgs &a, bool hard, hipStream_t st) {
   if (!small_epoch_ok(a.d, a.ld, a.P) || a.steps < 1 || a.steps > kSmallEpochSteps) return hipErrorInvalidValue;

@@ -27,12 +27,18 @@ struct SmallEpochArgs {
   float *loss, *prob;
   uint8_t *flags;
   int64_t ids_stride, loss_stride;
+  // what the blocks of a team tell each other, small_epoch_words_bytes() bytes (NULL: no team), and a control word of the
+  // workspace (see k_team_reset)
+  uint64_t *words;
+  const int32_t *shut;
 };
 
 constexpr int kSmallEpochSteps = 1024;  // steps of one launch at most
 
 // True if pools of P rows of d floats (16-byte aligned, d % 4 == 0) fit the registers of a block.
 bool small_epoch_ok(int32_t d, int64_t ld, int32_t P);
+
+size_t small_epoch_words_bytes();
 
 hipError_t launch_small_epoch(const SmallEpochArgs &a, bool hard, hipStream_t stream);
 
