@@ -319,7 +319,7 @@ hipError_t run_pass(const PassSpec &s, const Ws &ws, int32_t *nblk_out, hipStrea
   a.part = reinterpret_cast<float *>(ws.grad + general_part_offset(s.F->d));
   a.head = general_head_columns(s.F->d, nvec, csr);
   a.wp = nvec == 2 ? reinterpret_cast<const float2 *>(ws.grad + general_pairs_offset(s.F->d)) : nullptr;
-  a.bin_fill = reinterpret_cast<unsigned *>(acc + 16);
+  a.bin_fill = reinterpret_cast<unsigned *>(acc + 16 + 3 * kMaxBins);
   a.blk_late = reinterpret_cast<int32_t *>(acc + 16 + kMaxBins);
   a.recs = reinterpret_cast<int32_t *>(ws.grad + general_bins_offset(s.F->d));
   a.runs = reinterpret_cast<int32_t *>(ws.grad + general_runs_offset(s.F->d, s.count_max));
@@ -402,7 +402,7 @@ hipError_t run_update(const PassSpec &s, const UpdateSpec &u, const Ws &ws, int3
   p.part = reinterpret_cast<const float *>(ws.grad + general_part_offset(s.F->d));
   p.nvec = ((s.mode & kSvm) ? 1 : 0) + ((s.mode & kAssist) ? 1 : 0);
   p.head = general_head_columns(s.F->d, p.nvec, s.F->layout == AA_CSR);
-  p.bin_fill = reinterpret_cast<unsigned *>(acc + 16);
+  p.bin_fill = reinterpret_cast<unsigned *>(acc + 16 + 3 * kMaxBins);
   p.blk_late = reinterpret_cast<const int32_t *>(acc + 16 + kMaxBins);
   p.recs = reinterpret_cast<const int32_t *>(ws.grad + general_bins_offset(s.F->d));
   p.runs = reinterpret_cast<const int32_t *>(ws.grad + general_runs_offset(s.F->d, s.count_max));

@@ -216,7 +216,7 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
   float gb = 0.f;
   int kept = 0;
   const int held = binned ? R : 0, cap = held + (binned ? a.plan.pieces * a.plan.piece : 0);
-  int32_t *const late = a.recs + (size_t)a.plan.nb * a.plan.bin_cap * RW;  // records that LDS has no room for
+  int32_t *const late = a.recs + (size_t)a.plan.nb * a.plan.segments * a.plan.seg_cap * RW;  // records that LDS has no room for
   auto piece_at = [&](int piece) { return late + ((size_t)piece * gridDim.x + blockIdx.x) * a.plan.piece * RW; };
   // Late records are stored through a buffer resource: a lane without one gives an offset out of range, and the store
   // needs no branch.  Loads and stores share one counter here: behind a store under a condition the wait for the next
@@ -844,7 +844,7 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
   const int n = min(s_nrec[0], cap);
   int beyond = max(n - held, 0);
   {
-    const int m = min(n, held);
+    const int m = min(n, held), segment = blockIdx.x & (a.plan.segments - 1);
     constexpr int kPer = R / kGradThreads;
     static_assert(R % kGradThreads == 0, "whole turns of the block");
     if (threadIdx.x < kMaxBins) s_hist[threadIdx.x] = 0;
@@ -857,9 +857,10 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
     }
     __syncthreads();
     if ((int)threadIdx.x < a.plan.nb) {
-      const int h = s_hist[threadIdx.x], base = h > 0 ? (int)atomicAdd(a.bin_fill + threadIdx.x, (unsigned)h) : 0;
+      const int h = s_hist[threadIdx.x];
+      const int base = h > 0 ? (int)atomicAdd(a.bin_fill + segment * kMaxBins + threadIdx.x, (unsigned)h) : 0;
       s_base[threadIdx.x] = base;
-      const int over = min(base + h - a.plan.bin_cap, h);
+      const int over = min(base + h - a.plan.seg_cap, h);
       if (over > 0) atomicAdd(&s_more, over);
     }
     __syncthreads();
@@ -871,8 +872,8 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
 #pragma unroll
       for (int w = 0; w < RW; ++w) r[w] = s_held[i * RW + w];
       const int bin = bin_of(r[0], D, a.plan), pos = s_base[bin] + rank[q];
-      if (pos < a.plan.bin_cap) {
-        int32_t *const dst = a.recs + ((size_t)bin * a.plan.bin_cap + pos) * RW;
+      if (pos < a.plan.seg_cap) {
+        int32_t *const dst = a.recs + (((size_t)bin * a.plan.segments + segment) * a.plan.seg_cap + pos) * RW;
 #pragma unroll
         for (int w = 0; w < RW; ++w) dst[w] = r[w];
       } else {
@@ -1488,7 +1489,7 @@ __device__ __forceinline__ void late_records(const ApplyArgs &a, int bin, int n_
   constexpr int kGroups = kApplyThreads / 16, kRuns = 4, kShortRun = 128;
   const int tid = threadIdx.x, grp = tid / 16, sub = tid % 16, nblk = a.nblk_pass;
   const int32_t *const runs = a.runs + (size_t)bin * a.plan.pieces * nblk;
-  const int32_t *const late = a.recs + (size_t)a.plan.nb * a.plan.bin_cap * RW;
+  const int32_t *const late = a.recs + (size_t)a.plan.nb * a.plan.segments * a.plan.seg_cap * RW;
   for (int piece = 0; piece < pieces; ++piece) {
     __syncthreads();
     if (tid < kGeneralGradBlocks) {
@@ -1568,15 +1569,19 @@ __device__ __forceinline__ void apply_bin(const ApplyArgs &a, int bin, double *s
   // 4 * kCol * kApplyThreads covers any bin of a pass that updates two vectors, and half of the
   // largest bin of one that updates one
   constexpr int kRec = 2, kCol = 2;
-  const int tid = threadIdx.x, cols = a.plan.cols, cap = a.plan.bin_cap;
+  const int tid = threadIdx.x, cols = a.plan.cols, cap = a.plan.seg_cap;
   const int cnt = tid < a.nblk_pass ? a.blk_cnt[tid] : 0;
   const int n_mine = tid < a.nblk_pass ? a.blk_late[tid] : 0;
-  const int n = (int)min(a.bin_fill[bin], (unsigned)cap);
+  // a segment a wave, or one for all
+  static_assert(kBinSegments == kApplyWaves, "a segment a wave");
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), segment = a.plan.segments == 1 ? 0 : wave;
+  const int first = a.plan.segments == 1 ? tid : tid & 63, turn = a.plan.segments == 1 ? kApplyThreads : kWave;
+  const int n = (int)min(a.bin_fill[segment * kMaxBins + bin], (unsigned)cap);
   const int acc_used = a.acc_used[bin];
-  const int32_t *const rec = a.recs + (size_t)bin * cap * RW;
+  const int32_t *const rec = a.recs + ((size_t)bin * a.plan.segments + segment) * cap * RW;
   // two register sets, so that the loads of the next batch are in flight while this one is added up
   int r0[kRec][RW], r1[kRec][RW];
-  constexpr int kBatch = kRec * kApplyThreads;
+  const int batch = kRec * turn;
   // (Every load below is unconditional: a load under a condition makes the compiler wait for
   // all loads in flight where the paths join, and the requests would go out one at a time.
   // An index past the end is clamped to the last record, whose value is then not used.)
@@ -1584,7 +1589,7 @@ __device__ __forceinline__ void apply_bin(const ApplyArgs &a, int bin, double *s
 #pragma unroll
     for (int u = 0; u < kRec; ++u)
 #pragma unroll
-      for (int w = 0; w < RW; ++w) r[u][w] = rec[(size_t)min(base + tid + u * kApplyThreads, last) * RW + w];
+      for (int w = 0; w < RW; ++w) r[u][w] = rec[(size_t)min(base + first + u * turn, last) * RW + w];
   };
   load_batch(r0, 0, cap - 1);  // past the fill count: stale, in bounds, not used
   int col[kCol];   // first column of the run, -1: none, or not all four exist (the model's end)
@@ -1626,13 +1631,13 @@ __device__ __forceinline__ void apply_bin(const ApplyArgs &a, int bin, double *s
   auto add_batch = [&](const int (*r)[RW], int base) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < kRec; ++u)
-      if (base + tid + u * kApplyThreads < n) add(r[u]);
+      if (base + first + u * turn < n) add(r[u]);
   };
-  for (int base = 0; base < n; base += 2 * kBatch) {
-    load_batch(r1, base + kBatch, n - 1);
+  for (int base = 0; base < n; base += 2 * batch) {
+    load_batch(r1, base + batch, n - 1);
     add_batch(r0, base);
-    load_batch(r0, base + 2 * kBatch, n - 1);
-    add_batch(r1, base + kBatch);
+    load_batch(r0, base + 2 * batch, n - 1);
+    add_batch(r1, base + batch);
   }
   const int most = max(max(s_late[0], s_late[1]), max(s_late[2], s_late[3]));
   if (most > 0) late_records<RW>(a, bin, n_mine, s_run, s_late, s_long, (most + a.plan.piece - 1) / a.plan.piece, add);
@@ -1717,9 +1722,9 @@ __device__ __forceinline__ void apply_bin(const ApplyArgs &a, int bin, double *s
       if (a.phi) a.acc_p[c] = 0.0;
     }
   }
-  if (a.keep_ready && tid == 0) {  // (read at the top; the next pass counts from zero)
-    a.bin_fill[bin] = 0u;
-    a.acc_used[bin] = 0;
+  if (a.keep_ready && tid < kBinSegments) {  // (read at the top; the next pass counts from zero)
+    a.bin_fill[tid * kMaxBins + bin] = 0u;
+    if (tid == 0) a.acc_used[bin] = 0;
   }
 }
 
