@@ -858,9 +858,10 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
   // The records in LDS go to the bins, a run per bin (one integer atomic per block and bin reserves the space); one
   // that finds its bin full joins the late ones.
   const int n = min(s_nrec[0], cap);
+  const int segment = blockIdx.x & (a.plan.segments - 1);
   int beyond = max(n - held, 0);
   {
-    const int m = min(n, held), segment = blockIdx.x & (a.plan.segments - 1);
+    const int m = min(n, held);
     constexpr int kPer = R / kGradThreads;
     static_assert(R % kGradThreads == 0, "whole turns of the block");
     if (threadIdx.x < kMaxBins) s_hist[threadIdx.x] = 0;
@@ -906,8 +907,11 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
     }
     beyond = min(beyond + s_more, cap - held);
   }
-  // The others, a piece (at most C) at a time, sorted by bin: a counting sort by way of LDS, back to where they
-  // were.  The owner of a bin finds its records of a piece as one run (start, count).
+  // The others, a piece (at most C) at a time, sorted by bin (a counting sort by way of LDS) and on to the bins like
+  // those above.  What a bin has no room for goes back to where it was, and its owner finds it as one run
+  // (start, count) of the piece.  (They all went back: 5.4 M records of 460,000 sentence pairs, their owners' 512 runs of
+  // 41 a bin strewn over 60 MB: update kernel 27.5 us, now 14.2, and this pass 126.3 and 129.6.  The next piece's loads ahead
+  // of the stores: no gain; two bins' places with one atomic: 129.0, but 0.2 us more over small pools.)
   if (threadIdx.x == 0) a.blk_late[blockIdx.x] = beyond;
   int *const s_rec = reinterpret_cast<int *>(s_mem);
   constexpr int kPer = C / kGradThreads;
@@ -932,10 +936,14 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
       if ((int)threadIdx.x + q * kGradThreads < m) rank[q] = atomicAdd(s_hist + bin_of(r[q][0], D, a.plan), 1);
     }
     __syncthreads();
+    const bool owns = (int)threadIdx.x < a.plan.nb;
+    const int h = owns ? s_hist[threadIdx.x] : 0;
+    int to = 0;  // (used after the records have moved in LDS: the round trip is under way meanwhile)
+    if (h > 0) to = (int)atomicAdd(a.bin_fill + segment * kMaxBins + threadIdx.x, (unsigned)h);
     if (wave == 0) {  // four bins a lane
       static_assert(kMaxBins == 4 * kWave, "one wave scans the bins");
-      const int4 h = reinterpret_cast<const int4 *>(s_hist)[lane];
-      const int mine = h.x + h.y + h.z + h.w;
+      const int4 n4 = reinterpret_cast<const int4 *>(s_hist)[lane];
+      const int mine = n4.x + n4.y + n4.z + n4.w;
       int before = mine;
 #pragma unroll
       for (int off = 1; off < kWave; off <<= 1) {
@@ -943,12 +951,9 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
         if (lane >= off) before += v;
       }
       before -= mine;
-      reinterpret_cast<int4 *>(s_base)[lane] = make_int4(before, before + h.x, before + h.x + h.y, before + h.x + h.y + h.z);
+      reinterpret_cast<int4 *>(s_base)[lane] = make_int4(before, before + n4.x, before + n4.x + n4.y, before + n4.x + n4.y + n4.z);
     }
     __syncthreads();
-    if ((int)threadIdx.x < a.plan.nb)
-      a.runs[((size_t)threadIdx.x * a.plan.pieces + piece) * gridDim.x + blockIdx.x] =
-          s_base[threadIdx.x] | (s_hist[threadIdx.x] << 16);
 #pragma unroll
     for (int q = 0; q < kPer; ++q) {
       if (q * kGradThreads >= m) break;
@@ -959,9 +964,22 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
       }
     }
     __syncthreads();
-    // whole 128-bit words (a piece is a multiple of four records)
-    for (int i = threadIdx.x; 4 * i < m * RW; i += kGradThreads)
-      reinterpret_cast<int4 *>(src)[i] = reinterpret_cast<const int4 *>(s_rec)[i];
+    if (owns) {
+      const int start = s_base[threadIdx.x], fit = min(max(a.plan.seg_cap - to, 0), h);
+      a.runs[((size_t)threadIdx.x * a.plan.pieces + piece) * gridDim.x + blockIdx.x] = (start + fit) | ((h - fit) << 16);
+      s_hist[threadIdx.x] = to - start;  // (place in the bin less place in the piece)
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < m; i += kGradThreads) {
+      int r[RW];
+#pragma unroll
+      for (int w = 0; w < RW; ++w) r[w] = s_rec[i * RW + w];
+      const int bin = bin_of(r[0], D, a.plan), pos = i + s_hist[bin];
+      int32_t *const dst =
+          pos < a.plan.seg_cap ? a.recs + (((size_t)bin * a.plan.segments + segment) * a.plan.seg_cap + pos) * RW : src + i * RW;
+#pragma unroll
+      for (int w = 0; w < RW; ++w) dst[w] = r[w];
+    }
   }
 }
 
@@ -1494,7 +1512,7 @@ __device__ __forceinline__ int bin_column(int k, int bin, const ApplyArgs &a) {
   return a.head + ((g << gl) | (k & ((1 << gl) - 1)));
 }
 
-// The records of a bin that did not fit into a block's LDS: a run in every sorted piece of every block.
+// The late records of a bin that it had no room for: a run in every sorted piece of every block.
 // Sixteen lanes read a run, four runs of a lane group in flight together, two records a lane of each.  What a run has
 // beyond four times the average (of 64 runs, and beyond kShortRun) the whole block reads, run after run: a frequent
 // column that found no slot in one block makes one run of thousands, which sixteen lanes walked alone (256 rows of
@@ -1578,9 +1596,9 @@ __device__ __forceinline__ void late_records(const ApplyArgs &a, int bin, int n_
 template <int RW>
 __device__ __forceinline__ void apply_bin(const ApplyArgs &a, int bin, double *s_bin, int *s_m,
                                           float *s_g, int *s_run, int *s_late,
-                                          unsigned long long *s_long) {
-  // per thread: kRec records per batch (the first batch is requested before the bin's fill count
-  // is known: 1024 records a bin; with 4096, small pools read megabytes of stale ones); kCol runs
+                                          unsigned long long *s_long, int *s_over) {
+  // per thread: kRec records of the first batch, which is requested before the bin's fill count
+  // is known (1024 records a bin; with 4096, small pools read megabytes of stale ones); kCol runs
   // of four columns (a bin's columns come in groups of at least four neighbours) --
   // 4 * kCol * kApplyThreads covers any bin of a pass that updates two vectors, and half of the
   // largest bin of one that updates one
@@ -1592,11 +1610,11 @@ __device__ __forceinline__ void apply_bin(const ApplyArgs &a, int bin, double *s
   static_assert(kBinSegments == kApplyWaves, "a segment a wave");
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), segment = a.plan.segments == 1 ? 0 : wave;
   const int first = a.plan.segments == 1 ? tid : tid & 63, turn = a.plan.segments == 1 ? kApplyThreads : kWave;
-  const int n = (int)min(a.bin_fill[segment * kMaxBins + bin], (unsigned)cap);
+  const unsigned offered = a.bin_fill[segment * kMaxBins + bin];
+  const int n = (int)min(offered, (unsigned)cap);
   const int acc_used = a.acc_used[bin];
   const int32_t *const rec = a.recs + ((size_t)bin * a.plan.segments + segment) * cap * RW;
-  // two register sets, so that the loads of the next batch are in flight while this one is added up
-  int r0[kRec][RW], r1[kRec][RW];
+  int r0[kRec][RW];
   const int batch = kRec * turn;
   // (Every load below is unconditional: a load under a condition makes the compiler wait for
   // all loads in flight where the paths join, and the requests would go out one at a time.
@@ -1636,6 +1654,7 @@ __device__ __forceinline__ void apply_bin(const ApplyArgs &a, int bin, double *s
     if ((tid & 63) == 0) s_late[tid >> 6] = most;
   }
   float gb_unused;
+  if ((tid & 63) == 0) s_over[wave] = offered > (unsigned)cap;
   const int m = pass_totals(a, cnt, 0.f, s_m, s_g, &gb_unused);  // barrier: the sums are zero
   const Fold fold(a, m);
   auto add = [&](const int *r) __attribute__((always_inline)) {
@@ -1644,19 +1663,53 @@ __device__ __forceinline__ void apply_bin(const ApplyArgs &a, int bin, double *s
     if (ta != 0.f) unsafeAtomicAdd(s_mine + k, (double)ta);
     if (RW == 3 && tb != 0.f) unsafeAtomicAdd(s_mine + cols + k, (double)tb);
   };
-  auto add_batch = [&](const int (*r)[RW], int base) __attribute__((always_inline)) {
-#pragma unroll
-    for (int u = 0; u < kRec; ++u)
-      if (base + first + u * turn < n) add(r[u]);
+  // The records past the first batch: N neighbouring ones a load, kWide loads a lane, the next ones in flight while
+  // these are added up.  (Bins of 21,000: that is what a block's waves need in flight to read them at the rate of memory.)
+  constexpr int N = RW == 2 ? 2 : 1, kWide = 4;
+  const __amdgpu_buffer_rsrc_t r_bin =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t *>(rec), 0, ((n + 1) & ~1) * (4 * RW), 0x00020000);
+  struct Wide {
+    int r[kWide][N][RW];
   };
-  for (int base = 0; base < n; base += 2 * batch) {
-    load_batch(r1, base + batch, n - 1);
-    add_batch(r0, base);
-    load_batch(r0, base + 2 * batch, n - 1);
-    add_batch(r1, base + batch);
+  auto load_wide = [&](int base, Wide &b) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < kWide; ++u) {
+      const int off = (base + N * (first + u * turn)) * (4 * RW);
+      if constexpr (N == 2) {
+        const i4v v = __builtin_bit_cast(i4v, __builtin_amdgcn_raw_buffer_load_b128(r_bin, off, 0, 0));
+#pragma unroll
+        for (int w = 0; w < 4; ++w) b.r[u][w / 2][w % 2] = v[w];
+      } else {
+        const u3v v = __builtin_bit_cast(u3v, __builtin_amdgcn_raw_buffer_load_b96(r_bin, off, 0, 0));
+#pragma unroll
+        for (int w = 0; w < RW; ++w) b.r[u][0][w] = (int)v[w];
+      }
+    }
+  };
+  auto add_wide = [&](int base, const Wide &b) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < kWide; ++u)
+#pragma unroll
+      for (int k = 0; k < N; ++k)
+        if (base + N * (first + u * turn) + k < n) add(b.r[u][k]);
+  };
+  const int wide = kWide * N * turn;
+  Wide b0, b1;
+  load_wide(batch, b0);
+#pragma unroll
+  for (int u = 0; u < kRec; ++u)
+    if (first + u * turn < n) add(r0[u]);
+  for (int base = batch; base < n; base += 2 * wide) {
+    load_wide(base + wide, b1);
+    add_wide(base, b0);
+    load_wide(base + 2 * wide, b0);
+    add_wide(base + wide, b1);
   }
   const int most = max(max(s_late[0], s_late[1]), max(s_late[2], s_late[3]));
-  if (most > 0) late_records<RW>(a, bin, n_mine, s_run, s_late, s_long, (most + a.plan.piece - 1) / a.plan.piece, add);
+  bool over = false;  // (otherwise the bin has had room for all)
+#pragma unroll
+  for (int w = 0; w < kApplyWaves; ++w) over = over || s_over[w] != 0;
+  if (most > 0 && over) late_records<RW>(a, bin, n_mine, s_run, s_late, s_long, (most + a.plan.piece - 1) / a.plan.piece, add);
   __syncthreads();
   auto sum_of = [&](int k) {  // over the copies, in order
     double v = 0.0;
@@ -1752,6 +1805,7 @@ __global__ __launch_bounds__(kApplyThreads) void k_apply_general(const ApplyArgs
   __shared__ double s_bin[kBinColsMax + 1];  // (+1: the odd stride of a single copy)
   __shared__ int s_run[kGeneralGradBlocks], s_late[kGeneralGradBlocks / kWave];
   __shared__ unsigned long long s_long[kGeneralGradBlocks / kWave];
+  __shared__ int s_over[kApplyWaves];
   // roles by block number: the other columns first (the bin owners have the longest way to
   // go), then the first columns, then the compaction tiles
   const int bid = (int)blockIdx.x, hb = bid - nrest;
@@ -1775,9 +1829,9 @@ __global__ __launch_bounds__(kApplyThreads) void k_apply_general(const ApplyArgs
     // pools of 20,000 rows over 200,000 34.2 and 27.7, of 3000 over 40,000 21.3 and 20.1.)
     const int bin = (nrest & 7) != 0 ? bid : (bid & 7) * (nrest >> 3) + (bid >> 3);
     if (a.nvec == 2)
-      apply_bin<3>(a, bin, s_bin, s_m, s_g, s_run, s_late, s_long);
+      apply_bin<3>(a, bin, s_bin, s_m, s_g, s_run, s_late, s_long, s_over);
     else
-      apply_bin<2>(a, bin, s_bin, s_m, s_g, s_run, s_late, s_long);
+      apply_bin<2>(a, bin, s_bin, s_m, s_g, s_run, s_late, s_long, s_over);
     return;
   }
   const int t = threadIdx.x;

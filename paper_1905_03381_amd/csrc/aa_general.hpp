@@ -10,7 +10,8 @@ namespace aa {
 // words (column, term) when one vector is updated, of three (column, term for w, term for phi) when both
 // are.  The first kRecords* of a block stay in its LDS and go to the bins at the end.  Those that find no room
 // there, or their bin full ("late" ones), are written out as they come and in the end sorted by bin, in pieces of at most
-// kSort* (what LDS holds); the first pieces of all blocks lie side by side, then the second ones.
+// kSort* (what LDS holds), and go to the bins, too; what finds no room there stays in its piece.  The first pieces of all
+// blocks lie side by side, then the second ones.
 constexpr int kRecordsTwoVec = 5120, kRecordsTwoVecDense = 2048, kRecordsOneVec = 4096;
 constexpr int kSortOneVec = 16384, kSortTwoVec = 12288;
 
@@ -46,7 +47,8 @@ inline size_t general_record_capacity(int32_t count_max) {
 }
 // The workspace has 16 bytes per record of that capacity.  14 are for records: the bins take one and a quarter times what
 // the blocks' LDS holds, but at most seven eighths (late room is a block's own: with smaller bins the blocks that finish
-// last would find all of them full), late records, among them those that find their bin full, the rest.  Two are
+// last would find all of them full), or a quarter where that is more (late records pass through late room first: it
+// stays the larger part); late records, among them those that find their bin full, the rest.  Two are
 // for the runs (nb * pieces words per block: 64 bytes a candidate where a block has 16 rows, and beyond 256 blocks a
 // kilobyte for a piece, which is longer than 6000 records if there are several).
 constexpr size_t kRecordBytes = 16, kRecordWordBytes = 14;
@@ -73,7 +75,10 @@ inline BinPlan general_bin_plan(int32_t d, int32_t head, int nvec, int32_t count
   // (segments where all that the blocks hold fits them one and a quarter times: with less room the blocks that finish last
   // would find their segment full)
   p.segments = nblk >= 8 * kBinSegments && binned <= all / 8 * 7 ? kBinSegments : 1;
-  if (binned > all / 8 * 7) binned = all / 8 * 7;
+  if (binned > all / 8 * 7)
+    binned = all / 8 * 7;
+  else if (binned < all / 4)
+    binned = all / 4;
   p.seg_cap = (int32_t)(binned / ((int64_t)nb * p.segments)) & ~3;
   const int32_t each = (int32_t)((all - binned) / nblk), most = nvec == 2 ? kSortTwoVec : kSortOneVec;
   p.pieces = (each + most - 1) / most;

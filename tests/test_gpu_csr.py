@@ -663,6 +663,11 @@ def _check_csr_updates(ref, r, d, n, kind, lo, hi, with_val, misalign=False, all
         col = np.minimum(r.pareto(1.1, size=nnz).astype(np.int64), d - 1)
     elif kind == "fields":  # fields of 512 columns, each with a default in half of its entries
         col = 512 * r.integers(0, d // 512, size=nnz) + np.where(r.random(nnz) < 0.5, 0, r.integers(0, 512, size=nnz))
+    elif kind == "one_bin":  # half of the entries on 200 columns of one bin (groups of four, 256 bins, see BinPlan)
+        g = np.arange((d - 8192) // 4)
+        mine = 8192 + 4 * g[(g + 157 * (g >> 8)) % 256 == 7]
+        col = np.where(r.random(nnz) < 0.5, r.choice(mine, size=nnz) + r.integers(0, 4, size=nnz),
+                       r.integers(0, d, size=nnz))
     else:  # a few very hot columns at the end of the range
         col = np.where(r.random(nnz) < 0.5, d - 1 - r.integers(0, min(3, d), size=nnz),
                        r.integers(0, d, size=nnz))
@@ -764,7 +769,8 @@ def test_csr_updates_at_the_edges_of_the_column_bins(ref, d):
     (30_000, 70_000, "hot_tail", 127, 129, False, (0, 0)),        # both sides of two
     (20_000, 300_000, "uniform", 100, 200, True, (1000, 400)),    # rows past two pieces, no late room left
     (64, 200_000, "uniform", 380, 420, True, (16_384, 12_288)),   # one block, several sorted pieces
-    (110_000, 300_000, "uniform", 42, 46, True, (0, 12_288))])    # 256 blocks, two sorted pieces
+    (110_000, 300_000, "uniform", 42, 46, True, (0, 12_288)),     # 256 blocks, two sorted pieces
+    (40_000, 60_000, "one_bin", 40, 70, True, (2000, 1000))])     # late records of which one bin takes only the first
 def test_csr_updates_pieces_pairs_and_late_records(ref, n, d, kind, lo, hi, with_val, late):
     """All rows chosen.  30,000 rows are at least seven a wave, more than it has lane groups: short rows go two to a unit.
     Records beyond a block's LDS are late ones, sorted by bin in pieces of at most 16,384 (one vector) and 12,288 (two)."""
