@@ -1102,19 +1102,20 @@ __global__ __launch_bounds__(256) void k_zero_f32(float *p, size_t count) {
 // per launch: 163 us with a 32-bit load per entry (16 loads and 8 gathers a step, a sigmoid per row and
 // group), 155 with one 128-bit load per array and half slot and the sigmoids of 64 rows at a time, 151 with
 // the requests going on across rounds.  With non-temporal loads it is 128, but the rows are then gone from
-// the memory-side cache and the copy of the kept rows that follows takes 126 instead of 97.
+// the memory-side cache and the copy of the kept rows that follows takes 126 instead of 97.  With all of the
+// table's loads in flight together 137; 300,000 rows over 64,002 columns 57.9 -> 44.9, 30,000 over 40,002 20.1 -> 11.6.
 constexpr int kScoreTableCols = 39936;  // 156 KB of the 160 KB
 constexpr int kScoreTableThreads = 1024;
 // Taken for pools of at least kScoreTableMinRows rows over more than kScoreTableMinCols columns, and
-// for kScoreTableManyRows rows over fewer, when the table holds at least half of phi.  Whole batch
-// generator calls, k_rows_general / this: 1,000,000 rows over 16,002 columns 242 / 173 us, over 10,002
-// 347 / 276, over 4002 304 / 272; 200,000 over 4002 78.3 / 73.5; 100,000 over 4002 to 16,002 57 / 56.5, 54 /
-// 53, 58 / 59; 60,000 over 4002 49.8 / 52.0; 20,000 over 15,002 43.8 / 50.8.  Scoring calls alone, 100,000 rows
-// of 40 to 72 entries: over 64 columns 14.0 / 12.6, 512 14.3 / 12.6, 2000 14.4 / 12.6, 8002 15.2 / 14.2, 16,002 16.1 /
-// 16.2; 1,000,000: over 64 122 / 97, 2000 129 / 96, 16,002 195 / 102; of 4 to 20 entries over 64 to 2000 54.5 / 40.7.
+// for kScoreTableManyRows rows over fewer, when the table holds at least half of phi.  Scoring calls alone, values,
+// k_rows_general / this.  Rows of 30 to 82 entries, columns Zipf-like: 24,576 rows over 40,002 5.2 / 9.5, 32,768 over 64,002
+// 6.2 / 9.9, 49,152 8.8 / 10.2, 65,536 11.3 / 11.0, 98,304 17.8 / 14.0; over 8002 49,152 8.2 / 9.5, 65,536 10.2 / 10.1,
+// 98,304 15.8 / 13.0.  Columns uniform: 32,768 over 40,002 9.6 / 9.6, 49,152 13.3 / 9.7; over 8002 49,152 9.0 / 9.5,
+// 98,304 18.8 / 13.0.  Rows of 4 to 20 entries: 65,536 7.4 / 9.5, 98,304 10.7 / 9.5; of 150 to 250: 32,768 over 40,002
+// 17.0 / 18.2, 49,152 23.9 / 19.9, over 2002 49,152 17.4 / 20.0, 65,536 21.2 / 23.7, 98,304 31.9 / 29.6.
 // On 65,536 rows of about 100 entries over 2^20 Zipf-distributed columns, where a quarter of the entries lie
 // past the table, k_rows_general stays ahead (34 us against 48).
-constexpr int kScoreTableMinCols = 16384, kScoreTableMinRows = 16384, kScoreTableManyRows = 98304;
+constexpr int kScoreTableMinCols = 16384, kScoreTableMinRows = 49152, kScoreTableManyRows = 98304;
 constexpr int kScoreTableMaxCols = 2 * kScoreTableCols;
 
 // No load of the main loop sits behind a branch (a lane with nothing to read asks for an
@@ -1127,10 +1128,9 @@ constexpr int kScoreTableMaxCols = 2 * kScoreTableCols;
 template <bool VAL>
 __global__ __launch_bounds__(kScoreTableThreads) void k_score_table(const GenArgs a) {
   constexpr int GL = 16, G = kWave / GL, kUnroll = 8, kChunk = GL * kUnroll;
-  __shared__ float s_phi[kScoreTableCols];
+  __shared__ __attribute__((aligned(16))) float s_phi[kScoreTableCols];
   __shared__ float s_row[kScoreTableThreads / kWave][kWave];  // sums of a wave's round
   const int D = min(kScoreTableCols, a.d);
-  for (int k = threadIdx.x; k < D; k += kScoreTableThreads) s_phi[k] = a.phi[k];
   const int lane = threadIdx.x & 63, nw = kScoreTableThreads >> 6;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int grp = lane / GL, sub = lane % GL;
@@ -1142,7 +1142,6 @@ __global__ __launch_bounds__(kScoreTableThreads) void k_score_table(const GenArg
   const float b = a.bias ? *a.bias : 0.f;
   // an address that is always readable, for lanes with nothing to load
   const int *const nowhere = reinterpret_cast<const int *>(a.rowptr);
-  __syncthreads();
 
   // Entries and cold columns are read through buffer resources: a lane with nothing to read
   // gives an offset past the resource's range, for which the hardware returns zero without a
@@ -1216,10 +1215,31 @@ __global__ __launch_bounds__(kScoreTableThreads) void k_score_table(const GenArg
     e.hi = a.rowptr[row + 1];
     return e;
   };
-  const Extent first_rows = extent(lo + lane, row_id(lo + lane));
+  // The table: all of a thread's pieces in flight together, between the loads of the first rows' ids and extents.
+  // (A word at a time in a loop, and the ids behind it, a launch took at least 19 us.)
+  const int id_first = row_id(lo + lane), id_next = row_id(lo + kWave + lane);
+  const float last_phi = a.phi[min((D & ~3) + lane, a.d - 1)];  // (a column of the model's last few)
+  constexpr int kTurns = (kScoreTableCols / 4 + kScoreTableThreads - 1) / kScoreTableThreads;
+  f4v phi_in[kTurns];
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int q = 0; q < kTurns; ++q) {
+    const int k = 4 * ((int)threadIdx.x + q * kScoreTableThreads);
+    phi_in[q] = __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(r_phi, k * 4, 0, 0));
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  const Extent first_rows = extent(lo + lane, id_first);
   Extent cur = first_rows;
-  Extent next = extent(lo + kWave + lane, row_id(lo + kWave + lane));
+  Extent next = extent(lo + kWave + lane, id_next);
   int id_after = row_id(lo + 2 * kWave + lane);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int q = 0; q < kTurns; ++q) {
+    const int k = 4 * ((int)threadIdx.x + q * kScoreTableThreads);
+    if (k + 4 <= D) *reinterpret_cast<float4 *>(s_phi + k) = make_float4(phi_in[q].x, phi_in[q].y, phi_in[q].z, phi_in[q].w);
+  }
+  if (threadIdx.x < (D & 3)) s_phi[(D & ~3) + threadIdx.x] = last_phi;
+  __syncthreads();
   bool any_longer = false;
 
   // A step gives every group of 16 lanes two half slots of 64 entries: both chunks of one row of

@@ -777,6 +777,26 @@ def test_csr_updates_pieces_pairs_and_late_records(ref, n, d, kind, lo, hi, with
     _check_csr_updates(ref, rng(n + d), d, n, kind, lo, hi, with_val, all_rows=True, late=late)
 
 
+@pytest.mark.parametrize("d", [16_385, 16_387, 39_935, 39_936, 39_937, 64_002])
+@pytest.mark.parametrize("with_val", [True, False])
+def test_csr_scores_with_the_table_and_without(d, with_val):
+    """49,152 rows over more than 16,384 columns are scored with phi's first 39,936 entries in LDS, one row less without.  The
+    order of additions is the same: the same bits, whether the table ends with the model, between its fours or before it."""
+    n, r = 49_152, rng(d)
+    lens = r.integers(0, 140, size=n)
+    rowptr = np.zeros(n + 1, dtype=np.int64)
+    np.cumsum(lens, out=rowptr[1:])
+    nnz = int(rowptr[-1])
+    col = np.where(r.random(nnz) < 0.2, d - 1 - r.integers(0, 5, size=nnz), r.integers(0, d, size=nnz)).astype(np.int32)
+    F = csr_features(rowptr, col, r.standard_normal(nnz).astype(np.float32) if with_val else None, d)
+    phi, b = dev((0.1 * r.standard_normal(d + 1)).astype(np.float32))[1:], scalar_dev(0.1)
+    rows = dev(r.permutation(n).astype(np.int32))
+    with_table, without = torch.zeros(n, device="cuda"), torch.zeros(n, device="cuda")
+    api.assistant_score(F, rows, n, phi, b, None, with_table)
+    api.assistant_score(F, rows, n - 1, phi, b, None, without)
+    assert torch.equal(with_table[:-1], without[:-1]) and float(with_table[-1]) > 0.0
+
+
 @pytest.mark.parametrize("d", [80 * 512, 20 * 512])
 def test_csr_updates_frequent_columns_512_apart(ref, d):
     """Fields padded to 512 columns, each with a frequent default: columns 512, 1024, 2048 ... apart past the table
