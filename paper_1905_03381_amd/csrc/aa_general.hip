@@ -1307,6 +1307,7 @@ __global__ __launch_bounds__(kScoreTableThreads) void k_score_table(const GenArg
   if (lo < hi) {
     // `ask` is the round whose entries are being requested, `use` the one whose rows are added up,
     // kAhead steps behind: the requests go on across the end of a round.
+    __builtin_amdgcn_s_setprio(3);
     Round ask = make_round(lo);
     Round use = ask;
     int asked = 0, used = 0;
@@ -1345,6 +1346,17 @@ __global__ __launch_bounds__(kScoreTableThreads) void k_score_table(const GenArg
           __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
           more = use.base + kWave < hi;
           if (!more) break;
+          // (a wave that is behind goes first, as in k_rows_grad: 137.3 -> 136.4 us, 1,000,000 rows of 56 ones over
+          // 16,002 columns 68.2 -> 66.2, 300,000 23.8 -> 22.2)
+          const int left = hi - use.base - kWave, mine = hi - lo;
+          if (left * 4 > mine * 3)
+            __builtin_amdgcn_s_setprio(3);
+          else if (left * 2 > mine)
+            __builtin_amdgcn_s_setprio(2);
+          else if (left * 4 > mine)
+            __builtin_amdgcn_s_setprio(1);
+          else
+            __builtin_amdgcn_s_setprio(0);
           use = ask;
           used = 0;
         }
