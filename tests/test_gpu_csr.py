@@ -749,6 +749,14 @@ def test_csr_updates_with_model_vectors_off_16_byte_alignment(ref):
     _check_csr_updates(ref, r, 300000, 3000, "hot_tail", 20, 60, False, misalign=True)
 
 
+@pytest.mark.parametrize("d", [1, 3, 3071, 3072, 8191, 8192])
+def test_csr_updates_whose_columns_are_all_in_the_table(ref, d):
+    """3072 columns of a pass over two vectors, 8192 of one over one, have their own slots: no tags, records and gathers."""
+    r = rng(700 + d)
+    _check_csr_updates(ref, r, d, 2000, "hot_tail", 0, 70, True)
+    _check_csr_updates(ref, r, d, 300, "uniform", 120, 140, False)
+
+
 @pytest.mark.parametrize("d", [3073, 3075, 3079, 3072 + 1021, 8193, 8195, 8192 + 1022,
                                3072 + (1 << 18), 3072 + (1 << 18) + 5, 8192 + (1 << 18), 8192 + (1 << 18) + 6])
 def test_csr_updates_at_the_edges_of_the_column_bins(ref, d):
