@@ -28,7 +28,7 @@ namespace {
 
 constexpr int kCtlUpdateSnapshot = 0;  // control word: update counter before the running step
 constexpr int kCtlThresholdNext = 1;   // control word: the running threshold a pass worked out (a float)
-constexpr int kCtlTeamShut = 2;        // control word: see k_team_reset
+constexpr int kCtlTeamEnds = 2;        // control word: see SmallEpochArgs
 
 struct Ws {
   char *base;
@@ -1218,7 +1218,7 @@ static int32_t epoch_impl(const aa_features *F, const float *y, const int32_t *p
     if (check_ws(ws, ws_bytes, w_team.total) == AA_OK) {
       w_small = w_team;
       a.words = reinterpret_cast<uint64_t *>(w_team.grad);
-      a.shut = w_team.ctl + kCtlTeamShut;
+      a.ends = w_team.ctl + kCtlTeamEnds;
     }
     a.kept_pos = w_small.kept_pos;
     a.prob = hard ? nullptr : w_small.prob;

@@ -17,8 +17,10 @@
 // the next rows on their way would wait for those first.
 // The blocks of a team have to run at once.  k_team_reset clears words and gate ahead of the launch; a block counts
 // itself in, the last one opens the gate, and nobody publishes before it is open.  A block that has waited past its
-// limit shuts the gate for good; all of them leave then, and the launch behind, which has nothing to do otherwise, does the
-// epoch with one block.
+// limit shuts the gate for good; all of them leave then.  So they do if words do not come: the waits behind the gate are
+// bounded by the number of requests, which stands still with the waves of a queue that is suspended.  Blocks that have
+// got through the last step count themselves, too: the last of four writes the model, and if there are fewer nobody has, and
+// the launch behind, which has nothing to do otherwise, does the whole epoch with one block.
 #include "aa_small.hpp"
 
 namespace aa {
@@ -27,12 +29,14 @@ namespace {
 
 constexpr int kSmallWaves = 16, kSmallTurns = 8;
 constexpr int kTeamBlocks = 4, kTeamWaves = kSmallWaves / kTeamBlocks;  // row waves of a block, and as many others
-constexpr int kGateWords = 16;  // 64-bit words in front: blocks that are there, state of the gate
+constexpr int kGateWords = 16;  // 64-bit words in front; of 32 bits: blocks that are there, state of the gate, blocks that are through
 constexpr int kTeamExtra = 16;  // words behind a block's sums: its waves' kept rows (a byte each), bias gradient, nothing
-enum Gate : int { kGateOpen = 1, kGateShut = 2, kGateLost = 3 };
-// 100 MHz ticks: until the gate opens (some milliseconds, different from call to call), and for a word once it is
-// (whoever is waited for runs then: this ends a wait that could not end otherwise)
-constexpr long long kGateTicks = 200000, kWordTicks = 200000000;
+enum Gate : int { kGateOpen = 1, kGateShut = 2 };
+// 100 MHz ticks until the gate opens (some milliseconds, different from call to call)
+constexpr long long kGateTicks = 200000;
+// pairs of requests for a word once it is, some tenths of a second's (whoever is waited for runs then: this ends a wait that
+// could not end otherwise)
+constexpr int kWordPolls = 1 << 18;
 
 constexpr size_t team_words(int cols) { return kGateWords + 2 * (size_t)kTeamBlocks * (cols + kTeamExtra); }
 
@@ -53,10 +57,9 @@ __device__ __forceinline__ void move_gate(int32_t *state, int to) {
   __hip_atomic_compare_exchange_strong(state, &closed, to, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// (a control word of kGateShut has one block do the epochs: for tests)
-__global__ __launch_bounds__(256) void k_team_reset(uint64_t *words, int count, const int32_t *shut) {
+__global__ __launch_bounds__(256) void k_team_reset(uint64_t *words, int count, const int32_t *ends) {
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < count; i += gridDim.x * blockDim.x)
-    words[i] = i == 0 && *shut == kGateShut ? (uint64_t)kGateShut << 32 : 0;
+    words[i] = i == 0 && *ends == kGateShut ? (uint64_t)kGateShut << 32 : 0;
 }
 
 // lane I of every 16, in all 16
@@ -175,7 +178,7 @@ __global__ __launch_bounds__(kSmallWaves * 64)
   __shared__ float s_gb[NW];
   __shared__ float s_u[2][HARD ? 1 : kRows];  // draws of this step and the next
 
-  if (a.words && load_gate(reinterpret_cast<const int32_t *>(a.words) + 1) != kGateShut) return;  // (the team did it)
+  if (a.words && load_gate(reinterpret_cast<const int32_t *>(a.words) + 2) == kTeamBlocks) return;  // (the team did it)
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int grp = lane / LPR, sub = lane % LPR;
   const int piece = min(sub, a.d4 - 1);  // (lanes past the row re-read its last piece and are masked)
@@ -369,7 +372,7 @@ __global__ __launch_bounds__(2 * kTeamWaves * 64)
   constexpr int kStride = COLS + kTeamExtra;
   constexpr int kTeamNap = PER == 1 ? 6 : 1;  // between requests for words, in 64 cycles: 0 to 12 within 3 % for one column a reader
   __shared__ f4 s_model[NVEC][LPR], s_red[kTeamWaves][NVEC][LPR];
-  __shared__ int s_before[2][kTeamWaves], s_kept[kTeamWaves], s_state;
+  __shared__ int s_before[2][kTeamWaves], s_kept[kTeamWaves], s_state, s_through;
   __shared__ float s_b, s_gb[kTeamWaves];
   const int tid = threadIdx.x, lane = tid & 63, in_block = __builtin_amdgcn_readfirstlane(tid >> 6);
   int32_t *const gate = reinterpret_cast<int32_t *>(a.words);
@@ -416,13 +419,13 @@ __global__ __launch_bounds__(2 * kTeamWaves * 64)
     float o_loss = 0.f, o_prob = 0.f;
     int32_t *ids = a.ids;
     float *losses = a.loss;
-    auto put = [&](int before) __attribute__((always_inline)) {  // (before: kept rows ahead of this wave's)
+    auto put = [&](int before) __attribute__((always_inline)) {  // (before: kept rows ahead of this wave's, -1: not known)
       const unsigned long long mask = __ballot(o_keep);
       if (lane < o_cnt) {
         const int j = o_lo + lane;
         if (!HARD && a.prob) a.prob[j] = o_prob;
         if (a.flags) a.flags[j] = o_keep ? 1 : 0;
-        if (o_keep) {
+        if (o_keep && before >= 0) {
           const int pos = before + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
                                                                   __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
           if (a.kept_pos) a.kept_pos[pos] = j;
@@ -481,9 +484,10 @@ __global__ __launch_bounds__(2 * kTeamWaves * 64)
       if (t + 1 < a.steps) step(t + 1, xb, yb);
     }
     put(s_before[(a.steps - 1) & 1][in_block]);
+    __syncthreads();
   } else {
     const int rt = tid - NT;
-    bool lost = false;  // a wait has passed its limit: no more waits
+    const int ends_in = *a.ends;  // (see SmallEpochArgs)
     float b = !HARD && a.bias ? *a.bias : 0.f;
     int t_now = a.t_upd ? *a.t_upd : 0;
     float mine[PER];
@@ -494,6 +498,7 @@ __global__ __launch_bounds__(2 * kTeamWaves * 64)
     }
     if (rt == 0) {
       s_b = b;
+      s_through = 0;
       if (__hip_atomic_fetch_add(gate, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == kTeamBlocks - 1)
         move_gate(gate + 1, kGateOpen);
       const long long since = wall_clock64(), limit = kGateTicks * (1 + ((since >> 4) & 7));
@@ -504,8 +509,13 @@ __global__ __launch_bounds__(2 * kTeamWaves * 64)
     }
     __syncthreads();
     if (s_state != kGateOpen) return;
+    // A wait of the block has passed its limit: from the next step on it publishes nothing, waits for nothing and stores no
+    // batches, and it does not count itself at the end.
+    bool lost = false;
+    const int ends = __builtin_amdgcn_readfirstlane(ends_in);
+    const int leaves = ends >= 4 && (ends & 3) == (int)blockIdx.x ? (ends >> 2) - 1 : -1;
     for (int t = 0; t < a.steps; ++t) {
-      const int tag = t + 1;
+      const int tag = t + 1, tag_put = lost ? 0 : tag;  // (a word of number 0 is none)
       uint64_t *const words = a.words + kGateWords + (size_t)(t & 1) * kTeamBlocks * kStride;
       __syncthreads();  // the row waves' sums are in LDS
       {
@@ -518,7 +528,7 @@ __global__ __launch_bounds__(2 * kTeamWaves * 64)
           float four = red[c];
 #pragma unroll
           for (int i = 1; i < kTeamWaves; ++i) four += red[i * COLS + c];
-          store_word(to + c, word_of(__float_as_uint(four), tag));
+          store_word(to + c, word_of(__float_as_uint(four), tag_put));
         }
         if (rt < 2) {
           uint32_t kept = 0;
@@ -527,7 +537,7 @@ __global__ __launch_bounds__(2 * kTeamWaves * 64)
           for (int i = 0; i < kTeamWaves; ++i) kept |= (uint32_t)s_kept[i] << (8 * i);
 #pragma unroll
           for (int i = 1; i < kTeamWaves; ++i) four += s_gb[i];
-          store_word(to + COLS + rt, word_of(rt == 0 ? kept : __float_as_uint(four), tag));
+          store_word(to + COLS + rt, word_of(rt == 0 ? kept : __float_as_uint(four), tag_put));
         }
       }
       // (what does not depend on them, while they are on their way)
@@ -556,11 +566,11 @@ __global__ __launch_bounds__(2 * kTeamWaves * 64)
         for (int p = 0; p < PER; ++p)
 #pragma unroll
           for (int i = 0; i < kTeamBlocks; ++i) ok = ok && tag_of(w.v[p][i]) == tag;
-        return lost || __ballot(!ok) == 0ull;
+        return __ballot(!ok) == 0ull;
       };
       __builtin_amdgcn_s_sleep(kTeamNap);
       request(first);
-      const long long since = wall_clock64();
+      int polls = lost || t == leaves ? kWordPolls : 0;
       for (;;) {
         __builtin_amdgcn_s_sleep(kTeamNap);
         request(second);
@@ -571,11 +581,9 @@ __global__ __launch_bounds__(2 * kTeamWaves * 64)
           first = second;
           break;
         }
-        if (wall_clock64() - since > kWordTicks) {
-          lost = true;
-          __hip_atomic_store(gate + 1, (int)kGateLost, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
+        if (++polls >= kWordPolls) break;
       }
+      lost = polls >= kWordPolls;
       int m = 0, before = 0;
       float gbs = 0.f;
       const float ev = value_of(first.e);
@@ -608,22 +616,25 @@ __global__ __launch_bounds__(2 * kTeamWaves * 64)
         }
         if (!HARD && a.bias) b = b - a.lr_a * (gbs * inv_m);
       }
-      if (rt < kTeamWaves) s_before[t & 1][rt] = before;
+      if (rt < kTeamWaves) s_before[t & 1][rt] = lost ? -1 : before;
+      if (lost && lane == 0) s_state = kGateShut;
       if (rt == 0) {
         s_b = b;
         if (blockIdx.x == 0 && a.kept_hist) a.kept_hist[t] = m;
       }
       __syncthreads();
+      lost = __builtin_amdgcn_readfirstlane(s_state) != kGateOpen;
     }
-    if (blockIdx.x == 0) {
-      const bool void_ = load_gate(gate + 1) == kGateLost;  // (nothing here can be trusted, and it shows)
+    if (rt == 0 && !lost)
+      s_through = __hip_atomic_fetch_add(gate + 2, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
+    __syncthreads();
+    if (s_through == kTeamBlocks) {  // (the others are past their last step: nobody reads the old model any more)
       for (int c = rt; c < COLS; c += NT) {
         const int col = c % ROW;
-        if (col < a.d)
-          (c < ROW ? a.w : a.phi)[col] = void_ ? __int_as_float(0x7fc00000) : reinterpret_cast<const float *>(s_model)[c];
+        if (col < a.d) (c < ROW ? a.w : a.phi)[col] = reinterpret_cast<const float *>(s_model)[c];
       }
       if (rt == 0) {
-        if (!HARD && a.bias) *a.bias = void_ ? __int_as_float(0x7fc00000) : b;
+        if (!HARD && a.bias) *a.bias = b;
         if (a.t_upd) *a.t_upd = t_now;
       }
     }
@@ -642,7 +653,7 @@ hipError_t launch_team(SmallEpochArgs a, hipStream_t st) {
     team = a.words != nullptr && a.steps * IT >= 4 * kSmallTurns;
     if (team) {
       const int count = (int)team_words((HARD ? 1 : 2) * 4 * LPR);
-      hipLaunchKernelGGL(k_team_reset, dim3(16), dim3(256), 0, st, a.words, count, a.shut);
+      hipLaunchKernelGGL(k_team_reset, dim3(16), dim3(256), 0, st, a.words, count, a.ends);
       hipLaunchKernelGGL((k_team_epoch<LPR, HARD, IT>), dim3(kTeamBlocks), dim3(2 * kTeamWaves * 64), 0, st, a);
     }
   }

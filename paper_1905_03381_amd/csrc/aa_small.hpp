@@ -1,4 +1,4 @@
-// Host-side launch interface of the one-block epoch over small pools.
+// Host-side launch interface of the epochs over small pools.
 #pragma once
 
 #include "aa_common.hpp"
@@ -28,9 +28,10 @@ struct SmallEpochArgs {
   uint8_t *flags;
   int64_t ids_stride, loss_stride;
   // what the blocks of a team tell each other, small_epoch_words_bytes() bytes (NULL: no team), and a control word of the
-  // workspace (see k_team_reset)
+  // workspace with which tests end a team: 2: the gate is shut from the start; 4 (t + 1) + b: block b leaves in step t, as if
+  // the others' words had not come; anything else, as the zero that preparing a workspace leaves there, does nothing
   uint64_t *words;
-  const int32_t *shut;
+  const int32_t *ends;
 };
 
 constexpr int kSmallEpochSteps = 1024;  // steps of one launch at most

@@ -11,7 +11,9 @@ from stepwise import check_epoch
 
 pytestmark = pytest.mark.gpu
 
-SHUT = 2  # a workspace with this in its third control word has its epochs done by one block
+# third control word of a workspace (csrc/aa_small.hpp): SHUT: its epochs are done by one block; 4 (t + 1) + b: block b
+# leaves in step t.  The gate's states have the same numbers.
+OPEN, SHUT = 1, 2
 
 
 def _problem(n, d, ld=None):
@@ -22,12 +24,18 @@ def _problem(n, d, ld=None):
     return X, y, r.permutation(n).astype(np.int32), (0.8 * r.standard_normal(d)).astype(np.float32)
 
 
-def _workspace(P, d, alone):
+def _workspace(P, d, alone, ends=None):
     ws = api.Workspace(P, d)
-    if alone:
+    if alone or ends is not None:
         off = ws.ptr - ws.buf.data_ptr()
-        ws.buf[off:off + 256].view(torch.int32)[2] = SHUT
+        ws.buf[off:off + 256].view(torch.int32)[2] = SHUT if ends is None else ends
     return ws
+
+
+def _gate(ws):
+    """Blocks that were there, state of the gate, blocks that got through, of the last epoch that had a team."""
+    first = ws.ptr - ws.buf.data_ptr() + 256 + 2 * 4 * 1024 + 256  # (the gradients' part of the workspace)
+    return host(ws.buf[first:first + 12]).view(np.int32).tolist()
 
 
 # every lane layout at its first and last width and every number of turns, waves without rows, the smallest number of steps
@@ -43,6 +51,32 @@ def test_teams(ref, d, P, n, ld, hard, alone):
                             None if hard else w0[::-1].copy(), 0.1, gamma=0.0 if hard else 0.2, seed=5, step0=3, lam=1e-3,
                             lr0=0.5, lr_a=0.3, T=0.4, ws=_workspace(P, d, alone), hard=hard)
     assert len(counts) == -(-n // P)
+
+
+# early, late, and in the last step, when the other blocks have all they need: block 0, which tells the counts, and another
+@pytest.mark.parametrize("step,block", [(0, 1), (4, 0), (5, 3), (19, 0), (19, 2)])
+@pytest.mark.parametrize("d,P,hard", [(128, 256, False), (200, 128, False), (64, 300, True)])
+def test_team_that_loses_a_block(d, P, hard, step, block):
+    """A block whose wait for words has passed its limit leaves: the epoch is then done by one block, with the same bits
+    everywhere, and nothing of the team's is left in the model."""
+    n = 20 * P - 7
+    X, y, perm, w0 = _problem(n, d)
+    F, yd, pd, T = dense_features(X), dev(y), dev(perm), scalar_dev(0.4)
+    got = []
+    for ws in (_workspace(P, d, True), _workspace(P, d, False, ends=4 * (step + 1) + block)):
+        w, phi, b, tu = dev(w0), dev(w0), scalar_dev(0.1), torch.full((1,), 3, dtype=torch.int32, device="cuda")
+        hist = torch.full((20,), -1, dtype=torch.int32, device="cuda")
+        ids, loss = torch.full((20, P), -1, dtype=torch.int32, device="cuda"), torch.full((20, P), -3.0, device="cuda")
+        if hard:
+            api.sk_epoch(F, yd, pd, n, P, w, T, 1e-3, 0.5, tu, hist, ws, ids, loss)
+        else:
+            cfg = api.step_config(0.2, 1e-3, 0.5, 0.3, 0.01, 5, 0, T)
+            api.train_epoch(F, yd, pd, n, P, w, phi, b, cfg, tu, hist, ws, ids, loss)
+        got.append([host(t).copy() for t in (w, phi, b, tu, hist, ids, loss)])
+        there, state, through = _gate(ws)
+    assert there == 4 and state == OPEN and through == (3 if step == 19 else 0)
+    assert all(np.array_equal(u, v) for u, v in zip(*got))
+    assert (got[0][4] > 0).all() and got[0][3][0] == 23 and not np.array_equal(got[0][0], w0)
 
 
 def test_workspace_without_room_for_the_words():
