@@ -34,8 +34,21 @@ def _workspace(P, d, alone, ends=None):
 
 def _gate(ws):
     """Blocks that were there, state of the gate, blocks that got through, of the last epoch that had a team."""
+    return host(_gate_words(ws)).tolist()
+
+
+def _gate_words(ws):
     first = ws.ptr - ws.buf.data_ptr() + 256 + 2 * 4 * 1024 + 256  # (the gradients' part of the workspace)
-    return host(ws.buf[first:first + 12]).view(np.int32).tolist()
+    return ws.buf[first:first + 12].view(torch.int32)
+
+
+def _has_team(d, P, n, hard):
+    """The rule of launch_team (csrc/aa_small.hip): more than two turns of rows a wave, or soft keeps and rows narrower than a
+    wave, and 32 turns in all."""
+    lanes = 16 if d <= 64 else 32 if d <= 128 else 64
+    rows = 16 * (64 // lanes)
+    turns = 2 if P <= 2 * rows else 4 if P <= 4 * rows else 8
+    return (turns > 2 or (not hard and lanes < 64)) and -(-n // P) * turns >= 32
 
 
 # every lane layout at its first and last width and every number of turns, waves without rows, the smallest number of steps
@@ -47,10 +60,14 @@ def _gate(ws):
 @pytest.mark.parametrize("alone", [False, True])
 def test_teams(ref, d, P, n, ld, hard, alone):
     X, y, perm, w0 = _problem(n, d, ld)
+    ws = _workspace(P, d, alone)
+    _gate_words(ws).fill_(-7)
     counts, _ = check_epoch(ref, ref.Features.dense(X, d=d), dense_features(X, d=d), y, perm, n, P, w0,
                             None if hard else w0[::-1].copy(), 0.1, gamma=0.0 if hard else 0.2, seed=5, step0=3, lam=1e-3,
-                            lr0=0.5, lr_a=0.3, T=0.4, ws=_workspace(P, d, alone), hard=hard)
+                            lr0=0.5, lr_a=0.3, T=0.4, ws=ws, hard=hard)
     assert len(counts) == -(-n // P)
+    # (the steps one a call have no team, the epoch has: the same bits do not tell who made them)
+    assert _gate(ws) == ([-7] * 3 if not _has_team(d, P, n, hard) else [4, SHUT, 0] if alone else [4, OPEN, 4])
 
 
 # early, late, and in the last step, when the other blocks have all they need: block 0, which tells the counts, and another
@@ -90,7 +107,9 @@ def test_workspace_without_room_for_the_words():
         if small:
             ws.bytes = 30_000
         w, phi, b = dev(w0), dev(w0), scalar_dev(0.1)
+        _gate_words(ws).fill_(-7)
         api.train_epoch(F, yd, pd, n, P, w, phi, b, api.step_config(0.2, 1e-3, 0.5, 0.3, 0.01, 5, 0, T), None, None, ws)
+        assert _gate(ws) == ([-7] * 3 if small else [4, OPEN, 4])
         got.append((host(w), host(phi), host(b)))
     assert all(np.array_equal(u, v) for u, v in zip(*got)) and not np.array_equal(got[0][0], w0)
 
@@ -119,6 +138,7 @@ def test_graph_replays(alone):
         graph.replay()
         torch.cuda.synchronize()
         assert np.array_equal(host(w), want[k][0]) and np.array_equal(host(phi), want[k][1])
+        assert _gate(ws) == ([4, SHUT, 0] if alone else [4, OPEN, 4])
         dev(w0).mul_(2)
 
 
@@ -139,5 +159,7 @@ def test_streams():
             with torch.cuda.stream(s):
                 api.train_epoch(F, yd, pd, n, P, w, phi, None, cfg, None, None, ws)
     torch.cuda.synchronize()
-    for w, phi, _ in sets[:4]:
+    assert _gate(sets[4][2]) == [4, OPEN, 4]
+    for w, phi, ws in sets[:4]:
+        assert _gate(ws) in ([4, OPEN, 4], [4, SHUT, 0])  # (the blocks of four teams may not all be there at once)
         assert np.array_equal(host(w), host(sets[4][0])) and np.array_equal(host(phi), host(sets[4][1]))
