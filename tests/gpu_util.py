@@ -7,6 +7,9 @@ Tolerances (fp32 path against the fp64-accumulating oracle):
   * a keep decision is compared only when the draw is farther than 1e-6 from its
     probability; decisions on `margin < 1` only when farther than 1e-5 * S from 1.
 """
+import os
+import re
+
 import numpy as np
 import torch
 
@@ -14,6 +17,14 @@ from paper_1905_03381_amd import api
 
 RTOL = 1e-5
 DRAW_BAND = 1e-6
+
+
+def kernel_constant(name, source="aa_general.hip"):
+    """A whole number that a kernel source gives this name: tests that mean a kernel take its limits from there."""
+    with open(os.path.join(os.path.dirname(api.__file__), "csrc", source)) as f:
+        found = re.findall(rf"\b{name} = (\d+)[,;]", f.read())
+    assert len(found) == 1, (name, found)
+    return int(found[0])
 
 
 def dev(a, dtype=None):

@@ -7,9 +7,16 @@ import torch
 from paper_1905_03381_amd import api, synth
 
 from gpu_util import (RTOL, abs_dot_scale, assert_close_scaled, assert_logit_prob, clear_draws,
-                      csr_features, dev, host, scalar_dev)
+                      csr_features, dev, host, kernel_constant, scalar_dev)
 
 pytestmark = pytest.mark.gpu
+
+# The kernel that scores with the head of phi in LDS: its columns, the rows it takes over more than TABLE_MIN_COLS columns (and
+# at most twice TABLE_COLS), and over fewer.
+TABLE_COLS = kernel_constant("kScoreTableCols")
+TABLE_MIN_COLS = kernel_constant("kScoreTableMinCols")
+TABLE_ROWS = kernel_constant("kScoreTableMinRows")
+TABLE_MANY_ROWS = kernel_constant("kScoreTableManyRows")
 
 
 def rng(seed):
@@ -59,13 +66,14 @@ def test_csr_score_and_fused_keep(ref, ws, sparse):
 @pytest.mark.parametrize("ones", [False, True])
 @pytest.mark.parametrize("indexed", [True, False])
 def test_csr_score_large_pool_equals_small_pools(ref, ws, ones, indexed):
-    """Pools of 16,384 rows and more over 16,385 to 79,872 columns (and of 98,304 and more over fewer) are scored by the
-    kernel that keeps the head of phi in LDS, smaller ones by the general kernel: both add a row's terms in
-    the same order, so one pool of 25,001 rows and the same rows in pools of 9000 give the same
+    """Large pools are scored by the kernel that keeps the head of phi in LDS, smaller ones by the general
+    kernel: both add a row's terms in the same order, so one pool and the same rows in pools of a fifth give the same
     bits -- and the oracle's values.  Rows of 0 to 260 entries: half of them exceed the 128
     entries of the first kernel's main loop and take its walk over long rows; a fifth of the
     columns lie past its table."""
-    n, d, P = 30_000, 50_000, 25_001
+    P, d = TABLE_ROWS + 617, TABLE_COLS + TABLE_COLS // 4
+    n, part = P + 5000, P // 5
+    assert TABLE_MIN_COLS < d <= 2 * TABLE_COLS and part < TABLE_ROWS
     r = rng(41)
     lens = r.integers(0, 261, size=n)
     rowptr = np.zeros(n + 1, dtype=np.int64)
@@ -85,8 +93,8 @@ def test_csr_score_large_pool_equals_small_pools(ref, ws, ones, indexed):
     ref_logit, ref_prob = ref.assistant_score(Fh, ids, P, phi, bias=-0.4)
     assert_logit_prob(host(logit), host(prob), ref_logit, ref_prob, abs_dot_scale(Fh, ids, phi), bias=-0.4)
     logit2, prob2 = torch.zeros(P, device="cuda"), torch.zeros(P, device="cuda")
-    for lo in range(0, P, 9000):
-        m = min(9000, P - lo)
+    for lo in range(0, P, part):
+        m = min(part, P - lo)
         api.assistant_score(F, dev(ids[lo:lo + m]), m, dev(phi), bias, logit2[lo:], prob2[lo:])
     assert np.array_equal(host(logit), host(logit2)) and np.array_equal(host(prob), host(prob2))
     # keep flags of the fused score + keep + compact call: same draws, same probabilities
@@ -106,12 +114,12 @@ def test_csr_score_large_pool_equals_small_pools(ref, ws, ones, indexed):
 
 
 @pytest.mark.parametrize("ones", [True, False])
-@pytest.mark.parametrize("P", [5_000, 98_304 + 37])
+@pytest.mark.parametrize("P", [5_000, TABLE_MANY_ROWS + 37])
 def test_csr_score_row_ends(ref, ones, P):
     """Rows are read four entries at a time, the last piece ending with the row: rows of every length
     around the pieces (0 to 9, 61 to 68, 125 to 133 entries), the shortest first, where nothing lies before
     them in the matrix -- through the general kernel (5000 rows) and through the one with phi in
-    LDS, which takes over at 98,304 rows of so few columns.  No row holds column 0, whose model entry
+    LDS, which takes over at more rows of so few columns.  No row holds column 0, whose model entry
     is infinite: what a piece shares with another row or entry must not count."""
     lens = np.tile(np.r_[1, 1, 0, 0:10, 61:69, 125:134, 5, 3, 2], P // 33 + 1)[:P]
     r, d = rng(43), 3000
@@ -149,7 +157,7 @@ def test_csr_score_long_rows_in_a_large_pool(ref, ones):
     """Rows of more than 128 entries (up to 700) in a pool that the kernel with phi in LDS takes: the bits of the
     general kernel's scores of the halves, and about their time (four times that when such rows were walked
     one by one)."""
-    P, d = 98_304, 2000
+    P, d = TABLE_MANY_ROWS, 2000
     r = rng(47)
     lens = r.integers(129, 400, size=P)
     lens[::1000] = r.integers(400, 701, size=lens[::1000].size)
@@ -293,7 +301,8 @@ def test_csr_fused_scores_have_the_bits_of_separate_ones(d, ones):
     """The whole-step pass and the scoring kernels add a row's terms in the same order (20,000 columns: the kernel
     with phi in LDS): same logits, probabilities and draws for rows on both sides of 64 and 128 entries,
     long ones, and short ones at the matrix's start, before fewer and more rows than a wave's lane groups."""
-    n = 20_000
+    n, many = 20_000, TABLE_ROWS + 13  # (rows of the matrix; places of the large pool, some rows there more than once)
+    assert TABLE_MIN_COLS < 20_000
     r = rng(53)
     lens = np.where(r.random(n) < 0.5, r.integers(0, 70, size=n), r.integers(60, 300, size=n))
     lens[:4] = 1, 1, 0, 1
@@ -302,10 +311,10 @@ def test_csr_fused_scores_have_the_bits_of_separate_ones(d, ones):
     col = r.integers(0, d, size=int(rowptr[-1])).astype(np.int32)
     val = None if ones else (r.standard_normal(col.size) / 8.0).astype(np.float32)
     F = csr_features(rowptr, col, val, d)
-    y, idx = dev(np.where(r.random(n) < 0.5, -1.0, 1.0).astype(np.float32)), dev(r.permutation(n).astype(np.int32))
+    y, idx = dev(np.where(r.random(n) < 0.5, -1.0, 1.0).astype(np.float32)), dev(np.resize(r.permutation(n), many).astype(np.int32))
     phi = dev((r.standard_normal(d) / (8.0 if ones else 1.0)).astype(np.float32))
     cfg = api.step_config(0.1, 1e-3, 0.5, 0.3, 0.0, 7, 2, scalar_dev(0.1))
-    for P, ids in ((n, idx), (300, idx), (40, None)):
+    for P, ids in ((many, idx), (300, idx), (40, None)):
         ws = api.Workspace(P, d)
         got = [torch.zeros(P, device="cuda") for _ in range(5)]
         keep = [torch.zeros(P, dtype=torch.uint8, device="cuda") for _ in range(2)]
@@ -785,12 +794,12 @@ def test_csr_updates_pieces_pairs_and_late_records(ref, n, d, kind, lo, hi, with
     _check_csr_updates(ref, rng(n + d), d, n, kind, lo, hi, with_val, all_rows=True, late=late)
 
 
-@pytest.mark.parametrize("d", [16_385, 16_387, 39_935, 39_936, 39_937, 64_002])
+@pytest.mark.parametrize("d", [TABLE_MIN_COLS + 1, TABLE_MIN_COLS + 3, TABLE_COLS - 1, TABLE_COLS, TABLE_COLS + 1, 64_002])
 @pytest.mark.parametrize("with_val", [True, False])
 def test_csr_scores_with_the_table_and_without(d, with_val):
-    """49,152 rows over more than 16,384 columns are scored with phi's first 39,936 entries in LDS, one row less without.  The
+    """The fewest rows that are scored with phi's first entries in LDS, and one row less, without.  The
     order of additions is the same: the same bits, whether the table ends with the model, between its fours or before it."""
-    n, r = 49_152, rng(d)
+    n, r = TABLE_ROWS, rng(d)
     lens = r.integers(0, 140, size=n)
     rowptr = np.zeros(n + 1, dtype=np.int64)
     np.cumsum(lens, out=rowptr[1:])
@@ -893,10 +902,11 @@ def test_csr_records_that_find_their_bin_full(ref, kind):
 @pytest.mark.parametrize("ones", [True, False])
 def test_csr_rows_past_two_to_the_29_entries(ref, ones):
     """Rows on both sides of entry 2^29, where 32-bit byte offsets end, behind a row of half a thousand million entries that is
-    not chosen: scores (general kernel; 20,000 pool places over these columns: the one with phi in LDS) and updates have
+    not chosen: scores (general kernel; with many pool places over these columns the one with phi in LDS) and updates have
     the bits of the same rows in a matrix of their own, and the oracle's values."""
     r = rng(73)
     n, d = 400, 20_000
+    assert TABLE_MIN_COLS < d <= 2 * TABLE_COLS
     lens = np.where(r.random(n) < 0.5, r.integers(0, 70, size=n), r.integers(60, 300, size=n))
     own = np.zeros(n + 1, dtype=np.int64)
     np.cumsum(lens, out=own[1:])
@@ -918,7 +928,7 @@ def test_csr_rows_past_two_to_the_29_entries(ref, ones):
     ws, got = api.Workspace(n, d), {}
     for name, F, shift in (("near", near, 0), ("far", far, 1)):
         out = []
-        for P in (n, 20_000):
+        for P in (n, TABLE_ROWS):
             ids = dev((np.arange(P) % n + shift).astype(np.int32))
             out += [torch.zeros(P, device="cuda"), torch.zeros(P, device="cuda")]
             api.assistant_score(F, ids, P, dev(phi0), scalar_dev(0.1), out[-2], out[-1])
@@ -934,7 +944,7 @@ def test_csr_rows_past_two_to_the_29_entries(ref, ones):
         assert np.array_equal(x, z)
     ref_logit, ref_prob = ref.assistant_score(Fh, None, n, phi0, bias=0.1)
     assert_logit_prob(got["far"][0], got["far"][1], ref_logit, ref_prob, abs_dot_scale(Fh, np.arange(n), phi0), bias=0.1)
-    assert np.array_equal(got["far"][2], np.resize(got["far"][0], 20_000))
+    assert np.array_equal(got["far"][2], np.resize(got["far"][0], TABLE_ROWS))
     w_ref, loss_ref = ref.svm_sgd_step(Fh, y, np.arange(n, dtype=np.int32), n, w0, 1e-3, 0.7)
     assert_close_scaled(got["far"][7], loss_ref, abs_dot_scale(Fh, np.arange(n), w0), "loss", atol=1e-6)
     scale = np.abs(w0.astype(np.float64)) + 0.7 / n * _col_abs_sum(Fh, np.arange(n), d)
