@@ -58,14 +58,15 @@ size_t general_pairs_offset(int32_t d) {  // (w, phi) pairs of the columns, inde
 size_t general_part_offset(int32_t d) {
   return general_pairs_offset(d) + align_up(2 * (size_t)d * sizeof(float), 256);
 }
-size_t general_bins_offset(int32_t d) {
-  return general_part_offset(d) + align_up(general_part_floats(d) * sizeof(float), 256);
+size_t general_acc_bytes(int32_t d, int32_t count_max) {
+  return general_part_offset(d) + align_up(general_part_floats(d) * sizeof(float), 256) +
+         general_record_capacity(count_max) * kRecordBytes;
+}
+size_t general_bins_offset(int32_t d, int32_t head, int nvec) {  // (a multiple of 256)
+  return general_part_offset(d) + kGeneralGradBlocks * (size_t)head * nvec * sizeof(float);
 }
 size_t general_runs_offset(int32_t d, int32_t count_max) {
-  return general_bins_offset(d) + general_record_capacity(count_max) * kRecordWordBytes;
-}
-size_t general_acc_bytes(int32_t d, int32_t count_max) {
-  return general_bins_offset(d) + general_record_capacity(count_max) * kRecordBytes;
+  return general_acc_bytes(d, count_max) - general_run_bytes(count_max);
 }
 
 Ws carve(void *ws, size_t grad_bytes, int32_t P, bool epoch_outputs = false) {
@@ -321,7 +322,7 @@ hipError_t run_pass(const PassSpec &s, const Ws &ws, int32_t *nblk_out, hipStrea
   a.wp = nvec == 2 ? reinterpret_cast<const float2 *>(ws.grad + general_pairs_offset(s.F->d)) : nullptr;
   a.bin_fill = reinterpret_cast<unsigned *>(acc + 16 + 3 * kMaxBins);
   a.blk_late = reinterpret_cast<int32_t *>(acc + 16 + kMaxBins);
-  a.recs = reinterpret_cast<int32_t *>(ws.grad + general_bins_offset(s.F->d));
+  a.recs = reinterpret_cast<int32_t *>(ws.grad + general_bins_offset(s.F->d, a.head, nvec));
   a.runs = reinterpret_cast<int32_t *>(ws.grad + general_runs_offset(s.F->d, s.count_max));
   a.t_upd = s.t_upd;
   a.t_snap = ws.ctl + kCtlUpdateSnapshot;
@@ -403,8 +404,8 @@ hipError_t run_update(const PassSpec &s, const UpdateSpec &u, const Ws &ws, int3
   p.nvec = ((s.mode & kSvm) ? 1 : 0) + ((s.mode & kAssist) ? 1 : 0);
   p.head = general_head_columns(s.F->d, p.nvec, s.F->layout == AA_CSR);
   p.bin_fill = reinterpret_cast<unsigned *>(acc + 16 + 3 * kMaxBins);
-  p.blk_late = reinterpret_cast<const int32_t *>(acc + 16 + kMaxBins);
-  p.recs = reinterpret_cast<const int32_t *>(ws.grad + general_bins_offset(s.F->d));
+  p.blk_late = reinterpret_cast<int32_t *>(acc + 16 + kMaxBins);
+  p.recs = reinterpret_cast<const int32_t *>(ws.grad + general_bins_offset(s.F->d, p.head, p.nvec));
   p.runs = reinterpret_cast<const int32_t *>(ws.grad + general_runs_offset(s.F->d, s.count_max));
   p.plan = general_bin_plan(s.F->d, p.head, p.nvec, s.count_max, nblk);
   p.t_upd = u.t_upd;

@@ -908,11 +908,14 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
     beyond = min(beyond + s_more, cap - held);
   }
   // The others, a piece (at most C) at a time, sorted by bin (a counting sort by way of LDS) and on to the bins like
-  // those above.  What a bin has no room for goes back to where it was, and its owner finds it as one run
-  // (start, count) of the piece.  (They all went back: 5.4 M records of 460,000 sentence pairs, their owners' 512 runs of
-  // 41 a bin strewn over 60 MB: update kernel 27.5 us, now 14.2, and this pass 126.3 and 129.6.  The next piece's loads ahead
-  // of the stores: no gain; two bins' places with one atomic: 129.0, but 0.2 us more over small pools.)
+  // those above, if the block's share of the bins has room for all of its records.  What stays goes back to where it was,
+  // and its owner finds it as one run (start, count) of the piece.  (Nothing on to the bins / all that finds room / so: update
+  // kernel over 460,000 sentence pairs, whose 5.4 M records were 512 runs of 41 a bin strewn over 60 MB, 27.5 / 14.2 / 13.9
+  // us and this pass 126.3 / 129.6 / 129.1; whole update over as many rows of 60 uniform columns 333 / 347 / 335, of 82 480 / 702 /
+  // 482.  The next piece's loads ahead of the stores: no gain; two bins' places with one atomic: 129.0, but 0.2 us
+  // more over small pools.)
   if (threadIdx.x == 0) a.blk_late[blockIdx.x] = beyond;
+  const bool binnable = min(n, held) + beyond <= a.plan.share;
   int *const s_rec = reinterpret_cast<int *>(s_mem);
   constexpr int kPer = C / kGradThreads;
   for (int piece = 0; piece * a.plan.piece < beyond; ++piece) {
@@ -938,8 +941,8 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
     __syncthreads();
     const bool owns = (int)threadIdx.x < a.plan.nb;
     const int h = owns ? s_hist[threadIdx.x] : 0;
-    int to = 0;  // (used after the records have moved in LDS: the round trip is under way meanwhile)
-    if (h > 0) to = (int)atomicAdd(a.bin_fill + segment * kMaxBins + threadIdx.x, (unsigned)h);
+    int to = a.plan.seg_cap;  // (used after the records have moved in LDS: the round trip is under way meanwhile)
+    if (binnable && h > 0) to = (int)atomicAdd(a.bin_fill + segment * kMaxBins + threadIdx.x, (unsigned)h);
     if (wave == 0) {  // four bins a lane
       static_assert(kMaxBins == 4 * kWave, "one wave scans the bins");
       const int4 n4 = reinterpret_cast<const int4 *>(s_hist)[lane];
@@ -966,8 +969,14 @@ __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
     __syncthreads();
     if (owns) {
       const int start = s_base[threadIdx.x], fit = min(max(a.plan.seg_cap - to, 0), h);
+      if (fit < h) left_marks(a.blk_late)[threadIdx.x] = 1;
       a.runs[((size_t)threadIdx.x * a.plan.pieces + piece) * gridDim.x + blockIdx.x] = (start + fit) | ((h - fit) << 16);
       s_hist[threadIdx.x] = to - start;  // (place in the bin less place in the piece)
+    }
+    if (!binnable) {  // whole 128-bit words (a piece is a multiple of four records)
+      for (int i = threadIdx.x; 4 * i < m * RW; i += kGradThreads)
+        reinterpret_cast<int4 *>(src)[i] = reinterpret_cast<const int4 *>(s_rec)[i];
+      continue;
     }
     __syncthreads();
     for (int i = threadIdx.x; i < m; i += kGradThreads) {
@@ -1628,7 +1637,7 @@ __device__ __forceinline__ void late_records(const ApplyArgs &a, int bin, int n_
 template <int RW>
 __device__ __forceinline__ void apply_bin(const ApplyArgs &a, int bin, double *s_bin, int *s_m,
                                           float *s_g, int *s_run, int *s_late,
-                                          unsigned long long *s_long, int *s_over) {
+                                          unsigned long long *s_long) {
   // per thread: kRec records of the first batch, which is requested before the bin's fill count
   // is known (1024 records a bin; with 4096, small pools read megabytes of stale ones); kCol runs
   // of four columns (a bin's columns come in groups of at least four neighbours) --
@@ -1642,8 +1651,8 @@ __device__ __forceinline__ void apply_bin(const ApplyArgs &a, int bin, double *s
   static_assert(kBinSegments == kApplyWaves, "a segment a wave");
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), segment = a.plan.segments == 1 ? 0 : wave;
   const int first = a.plan.segments == 1 ? tid : tid & 63, turn = a.plan.segments == 1 ? kApplyThreads : kWave;
-  const unsigned offered = a.bin_fill[segment * kMaxBins + bin];
-  const int n = (int)min(offered, (unsigned)cap);
+  const int n = (int)min(a.bin_fill[segment * kMaxBins + bin], (unsigned)cap);
+  const int left = left_marks(a.blk_late)[bin];
   const int acc_used = a.acc_used[bin];
   const int32_t *const rec = a.recs + ((size_t)bin * a.plan.segments + segment) * cap * RW;
   int r0[kRec][RW];
@@ -1686,7 +1695,6 @@ __device__ __forceinline__ void apply_bin(const ApplyArgs &a, int bin, double *s
     if ((tid & 63) == 0) s_late[tid >> 6] = most;
   }
   float gb_unused;
-  if ((tid & 63) == 0) s_over[wave] = offered > (unsigned)cap;
   const int m = pass_totals(a, cnt, 0.f, s_m, s_g, &gb_unused);  // barrier: the sums are zero
   const Fold fold(a, m);
   auto add = [&](const int *r) __attribute__((always_inline)) {
@@ -1738,10 +1746,7 @@ __device__ __forceinline__ void apply_bin(const ApplyArgs &a, int bin, double *s
     add_wide(base + wide, b1);
   }
   const int most = max(max(s_late[0], s_late[1]), max(s_late[2], s_late[3]));
-  bool over = false;  // (otherwise the bin has had room for all)
-#pragma unroll
-  for (int w = 0; w < kApplyWaves; ++w) over = over || s_over[w] != 0;
-  if (most > 0 && over) late_records<RW>(a, bin, n_mine, s_run, s_late, s_long, (most + a.plan.piece - 1) / a.plan.piece, add);
+  if (most > 0 && left != 0) late_records<RW>(a, bin, n_mine, s_run, s_late, s_long, (most + a.plan.piece - 1) / a.plan.piece, add);
   __syncthreads();
   auto sum_of = [&](int k) {  // over the copies, in order
     double v = 0.0;
@@ -1825,7 +1830,7 @@ __device__ __forceinline__ void apply_bin(const ApplyArgs &a, int bin, double *s
   }
   if (a.keep_ready && tid < kBinSegments) {  // (read at the top; the next pass counts from zero)
     a.bin_fill[tid * kMaxBins + bin] = 0u;
-    if (tid == 0) a.acc_used[bin] = 0;
+    if (tid == 0) a.acc_used[bin] = left_marks(a.blk_late)[bin] = 0;
   }
 }
 
@@ -1837,7 +1842,6 @@ __global__ __launch_bounds__(kApplyThreads) void k_apply_general(const ApplyArgs
   __shared__ double s_bin[kBinColsMax + 1];  // (+1: the odd stride of a single copy)
   __shared__ int s_run[kGeneralGradBlocks], s_late[kGeneralGradBlocks / kWave];
   __shared__ unsigned long long s_long[kGeneralGradBlocks / kWave];
-  __shared__ int s_over[kApplyWaves];
   // roles by block number: the other columns first (the bin owners have the longest way to
   // go), then the first columns, then the compaction tiles
   const int bid = (int)blockIdx.x, hb = bid - nrest;
@@ -1861,9 +1865,9 @@ __global__ __launch_bounds__(kApplyThreads) void k_apply_general(const ApplyArgs
     // pools of 20,000 rows over 200,000 34.2 and 27.7, of 3000 over 40,000 21.3 and 20.1.)
     const int bin = (nrest & 7) != 0 ? bid : (bid & 7) * (nrest >> 3) + (bid >> 3);
     if (a.nvec == 2)
-      apply_bin<3>(a, bin, s_bin, s_m, s_g, s_run, s_late, s_long, s_over);
+      apply_bin<3>(a, bin, s_bin, s_m, s_g, s_run, s_late, s_long);
     else
-      apply_bin<2>(a, bin, s_bin, s_m, s_g, s_run, s_late, s_long, s_over);
+      apply_bin<2>(a, bin, s_bin, s_m, s_g, s_run, s_late, s_long);
     return;
   }
   const int t = threadIdx.x;

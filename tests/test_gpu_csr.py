@@ -633,8 +633,8 @@ def test_csr_fused_step_more_columns_than_the_bins_cover(ref):
 
 
 def _workspace_counts(ws, table):
-    """Table 0 (records offered to a bin), 1 (late records of a block) or 2 (bins whose accumulators were used) of the last
-    pass: 256 integers each behind the 16 scalars that open the general kernels' part of the workspace."""
+    """Table 0 (bins that left records in the blocks' late room), 1 (late records of a block) or 2 (bins whose accumulators
+    were used) of the last pass: 256 integers each behind the 16 scalars that open the general kernels' part of the workspace."""
     first = ws.ptr - ws.buf.data_ptr() + 256 + 2 * 4 * 1024 + 256 + 4 * (16 + 256 * table)
     return host(ws.buf[first:first + 4 * 256]).view(np.int32)
 
@@ -897,6 +897,48 @@ def test_csr_records_that_find_their_bin_full(ref, kind):
     api.boss_assistant_step(F, y, None, m, n, w, phi, b, cfg, loss, ws)               # (margin 0, loss 1)
     assert _bins_with_accumulators(ws) == 0
     assert np.array_equal(host(phi), want) and np.array_equal(host(w), want)
+
+
+def _exact_updates(n, d, rowptr, col, two):
+    """One update (g = 1/2 and z = 1, with margin 0 and loss 1) of an Assistant, or of both vectors, that moves a column by 1 /
+    (2 n) for every entry, exactly; returns the workspace."""
+    F, ws = csr_features(rowptr, col, None, d), api.Workspace(n, d)
+    m, y, loss = scalar_dev(n, torch.int32), dev(np.ones(n, np.float32)), torch.full((n,), 0.7, device="cuda")
+    phi, w, b = torch.zeros(d, device="cuda"), torch.zeros(d, device="cuda"), scalar_dev(0.0)
+    if two:
+        cfg = api.step_config(0.0, 0.0, 0.5, 1.0, 0.0, 1, 0, scalar_dev(0.5))
+        api.boss_assistant_step(F, y, None, m, n, w, phi, b, cfg, loss, ws)
+    else:
+        api.assistant_update(F, None, m, n, loss, scalar_dev(0.5), phi, b, 1.0, 0.0, ws)
+    want = (np.bincount(col, minlength=d) / (2.0 * n)).astype(np.float32)
+    assert np.array_equal(host(phi), want) and (not two or np.array_equal(host(w), want))
+    return ws
+
+
+@pytest.mark.parametrize("two,per", [(False, 78), (True, 52)])
+def test_csr_room_for_the_late_records_of_a_large_pool(two, per):
+    """Of 84 records a candidate (56 of both vectors) the blocks of a large pool can place nearly all while they walk their
+    rows, whatever the bins have room for meanwhile: rows of 78 (52) columns that are not in the table leave nothing to the
+    accumulators."""
+    n, d = 1 << 18, 500_000
+    col = rng(79).integers(8192, d, size=n * per, dtype=np.int32)
+    ws = _exact_updates(n, d, np.arange(0, n * per + 1, per, dtype=np.int64), col, two)
+    assert _bins_with_accumulators(ws) == 0 and _late_records(ws).min() > (per - 10) * n // 256 - 6000
+
+
+@pytest.mark.parametrize("two", [False, True])
+@pytest.mark.parametrize("first,second", [("long", "long"), ("long", "short"), ("short", "short")])
+def test_csr_late_records_stay_or_go_to_the_bins(two, first, second):
+    """Blocks with more late records than their share of the bins has room for leave all of them in their pieces, others none:
+    all blocks, half of them, and none, in the first and the second half of the rows."""
+    n, d = 65_536, 300_000
+    lens = {"long": 49 if two else 70, "short": 28 if two else 34}  # (a block has 256 rows, and room for 13,056 or 20,480 records)
+    rowptr = np.r_[0, np.cumsum(np.repeat([lens[first], lens[second]], n // 2))]
+    col = rng(83).integers(8192, d, size=int(rowptr[-1]), dtype=np.int32)
+    ws = _exact_updates(n, d, rowptr, col, two)
+    late, left = _late_records(ws), int(np.count_nonzero(_workspace_counts(ws, 0)))
+    assert late.min() > 0 and (late[:128] > 2 * late[128:]).all() == (first != second)
+    assert _bins_with_accumulators(ws) == 0 and left == (256 if first == "long" else 0)
 
 
 @pytest.mark.parametrize("ones", [True, False])
