@@ -107,11 +107,14 @@ __device__ __forceinline__ void add_global(const GenArgs &a, int c, double ta, d
 // an LDS buffer that the block looked at, and emptied, together every eight rows of a wave:
 // 55 % of the wave cycles were waits.  Now those that the buffer has no room for go to memory as they
 // come, and the block sorts all of them by bin once, at the end.
-// An entry cost about 96 vector instructions; 25.8 M of them over 64,002 columns kept a pass at 58 % of its issue
-// cycles.  Lane sets in scalar registers, one sum's address instead of two branches, no division a record, row extents
-// clipped once a round and record stores without a branch leave 62: the update over 460,000 sentence pairs 170.4 ->
-// 157.1 us, an epoch of four pools of 65,536 rows over 2^20 columns 233.3 -> 228.3.
-// NEAR: every column is in the table; no tags, records and gathers.
+// The loop's code had about 96 vector instructions an entry, and a pass over 456,000 sentence pairs (25.8 M entries) issued
+// 47.6 M for all it does, 58 % of its issue cycles.  Lane sets in scalar registers, one sum's address instead of two branches, no
+// division a record, row extents clipped once a round and record stores without a branch leave 62, and 41.8 M, 55 %, with the
+// waves waiting 38 instead of 50 % of their cycles: the update over 460,000 pairs 170.4 -> 157.1 us, an epoch of four
+// pools of 65,536 rows over 2^20 columns 233.3 -> 228.3 (all of it together: which part gave how much was not measured).
+// NEAR: every column is in the table; no tags, records and gathers.  Whole updates without / so, rows of 56 entries, one
+// vector over 8000 columns: 1000 rows 14.9 / 11.7 us, 20,000 20.2 / 16.6, 300,000 49.4 / 35.2; both over 3000: 20,000 20.1 / 17.0,
+// 300,000 57.2 / 46.9.
 template <int GL, int MODE, bool CSR, bool NEAR>
 __global__ __launch_bounds__(kGradThreads) void k_rows_grad(const GenArgs a) {
   static_assert(CSR || !NEAR, "dense rows choose turn by turn");

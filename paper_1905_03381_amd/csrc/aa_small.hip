@@ -7,7 +7,7 @@
 // memory system (about 28 bytes per ns) for pools near the limit, the waves' arithmetic below.
 //
 // In a team every wave has a SIMD to itself (nearly), and four compute units read: an epoch of 40 pools of 256 x 128
-// 192 -> 118 us.  The waves' gradient sums, added up by fours in each block, then go through memory, each in a
+// 192 -> 120 us.  The waves' gradient sums, added up by fours in each block, then go through memory, each in a
 // 64-bit word with the step's number beside it, stored and read with relaxed device-scope atomics: a reader takes a word
 // whose number is the step's and asks again otherwise, so nothing has to be ordered or counted.  (Four blocks that read
 // 256 words of each other: 0.7 to 1.0 us a round; every wave's sums without the additions, four times the words, 3.)
